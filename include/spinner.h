@@ -349,12 +349,13 @@ int spinner_sketch_gram_static(const float *B, int m, int d, float *G, void *str
  * prepares all parameters in advance.  spinner_struct_apply computes
  *     out[batch][m] = scale * (first m rows of G_struct D2 H D1 x)
  * with H the normalised Hadamard matrix.  The product with G_struct is an O(n log n)
- * FFT convolution of length P = n (circulant) or 2n (the others).  While the transform
- * fits the LDS (P <= 2^14: n = 2^5 .. 2^14 for the circulant, .. 2^13 for the others)
+ * FFT convolution of length P = n (circulant) or 2n (the others).  Up to P = 2^14
+ * (n = 2^5 .. 2^14 for the circulant, .. 2^13 for the others)
  * the call is one kernel that needs no scratch memory; spinner_struct_apply returns
  * SPINNER_ERR_UNSUPPORTED above that.  spinner_struct_apply_ws takes a workspace of
  * spinner_struct_workspace_bytes(kind, n, batch) bytes (0 for the sizes above) and also
- * serves P = 2^15 .. 2^22 (n up to 2^22 / 2^21): H D1 x by a pass over rows and a pass
+ * serves P = 2^15 .. 2^22 (n up to 2^22 / 2^21): one kernel at n = 2^14 (the workspace is
+ * asked for but not touched); above, H D1 x by a pass over rows and a pass
  * over columns, then the transform in three passes through global memory (its top
  * stages over column tiles, blocks of 2^12 points with the spectrum product, the top
  * stages back).  spinner_struct_prepare serves all of these sizes.  An unknown kind

@@ -799,10 +799,18 @@ static int struct_apply_impl(const float* x, int n, long batch, int kind, const 
     // the Hadamard stages and both transforms of the convolution run unnormalised: 1 / sqrt(n) and 1 / P go into the last scale
     const double factor = (double)scale / ((double)((size_t)1 << lp) * sqrt((double)n));
     if (lp > kStructLdsMaxLog2p) {
-        // H D1 x (unnormalised) of every vector by a pass over rows and a pass over columns, then the convolution
-        // through global memory: column stages, blocks of 2^12 points (with the spectrum product), column stages back
         if (!workspace) return SPINNER_ERR_WORKSPACE;
         if (!aligned16(workspace)) return SPINNER_ERR_ALIGNMENT;
+    }
+    if (spinner::struct_fft_serves(log2n)) {
+        const hipError_t e = spinner::launch_struct_fft(x, d1, d2, spec, spec + ((size_t)1 << lp), out, batch, log2n, lp, m,
+                                                        kind == SPINNER_STRUCT_HANKEL ? 1 : 0, (float)factor,
+                                                        static_cast<hipStream_t>(stream));
+        return e == hipSuccess ? SPINNER_OK : hip_fail(e);
+    }
+    if (lp > kStructLdsMaxLog2p) {
+        // H D1 x (unnormalised) of every vector by a pass over rows and a pass over columns, then the convolution
+        // through global memory: column stages, blocks of 2^12 points (with the spectrum product), column stages back
         hipStream_t s = static_cast<hipStream_t>(stream);
         float* t = static_cast<float*>(workspace);
         float2* z = reinterpret_cast<float2*>(static_cast<char*>(workspace) + align256((size_t)batch * (size_t)n * sizeof(float)));

@@ -149,3 +149,21 @@ def test_struct_argument_errors(gpu):
     assert f(64, 1024, 4, 0, 64, 64, 64, 1024, one, 72, None) == b.SPINNER_ERR_ALIGNMENT
     assert f(64, 1024, 4, 0, None, 64, 64, 1024, one, 64, None) == b.SPINNER_ERR_NULL_PTR
     assert f(None, 1024, 0, 0, None, None, None, 1024, one, None, None) == b.SPINNER_OK
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("log2n", [8, 9, 10, 14])
+def test_struct_register_transforms_at_the_edges_of_their_range(gpu, oracle, kind, log2n):
+    # n = 2^9 .. 2^14 run every stage between registers (2^8 is the last size of the general kernel below); one vector
+    # and a full pair, one row, all but one row; at 2^14 sampled rows, the padded kinds through the call with a workspace
+    n = 1 << log2n
+    rows = np.arange(n) if log2n < 14 else np.unique(np.concatenate([np.arange(8), np.arange(n - 8, n), np.random.default_rng(1).integers(0, n, 48)]))
+    for batch in (1, 2):
+        x, d, params = _case(kind, n, batch, 10500 + log2n)
+        spec = gpu.b.spinner_struct_prepare(kind, _to(gpu, params), n)
+        want = oracle.struct_apply_rows(x, kind, params, d[0], d[1], rows, 0.75)
+        args = (_to(gpu, x), kind, spec, _to(gpu, d[0]), _to(gpu, d[1]))
+        got = gpu.b.spinner_struct_apply_ws(*args, n, 0.75).cpu().numpy()
+        assert rel_l2_per_vector(got[:, rows], want).max() <= REL_L2_TOL
+        for m in (1, n - 1):
+            assert np.array_equal(gpu.b.spinner_struct_apply_ws(*args, m, 0.75).cpu().numpy(), got[:, :m])
