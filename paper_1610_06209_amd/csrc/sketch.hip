@@ -54,24 +54,47 @@ hipError_t launch_transpose_scale(const float* src, long long rows, long long co
     return hipGetLastError();
 }
 
-// G = B^T B for B [m][d] row-major: G[a][b] = sum_k B[k][a] B[k][b].  A workgroup of four waves owns a
-// 128 x 128 block of G (each wave 64 x 64 = 2 x 2 tiles of v_mfma_f32_32x32x2_f32) and walks k in chunks
-// of 16 rows of B staged in LDS.  Both MFMA operands are rows of B: lane l supplies B[k + l / 32][. + l % 32].
+// G = B^T B for B [m][d] row-major: G[a][b] = sum_k B[k][a] B[k][b], on the fp32 matrix pipe (v_mfma_f32_32x32x2_f32).
+// G is symmetric, so only the 64 x 64 tiles on and above the diagonal are computed and each is stored twice.  A
+// workgroup owns one tile (of one slab of rows); its four waves take a quarter of the rows each, hold the whole tile
+// (2 x 2 MFMA tiles) and are added up through LDS at the end, in a fixed order.  Both operands are rows of B as they
+// lie: lane l supplies row k + l / 32 of columns 2 (l % 32) and 2 (l % 32) + 1, one for either MFMA tile (EVEN: one 8-byte
+// load, which an even d aligns; else two), so they come straight from memory into registers, a group of UNROLL row
+// pairs ahead of the group being multiplied; no barrier stands in the loop.
+// What bounds it: the matrix pipe at large d (busy 43 % of the time at d = 4096, the rest waits for loads that miss the
+// L2), latency below.  Measured against all 128 x 128 tiles of G staged through LDS, m = 2048, in us: d = 64 13.9 -> 12.3,
+// 256 17.4 -> 14.4, 500 26.5 -> 17.2, 1000 65 -> 48, 2000 211 -> 171, 4096 621 -> 513 (m = 4096, d = 768: 94 -> 37).  A third
+// group in flight: 4096 479, but 64 14.5; tiles dealt to the XCDs in 4 x 4 groups halve the misses and gain nothing.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-constexpr int kGramBlock = 128, kGramK = 16;
-// Split over k: block z handles rows [z * kchunk, (z + 1) * kchunk) of B and writes its own d x d slab of `out`
-// (G itself when there is a single slab); the slabs are added up afterwards in a fixed order.
-__global__ void __launch_bounds__(256) sketch_gram_kernel(const float* __restrict__ B, int m_total, int d, int kchunk,
-                                                          float* __restrict__ out)
+constexpr int kGramTile = 64;
+
+// t -> (ta, tb), ta <= tb, t = tb (tb + 1) / 2 + ta
+__device__ __forceinline__ void upper_tile(int t, int& ta, int& tb)
 {
-    const int k_begin = blockIdx.z * kchunk;
-    const int m = k_begin + kchunk < m_total ? k_begin + kchunk : m_total;
-    float* G = out + (long long)blockIdx.z * d * d;
-    __shared__ float sa[kGramK][kGramBlock];
-    __shared__ float sb[kGramK][kGramBlock];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wa = wave >> 1, wb = wave & 1;
-    const int a0 = blockIdx.y * kGramBlock, b0 = blockIdx.x * kGramBlock;
+    tb = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((tb + 1) * (tb + 2) / 2 <= t) ++tb;
+    while (tb * (tb + 1) / 2 > t) --tb;
+    ta = t - tb * (tb + 1) / 2;
+}
+
+// Slab z handles rows [z * kchunk, (z + 1) * kchunk) of B and writes its own d x d matrix of `out`, tiles on and above the
+// diagonal only (gram_reduce_kernel adds the slabs up and mirrors); with a single slab `out` is G, mirrored here.
+template <bool EVEN>
+__global__ void __launch_bounds__(256, 2) sketch_gram_kernel(const float* __restrict__ B, int m_total, int d, int kchunk, int mirror,
+                                                             float* __restrict__ out)
+{
+    __shared__ float red[4][3][16][64];      // [quadrant][contributor][register][lane]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    int ta, tb;
+    upper_tile((int)blockIdx.x, ta, tb);
+    const int a0 = ta * kGramTile, b0 = tb * kGramTile;
+    const int s_begin = blockIdx.y * kchunk;
+    const int s_end = s_begin + kchunk < m_total ? s_begin + kchunk : m_total;
+    const int quarter = (((s_end - s_begin + 3) >> 2) + 1) & ~1;
+    const int k_begin = s_begin + wave * quarter;
+    const int k_end = k_begin + quarter < s_end ? k_begin + quarter : s_end;
+
     floatx16 acc[2][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -80,87 +103,163 @@ __global__ void __launch_bounds__(256) sketch_gram_kernel(const float* __restric
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.f;
 
-    // 16 rows x 128 columns per operand, 256 threads: 8 values per thread and operand.  A chunk is loaded into
-    // registers while the chunk before it is multiplied (addresses clamped to the last row / column, what lies
-    // outside set to zero afterwards: no load under a condition).
-    float ra[8], rb[8];
-    auto load_chunk = [&](int k0) {
+    constexpr int UNROLL = 8;
+    // columns past the last one are read from it: they only reach entries that are not stored
+    int ca[2], cb[2];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int idx = q * 256 + threadIdx.x;
-            const int kk = idx >> 7, col = idx & 127;
-            const int row = k0 + kk < m ? k0 + kk : m - 1;
-            const int ca = a0 + col < d ? a0 + col : d - 1, cb = b0 + col < d ? b0 + col : d - 1;
-            ra[q] = B[(long long)row * d + ca];
-            rb[q] = B[(long long)row * d + cb];
-        }
+    for (int t = 0; t < 2; ++t) {
+        const int last = EVEN ? d - 2 + t : d - 1;
+        ca[t] = a0 + 2 * l32 + t < d ? a0 + 2 * l32 + t : last;
+        cb[t] = b0 + 2 * l32 + t < d ? b0 + 2 * l32 + t : last;
+    }
+    struct Group { float a[UNROLL][2], b[UNROLL][2]; };
+    auto load = [&](Group& g, int k0) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int idx = q * 256 + threadIdx.x;
-            const int kk = idx >> 7, col = idx & 127;
-            const bool row_ok = k0 + kk < m;
-            if (!(row_ok && a0 + col < d)) ra[q] = 0.f;
-            if (!(row_ok && b0 + col < d)) rb[q] = 0.f;
+        for (int i = 0; i < UNROLL; ++i) {
+            const int row = k0 + 2 * i + half;
+            const float* r = B + (long long)(row < k_end ? row : k_end - 1) * d;      // clamped: no load under a condition
+            if constexpr (EVEN) {
+                const float2 fa = *reinterpret_cast<const float2*>(r + ca[0]), fb = *reinterpret_cast<const float2*>(r + cb[0]);
+                g.a[i][0] = fa.x; g.a[i][1] = fa.y;
+                g.b[i][0] = fb.x; g.b[i][1] = fb.y;
+            } else {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) { g.a[i][t] = r[ca[t]]; g.b[i][t] = r[cb[t]]; }
+            }
         }
     };
-    if (k_begin < m) load_chunk(k_begin);
-    for (int k0 = k_begin; k0 < m; k0 += kGramK) {
+    auto multiply = [&](Group& g, int k0) {
+        if (k0 + 2 * UNROLL > k_end) {               // rows past the end count as zero in both operands
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int idx = q * 256 + threadIdx.x;
-            sa[idx >> 7][idx & 127] = ra[q];
-            sb[idx >> 7][idx & 127] = rb[q];
+            for (int i = 0; i < UNROLL; ++i)
+                if (k0 + 2 * i + half >= k_end) { g.a[i][0] = g.a[i][1] = g.b[i][0] = g.b[i][1] = 0.f; }
         }
-        __syncthreads();
-        if (k0 + kGramK < m) load_chunk(k0 + kGramK);
 #pragma unroll
-        for (int kk = 0; kk < kGramK; kk += 2) {
-            float fa[2], fb[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                fa[t] = sa[kk + (lane >> 5)][wa * 64 + t * 32 + (lane & 31)];
-                fb[t] = sb[kk + (lane >> 5)][wb * 64 + t * 32 + (lane & 31)];
-            }
+        for (int i = 0; i < UNROLL; ++i)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[t], fb[u], acc[t][u], 0, 0, 0);
-        }
-        __syncthreads();
+                for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(g.a[i][t], g.b[i][u], acc[t][u], 0, 0, 0);
+    };
+    if (k_begin < k_end) {
+        constexpr int STEP = 2 * UNROLL;
+        Group g0, g1;
+        load(g0, k_begin);
+        int k0 = k_begin;
+        do {
+            load(g1, k0 + STEP);
+            multiply(g0, k0);
+            load(g0, k0 + 2 * STEP);
+            if (k0 + STEP < k_end) multiply(g1, k0 + STEP);
+            k0 += 2 * STEP;
+        } while (k0 < k_end);
     }
-    // result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its 32 x 32 tile
+
+    // wave w ends up with quadrant (w / 2, w % 2): the others hand it theirs
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int q = 0; q < 4; ++q)
+        if (q != wave) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+            for (int v = 0; v < 16; ++v) red[q][wave < q ? wave : wave - 1][v][lane] = acc[q >> 1][q & 1][v];
+        }
+    __syncthreads();
+    float sum[16];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {            // always in the order of the rows, so that the diagonal tiles are symmetric too
+        if (c == wave) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q == wave) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sum[v] = c ? sum[v] + acc[q >> 1][q & 1][v] : acc[q >> 1][q & 1][v];
+                }
+        } else {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = a0 + wa * 64 + t * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const int col = b0 + wb * 64 + u * 32 + (lane & 31);
-                if (row < d && col < d) G[(long long)row * d + col] = acc[t][u][v];
+                const float r = red[wave][c < wave ? c : c - 1][v][lane];
+                sum[v] = c ? sum[v] + r : r;
             }
-}
-
-__global__ void __launch_bounds__(256) gram_reduce_kernel(const float* __restrict__ slabs, int count, long long len,
-                                                          float* __restrict__ G)
-{
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= len) return;
-    float s = 0.f;
-    int k = 0;
-    for (; k + 3 < count; k += 4) {         // four loads in flight; the order of the additions stays fixed
-        const float a0 = slabs[k * len + i], a1 = slabs[(k + 1) * len + i], a2 = slabs[(k + 2) * len + i], a3 = slabs[(k + 3) * len + i];
-        s += a0; s += a1; s += a2; s += a3;
+        }
     }
-    for (; k < count; ++k) s += slabs[k * len + i];
-    G[i] = s;
+
+    // Result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its quadrant (i, j) = (wave / 2,
+    // wave % 2), which stand for row 2 row + i and column 2 column + j of the tile.  The tile is put together in LDS (64 rows
+    // of 65) and stored from there, once more turned over.
+    __syncthreads();
+    float* T = &red[0][0][0][0];
+    static_assert(sizeof(red) >= 64 * 65 * sizeof(float), "the tile fits the exchange buffer");
+#pragma unroll
+    for (int v = 0; v < 16; ++v) T[(2 * (8 * (v >> 2) + 4 * half + (v & 3)) + (wave >> 1)) * 65 + 2 * l32 + (wave & 1)] = sum[v];
+    __syncthreads();
+    float* G = out + (long long)blockIdx.y * d * d;
+    if (b0 + lane < d) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = wave * 16 + i;
+            if (a0 + r < d) G[(long long)(a0 + r) * d + b0 + lane] = T[r * 65 + lane];
+        }
+    }
+    if (mirror && ta < tb && a0 + lane < d) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = wave * 16 + i;
+            if (b0 + r < d) G[(long long)(b0 + r) * d + a0 + lane] = T[lane * 65 + r];
+        }
+    }
 }
 
-// number of k-slabs: enough blocks to fill the chip, at least 64 rows of B per slab, at most 64 slabs
+// G from the slabs: a block adds up one 32 x 32 tile on or above the diagonal (fixed order) and stores it twice
+__global__ void __launch_bounds__(256) gram_reduce_kernel(const float* __restrict__ slabs, int count, int d, float* __restrict__ G)
+{
+    __shared__ float tile[32][33];
+    int ta, tb;
+    upper_tile((int)blockIdx.x, ta, tb);
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const long long len = (long long)d * d;
+    const int col = tb * 32 + tx, cc = col < d ? col : d - 1;
+    const float* p[4];
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = ta * 32 + ty + 8 * i;
+        p[i] = slabs + (long long)(row < d ? row : d - 1) * d + cc;
+    }
+    int k = 0;
+    for (; k + 7 < count; k += 8) {         // 32 loads in flight; the order of the additions stays fixed
+        float v[4][8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[i][j] = p[i][(k + j) * len];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[i] += v[i][j];
+    }
+    for (; k < count; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += p[i][k * len];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = ta * 32 + ty + 8 * i;
+        tile[ty + 8 * i][tx] = s[i];
+        if (row < d && col < d) G[(long long)row * d + col] = s[i];
+    }
+    if (ta == tb) return;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = tb * 32 + ty + 8 * i, c = ta * 32 + tx;
+        if (r < d && c < d) G[(long long)r * d + c] = tile[tx][ty + 8 * i];
+    }
+}
+
+// Slabs that the scratch of a call has room for: what 128 x 128 tiles would need to fill the chip, at least 64 rows of B
+// per slab, at most 64 slabs (the sizes of workspaces, and which calls the built-in scratch serves, follow from it)
 int sketch_gram_slabs(int m, int d)
 {
-    const long long tiles = (long long)((d + kGramBlock - 1) / kGramBlock) * ((d + kGramBlock - 1) / kGramBlock);
-    constexpr int kGramWorkgroups = 256;      // workgroups aimed at when the sum over k is split (128 .. 1024 measured alike)
+    const long long tiles = (long long)((d + 127) / 128) * ((d + 127) / 128);
+    constexpr int kGramWorkgroups = 256;
     long long ks = (kGramWorkgroups + tiles - 1) / tiles;
     if (ks > (m + 63) / 64) ks = (m + 63) / 64;
     if (ks > 64) ks = 64;
@@ -197,17 +296,24 @@ hipError_t gram_static_scratch_ptr(float** ptr)
 hipError_t launch_sketch_gram(const float* B, int m, int d, float* G, float* slabs, hipStream_t s)
 {
     if (m <= 0 || d <= 0) return hipSuccess;
-    const int g = (d + kGramBlock - 1) / kGramBlock;
-    if (g > 65535) return hipErrorInvalidConfiguration;
-    const int ks = sketch_gram_slabs(m, d);
-    int kchunk = (m + ks - 1) / ks;
-    kchunk = (kchunk + kGramK - 1) / kGramK * kGramK;
-    hipLaunchKernelGGL(sketch_gram_kernel, dim3((unsigned)g, (unsigned)g, (unsigned)ks), dim3(256), 0, s, B, m, d, kchunk,
-                       ks > 1 ? slabs : G);
+    const long long g = (d + kGramTile - 1) / kGramTile, tiles = g * (g + 1) / 2;
+    if (tiles > 0x1fffffffLL) return hipErrorInvalidConfiguration;
+    // slabs: the fewest that bring the busiest compute unit's share of the rows within 10 % of the least, as far as the
+    // scratch goes
+    const int room = sketch_gram_slabs(m, d);
+    auto share = [&](int k) { return (double)((tiles * k + 255) / 256) / k; };
+    double least = share(1);
+    for (int k = 2; k <= room; ++k) least = share(k) < least ? share(k) : least;
+    int ks = 1;
+    while (share(ks) > 1.1 * least) ++ks;
+    const int kchunk = ((m + ks - 1) / ks + 1) & ~1;
+    float* to = ks > 1 ? slabs : G;
+    if (d & 1) hipLaunchKernelGGL(sketch_gram_kernel<false>, dim3((unsigned)tiles, (unsigned)ks), dim3(256), 0, s, B, m, d, kchunk, ks == 1, to);
+    else hipLaunchKernelGGL(sketch_gram_kernel<true>, dim3((unsigned)tiles, (unsigned)ks), dim3(256), 0, s, B, m, d, kchunk, ks == 1, to);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ks == 1) return e;
-    const long long len = (long long)d * d;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, slabs, ks, len, G);
+    const long long g32 = (d + 31) / 32;
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(g32 * (g32 + 1) / 2)), dim3(256), 0, s, slabs, (int)ks, d, G);
     return hipGetLastError();
 }
 }  // namespace spinner

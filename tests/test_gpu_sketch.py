@@ -108,6 +108,26 @@ def test_gram_matches_oracle(gpu, oracle, m, d):
     assert np.abs(G - G.T).max() <= 1e-5 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("m,d", [(1, 2), (15, 63), (16, 64), (33, 65), (130, 66), (2047, 130), (700, 1922), (3, 1921)])
+def test_gram_tiles_at_their_edges(gpu, oracle, m, d):
+    # 64 x 64 tiles on and above the diagonal, even and odd d (8-byte and 4-byte loads), rows that do not fill the waves'
+    # quarters or groups, one slab (d > 1920) and several; the result is symmetric to the last bit, and a column that
+    # holds an infinity reaches its own row and column only
+    rng = np.random.default_rng(m * 13 + d)
+    B = rng.standard_normal((m, d)).astype(np.float32)
+    G = gpu.b.spinner_sketch_gram(_to(gpu, B)).cpu().numpy()
+    want = oracle.sketched_gram(B)
+    # m products and additions in fp32: error of an entry at most (m + 2) 2^-24 |b_a| |b_b|; random signs give its root
+    norms = np.linalg.norm(B.astype(np.float64), axis=0)
+    assert (np.abs(G - want) <= 4 * np.sqrt(m + 2) * 2.0 ** -24 * np.outer(norms, norms)).all()
+    assert np.array_equal(G, G.T)
+    c = d - 1
+    B[m - 1, c] = np.inf
+    H = gpu.b.spinner_sketch_gram(_to(gpu, B)).cpu().numpy()
+    keep = np.arange(d) != c
+    assert np.array_equal(H[np.ix_(keep, keep)], G[np.ix_(keep, keep)]) and not np.isfinite(H[c]).any()
+
+
 def test_full_sketch_gives_the_exact_hessian(gpu):
     # m = n, scale 1: S is orthogonal, so the sketched Hessian equals A^T W A
     n, d = 2048, 96
