@@ -106,16 +106,30 @@ __device__ __forceinline__ void feat_ar_diag_b(double (&v)[G::R], const float* d
     }
 }
 
-template <typename G, bool SIGNS>
+// BLOCKS: L stacked blocks (fp32 triples [L][3][n] from p.d[0] on, block l in columns [l m, (l + 1) m) of the cos and of the
+// sin part), one wave per block and vector (or pair of vectors).  This kernel cannot keep x beside its 64 fp64 values per thread, so a
+// vector's L workgroups each read it, and they have to do so from one L2: workgroups go to the eight XCDs in turn
+// (workgroup b to XCD b mod 8), so the L blocks of a vector are workgroups eight apart.  Against the kernel of blocks.hip,
+// which keeps x in registers but needs lane stages on fp64 values: L = 4, 2^27 elements in all, 2^10 336 -> 290 us, 2^12
+// 393 -> 337 us; n = 4096, L = 4, batch 32768: 1512 -> 1372 us.  Bound: fp64 vector ALU, then HBM (779 us).
+template <typename G, bool SIGNS, bool BLOCKS = false>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::r >= 6 ? 2 : 4)))
-spinner_feature_ar_kernel(TileParams p)
+spinner_feature_ar_kernel(TileParams p, int L)
 {
+    static_assert(!BLOCKS || (!SIGNS && G::WAVES == 1), "stacked blocks: fp32 diagonals, one wave per workgroup");
     static_assert(G::LB == G::r, "no lane bit is shared by the two layouts");
     constexpr int R = G::R, r = G::r, n = 1 << G::NT;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int g = lane >> G::LB, l = lane & (G::LANES - 1);
-    const long long wvec = ((long long)blockIdx.x * G::WAVES + wave) * G::TPW;     // first vector of this wave (wave-uniform)
+    long long wvec = ((long long)blockIdx.x * G::WAVES + wave) * G::TPW;     // first vector of this wave (wave-uniform)
+    if constexpr (BLOCKS) {
+        const unsigned q = blockIdx.x >> 3, vgroup = q / (unsigned)L, block = q - vgroup * (unsigned)L;
+        wvec = ((long long)vgroup * 8 + (blockIdx.x & 7)) * G::TPW;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p.d[k] += (long long)block * 3 * n;
+        p.out += (long long)block * p.m;
+    }
     // a wave with no vector at all leaves (the exchange buffer is private to the wave: no barrier waits for it)
     if (wvec >= p.batch) return;
 
@@ -136,7 +150,7 @@ spinner_feature_ar_kernel(TileParams p)
         const float* src = p.x + (active ? vec : 0) * p.in_stride + 4 * l;
 #pragma unroll
         for (int k = 0; k < R / 4; ++k) {
-            const float4 t = load4<true>(src + 4 * k * G::LANES);      // a vector past the end reads the first one
+            const float4 t = load4<!BLOCKS>(src + 4 * k * G::LANES);      // a vector past the end reads the first one
             *reinterpret_cast<float4*>(w + ar_word_of<G>(4 * (k * G::LANES + l))) = t;
         }
         wave_lds_fence();
@@ -199,10 +213,42 @@ static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_
         const long long blocks = (tiles + GA::VECS_PER_WG - 1) / GA::VECS_PER_WG;
         if (blocks <= 0) return hipSuccess;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((spinner_feature_ar_kernel<GA, SIGNS>), dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p);
+        hipLaunchKernelGGL((spinner_feature_ar_kernel<GA, SIGNS>), dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p, 1);
         return hipGetLastError();
     }
     return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
+}
+
+// p as for one block (out_stride = the whole row, sin_off = L m, inv_sqrt_m = 1 / sqrt(L m))
+template <int NT>
+static hipError_t launch_feature_blocks_nt(const TileParams& p, const float* diag_sets, int L, hipStream_t s)
+{
+    using GA = HashArGeom<NT, feature_ar_log2r(NT), kFeatureArWaves>;
+    // one workgroup per block and group of vectors, in slices of at most 2^24 workgroups (a grid holds 2^32 threads)
+    for (int l0 = 0; l0 < L; l0 += 1 << 21) {
+        const int nl = L - l0 < (1 << 21) ? L - l0 : 1 << 21;
+        const long long slice = (long long)((1 << 21) / nl) * 8 * GA::VECS_PER_WG;
+        TileParams q = p;
+        for (int k = 0; k < 3; ++k) q.d[k] = diag_sets + ((3LL * l0 + k) << NT);
+        for (long long b0 = 0; b0 < p.batch; b0 += slice) {
+            q.batch = p.batch - b0 < slice ? p.batch - b0 : slice;
+            q.x = p.x + b0 * p.in_stride;
+            q.out = p.out + b0 * p.out_stride + (long long)l0 * p.m;
+            const long long groups = (q.batch + GA::VECS_PER_WG - 1) / GA::VECS_PER_WG;
+            hipLaunchKernelGGL((spinner_feature_ar_kernel<GA, false, true>), dim3((unsigned)(8 * ((groups + 7) / 8) * nl)), dim3(GA::THREADS), 0, s, q, nl);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
+}
+hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float* diag_sets, int L, hipStream_t s)
+{
+    switch (log2n) {
+    case 10: return launch_feature_blocks_nt<10>(p, diag_sets, L, s);
+    case 12: return launch_feature_blocks_nt<12>(p, diag_sets, L, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 #define CASE(NT) case NT: return signs ? launch_cossin<NT, true>(p, tiles, s) : launch_cossin<NT, false>(p, tiles, s);

@@ -18,6 +18,11 @@ constexpr int kFusedMaxLogOther = 14;     // fp64 feature map, hash
 struct NotWide { static constexpr int wide = 0, start = 0, chunk = kLaneChunk; };
 template <typename T, int NT> struct Tuning : NotWide { static constexpr int rmax = std::is_same<T, double>::value ? clamp_rmax(NT, 5) : 6, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<double, 12> : NotWide { static constexpr int rmax = 4, waves = 4, min_waves = 0, trips = 0; };
+// held to 128 registers (they take 133 .. 147 otherwise): four and two tiles per compute unit instead of three and one.
+// Measured on 2^27 elements, sign words / fp32 diagonals, in us: 2^13 428 -> 405 / 461 -> 439, 2^14 581 -> 472 / 619 -> 504
+// (no gain for 2^7 .. 2^11, where the same limit spills)
+template <> struct Tuning<double, 13> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
+template <> struct Tuning<double, 14> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
 template <> struct Tuning<float, 4> : NotWide { static constexpr int rmax = 2, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<float, 5> : NotWide { static constexpr int rmax = 2, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<float, 6> : NotWide { static constexpr int rmax = 3, waves = 4, min_waves = 0, trips = 0; };
@@ -133,6 +138,9 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
 // stacked blocks in one launch (blocks.hip): L fp32 triples [L][3][n] applied to a resident copy of x, n <= 2^kBlocksMaxLog;
 // p as for one block (out_stride = the whole row, sin_off = L m, inv_sqrt_m = 1 / sqrt(L m))
 constexpr int kBlocksMaxLog = 14;
+// The feature blocks at n = 2^14 are one launch of the feature kernel per block: with x resident beside the fp64 values the
+// kernel takes 248 registers, two waves per SIMD, and four blocks of 2048 vectors take 562 us against 4 x 125.
+constexpr bool blocks_in_one_launch(int log2n, bool cossin) { return log2n <= (cossin ? 13 : kBlocksMaxLog); }
 hipError_t launch_blocks(int log2n, bool cossin, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 
 // sign words per diagonal in the packed format
@@ -143,9 +151,14 @@ constexpr int hash_ar_log2r(int log2n)      // values per thread (log2) at n = 2
 {
     return log2n == 8 ? 4 : (log2n == 10 ? 5 : 0);
 }
-// The fp64 feature map has such a kernel too (fused_cossin.hip), for n = 2^(2r), and reads the same lane masks.
-constexpr int feature_ar_log2r(int log2n) { return log2n == 12 ? 6 : 0; }
+// The fp64 feature map has such a kernel too (fused_cossin.hip), for n = 2^(2r), and reads the same lane masks: 2^10 and
+// 2^12.  Measured against the tile kernel on 2^27 elements, sign words / fp32 diagonals, in us: 2^10 332 -> 279 /
+// 340 -> 302; 2^8 291 -> 302 / 306 -> 318, so not there.
+constexpr int feature_ar_log2r(int log2n) { return log2n == 10 ? 5 : (log2n == 12 ? 6 : 0); }
 constexpr int ar_log2r(int log2n) { return hash_ar_log2r(log2n) ? hash_ar_log2r(log2n) : feature_ar_log2r(log2n); }
+// the cos / sin blocks of the sizes of the all-register feature kernel run on it, one wave per block (fused_cossin.hip)
+constexpr bool has_feature_blocks_ar(int log2n) { return feature_ar_log2r(log2n) != 0; }
+hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 // n = 2^12 .. 2^14: the wide geometries flip signs in a layout whose lane masks are no words of the packed format;
 // they follow as a block of their own, [3 diagonals][n / 64 words], word (wave << r) | register (fused_none.hip).
 inline long long wide_words_offset(int n, int log2n)      // from a triple's first sign word

@@ -869,7 +869,7 @@ __device__ __forceinline__ void feature_sincos(double y, const TileParams& p, fl
 //         whole kernel (dozens of scalar register pairs, spilled to vector-register lanes and read back at the end).
 template <typename T, typename G, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS, int PRUNE = 0, bool RAGGED = true>
 __global__ void __launch_bounds__(G::THREADS)
-__attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 && std::is_same<T, float>::value ? G::MIN_WAVES : 1)))
+__attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
 spinner_tile_kernel(TileParams p)
 {
     // packed sign words describe contiguous tiles; the column pass that applies the second diagonal takes lane masks

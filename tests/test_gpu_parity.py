@@ -651,6 +651,21 @@ def test_stacked_blocks_every_one_launch_size(gpu, oracle, log2n):
         assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL, (log2n, m)
 
 
+def test_stacked_feature_blocks_in_slices(gpu):
+    # n = 1024: one wave per pair of vectors and block, at most 2^24 workgroups per launch; with 2^18 blocks a launch takes
+    # 128 vectors, so the last three rows of 131 come from a second one
+    n, L, batch, m = 1024, 1 << 18, 131, 4
+    g = gpu.torch.Generator(device=gpu.dev)
+    g.manual_seed(9300)
+    x = gpu.torch.randn((batch, n), generator=g, device=gpu.dev)
+    ds = gpu.torch.randint(0, 2, (L, 3, n), generator=g, device=gpu.dev, dtype=gpu.torch.int8).to(gpu.torch.float32).mul_(2).sub_(1)
+    got = gpu.b.spinner_apply_blocks(x, ds, m, "cossin", 32.0)
+    assert gpu.torch.equal(got[120:], gpu.b.spinner_apply_blocks(x[120:].clone(), ds, m, "cossin", 32.0))
+    one = gpu.b.spinner_apply(x, ds[L - 1, 0], ds[L - 1, 1], ds[L - 1, 2], m, "cossin", 32.0)
+    last = gpu.torch.cat((got[:, (L - 1) * m:L * m], got[:, (2 * L - 1) * m:]), 1) * math.sqrt(L)
+    assert gpu.torch.allclose(last, one, rtol=1e-6, atol=1e-6)
+
+
 def test_stacked_blocks_errors(gpu):
     b, t = gpu.b, gpu.torch
     x = t.zeros((2, 256), dtype=t.float32, device=gpu.dev)
