@@ -77,43 +77,62 @@ hipError_t launch_pack_codes(const float* y, long long y_stride, unsigned long l
     return hipGetLastError();
 }
 
-// out[i][j] = 1 - popcount(a_i xor b_j) / m.  With the code bits as 0 / 1 numbers,
-//     popcount(a xor b) = |a| + |b| - 2 <a, b>,
+// out[i][j] = 1 - popcount(a_i xor b_j) / m.  With the code bits as numbers +1 (0) and -1 (1),
+//     popcount(a xor b) = (m - <a, b>) / 2,
 // and the table of inner products <a_i, b_j> is a dense contraction over the m code bits: it runs on the matrix
-// pipe in the narrowest format that holds 0 and 1, fp4 (E2M1, 0x2 = 1.0; v_mfma_scale_f32_32x32x64_f8f6f4 with
+// pipe in the narrowest format that holds +-1, fp4 (E2M1, 0x2 = 1.0, bit 3 the sign; v_mfma_scale_f32_32x32x64_f8f6f4 with
 // unit scales; products and fp32 sums of at most 2^24 ones: exact).  A workgroup of four waves owns 128 x 128 pairs
-// (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 16 staged in LDS (rows padded by one
-// word: the 2 x 32 half words a wave reads at once fall on 64 different banks).  One instruction consumes a whole
-// 64-bit code word: lane group g = lane / 32 takes half word g and spreads it into nibbles in registers, dword q
-// holding bits q, q + 4, .., q + 28 (each moved to bit 1 of its nibble).  Which bit lands in which of the 64
-// k-slots does not matter, as long as both operands are spread the same way.  The row weights |a_i|, |b_j| are
-// counted on the way (v_bcnt, each lane group its half), |a_i| goes through LDS to the lanes that hold row i of
-// the result.  (Bits as +1 / -1, which need no weights, take one more instruction per dword to spread: slower.)
+// (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 16 staged in LDS; the next chunk is already in
+// registers while one is multiplied.  A row is read from LDS 16 bytes per lane (rows padded to 144 bytes: the sixteen
+// lanes of a phase cover all banks once): lane group g = lane / 32 takes the g-th 16 bytes of every 32, that is the operand
+// dwords of four instructions.  An instruction's operand is a dword of code bits spread into nibbles: dword q of the fp4
+// vector holds bits q, q + 4, .., q + 28, each moved to bit 3 of its nibble by doubling and joined with 1.0 by one
+// three-operand logic instruction (shifts and v_and_or issue at half its rate).  Which bit lands in which of the 64
+// k-slots does not matter, as long as both operands are spread the same way.
+// Bound: per code word a wave has four operands to spread at 19 cycles beside four products at 32 (4.9 PFLOP/s of 10.1 for
+// long codes, at the clock the chip holds under them), and the results' way out: rows of `out` that are no multiple of 64
+// bytes long take twice the write requests.  Against bits as 0 / 1 with the rows' weights counted on the way, half words read
+// from LDS and tiles dealt to the XCDs one by one, in us: 16384 x 16384, m = 256 284 -> 191, m = 4096 656 -> 622, m = 16384
+// 1808 -> 1785; 16384 x 10007, m = 256 255 -> 154, m = 4096 479 -> 420; 4096 x 4096, m = 1024 23.3 -> 18.3.  Bands of one or
+// eight tile rows: 435, 428 at 16384 x 10007, m = 4096.
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-constexpr int kGramRows = 128, kGramCols = 128, kGramChunk = 16;
+constexpr int kGramRows = 128, kGramCols = 128, kGramChunk = 16;      // chunk: code words per row
+constexpr int kGramPitch = kGramChunk / 2 + 1;                        // LDS row, in 16-byte units
+constexpr unsigned kGramBand = 4;                                     // tile rows per band (see the kernel)
 
-// the 32 bits of w as 32 fp4 numbers (0 or 1.0) in four dwords
-__device__ __forceinline__ intx8 spread_bits_fp4(unsigned w)
+// the 32 bits of w as 32 fp4 numbers (+1.0 or -1.0) in four dwords
+__device__ __forceinline__ intx8 spread_bits_fp4(unsigned w, unsigned sign, unsigned one)
 {
     intx8 f = {0, 0, 0, 0, 0, 0, 0, 0};
-    f[0] = (int)((w << 1) & 0x22222222u);
-    f[1] = (int)(w & 0x22222222u);
-    f[2] = (int)((w >> 1) & 0x22222222u);
-    f[3] = (int)((w >> 2) & 0x22222222u);
+    f[3] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);      // (w & sign) | one
+    w += w;
+    f[2] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
+    w += w;
+    f[1] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
+    w += w;
+    f[0] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
     return f;
 }
 
-__global__ void __launch_bounds__(256) hamming_gram_kernel(const unsigned long long* __restrict__ a, long long na,
-                                                           const unsigned long long* __restrict__ b, long long nb,
-                                                           int words, float inv_m, float* __restrict__ out)
+__global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __restrict__ a, long long na, const uintx4* __restrict__ b,
+                                                           long long nb, int words, float inv_m, unsigned gx, unsigned gy, float* __restrict__ out)
 {
-    __shared__ unsigned long long sa[kGramRows][kGramChunk + 1];
-    __shared__ unsigned long long sb[kGramCols][kGramChunk + 1];
-    __shared__ int weight_a[kGramRows];
+    __shared__ uintx4 sa[kGramRows * kGramPitch];
+    __shared__ uintx4 sb[kGramCols * kGramPitch];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wr = wave >> 1, wc = wave & 1, g = lane >> 5, l32 = lane & 31;
-    const long long i0 = (long long)blockIdx.y * kGramRows, j0 = (long long)blockIdx.x * kGramCols;
+    // Tiles in bands of four tile rows, column by column, and an equal run of that order per XCD (workgroups go to the eight
+    // XCDs in turn): the tiles in flight on an XCD share their codes in its L2, and the two halves of a 128-byte line of
+    // `out` that straddles two tiles (rows of any length are allowed) meet there instead of leaving two L2s in pieces
+    const unsigned total = gx * gy, run = (total + 7) >> 3;
+    const unsigned tile = (blockIdx.x & 7) * run + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= run || tile >= total) return;
+    const unsigned band = tile / (kGramBand * gx), in_band = tile - band * kGramBand * gx;
+    const unsigned height = gy - kGramBand * band < kGramBand ? gy - kGramBand * band : kGramBand;
+    const unsigned tj = in_band / height, ti = kGramBand * band + in_band - tj * height;
+    const long long i0 = (long long)ti * kGramRows, j0 = (long long)tj * kGramCols;
     floatx16 acc[2][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -121,75 +140,81 @@ __global__ void __launch_bounds__(256) hamming_gram_kernel(const unsigned long l
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.0f;
-    int wa[2] = {0, 0}, wb[2] = {0, 0};
-    const int one = 0x7f7f7f7f;                      // scale exponents (E8M0): 2^0
-    // this lane's half words: row (.. + l32) of each tile, 32-bit half g of word k
-    const unsigned* ha[2];
-    const unsigned* hb[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        ha[t] = reinterpret_cast<const unsigned*>(&sa[wr * 64 + t * 32 + l32][0]) + g;
-        hb[t] = reinterpret_cast<const unsigned*>(&sb[wc * 64 + t * 32 + l32][0]) + g;
-    }
+    const int scale = 0x7f7f7f7f;                    // scale exponents (E8M0): 2^0
+    unsigned sign = 0x88888888u, one = 0x22222222u;
+    asm("" : "+v"(sign), "+v"(one));                 // in vector registers: scalar operands halve the issue rate
 
-    // staging: 128 rows x 16 words per operand, 256 threads: 8 words per thread and operand
-    const int srow = threadIdx.x >> 4, scol = threadIdx.x & 15;
-    for (int k0 = 0; k0 < words; k0 += kGramChunk) {
-        unsigned long long pa[8], pb[8];
-        const bool in_k = k0 + scol < words;
+    // staging: 128 rows of 8 16-byte pieces per operand, four pieces per thread and operand; rows and pieces past the end
+    // are read from the last one (they reach no stored result)
+    const int srow = threadIdx.x >> 3, scol = threadIdx.x & 7;
+    const int pieces = words >> 1;                   // 16-byte pieces per row (words is a multiple of 4)
+    const uintx4* ra[4];
+    const uintx4* rb[4];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            pa[t] = (in_k && i0 + t * 16 + srow < na) ? a[(i0 + t * 16 + srow) * words + k0 + scol] : 0ull;
-            pb[t] = (in_k && j0 + t * 16 + srow < nb) ? b[(j0 + t * 16 + srow) * words + k0 + scol] : 0ull;
-        }
+    for (int t = 0; t < 4; ++t) {
+        const long long i = i0 + t * 32 + srow, j = j0 + t * 32 + srow;
+        ra[t] = a + (i < na ? i : na - 1) * pieces;
+        rb[t] = b + (j < nb ? j : nb - 1) * pieces;
+    }
+    uintx4 pa[4], pb[4];
+    auto load = [&](int piece0) {
+        const int c = piece0 + scol < pieces ? piece0 + scol : pieces - 1;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            sa[t * 16 + srow][scol] = pa[t];
-            sb[t * 16 + srow][scol] = pb[t];
+        for (int t = 0; t < 4; ++t) { pa[t] = ra[t][c]; pb[t] = rb[t][c]; }
+    };
+    load(0);
+    const uintx4* ha = sa + (wr * 64 + l32) * kGramPitch + g;
+    const uintx4* hb = sb + (wc * 64 + l32) * kGramPitch + g;
+    for (int p0 = 0; p0 < pieces; p0 += kGramChunk / 2) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            sa[(t * 32 + srow) * kGramPitch + scol] = pa[t];
+            sb[(t * 32 + srow) * kGramPitch + scol] = pb[t];
         }
         __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < kGramChunk; ++k) {
-            intx8 fa[2], fb[2];
+        if (p0 + kGramChunk / 2 < pieces) load(p0 + kGramChunk / 2);
+        const int steps = pieces - p0 < kGramChunk / 2 ? pieces - p0 : kGramChunk / 2;
+        for (int s = 0; s < steps; s += 2) {
+            uintx4 qa[2], qb[2];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const unsigned xa = ha[t][2 * k], xb = hb[t][2 * k];
-                wa[t] += __popc(xa);
-                wb[t] += __popc(xb);
-                fa[t] = spread_bits_fp4(xa);
-                fb[t] = spread_bits_fp4(xb);
+            for (int t = 0; t < 2; ++t) { qa[t] = ha[t * 32 * kGramPitch + s]; qb[t] = hb[t * 32 * kGramPitch + s]; }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                intx8 fa[2], fb[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    fa[t] = spread_bits_fp4(qa[t][k], sign, one);
+                    fb[t] = spread_bits_fp4(qb[t][k], sign, one);
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[t], fb[u], acc[t][u], 4, 4, 0, scale, 0, scale);
             }
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    acc[t][u] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[t], fb[u], acc[t][u], 4, 4, 0, one, 0, one);
         }
         __syncthreads();
     }
-    // a row's weight is the sum of what the two lane groups counted
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        wa[t] += lane_xor_i<32>(wa[t]);
-        wb[t] += lane_xor_i<32>(wb[t]);
-    }
-    if (wc == 0 && g == 0) {
-        weight_a[wr * 64 + l32] = wa[0];
-        weight_a[wr * 64 + 32 + l32] = wa[1];
-    }
-    __syncthreads();
     // result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its 32 x 32 tile
+    const int m = words * 64;
+    const long long i = i0 + wr * 64 + 4 * g, j = j0 + wc * 64 + l32;
+    float* dst = out + i * nb + j;
+    const int rows = na - i < 64 ? (int)(na - i) : 64, cols = nb - j < 64 ? (int)(nb - j) : 64;      // what is left below and right of it
+    auto store = [&](auto whole) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int rl = wr * 64 + t * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                const long long i = i0 + rl, j = j0 + wc * 64 + u * 32 + l32;
-                const int dh = weight_a[rl] + wb[u] - 2 * (int)acc[t][u][v];
-                if (i < na && j < nb) out[i * nb + j] = 1.0f - (float)dh * inv_m;
+                const int r = t * 32 + 8 * (v >> 2) + (v & 3);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int dh = (m - (int)acc[t][u][v]) >> 1;
+                    if (decltype(whole)::value || (r < rows && u * 32 < cols)) dst[r * nb + u * 32] = 1.0f - (float)dh * inv_m;
+                }
             }
+    };
+    if (i0 + kGramRows <= na && j0 + kGramCols <= nb) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const unsigned long long* b, long long nb, int m,
@@ -197,9 +222,9 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
 {
     if (na <= 0 || nb <= 0) return hipSuccess;
     const long long gx = (nb + kGramCols - 1) / kGramCols, gy = (na + kGramRows - 1) / kGramRows;
-    if (gx > 0x7fffffffLL || gy > 65535) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(hamming_gram_kernel, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, s, a, na, b, nb, m / 64,
-                       1.0f / (float)m, out);
+    if (gy > 65535 || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;      // 2^24 tiles are 1 TiB of results
+    hipLaunchKernelGGL(hamming_gram_kernel, dim3((unsigned)((gx * gy + 7) / 8 * 8)), dim3(256), 0, s, reinterpret_cast<const uintx4*>(a), na,
+                       reinterpret_cast<const uintx4*>(b), nb, m / 64, 1.0f / (float)m, (unsigned)gx, (unsigned)gy, out);
     return hipGetLastError();
 }
 }  // namespace spinner

@@ -165,6 +165,24 @@ def test_angular_gram_is_exact_on_its_codes(gpu, oracle, na, nb, m):
     assert np.all(np.diag(got[: min(na, nb), : min(na, nb)]) == 1.0)
 
 
+@pytest.mark.parametrize("na,nb,m", [(1, 1, 256), (128, 128, 768), (1100, 643, 1280), (130, 2050, 256), (2500, 3, 1024)])
+def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
+    # 128 x 128 tiles in bands of four tile rows (a shorter last band), dealt to the XCDs in runs; code words in chunks of
+    # sixteen (a shorter last chunk): every entry, from the Hamming distance counted in numpy
+    rng = np.random.default_rng(na * 7 + nb + m)
+    ca = rng.integers(-2**63, 2**63 - 1, (na, m // 64), dtype=np.int64)
+    cb = rng.integers(-2**63, 2**63 - 1, (nb, m // 64), dtype=np.int64)
+    cb[-1] = ~ca[0]                                              # every bit differs
+    cb[0] = ca[-1]                                               # none does (the two meet at na = nb = 1: then none)
+    got = gpu.b.spinner_angular_gram(gpu.torch.from_numpy(ca).to(gpu.dev), gpu.torch.from_numpy(cb).to(gpu.dev), m).cpu().numpy()
+    ba = np.unpackbits(ca.view(np.uint8), axis=1).astype(np.float32)
+    bb = np.unpackbits(cb.view(np.uint8), axis=1).astype(np.float32)
+    dh = ba.sum(1)[:, None] + bb.sum(1)[None] - 2 * ba @ bb.T    # whole numbers below 2^24: exact in fp32
+    # one product and one subtraction in fp32 (or one fused step): two roundings of numbers up to 1
+    assert np.abs(got.astype(np.float64) - (1.0 - dh.astype(np.float64) / m)).max() <= 2.0 ** -23
+    assert got[-1, 0] == 1.0
+
+
 def test_angular_kernel_end_to_end(gpu, oracle):
     # pairs of known angle: codes on the GPU, Gram on the GPU, against 1 - theta / pi (Section 5) and against
     # the oracle's estimate from its own sign bits
