@@ -55,6 +55,84 @@ __device__ __forceinline__ void hash_ar_b_to_a(float (&v)[G::R], float4* pa, flo
     wave_lds_fence();
 }
 
+// Largest value over the 2^LB lanes of each vector, in all of them.  Rows of 16 lanes combine by DPP forms (neighbours,
+// pairs, mirrored halves, mirrored rows), rows by a swap of the odd rows of one copy with the even rows of another.
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float m)
+{
+    return __builtin_fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), CTRL, 0xF, 0xF, true)));
+}
+template <int LB>
+__device__ __forceinline__ float lanes_max(float m)
+{
+    static_assert(LB == 4 || LB == 5, "one or two rows of 16 lanes per vector");
+    m = dpp_max<0xB1>(m);       // quad_perm:[1,0,3,2]
+    m = dpp_max<0x4E>(m);       // quad_perm:[2,3,0,1]
+    m = dpp_max<0x141>(m);      // row_half_mirror
+    m = dpp_max<0x140>(m);      // row_mirror
+    if constexpr (LB == 5) {
+        float a = m, b = m;
+        lane_swap<4>(a, b);
+        m = __builtin_fmaxf(a, b);
+    }
+    return m;
+}
+
+// Buckets of the wave's TPW vectors from layout B (register j of lane l holds element l + (j << r)): the largest |y_i| first,
+// as a value alone, then the place that holds it.  Most of the search is scalar: a comparison of one register against the
+// maximum leaves the lanes that hold it as a mask, so the first register with a bit of a vector's lanes set, and its lowest
+// bit, is the lowest index; its sign is read from that lane.  Registers are searched only in the groups of eight whose own
+// maximum is the vector's.  (Carrying value and index through every comparison took a compare and two selects per register
+// and about forty instructions per exchange between lanes, all of them at half the rate of an addition: n = 1024, L = 16,
+// batch 65536: 723 -> 700 us; what is left is 30 additions at 2.6 cycles and three flips at 4.4 per element.)
+template <typename G>
+__device__ __forceinline__ void hash_ar_bucket(const float (&v)[G::R], long long wvec, const HashParams& p, int triple)
+{
+    constexpr int R = G::R, LANES = G::LANES, GROUP = 8;
+    static_assert(G::LB == G::r && R % GROUP == 0, "a lane's registers step over whole runs of lanes");
+    float gm[R / GROUP];
+#pragma unroll
+    for (int g = 0; g < R / GROUP; ++g) {
+        gm[g] = __builtin_fmaxf(__builtin_fabsf(v[GROUP * g]), __builtin_fabsf(v[GROUP * g + 1]));
+#pragma unroll
+        for (int j = 2; j < GROUP; j += 2)
+            gm[g] = __builtin_fmaxf(__builtin_fmaxf(gm[g], __builtin_fabsf(v[GROUP * g + j])), __builtin_fabsf(v[GROUP * g + j + 1]));
+    }
+    float top = gm[0];
+#pragma unroll
+    for (int g = 1; g < R / GROUP; ++g) top = __builtin_fmaxf(top, gm[g]);
+    top = lanes_max<G::LB>(top);
+
+    constexpr unsigned long long ONE = (LANES < 64 ? (1ull << LANES) : 0ull) - 1ull;      // lanes of the first vector
+    unsigned long long open = ~0ull;                 // lanes of the vectors whose place is not found yet
+    int bucket[G::TPW];
+#pragma unroll
+    for (int q = 0; q < G::TPW; ++q) bucket[q] = 0;  // nothing compares equal (every coordinate NaN): bucket 0
+#pragma unroll
+    for (int g = 0; g < R / GROUP; ++g) {
+        if ((__ballot(gm[g] == top) & open) == 0) continue;
+#pragma unroll
+        for (int j = GROUP * g; j < GROUP * (g + 1); ++j) {
+            const unsigned long long hit = __ballot(__builtin_fabsf(v[j]) == top) & open;
+            if (hit == 0) continue;
+#pragma unroll
+            for (int q = 0; q < G::TPW; ++q) {
+                const unsigned long long mine = hit & (ONE << (q * LANES));
+                if (mine) {
+                    const int at = __builtin_ctzll(mine);
+                    const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[j]), at));
+                    bucket[q] = (at & (LANES - 1)) + (j << G::r) + (y < 0.0f ? 1 << G::NT : 0);
+                    open &= ~(ONE << (q * LANES));
+                }
+            }
+        }
+    }
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < G::TPW; ++q)
+        if (lane == q && wvec + q < p.batch) p.out_idx[(wvec + q) * p.L + triple] = bucket[q];
+}
+
 template <typename G>
 __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams p)
 {
@@ -62,7 +140,8 @@ __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int g = lane >> G::LB, l = lane & (G::LANES - 1);
-    const long long vec = ((long long)blockIdx.x * G::WAVES + wave) * G::TPW + g;
+    const long long wvec = ((long long)blockIdx.x * G::WAVES + __builtin_amdgcn_readfirstlane(wave)) * G::TPW;      // first vector of the wave
+    const long long vec = wvec + g;
     const bool active = vec < p.batch;
 
     __shared__ float4 lds_store[G::WAVES * G::TPW * G::VEC_WORDS / 4];
@@ -109,25 +188,7 @@ __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams 
         hash_ar_stages<G>(v);
         hash_ar_shared_lane_stages<G>(v, l);
 
-        // layout B: register j holds element ebase + (j << r); increasing j is increasing index, strict '>' keeps the lowest
-        const int ebase = (l & (R - 1)) + ((l >> r) << (2 * r));
-        float best = v[0];
-        int best_i = ebase;
-#pragma unroll
-        for (int j = 1; j < R; ++j) {
-            const bool take = __builtin_fabsf(v[j]) > __builtin_fabsf(best);
-            best = take ? v[j] : best;
-            best_i = take ? (ebase + (j << r)) : best_i;
-        }
-        static_for<0, G::LB>([&](auto b) {
-            const float ov = lane_xor<(1 << b.value)>(best);
-            const int oi = lane_xor_i<(1 << b.value)>(best_i);
-            const float fa = __builtin_fabsf(ov), fb = __builtin_fabsf(best);
-            const bool take = (fa > fb) || (fa == fb && oi < best_i);
-            best = take ? ov : best;
-            best_i = take ? oi : best_i;
-        });
-        if (active && l == 0) p.out_idx[vec * p.L + t] = best_i + ((best < 0.0f) ? n : 0);
+        hash_ar_bucket<G>(v, wvec, p, t);
     }
 }
 

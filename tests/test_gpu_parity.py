@@ -282,6 +282,33 @@ def test_hash_above_the_fused_range_on_constructed_inputs(gpu):
     assert got[-3] == 5 and got[-2] == 131072 + n and got[-1] == 0
 
 
+@pytest.mark.parametrize("n", [256, 1024])
+def test_hash_from_sign_words_on_constructed_inputs(gpu, n):
+    # D = I as packed words: x = H z for sums z of few unit vectors gives y = z exactly (entries are multiples of a power of
+    # two).  Several vectors share a wave and are searched together: maxima in every group of registers, at the ends, of
+    # either sign, exact ties across registers, lanes and signs (lowest index), the zero vector, a NaN vector (bucket 0)
+    t = gpu.torch
+    i = np.arange(n)
+    H = 1.0 - 2.0 * (np.array([bin(v).count("1") & 1 for v in range(n)])[i[:, None] & i[None]])
+    z, want = [], []
+    for j in list(range(0, n, 37)) + [n - 1]:
+        for s in (1.0, -1.0):
+            row = np.zeros(n); row[j] = s; z.append(row); want.append(j + (n if s < 0 else 0))
+    rng = np.random.default_rng(n)
+    for _ in range(60):
+        at = np.sort(rng.choice(n, 4, replace=False))
+        val = rng.choice([-1.0, 1.0], 4)
+        row = np.zeros(n); row[at] = val; z.append(row); want.append(at[0] + (n if val[0] < 0 else 0))
+    z.append(np.zeros(n)); want.append(0)
+    x = (np.array(z) @ H / math.sqrt(n)).astype(np.float32)
+    x = np.concatenate([x, np.full((1, n), np.nan, dtype=np.float32), x[:3]])
+    want = np.array(want + [0] + want[:3])
+    assert len(want) % 4                                       # the last wave is not full
+    signs = gpu.b.spinner_pack_signs(t.ones((2, 3, n), dtype=t.float32, device=gpu.dev))
+    got = gpu.b.spinner_hash_signs(_to(gpu, x), signs, 2).cpu().numpy()
+    assert np.array_equal(got, np.stack([want, want], 1))
+
+
 def test_hash_rules_on_constructed_inputs(gpu):
     # D = I, x = +-(column j of normalised H)  ->  bucket j / j + n ; zero vector -> bucket 0 ;
     # exact tie -> lowest index.
