@@ -8,6 +8,7 @@ raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -49,7 +50,7 @@ if not os.path.exists(LIB_PATH):
 # PyTorch ships its own HIP runtime and loads it by path; the library must bind to that same copy (it owns
 # the device memory and the streams handed in here), so torch is loaded first and the library's
 # dependency on libamdhip64 then resolves to the runtime already in the process.
-import torch  # noqa: E402,F401
+import torch  # noqa: E402
 
 lib = ctypes.CDLL(LIB_PATH)
 _vp = ctypes.c_void_p
@@ -151,19 +152,41 @@ def spinner_version() -> int:
 
 
 def spinner_workspace_bytes(n: int, batch: int, m: int, epilogue) -> int:
-    return int(lib.spinner_workspace_bytes(int(n), int(batch), int(m), _epi(epilogue)))
+    return _workspace_bytes(int(n), int(batch), int(m), _epi(epilogue))
+
+
+# The sizes that every call looks up are pure functions of whole numbers: the last ones asked for are remembered.
+@functools.lru_cache(maxsize=256)
+def _workspace_bytes(n, batch, m, epi):
+    return int(lib.spinner_workspace_bytes(n, batch, m, epi))
+
+
+@functools.lru_cache(maxsize=256)
+def _signs_bytes(n, L):
+    return int(lib.spinner_signs_bytes(n, L))
+
+
+@functools.lru_cache(maxsize=256)
+def _layer_workspace_bytes(n, batch):
+    return int(lib.spinner_layer_workspace_bytes(n, batch))
 
 
 def _epi(e) -> int:
     return EPILOGUES[e] if isinstance(e, str) else int(e)
 
 
-def _stream_handle(stream):
-    import torch
+# The handle of torch's current stream without the Stream object that torch.cuda.current_stream() makes of it on every
+# call (1.2 us of the 10 us that a small call took); a torch without these two functions takes the long way.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+
+def _stream_handle(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is not None and _current_device is not None:
+        return _current_raw_stream(_current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check_tensor(t, name, dtype):
@@ -178,8 +201,6 @@ def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, w
     ``out`` (and the workspace when one is needed) unless given.  Asynchronous
     on ``stream`` (default: torch's current stream).
     """
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -211,8 +232,6 @@ def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, w
 
 def spinner_hash(x, diag_sets, out_idx=None, stream=None):
     """Cross-polytope buckets, int32 [batch][L], for L diagonal triples diag_sets fp32 [L][3][n]."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     batch, n = x.shape
@@ -236,8 +255,6 @@ def spinner_hash_workspace_bytes(n: int, batch: int) -> int:
 
 
 def _hash_workspace(x, n, batch, workspace):
-    import torch
-
     need = spinner_hash_workspace_bytes(n, batch)
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
@@ -248,8 +265,6 @@ def _hash_workspace(x, n, batch, workspace):
 
 def spinner_hash_ws(x, diag_sets, out_idx=None, workspace=None, stream=None):
     """spinner_hash for every n up to 2^24 (a workspace tensor is made when none is given and one is needed)."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     batch, n = x.shape
@@ -272,8 +287,6 @@ def spinner_hash_ws(x, diag_sets, out_idx=None, workspace=None, stream=None):
 
 def spinner_hash_signs_ws(x, signs, L, out_idx=None, workspace=None, stream=None):
     """spinner_hash_signs for every n up to 2^24."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     if signs.numel() < spinner_signs_bytes(n, L):
@@ -293,13 +306,11 @@ def spinner_hash_signs_ws(x, signs, L, out_idx=None, workspace=None, stream=None
 
 
 def spinner_signs_bytes(n: int, L: int) -> int:
-    return int(lib.spinner_signs_bytes(int(n), int(L)))
+    return _signs_bytes(int(n), int(L))
 
 
 def spinner_pack_signs(diag_sets, stream=None):
     """Pack fp32 +-1 diagonals [L][3][n] into the library's sign words (uint8 CUDA tensor, opaque)."""
-    import torch
-
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     if diag_sets.dim() != 3 or diag_sets.shape[1] != 3:
         raise ValueError("diag_sets must be [L][3][n]")
@@ -317,8 +328,6 @@ def spinner_pack_signs(diag_sets, stream=None):
 def spinner_apply_signs(x, signs, m=None, epilogue="none", scale=1.0, out=None, workspace=None, stream=None,
                         triple=0):
     """spinner_apply for +-1 diagonals given as packed sign words (see spinner_pack_signs)."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     m = n if m is None else int(m)
@@ -348,8 +357,6 @@ def spinner_apply_signs(x, signs, m=None, epilogue="none", scale=1.0, out=None, 
 
 def spinner_hash_signs(x, signs, L, out_idx=None, stream=None):
     """spinner_hash for +-1 diagonals given as packed sign words of L triples."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     if signs.numel() < spinner_signs_bytes(n, L):
@@ -368,8 +375,6 @@ def spinner_hash_signs(x, signs, L, out_idx=None, stream=None):
 
 def spinner_stream_copy(src, dst, stream=None):
     """dst[:] = src with the library's plain copy kernel (measurement aid)."""
-    import torch
-
     _check_tensor(src, "src", torch.float32)
     _check_tensor(dst, "dst", torch.float32)
     if src.numel() != dst.numel():
@@ -398,8 +403,6 @@ def spinner_code_position(coordinate: int):
 
 
 def _codes_out(x, m, codes):
-    import torch
-
     batch = x.shape[0]
     nbytes = spinner_code_bytes(m)
     if nbytes == 0:
@@ -414,8 +417,6 @@ def _codes_out(x, m, codes):
 
 
 def _codes_workspace(x, workspace):
-    import torch
-
     batch, n = x.shape
     need = spinner_codes_workspace_bytes(n, batch)
     if need and workspace is None:
@@ -427,8 +428,6 @@ def _codes_workspace(x, workspace):
 
 def spinner_sign_codes(x, d1, d2, d3, m=None, codes=None, workspace=None, stream=None):
     """Sign bits of the first m coordinates of H D3 H D2 H D1 x, int64 CUDA tensor [batch][m/64]."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -445,8 +444,6 @@ def spinner_sign_codes(x, d1, d2, d3, m=None, codes=None, workspace=None, stream
 
 def spinner_sign_codes_signs(x, signs, m=None, codes=None, workspace=None, stream=None, triple=0):
     """spinner_sign_codes for +-1 diagonals given as packed sign words (see spinner_pack_signs)."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     m = n if m is None else int(m)
@@ -464,8 +461,6 @@ def spinner_sign_codes_signs(x, signs, m=None, codes=None, workspace=None, strea
 
 def spinner_angular_gram(codes_a, codes_b, m, out=None, stream=None):
     """out[i][j] = 1 - Hamming(codes_a[i], codes_b[j]) / m, fp32 CUDA tensor [na][nb]."""
-    import torch
-
     _check_tensor(codes_a, "codes_a", torch.int64)
     _check_tensor(codes_b, "codes_b", torch.int64)
     words = spinner_code_bytes(m) // 8
@@ -492,13 +487,11 @@ def spinner_layer_saved_bytes(n: int, batch: int) -> int:
 
 
 def spinner_layer_workspace_bytes(n: int, batch: int) -> int:
-    return int(lib.spinner_layer_workspace_bytes(int(n), int(batch)))
+    return _layer_workspace_bytes(int(n), int(batch))
 
 
 def spinner_layer_forward(x, d1, d2, d3, scale=1.0, y=None, saved=None, stream=None):
     """y = scale * H D3 H D2 H D1 x and the opaque activations the backward pass needs: returns (y, saved)."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -522,8 +515,6 @@ def spinner_layer_forward(x, d1, d2, d3, scale=1.0, y=None, saved=None, stream=N
 
 def spinner_layer_backward(dy, x, saved, d1, d2, d3, scale=1.0, dx=None, dd=None, workspace=None, stream=None):
     """Gradients for x ([batch][n]) and for the three diagonals ([3][n], summed over the batch): returns (dx, dd)."""
-    import torch
-
     for name, t in (("dy", dy), ("x", x), ("saved", saved), ("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(t, name, torch.float32)
     batch, n = x.shape
@@ -552,8 +543,6 @@ def spinner_sketch_workspace_bytes(n: int, d: int, m: int) -> int:
 
 def spinner_sketch(A, w, d1, d2, d3, m, scale=1.0, out=None, workspace=None, stream=None):
     """B = scale * (first m rows of H D3 H D2 H D1) diag(w) A for A fp32 [n][d]; w may be None.  Returns B [m][d]."""
-    import torch
-
     _check_tensor(A, "A", torch.float32)
     for name, t in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(t, name, torch.float32)
@@ -585,8 +574,6 @@ def spinner_sketch_gram_static_limit() -> int:
 
 def spinner_sketch_gram_static(B, out, stream=None):
     """G = B^T B into the caller's `out` [d][d]; the call allocates nothing (the library's built-in scratch)."""
-    import torch
-
     _check_tensor(B, "B", torch.float32)
     _check_tensor(out, "out", torch.float32)
     m, d = B.shape
@@ -604,8 +591,6 @@ def spinner_sketch_gram_workspace_bytes(m: int, d: int) -> int:
 
 def spinner_sketch_gram(B, out=None, workspace=None, stream=None):
     """G = B^T B, fp32 CUDA tensor [d][d]."""
-    import torch
-
     _check_tensor(B, "B", torch.float32)
     m, d = B.shape
     if out is None:
@@ -629,8 +614,6 @@ def spinner_sketch_gram(B, out=None, workspace=None, stream=None):
 def spinner_apply_blocks(x, diag_sets, m=None, epilogue="none", scale=1.0, out=None, workspace=None, stream=None):
     """L independent triples (diag_sets fp32 [L][3][n]) applied to the same x, their m-row blocks side by side:
     out [batch][L m] (epilogue none) or [batch][2 L m] (cos block | sin block)."""
-    import torch
-
     _check_tensor(x, "x", torch.float32)
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     batch, n = x.shape
@@ -661,8 +644,6 @@ def spinner_apply_blocks(x, diag_sets, m=None, epilogue="none", scale=1.0, out=N
 
 def spinner_struct_prepare(kind, params, n, stream=None):
     """Opaque spectrum (uint8 CUDA tensor) of a structured third block from its generating vector (fp32 CUDA tensor)."""
-    import torch
-
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
     _check_tensor(params, "params", torch.float32)
     nbytes = int(lib.spinner_struct_spectrum_bytes(k, int(n)))
@@ -679,8 +660,6 @@ def spinner_struct_prepare(kind, params, n, stream=None):
 
 def spinner_struct_apply(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=None, stream=None):
     """out [batch][m] = scale * (first m rows of G_struct D2 H D1 x)."""
-    import torch
-
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
     for name, t in (("x", x), ("d1", d1), ("d2", d2)):
         _check_tensor(t, name, torch.float32)
@@ -706,8 +685,6 @@ def spinner_struct_workspace_bytes(kind, n: int, batch: int) -> int:
 
 def spinner_struct_apply_ws(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=None, workspace=None, stream=None):
     """spinner_struct_apply for every supported n (a workspace tensor is made when none is given and one is needed)."""
-    import torch
-
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
     for name, t in (("x", x), ("d1", d1), ("d2", d2)):
         _check_tensor(t, name, torch.float32)
