@@ -18,35 +18,34 @@ constexpr int kLayerBackwardWaves = 3;
 
 // `base` must be readable also for a tile past the end of the batch (the callers pass the first vector then and
 // store nothing): loads under a condition end up in a branch each, with waits where the branches join
-template <typename G, int LAY>
+template <typename G, int LAY, bool STREAM>
 __device__ __forceinline__ void tile_load(float (&v)[G::R], const ThreadCtx<G>& c, const float* base)
 {
     const float* src = base + c.base_index(LAY);
 #pragma unroll
     for (int jh = 0; jh < G::R / 4; ++jh) {
-        const float4 t = *reinterpret_cast<const float4*>(src + G::reg_index(LAY, jh * 4));
+        const float4 t = load4<STREAM>(src + G::reg_index(LAY, jh * 4));
         v[jh * 4] = t.x; v[jh * 4 + 1] = t.y; v[jh * 4 + 2] = t.z; v[jh * 4 + 3] = t.w;
     }
 }
 
-template <typename G, int LAY>
+template <typename G, int LAY, bool STREAM>
 __device__ __forceinline__ void tile_store(const float (&v)[G::R], const ThreadCtx<G>& c, float* base, float f)
 {
     float* dst = base + c.base_index(LAY);
 #pragma unroll
     for (int jh = 0; jh < G::R / 4; ++jh)
-        *reinterpret_cast<float4*>(dst + G::reg_index(LAY, jh * 4)) =
-            make_float4(v[jh * 4] * f, v[jh * 4 + 1] * f, v[jh * 4 + 2] * f, v[jh * 4 + 3] * f);
+        store4<STREAM>(dst + G::reg_index(LAY, jh * 4), v[jh * 4] * f, v[jh * 4 + 1] * f, v[jh * 4 + 2] * f, v[jh * 4 + 3] * f);
 }
 
 // acc += g * (tile of `base` in layout LAY)
-template <typename G, int LAY>
+template <typename G, int LAY, bool STREAM>
 __device__ __forceinline__ void tile_mac(float (&acc)[G::R], const float (&g)[G::R], const ThreadCtx<G>& c, const float* base)
 {
     const float* src = base + c.base_index(LAY);
 #pragma unroll
     for (int jh = 0; jh < G::R / 4; ++jh) {
-        const float4 t = *reinterpret_cast<const float4*>(src + G::reg_index(LAY, jh * 4));
+        const float4 t = load4<STREAM>(src + G::reg_index(LAY, jh * 4));
         acc[jh * 4] = __builtin_fmaf(g[jh * 4], t.x, acc[jh * 4]);
         acc[jh * 4 + 1] = __builtin_fmaf(g[jh * 4 + 1], t.y, acc[jh * 4 + 1]);
         acc[jh * 4 + 2] = __builtin_fmaf(g[jh * 4 + 2], t.z, acc[jh * 4 + 2]);
@@ -98,7 +97,7 @@ __device__ __forceinline__ void layer_ctx(ThreadCtx<G>& c, long long& slot)
 
 // One vector per tile.  The held values carry the tracked lane sign after an odd number of
 // transforms (see lane_stage_fmac_dpp); it is folded into the factors of what is stored.
-template <typename G>
+template <typename G, bool STREAM>
 __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardParams p)
 {
     constexpr int NT = G::NT;
@@ -113,18 +112,18 @@ __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardP
     const float sgn = tracked_sign<G, 0, float>(c);
 
     float v[G::R];
-    tile_load<G, G::layout_after(0)>(v, c, p.x + off);
+    tile_load<G, G::layout_after(0), STREAM>(v, c, p.x + off);
     spinner_step<G, NT, 0, G::layout_after(0), true, true, false, false>(v, c, p.d[0], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(1)>(v, c, p.saved1 + off, sgn);
+    if (active) tile_store<G, G::layout_after(1), STREAM>(v, c, p.saved1 + off, sgn);
     spinner_step<G, NT, 0, G::layout_after(1), true, false, true, false>(v, c, p.d[1], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(2)>(v, c, p.saved2 + off, 1.0f);
+    if (active) tile_store<G, G::layout_after(2), STREAM>(v, c, p.saved2 + off, 1.0f);
     spinner_step<G, NT, 0, G::layout_after(2), true, false, false, false>(v, c, p.d[2], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(3)>(v, c, p.y + off, p.factor * sgn);
+    if (active) tile_store<G, G::layout_after(3), STREAM>(v, c, p.y + off, p.factor * sgn);
 }
 
 // Slot s (one tile position of one workgroup) handles vectors s, s + slots, s + 2 slots, ... and
 // keeps its three per-coordinate sums in registers; they are written once at the end.
-template <typename G>
+template <typename G, bool STREAM>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu((G::R == 16 && G::WB > 0) ? kLayerBackwardWaves : (G::R == 32 ? 2 : 1))))
 layer_backward_kernel(LayerBackwardParams p)
 {
@@ -155,16 +154,16 @@ layer_backward_kernel(LayerBackwardParams p)
         const bool active = vec < p.batch;
         const long long off = (active ? vec : 0) * (long long)n;
         float g[R];
-        tile_load<G, G::layout_after(0)>(g, c, p.dy + off);
+        tile_load<G, G::layout_after(0), STREAM>(g, c, p.dy + off);
         if constexpr (PREFETCH) {
             // each saved tile is asked for one transform ahead of its use (the scheduling barriers keep the loads
             // where they are written: left alone, the compiler moves each next to its use to save registers)
             float ta[R];
-            tile_load<G, L1>(ta, c, p.saved2 + off);
+            tile_load<G, L1, STREAM>(ta, c, p.saved2 + off);
             __builtin_amdgcn_sched_barrier(0);
             spinner_step<G, NT, 0, G::layout_after(0), false, true, false, false>(g, c, nullptr, nullptr, 0, lds);
             if (active) tile_fma<R>(acc3, g, ta);
-            tile_load<G, L2>(ta, c, p.saved1 + off);
+            tile_load<G, L2, STREAM>(ta, c, p.saved1 + off);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (GROUPED_DIAG) {
                 tile_scale<G, L1, true>(g, c, p.d[2]);
@@ -173,7 +172,7 @@ layer_backward_kernel(LayerBackwardParams p)
                 spinner_step<G, NT, 0, L1, true, false, true, false>(g, c, p.d[2], nullptr, 0, lds);
             }
             if (active) tile_fma<R>(acc2, g, ta);
-            tile_load<G, L3>(ta, c, p.x + off);
+            tile_load<G, L3, STREAM>(ta, c, p.x + off);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (GROUPED_DIAG) {
                 tile_scale<G, L2, true>(g, c, p.d[1]);
@@ -184,11 +183,11 @@ layer_backward_kernel(LayerBackwardParams p)
             if (active) tile_fma<R>(acc1, g, ta);
         } else {
             spinner_step<G, NT, 0, G::layout_after(0), false, true, false, false>(g, c, nullptr, nullptr, 0, lds);
-            if (active) tile_mac<G, L1>(acc3, g, c, p.saved2 + off);
+            if (active) tile_mac<G, L1, STREAM>(acc3, g, c, p.saved2 + off);
             spinner_step<G, NT, 0, L1, true, false, true, false>(g, c, p.d[2], nullptr, 0, lds);
-            if (active) tile_mac<G, L2>(acc2, g, c, p.saved1 + off);
+            if (active) tile_mac<G, L2, STREAM>(acc2, g, c, p.saved1 + off);
             spinner_step<G, NT, 0, L2, true, false, false, false>(g, c, p.d[1], nullptr, 0, lds);
-            if (active) tile_mac<G, L3>(acc1, g, c, p.x + off);
+            if (active) tile_mac<G, L3, STREAM>(acc1, g, c, p.x + off);
         }
         if (active) {
             // dx = factor * D1 t3
@@ -205,23 +204,23 @@ layer_backward_kernel(LayerBackwardParams p)
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int jh = 0; jh < R / 4; ++jh)
-                    *reinterpret_cast<float4*>(dst + G::reg_index(L3, jh * 4)) =
-                        make_float4(g[jh * 4] * f * t[jh].x, g[jh * 4 + 1] * f * t[jh].y, g[jh * 4 + 2] * f * t[jh].z, g[jh * 4 + 3] * f * t[jh].w);
+                    store4<STREAM>(dst + G::reg_index(L3, jh * 4), g[jh * 4] * f * t[jh].x, g[jh * 4 + 1] * f * t[jh].y,
+                                   g[jh * 4 + 2] * f * t[jh].z, g[jh * 4 + 3] * f * t[jh].w);
             } else {
 #pragma unroll
                 for (int jh = 0; jh < R / 4; ++jh) {
                     const float4 t = *reinterpret_cast<const float4*>(d1 + G::reg_index(L3, jh * 4));
-                    *reinterpret_cast<float4*>(dst + G::reg_index(L3, jh * 4)) =
-                        make_float4(g[jh * 4] * f * t.x, g[jh * 4 + 1] * f * t.y, g[jh * 4 + 2] * f * t.z, g[jh * 4 + 3] * f * t.w);
+                    store4<STREAM>(dst + G::reg_index(L3, jh * 4), g[jh * 4] * f * t.x, g[jh * 4 + 1] * f * t.y, g[jh * 4 + 2] * f * t.z,
+                                   g[jh * 4 + 3] * f * t.w);
                 }
             }
         }
     }
     if (slot < p.slots) {
         float* part = p.partial + slot * 3LL * n;
-        tile_store<G, L3>(acc1, c, part, sgn);            // t3 carries the tracked sign (three transforms)
-        tile_store<G, L2>(acc2, c, part + n, 1.0f);       // t2: two transforms
-        tile_store<G, L1>(acc3, c, part + 2 * n, sgn);    // t1: one transform
+        tile_store<G, L3, false>(acc1, c, part, sgn);            // t3 carries the tracked sign (three transforms)
+        tile_store<G, L2, false>(acc2, c, part + n, 1.0f);       // t2: two transforms
+        tile_store<G, L1, false>(acc3, c, part + 2 * n, sgn);    // t1: one transform
     }
 }
 

@@ -129,6 +129,30 @@ def test_layer_backward_many_vectors_per_slot(gpu, oracle, n, batch):
     _check(oracle, x, d, dy, 1.0, y, dx, dd)
 
 
+@pytest.mark.parametrize("n", [16, 256, 2048, 1 << 14])
+def test_layer_of_large_batches(gpu, n):
+    # from 2^25 (forward) and 2^24 (backward) elements on the kernels carry the non-temporal hint: the same bits per vector as
+    # for a small batch, and diagonal gradients that are the sum of those of two halves below the limits (fp32 running sums
+    # over at most batch / 8192 .. batch / 512 vectors per slot, slots added in fp64: 1e-6 of the norm leaves a factor of five)
+    t = gpu.torch
+    batch = (1 << 25) // n + 3
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n)
+    x = t.randn((batch, n), generator=g, device=gpu.dev)
+    dy = t.randn((batch, n), generator=g, device=gpu.dev)
+    d = 1.0 + 0.5 * t.randn((3, n), generator=g, device=gpu.dev)
+
+    def step(r):
+        y, saved = gpu.b.spinner_layer_forward(x[r], d[0], d[1], d[2], 0.75)
+        return (y, *gpu.b.spinner_layer_backward(dy[r], x[r], saved, d[0], d[1], d[2], 0.75))
+
+    y, dx, dd = step(slice(0, batch))
+    parts = [step(slice(i, min(batch, i + (1 << 23) // n))) for i in range(0, batch, (1 << 23) // n)]
+    assert t.equal(y, t.cat([p[0] for p in parts])) and t.equal(dx, t.cat([p[1] for p in parts]))
+    want = sum(p[2].double() for p in parts)
+    assert float((dd.double() - want).norm() / want.norm()) <= 1e-6
+
+
 def test_layer_special_cases(gpu, oracle):
     n, batch = 1024, 19
     x, d, dy = _case(n, batch, 6200)
