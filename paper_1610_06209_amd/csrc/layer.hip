@@ -83,12 +83,13 @@ hipError_t launch_layer_large_dd(const float* g, const float* a, int log2n, long
     return launch_layer_reduce(partial, slabs, n, 1.0, dd, s);
 }
 
-// Large batches are touched once per call and bypass cache retention (non-temporal hint); what a training step of a smaller
-// one moves (nine tensors of batch * n floats) is partly still in the 256 MB memory-side cache when the next call reads it.
-// Elements (log2) from which on the hint pays; a step without it / with it in both passes, in us, n = 2^12: 2^28 1800 -> 1746
-// (backward 1025 -> 952), 2^26 464 -> 431, 2^25 251 -> 225, 2^24 137 -> 127 (in the backward pass alone 117), 2^23 64 -> 76.
-constexpr int kLayerForwardStreamLog = 25, kLayerBackwardStreamLog = 24;
-static bool layer_streams(int log2n, long long batch, int from_log) { return (batch << log2n) >= (1LL << from_log); }
+// The backward pass of a large batch bypasses cache retention (non-temporal hint on dy, x, the saved activations and dx);
+// what a training step of a smaller one moves (nine tensors of batch * n floats) is partly still in the 256 MB memory-side
+// cache when the next call reads it.  Backward pass inside a step without / with the hint, in us: n = 2^12, batch 65536 1064 ->
+// 960, 16384 295 -> 250, n = 2^10, batch 65536 308 -> 267; whole step at 2^24 elements 137 -> 117, at 2^23 64 -> 76.  The
+// forward pass, which writes three tensors for the one it reads, loses with it (782 -> 852, batch 16384 191 -> 202).
+constexpr int kLayerBackwardStreamLog = 24;
+static bool layer_streams(int log2n, long long batch) { return (batch << log2n) >= (1LL << kLayerBackwardStreamLog); }
 
 template <int NT>
 static hipError_t forward_nt(const LayerForwardParams& p, hipStream_t s)
@@ -97,8 +98,7 @@ static hipError_t forward_nt(const LayerForwardParams& p, hipStream_t s)
     const long long blocks = (p.batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    if (layer_streams(NT, p.batch, kLayerForwardStreamLog)) hipLaunchKernelGGL((layer_forward_kernel<G, true>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
-    else hipLaunchKernelGGL((layer_forward_kernel<G, false>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
+    hipLaunchKernelGGL((layer_forward_kernel<G>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     return hipGetLastError();
 }
 
@@ -123,7 +123,7 @@ static hipError_t backward_nt(const LayerBackwardParams& p, hipStream_t s)
     using G = LayerGeom<NT>;
     const long long blocks = p.slots / G::TILES_PER_WG;
     if (blocks <= 0) return hipSuccess;
-    if (layer_streams(NT, p.batch, kLayerBackwardStreamLog)) hipLaunchKernelGGL((layer_backward_kernel<G, true>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
+    if (layer_streams(NT, p.batch)) hipLaunchKernelGGL((layer_backward_kernel<G, true>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     else hipLaunchKernelGGL((layer_backward_kernel<G, false>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     return hipGetLastError();
 }

@@ -97,7 +97,7 @@ __device__ __forceinline__ void layer_ctx(ThreadCtx<G>& c, long long& slot)
 
 // One vector per tile.  The held values carry the tracked lane sign after an odd number of
 // transforms (see lane_stage_fmac_dpp); it is folded into the factors of what is stored.
-template <typename G, bool STREAM>
+template <typename G>
 __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardParams p)
 {
     constexpr int NT = G::NT;
@@ -112,13 +112,13 @@ __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardP
     const float sgn = tracked_sign<G, 0, float>(c);
 
     float v[G::R];
-    tile_load<G, G::layout_after(0), STREAM>(v, c, p.x + off);
+    tile_load<G, G::layout_after(0), false>(v, c, p.x + off);
     spinner_step<G, NT, 0, G::layout_after(0), true, true, false, false>(v, c, p.d[0], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(1), STREAM>(v, c, p.saved1 + off, sgn);
+    if (active) tile_store<G, G::layout_after(1), false>(v, c, p.saved1 + off, sgn);
     spinner_step<G, NT, 0, G::layout_after(1), true, false, true, false>(v, c, p.d[1], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(2), STREAM>(v, c, p.saved2 + off, 1.0f);
+    if (active) tile_store<G, G::layout_after(2), false>(v, c, p.saved2 + off, 1.0f);
     spinner_step<G, NT, 0, G::layout_after(2), true, false, false, false>(v, c, p.d[2], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(3), STREAM>(v, c, p.y + off, p.factor * sgn);
+    if (active) tile_store<G, G::layout_after(3), false>(v, c, p.y + off, p.factor * sgn);
 }
 
 // Slot s (one tile position of one workgroup) handles vectors s, s + slots, s + 2 slots, ... and
