@@ -883,6 +883,8 @@ spinner_tile_kernel(TileParams p)
     // data touched once bypass cache retention: x and out of the fused kernels, and, in the four-pass schedule,
     // x read by the first pass and what the last pass reads and writes (what lies between is read again soon)
     constexpr bool FIRST_PASS = NSTEPS == 1 && FIRST_DIAG && C >= NT, LAST_PASS = NSTEPS == 1 && !FIRST_DIAG && C < NT;
+    // (feature rows, 2^22 .. 2^27 elements: the hint on the stores 2^9 15.6 -> 12.2 us .. +0 %, 2^11 19.9 -> 15.7 .. +5 %, 2^13
+    // 21.5 -> 16.9 .. +5 %, 2^14 25.5 -> 21.4 .. +4 %, 2^15 +0 .. 10 %)
     // (measured on the four-pass schedule: the hint on the first pass alone +2-3 % at n = 2^17 .. 2^20, on the last pass too +0.4 .. 4 %)
     constexpr bool STREAM_LD = NSTEPS == 3 || FIRST_PASS || LAST_PASS;
     constexpr bool STREAM = NSTEPS == 3 || LAST_PASS;
@@ -989,7 +991,7 @@ spinner_tile_kernel(TileParams p)
                         const float a0 = (float)(v[jh * 4] * (T)lane_factor), a1 = (float)(v[jh * 4 + 1] * (T)lane_factor);
                         const float a2 = (float)(v[jh * 4 + 2] * (T)lane_factor), a3 = (float)(v[jh * 4 + 3] * (T)lane_factor);
                         if (i + 3 < m && (p.out_stride & 3) == 0) {
-                            *reinterpret_cast<float4*>(dst + i) = make_float4(a0, a1, a2, a3);
+                            store4<STREAM>(dst + i, a0, a1, a2, a3);
                         } else {
                             if (i < m) dst[i] = a0;
                             if (i + 1 < m) dst[i + 1] = a1;
@@ -1090,11 +1092,11 @@ spinner_tile_kernel(TileParams p)
                         cs[k] *= p.inv_sqrt_m;
                     }
                     if (full && ((m | so) & 3) == 0) {
-                        *reinterpret_cast<float4*>(dst + i) = make_float4(cs[0], cs[1], cs[2], cs[3]);
-                        *reinterpret_cast<float4*>(dst + so + i) = make_float4(sn[0], sn[1], sn[2], sn[3]);
+                        store4<STREAM>(dst + i, cs[0], cs[1], cs[2], cs[3]);
+                        store4<STREAM>(dst + so + i, sn[0], sn[1], sn[2], sn[3]);
                     } else if (i + 3 < m && ((m | so | p.out_stride) & 3) == 0) {
-                        *reinterpret_cast<float4*>(dst + i) = make_float4(cs[0], cs[1], cs[2], cs[3]);
-                        *reinterpret_cast<float4*>(dst + so + i) = make_float4(sn[0], sn[1], sn[2], sn[3]);
+                        store4<STREAM>(dst + i, cs[0], cs[1], cs[2], cs[3]);
+                        store4<STREAM>(dst + so + i, sn[0], sn[1], sn[2], sn[3]);
                     } else {
         #pragma unroll
                         for (int k = 0; k < 4; ++k)

