@@ -184,8 +184,8 @@ int spinner_hash_signs_ws(const float *x, int n, long batch, int L,
  *   diag_sets  in   device fp32 [L][3][n], order d1, d2, d3 within a triple
  *   workspace  in   spinner_blocks_workspace_bytes(n, batch, m, epilogue) bytes
  * For L > 1, m must be a multiple of 4.  Up to n = 2^14 the L blocks come from one
- * kernel launch that reads x once and keeps it in registers while the triples are
- * applied one after the other (the feature blocks in fp64 as in spinner_apply); above
+ * kernel launch that reads x once (the feature blocks in fp64 as in spinner_apply, at
+ * n = 2^14 one launch per block); above
  * that size every block runs the four-pass path and reads x again.  Otherwise as
  * spinner_apply (which is the case L = 1).
  */
