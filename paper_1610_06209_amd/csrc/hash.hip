@@ -55,15 +55,16 @@ __device__ __forceinline__ void hash_ar_b_to_a(float (&v)[G::R], float4* pa, flo
     wave_lds_fence();
 }
 
-// Largest value over the 2^LB lanes of each vector, in all of them.  Rows of 16 lanes combine by DPP forms (neighbours,
-// pairs, mirrored halves, mirrored rows), rows by a swap of the odd rows of one copy with the even rows of another.
+// Largest of the unsigned numbers in the 2^LB lanes of each vector, in all of them.  Rows of 16 lanes combine by DPP forms
+// (neighbours, pairs, mirrored halves, mirrored rows), rows by a swap of the odd rows of one copy with the even rows of another.
+__device__ __forceinline__ unsigned larger(unsigned a, unsigned b) { return a > b ? a : b; }
 template <int CTRL>
-__device__ __forceinline__ float dpp_max(float m)
+__device__ __forceinline__ unsigned dpp_max(unsigned m)
 {
-    return __builtin_fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), CTRL, 0xF, 0xF, true)));
+    return larger(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, CTRL, 0xF, 0xF, true));
 }
 template <int LB>
-__device__ __forceinline__ float lanes_max(float m)
+__device__ __forceinline__ unsigned lanes_max(unsigned m)
 {
     static_assert(LB == 4 || LB == 5, "one or two rows of 16 lanes per vector");
     m = dpp_max<0xB1>(m);       // quad_perm:[1,0,3,2]
@@ -71,43 +72,74 @@ __device__ __forceinline__ float lanes_max(float m)
     m = dpp_max<0x141>(m);      // row_half_mirror
     m = dpp_max<0x140>(m);      // row_mirror
     if constexpr (LB == 5) {
-        float a = m, b = m;
+        float a = __uint_as_float(m), b = a;
         lane_swap<4>(a, b);
-        m = __builtin_fmaxf(a, b);
+        m = larger(__float_as_uint(a), __float_as_uint(b));
     }
     return m;
 }
 
-// Buckets of the wave's TPW vectors from layout B (register j of lane l holds element l + (j << r)): the largest |y_i| first,
-// as a value alone, then the place that holds it.  Most of the search is scalar: a comparison of one register against the
-// maximum leaves the lanes that hold it as a mask, so the first register with a bit of a vector's lanes set, and its lowest
-// bit, is the lowest index; its sign is read from that lane.  Registers are searched only in the groups of eight whose own
-// maximum is the vector's.  (Carrying value and index through every comparison took a compare and two selects per register
-// and about forty instructions per exchange between lanes, all of them at half the rate of an addition: n = 1024, L = 16,
-// batch 65536: 723 -> 700 us; what is left is 30 additions at 2.6 cycles and three flips at 4.4 per element.)
+// Buckets of the wave's TPW vectors from layout B (register j of lane l holds element l + (j << r)) by the comparisons of
+// spinner_hash_kernel: value and index go through every one, increasing j is increasing index, strict '>' keeps the lowest.
+// A NaN stays where a thread starts with one and is passed over elsewhere.
+template <typename G>
+__device__ __forceinline__ void hash_ar_bucket_by_steps(const float (&v)[G::R], long long wvec, const HashParams& p, int triple)
+{
+    static_assert(G::LB == G::r, "a lane's registers step over whole runs of lanes");
+    const int lane = threadIdx.x & 63, l = lane & (G::LANES - 1);
+    float best = v[0];
+    int best_i = l;
+#pragma unroll
+    for (int j = 1; j < G::R; ++j) {
+        const bool take = __builtin_fabsf(v[j]) > __builtin_fabsf(best);
+        best = take ? v[j] : best;
+        best_i = take ? l + (j << G::r) : best_i;
+    }
+    static_for<0, G::LB>([&](auto b) {
+        const float ov = lane_xor<(1 << b.value)>(best);
+        const int oi = lane_xor_i<(1 << b.value)>(best_i);
+        const float fa = __builtin_fabsf(ov), fb = __builtin_fabsf(best);
+        const bool take = (fa > fb) || (fa == fb && oi < best_i);
+        best = take ? ov : best;
+        best_i = take ? oi : best_i;
+    });
+    const long long vec = wvec + (lane >> G::LB);
+    if (l == 0 && vec < p.batch) p.out_idx[vec * p.L + triple] = best_i + (best < 0.0f ? 1 << G::NT : 0);
+}
+
+// The same with the largest |y_i| first, as a value alone, then the place that holds it.  Most of the search is scalar: a
+// comparison of one register against the maximum leaves the lanes that hold it as a mask, so the first register with a bit
+// of a vector's lanes set, and its lowest bit, is the lowest index; its sign is read from that lane.  Registers are searched
+// only in the groups of eight whose own maximum is the vector's.  The maximum keeps a NaN (v_maximum3 issues like v_max3),
+// whose bits lie above those of every number; a wave that holds one goes by comparisons.
+// (Carrying value and index through every comparison takes a compare and two selects per register and about forty
+// instructions per exchange between lanes, all of them at half the rate of an addition: n = 1024, L = 16, batch 65536: 723
+// -> 700 us; what is left is 30 additions at 2.6 cycles and three flips at 4.4 per element.)
 template <typename G>
 __device__ __forceinline__ void hash_ar_bucket(const float (&v)[G::R], long long wvec, const HashParams& p, int triple)
 {
     constexpr int R = G::R, LANES = G::LANES, GROUP = 8;
-    static_assert(G::LB == G::r && R % GROUP == 0, "a lane's registers step over whole runs of lanes");
+    static_assert(R % GROUP == 0, "whole groups");
+    auto max_abs = [](float a, float b) { return __builtin_elementwise_maximum(a, __builtin_fabsf(b)); };
     float gm[R / GROUP];
 #pragma unroll
     for (int g = 0; g < R / GROUP; ++g) {
-        gm[g] = __builtin_fmaxf(__builtin_fabsf(v[GROUP * g]), __builtin_fabsf(v[GROUP * g + 1]));
+        gm[g] = max_abs(__builtin_fabsf(v[GROUP * g]), v[GROUP * g + 1]);
 #pragma unroll
-        for (int j = 2; j < GROUP; j += 2)
-            gm[g] = __builtin_fmaxf(__builtin_fmaxf(gm[g], __builtin_fabsf(v[GROUP * g + j])), __builtin_fabsf(v[GROUP * g + j + 1]));
+        for (int j = 2; j < GROUP; j += 2) gm[g] = max_abs(max_abs(gm[g], v[GROUP * g + j]), v[GROUP * g + j + 1]);
     }
-    float top = gm[0];
+    float most = gm[0];
 #pragma unroll
-    for (int g = 1; g < R / GROUP; ++g) top = __builtin_fmaxf(top, gm[g]);
-    top = lanes_max<G::LB>(top);
+    for (int g = 1; g < R / GROUP; ++g) most = max_abs(most, gm[g]);
+    const unsigned top_bits = lanes_max<G::LB>(__float_as_uint(most) & 0x7fffffffu);
+    if (__ballot(top_bits > 0x7f800000u)) return hash_ar_bucket_by_steps<G>(v, wvec, p, triple);
+    const float top = __uint_as_float(top_bits);
 
     constexpr unsigned long long ONE = (LANES < 64 ? (1ull << LANES) : 0ull) - 1ull;      // lanes of the first vector
     unsigned long long open = ~0ull;                 // lanes of the vectors whose place is not found yet
     int bucket[G::TPW];
 #pragma unroll
-    for (int q = 0; q < G::TPW; ++q) bucket[q] = 0;  // nothing compares equal (every coordinate NaN): bucket 0
+    for (int q = 0; q < G::TPW; ++q) bucket[q] = 0;
 #pragma unroll
     for (int g = 0; g < R / GROUP; ++g) {
         if ((__ballot(gm[g] == top) & open) == 0) continue;

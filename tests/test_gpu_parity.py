@@ -309,6 +309,27 @@ def test_hash_from_sign_words_on_constructed_inputs(gpu, n):
     assert np.array_equal(got, np.stack([want, want], 1))
 
 
+@pytest.mark.parametrize("n", [256, 1024])
+def test_hash_of_vectors_that_overflow_is_the_same_from_sign_words(gpu, n):
+    # D = I and x = (z / n) with z = 2^127 at 0, 1, n/2, n/2 + 1 and -2^127 two places further on: two transforms give z exactly, and
+    # the third adds +inf and -inf into coordinate 0 whatever the order of its stages, so y_0 is NaN, half of the rest +-inf or NaN
+    # and half 0.  A NaN in the first coordinate is kept (numpy's argmax does the same): bucket 0 from either form of the
+    # diagonals, and the vector beside it in the same wave keeps its own
+    t = gpu.torch
+    z = np.zeros(n)
+    z[[0, 1, n // 2, n // 2 + 1]] = 2.0 ** 127
+    z[[2, 3, n // 2 + 2, n // 2 + 3]] = -(2.0 ** 127)
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((7, n)).astype(np.float32)
+    x[[0, 3, 6]] = (z / n).astype(np.float32)
+    ones = t.ones((1, 3, n), dtype=t.float32, device=gpu.dev)
+    x = _to(gpu, x)
+    from_fp32 = gpu.b.spinner_hash(x, ones).cpu().numpy()[:, 0]
+    from_words = gpu.b.spinner_hash_signs(x, gpu.b.spinner_pack_signs(ones), 1).cpu().numpy()[:, 0]
+    assert list(from_fp32[[0, 3, 6]]) == [0, 0, 0]
+    assert np.array_equal(from_words, from_fp32)
+
+
 def test_hash_rules_on_constructed_inputs(gpu):
     # D = I, x = +-(column j of normalised H)  ->  bucket j / j + n ; zero vector -> bucket 0 ;
     # exact tie -> lowest index.
