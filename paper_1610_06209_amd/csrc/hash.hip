@@ -66,17 +66,14 @@ __device__ __forceinline__ unsigned dpp_max(unsigned m)
 template <int LB>
 __device__ __forceinline__ unsigned lanes_max(unsigned m)
 {
-    static_assert(LB == 4 || LB == 5, "one or two rows of 16 lanes per vector");
+    static_assert(LB == 5, "two rows of 16 lanes per vector");
     m = dpp_max<0xB1>(m);       // quad_perm:[1,0,3,2]
     m = dpp_max<0x4E>(m);       // quad_perm:[2,3,0,1]
     m = dpp_max<0x141>(m);      // row_half_mirror
     m = dpp_max<0x140>(m);      // row_mirror
-    if constexpr (LB == 5) {
-        float a = __uint_as_float(m), b = a;
-        lane_swap<4>(a, b);
-        m = larger(__float_as_uint(a), __float_as_uint(b));
-    }
-    return m;
+    float a = __uint_as_float(m), b = a;
+    lane_swap<4>(a, b);
+    return larger(__float_as_uint(a), __float_as_uint(b));
 }
 
 // Buckets of the wave's TPW vectors from layout B (register j of lane l holds element l + (j << r)) by the comparisons of
@@ -114,7 +111,9 @@ __device__ __forceinline__ void hash_ar_bucket_by_steps(const float (&v)[G::R], 
 // whose bits lie above those of every number; a wave that holds one goes by comparisons.
 // (Carrying value and index through every comparison takes a compare and two selects per register and about forty
 // instructions per exchange between lanes, all of them at half the rate of an addition: n = 1024, L = 16, batch 65536: 723
-// -> 700 us; what is left is 30 additions at 2.6 cycles and three flips at 4.4 per element.)
+// -> 700 us; what is left is 30 additions at 2.6 cycles and three flips at 4.4 per element.  Only there: at n = 256 a wave
+// holds four vectors, whose places are found one after the other, and sixteen registers leave less to save: L = 16, batch
+// 256 35.4 -> 42.3, batch 65536 151 -> 158.)
 template <typename G>
 __device__ __forceinline__ void hash_ar_bucket(const float (&v)[G::R], long long wvec, const HashParams& p, int triple)
 {
@@ -220,7 +219,8 @@ __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams 
         hash_ar_stages<G>(v);
         hash_ar_shared_lane_stages<G>(v, l);
 
-        hash_ar_bucket<G>(v, wvec, p, t);
+        if constexpr (G::NT == 10) hash_ar_bucket<G>(v, wvec, p, t);
+        else hash_ar_bucket_by_steps<G>(v, wvec, p, t);
     }
 }
 
