@@ -307,7 +307,8 @@ int spinner_layer_backward(const float *dy, const float *x, const void *saved,
  * on the fp32 matrix pipe; the sum over the m rows is split into slabs that are added
  * up in a fixed order, for which it needs spinner_sketch_gram_workspace_bytes(m, d)
  * bytes of device scratch (0 for small m).
- * n a power of two in [2^4, 2^24]; d and m arbitrary (1 <= m <= n).
+ * n a power of two in [2^4, 2^24]; d and m arbitrary (1 <= m <= n; a matrix to transpose has
+ * fewer than 2^24 tiles of 64 x 64, SPINNER_ERR_HIP otherwise).
  */
 size_t spinner_sketch_workspace_bytes(int n, int d, int m);
 int spinner_sketch(const float *A, int n, int d, const float *w,

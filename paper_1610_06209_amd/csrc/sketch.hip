@@ -52,7 +52,7 @@ hipError_t launch_transpose_scale(const float* src, long long rows, long long co
 {
     if (rows <= 0 || cols <= 0) return hipSuccess;
     const long long gx = (cols + 63) / 64, gy = (rows + 63) / 64;
-    if (gx > 0x7fffffffLL || gy > 65535 || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;
+    if (gx > 0xffffffLL || gy > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;      // 2^32 threads per grid
     const dim3 grid((unsigned)(gx * gy));
     if (row_scale) hipLaunchKernelGGL(transpose_scale_kernel<true>, grid, dim3(256), 0, s, src, rows, cols, (unsigned)gx, row_scale, dst);
     else hipLaunchKernelGGL(transpose_scale_kernel<false>, grid, dim3(256), 0, s, src, rows, cols, (unsigned)gx, row_scale, dst);

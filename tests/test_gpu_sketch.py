@@ -60,6 +60,22 @@ def test_sketch_matches_oracle(gpu, oracle, n, d, m, weights):
     assert err.max() <= REL_L2_TOL, err.max()
 
 
+@pytest.mark.parametrize("log2n", [22, 24])
+def test_sketch_of_the_longest_columns(gpu, log2n):
+    # 2^16 and more tiles of rows in the transposition; projections of these sizes are compared with the oracle in
+    # test_gpu_parity.py, so the sketch has to hold the very bits that spinner_apply gives for each weighted column
+    t = gpu.torch
+    n, d, m = 1 << log2n, 3, 65
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(log2n)
+    A = t.randn((n, d), generator=g, device=gpu.dev)
+    w = t.rand(n, generator=g, device=gpu.dev) + 0.5
+    dg = t.randint(0, 2, (3, n), generator=g, device=gpu.dev).float() * 2.0 - 1.0
+    B = gpu.b.spinner_sketch(A, w, dg[0], dg[1], dg[2], m, 1.5)
+    want = gpu.b.spinner_apply((A * w[:, None]).t().contiguous(), dg[0], dg[1], dg[2], m, "none", 1.5)
+    assert t.equal(B, want.t())
+
+
 @pytest.mark.parametrize("log2n", list(range(4, 13)))
 def test_sketch_on_the_columns_as_they_lie(gpu, oracle, log2n):
     # Shapes that take the kernel which loads the columns of the row-major matrix directly (n <= 2^12, d a multiple
