@@ -130,9 +130,8 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
     // Tiles in bands of four tile rows, column by column, and an equal run of that order per XCD (workgroups go to the eight
     // XCDs in turn): the tiles in flight on an XCD share their codes in its L2, and the two halves of a 128-byte line of
     // `out` that straddles two tiles (rows of any length are allowed) meet there instead of leaving two L2s in pieces
-    const unsigned total = gx * gy, run = (total + 7) >> 3;
-    const unsigned tile = (blockIdx.x & 7) * run + (blockIdx.x >> 3);
-    if ((blockIdx.x >> 3) >= run || tile >= total) return;
+    const unsigned total = gx * gy, xcd = blockIdx.x & 7, longer = total & 7;      // the first `longer` XCDs take one tile more
+    const unsigned tile = xcd * (total >> 3) + (xcd < longer ? xcd : longer) + (blockIdx.x >> 3);
     const unsigned band = tile / (kGramBand * gx), in_band = tile - band * kGramBand * gx;
     const unsigned height = gy - kGramBand * band < kGramBand ? gy - kGramBand * band : kGramBand;
     const unsigned tj = in_band / height, ti = kGramBand * band + in_band - tj * height;
@@ -230,9 +229,10 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
 {
     if (na <= 0 || nb <= 0) return hipSuccess;
     const long long gx = (nb + kGramCols - 1) / kGramCols, gy = (na + kGramRows - 1) / kGramRows;
-    if (gy > 65535 || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;      // 2^24 tiles are 1 TiB of results
+    // one workgroup of 256 threads per tile, and a grid holds fewer than 2^32 threads; the caller keeps gy below 2^16
+    if (gx > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;
     const auto kernel = (nb & 31) == 0 ? hamming_gram_kernel<true> : hamming_gram_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((gx * gy + 7) / 8 * 8)), dim3(256), 0, s, reinterpret_cast<const uintx4*>(a), na,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(256), 0, s, reinterpret_cast<const uintx4*>(a), na,
                        reinterpret_cast<const uintx4*>(b), nb, m / 64, 1.0f / (float)m, (unsigned)gx, (unsigned)gy, out);
     return hipGetLastError();
 }

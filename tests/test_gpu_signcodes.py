@@ -184,6 +184,29 @@ def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
     assert got[-1, 0] == 1.0
 
 
+def test_angular_gram_of_the_most_tiles(gpu):
+    # one row of codes against as many as a grid of one workgroup per tile takes (2^24 - 1 tiles, 64 GiB of codes): every tile
+    # is computed once, the last and ragged one included
+    t = gpu.torch
+    nb, m = 128 * (2**24 - 1) - 5, 256
+    t.cuda.empty_cache()
+    if t.cuda.mem_get_info()[0] < 85 << 30:
+        pytest.skip("needs 73 GiB of device memory")
+    codes = t.zeros((nb, m // 64), dtype=t.int64, device=gpu.dev)
+    at = [0, 1, 127, 128, 2**30 - 1, 2**30, nb - 257, nb - 124, nb - 123, nb - 1]
+    for k, j in enumerate(at):
+        codes[j] = -1 if k % 2 else 2**40 - 1                    # 256 and 160 bits set
+    out = t.full((1, nb), -1.0, device=gpu.dev)
+    gpu.b.spinner_angular_gram(t.zeros((1, m // 64), dtype=t.int64, device=gpu.dev), codes, m, out=out)
+    assert [float(out[0, j]) for j in at] == [0.0 if k % 2 else 0.375 for k in range(len(at))]
+    same = 0
+    for part in out[0].split(1 << 28):
+        same += int((part == 1.0).sum())
+    assert same == nb - len(at)
+    del codes, out
+    t.cuda.empty_cache()
+
+
 def test_angular_kernel_end_to_end(gpu, oracle):
     # pairs of known angle: codes on the GPU, Gram on the GPU, against 1 - theta / pi (Section 5) and against
     # the oracle's estimate from its own sign bits
