@@ -106,13 +106,24 @@ __device__ __forceinline__ void feat_ar_diag_b(double (&v)[G::R], const float* d
     }
 }
 
+template <bool STREAM>
+__device__ __forceinline__ void store1(float* p, float v)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // BLOCKS: L stacked blocks (fp32 triples [L][3][n] from p.d[0] on, block l in columns [l m, (l + 1) m) of the cos and of the
 // sin part), one wave per block and vector (or pair of vectors).  This kernel cannot keep x beside its 64 fp64 values per thread, so a
 // vector's L workgroups each read it, and they have to do so from one L2: workgroups go to the eight XCDs in turn
 // (workgroup b to XCD b mod 8), so the L blocks of a vector are workgroups eight apart.  Against the kernel of blocks.hip,
 // which keeps x in registers but needs lane stages on fp64 values: L = 4, 2^27 elements in all, 2^10 336 -> 290 us, 2^12
 // 393 -> 337 us; n = 4096, L = 4, batch 32768: 1512 -> 1372 us.  Bound: fp64 vector ALU, then HBM (779 us).
-template <typename G, bool SIGNS, bool BLOCKS = false>
+// STREAM: results bypass cache retention.  At n = 2^10 a store of a vector is one 128-byte line when rows and blocks are whole
+// lines; the pieces of other rows' lines should meet in the L2.  Sign words, hint -> none, in us: m = 1001, batch 4096 19.1 ->
+// 14.7, 16384 76 -> 46; m = 1000, 16384 61 -> 45; m = 640 (whole lines), 52428 86 -> 89.  Short rows lose less by pieces than by
+// retention: m = 500 33.6 -> 35.3, m = 333 29.2 -> 35.0 (16384).  At n = 2^12 a store is two lines and the hint stays.
+template <typename G, bool SIGNS, bool STREAM, bool BLOCKS = false>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::r >= 6 ? 2 : 4)))
 spinner_feature_ar_kernel(TileParams p, int L)
 {
@@ -184,8 +195,8 @@ spinner_feature_ar_kernel(TileParams p, int L)
                 float sn, cs;
                 feature_sincos(v[j], p, 0.0f, sn, cs);
                 if (G::TPW == 1 || active) {
-                    __builtin_nontemporal_store(cs * p.inv_sqrt_m, dst + (j << r));
-                    __builtin_nontemporal_store(sn * p.inv_sqrt_m, dst + so + (j << r));
+                    store1<STREAM>(dst + (j << r), cs * p.inv_sqrt_m);
+                    store1<STREAM>(dst + so + (j << r), sn * p.inv_sqrt_m);
                 }
             }
         } else {
@@ -195,8 +206,8 @@ spinner_feature_ar_kernel(TileParams p, int L)
                 float sn, cs;
                 feature_sincos(v[j], p, 0.0f, sn, cs);
                 if (ebase + (j << r) < m) {
-                    __builtin_nontemporal_store(cs * p.inv_sqrt_m, dst + (j << r));
-                    __builtin_nontemporal_store(sn * p.inv_sqrt_m, dst + so + (j << r));
+                    store1<STREAM>(dst + (j << r), cs * p.inv_sqrt_m);
+                    store1<STREAM>(dst + so + (j << r), sn * p.inv_sqrt_m);
                 }
             }
         }
@@ -205,6 +216,8 @@ spinner_feature_ar_kernel(TileParams p, int L)
 
 // one wave per workgroup (each wave owns its vectors and its exchange buffer): measured 3-4 % faster than two
 constexpr int kFeatureArWaves = 1;
+template <int NT>
+static bool feature_ar_streams(int m) { return NT != 10 || (m & 31) == 0 || m < (1 << NT) / 2; }
 template <int NT, bool SIGNS>
 static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_t s)
 {
@@ -213,7 +226,8 @@ static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_
         const long long blocks = (tiles + GA::VECS_PER_WG - 1) / GA::VECS_PER_WG;
         if (blocks <= 0) return hipSuccess;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((spinner_feature_ar_kernel<GA, SIGNS>), dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p, 1);
+        const auto kernel = feature_ar_streams<NT>(p.m) ? spinner_feature_ar_kernel<GA, SIGNS, true> : spinner_feature_ar_kernel<GA, SIGNS, NT != 10>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p, 1);
         return hipGetLastError();
     }
     return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
@@ -224,6 +238,7 @@ template <int NT>
 static hipError_t launch_feature_blocks_nt(const TileParams& p, const float* diag_sets, int L, hipStream_t s)
 {
     using GA = HashArGeom<NT, feature_ar_log2r(NT), kFeatureArWaves>;
+    const auto kernel = feature_ar_streams<NT>(p.m) ? spinner_feature_ar_kernel<GA, false, true, true> : spinner_feature_ar_kernel<GA, false, NT != 10, true>;
     // one workgroup per block and group of vectors, in slices of at most 2^24 workgroups (a grid holds 2^32 threads)
     for (int l0 = 0; l0 < L; l0 += 1 << 21) {
         const int nl = L - l0 < (1 << 21) ? L - l0 : 1 << 21;
@@ -235,7 +250,7 @@ static hipError_t launch_feature_blocks_nt(const TileParams& p, const float* dia
             q.x = p.x + b0 * p.in_stride;
             q.out = p.out + b0 * p.out_stride + (long long)l0 * p.m;
             const long long groups = (q.batch + GA::VECS_PER_WG - 1) / GA::VECS_PER_WG;
-            hipLaunchKernelGGL((spinner_feature_ar_kernel<GA, false, true>), dim3((unsigned)(8 * ((groups + 7) / 8) * nl)), dim3(GA::THREADS), 0, s, q, nl);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((groups + 7) / 8) * nl)), dim3(GA::THREADS), 0, s, q, nl);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

@@ -573,6 +573,23 @@ def test_features_from_sign_words_n4096(gpu, oracle, m, scale, batch):
     assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL, (m, "general diagonals")
 
 
+@pytest.mark.parametrize("m", [1, 33, 511, 512, 513, 992, 1001])
+def test_features_n1024_rows_of_whole_lines_and_others(gpu, oracle, m):
+    # n = 1024: rows of whole 128-byte lines (m a multiple of 32) and short ones (m < 512) are stored past the caches, others
+    # are not; an odd batch leaves half of the last wave without a vector
+    n, batch, scale = 1024, 7, 32.0
+    x, d = _rng_case(n, batch, 53 * m)
+    want = oracle.apply(x, d[0], d[1], d[2], m, "cossin", scale)
+    got = gpu.b.spinner_apply_signs(_to(gpu, x), gpu.b.spinner_pack_signs(_to(gpu, d[None])), m, "cossin", scale).cpu().numpy()
+    assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL
+    assert rel_l2_per_vector(_run_apply(gpu, x, d, m, "cossin", scale), want).max() <= REL_L2_TOL
+    if m in (512, 992):                               # blocks: m a multiple of 4
+        for mb in (m, m + 4):
+            ds = np.stack([d, W.rademacher_diagonals(n, 3, 54 * m)])
+            got = gpu.b.spinner_apply_blocks(_to(gpu, x), _to(gpu, ds), mb, "cossin", scale).cpu().numpy()
+            assert rel_l2_per_vector(got, oracle.apply_blocks(x, ds, mb, "cossin", scale)).max() <= REL_L2_TOL
+
+
 @pytest.mark.parametrize("log2n", [15, 16, 17, 18, 19, 20, 21, 22])
 def test_sign_word_path_above_the_feature_and_hash_range(gpu, oracle, log2n):
     # Above 2^14 the packed form is sign words followed by the fp32 diagonals.  n = 2^15, 2^16: the words serve the fused
