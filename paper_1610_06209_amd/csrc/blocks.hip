@@ -1,8 +1,8 @@
 // Stacked independent blocks in one launch (Section 3.2: independently constructed m x n spinners stacked vertically;
 // Section 5 takes k = L m > n random features this way).  One contiguous tile is one whole vector; x is loaded once
 // and stays in registers while the L diagonal triples are applied one after the other, each block's epilogue going
-// to its own column range of the output row.  fp32 diagonals [L][3][n]; n = 2^4 .. 2^14 (features: up to 2^13, and at
-// 2^10 and 2^12 the all-register feature kernel, which reads x once per block, takes them).
+// to its own column range of the output row.  fp32 diagonals [L][3][n]; n = 2^4 .. 2^14 (features at 2^10 and 2^12: the
+// all-register feature kernel, which reads x once per block; at 2^14 small batches only).
 #include "launch.hpp"
 namespace spinner {
 
@@ -95,6 +95,7 @@ spinner_blocks_kernel(BlockParams p)
 // 32 values per thread at most, so that the resident copy of x fits beside the working values
 template <typename T, int NT> struct BlocksTuning : Tuning<T, NT> {};
 template <> struct BlocksTuning<double, 13> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
+template <> struct BlocksTuning<double, 14> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 template <> struct BlocksTuning<float, 11> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 template <> struct BlocksTuning<float, 12> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 template <> struct BlocksTuning<float, 13> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
@@ -115,7 +116,7 @@ static hipError_t launch_blocks_nt(const BlockParams& p, hipStream_t s)
 template <int NT>
 static hipError_t launch_blocks_epi(const BlockParams& p, bool cossin, hipStream_t s)
 {
-    if constexpr (blocks_in_one_launch(NT, true) && !has_feature_blocks_ar(NT)) {
+    if constexpr (!has_feature_blocks_ar(NT)) {
         if (cossin) return launch_blocks_nt<double, NT, EPI_STORE_COSSIN>(p, s);
     }
     return cossin ? hipErrorInvalidValue : launch_blocks_nt<float, NT, EPI_STORE_NONE>(p, s);

@@ -138,9 +138,17 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
 // stacked blocks in one launch (blocks.hip): L fp32 triples [L][3][n] applied to a resident copy of x, n <= 2^kBlocksMaxLog;
 // p as for one block (out_stride = the whole row, sin_off = L m, inv_sqrt_m = 1 / sqrt(L m))
 constexpr int kBlocksMaxLog = 14;
-// The feature blocks at n = 2^14 are one launch of the feature kernel per block: with x resident beside the fp64 values the
-// kernel takes 248 registers, two waves per SIMD, and four blocks of 2048 vectors take 562 us against 4 x 125.
-constexpr bool blocks_in_one_launch(int log2n, bool cossin) { return log2n <= (cossin ? 13 : kBlocksMaxLog); }
+// The feature blocks at n = 2^14: with x resident beside the fp64 values the kernel takes 248 registers, two waves per SIMD,
+// one vector per compute unit.  While every vector has a compute unit of its own (short rows: up to two rounds of that) it is
+// the shortest way; larger batches take one launch of the feature kernel per block, whose vectors share a compute unit in
+// twos.  One launch / one per block, in us: m = n, L = 2, batch 128 34.7 / 38.7, 256 42.6 / 48.7, 384 75.5 / 68.1, 1024 153 /
+// 134; L = 8, 256 142 / 187, 512 270 / 290 (with a reader of the result behind it 511 / 470), 1024 521 / 530 (943 / 876);
+// L = 4, 2048 562 / 500; m = 1000, L = 4, 256 60 / 83, 512 116 / 131, 1024 232 / 235 (255 / 247).
+constexpr int kComputeUnits = 256;
+constexpr bool blocks_in_one_launch(int log2n, bool cossin, long long batch, int m)
+{
+    return log2n <= (cossin && batch > (m <= 1 << (kBlocksMaxLog - 2) ? 2 : 1) * kComputeUnits ? 13 : kBlocksMaxLog);
+}
 hipError_t launch_blocks(int log2n, bool cossin, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 
 // sign words per diagonal in the packed format

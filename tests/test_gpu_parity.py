@@ -716,6 +716,26 @@ def test_stacked_blocks_every_one_launch_size(gpu, oracle, log2n):
         assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL, (log2n, m)
 
 
+@pytest.mark.parametrize("n,m,L,batch", [(1 << 14, 1 << 14, 2, 256), (1 << 14, 4100, 3, 256), (1 << 14, 4096, 2, 512)])
+def test_stacked_features_on_both_sides_of_a_batch_limit(gpu, n, m, L, batch):
+    # `batch` vectors and one more go to different kernels: fp64 butterflies in another order, so the features of the same
+    # vectors agree to the rounding of their last two fp32 operations (a feature is at most 1 / sqrt(L m)), and the vector
+    # that only the larger call has agrees with the single-triple calls
+    t = gpu.torch
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + m + L)
+    x = t.randn((batch + 1, n), generator=g, device=gpu.dev)
+    ds = t.randint(0, 2, (L, 3, n), generator=g, device=gpu.dev).float() * 2.0 - 1.0
+    below = gpu.b.spinner_apply_blocks(x[:batch], ds, m, "cossin", 64.0)
+    above = gpu.b.spinner_apply_blocks(x, ds, m, "cossin", 64.0)
+    tol = 2.0 ** -22 / math.sqrt(L * m)
+    assert float((above[:batch] - below).abs().max()) <= tol
+    for l in range(L):
+        one = gpu.b.spinner_apply(x[batch:], ds[l, 0], ds[l, 1], ds[l, 2], m, "cossin", 64.0) / math.sqrt(L)
+        both = t.cat((above[batch:, l * m:(l + 1) * m], above[batch:, (L + l) * m:(L + l + 1) * m]), 1)
+        assert float((both - one).abs().max()) <= 2.0 * tol
+
+
 def test_stacked_feature_blocks_in_slices(gpu):
     # n = 1024: one wave per pair of vectors and block, at most 2^24 workgroups per launch; with 2^18 blocks a launch takes
     # 128 vectors, so the last three rows of 131 come from a second one
