@@ -1,8 +1,8 @@
 // Stacked independent blocks in one launch (Section 3.2: independently constructed m x n spinners stacked vertically;
 // Section 5 takes k = L m > n random features this way).  One contiguous tile is one whole vector; x is loaded once
 // and stays in registers while the L diagonal triples are applied one after the other, each block's epilogue going
-// to its own column range of the output row.  fp32 diagonals [L][3][n]; n = 2^4 .. 2^14 (features at 2^10 and 2^12: the
-// all-register feature kernel, which reads x once per block; at 2^14 small batches only).
+// to its own column range of the output row.  fp32 diagonals [L][3][n]; n = 2^4 .. 2^14 (features at 2^10 and, but for
+// some small batches, 2^12: the all-register feature kernel, which reads x once per block; at 2^14 small batches only).
 #include "launch.hpp"
 namespace spinner {
 
@@ -116,7 +116,7 @@ static hipError_t launch_blocks_nt(const BlockParams& p, hipStream_t s)
 template <int NT>
 static hipError_t launch_blocks_epi(const BlockParams& p, bool cossin, hipStream_t s)
 {
-    if constexpr (!has_feature_blocks_ar(NT)) {
+    if constexpr (NT != 10) {
         if (cossin) return launch_blocks_nt<double, NT, EPI_STORE_COSSIN>(p, s);
     }
     return cossin ? hipErrorInvalidValue : launch_blocks_nt<float, NT, EPI_STORE_NONE>(p, s);
@@ -124,7 +124,7 @@ static hipError_t launch_blocks_epi(const BlockParams& p, bool cossin, hipStream
 #define CASE(NT) case NT: return launch_blocks_epi<NT>(bp, cossin, s);
 hipError_t launch_blocks(int log2n, bool cossin, const TileParams& p, const float* diag_sets, int L, hipStream_t s)
 {
-    if (cossin && has_feature_blocks_ar(log2n)) return launch_feature_blocks_ar(log2n, p, diag_sets, L, s);
+    if (cossin && feature_blocks_on_ar(log2n, L, p.m, p.batch)) return launch_feature_blocks_ar(log2n, p, diag_sets, L, s);
     BlockParams bp;
     bp.t = p;
     bp.diag_sets = diag_sets;

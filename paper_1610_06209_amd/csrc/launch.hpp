@@ -164,8 +164,16 @@ constexpr int hash_ar_log2r(int log2n)      // values per thread (log2) at n = 2
 // 340 -> 302; 2^8 291 -> 302 / 306 -> 318, so not there.
 constexpr int feature_ar_log2r(int log2n) { return log2n == 10 ? 5 : (log2n == 12 ? 6 : 0); }
 constexpr int ar_log2r(int log2n) { return hash_ar_log2r(log2n) ? hash_ar_log2r(log2n) : feature_ar_log2r(log2n); }
-// the cos / sin blocks of the sizes of the all-register feature kernel run on it, one wave per block (fused_cossin.hip)
+// The cos / sin blocks of the sizes of the all-register feature kernel run on it, one wave per block (fused_cossin.hip), but
+// for two blocks at n = 2^12 with a row limit: the kernel of blocks.hip is ahead while its workgroups of one vector have a
+// compute unit each (batch 256, in us: m = 1000 13.5 against 14.3, 2560 14.0 / 15.3, 4072 14.8 / 16.5; 512: 18.0 / 16.2, 18.1 /
+// 17.2), and up to 1024 with long rows that are no whole 128-byte lines, which cost its 16-byte stores less (m = 3588, 512 19.3 /
+// 21.0, 1024 26.5 / 30.1, 2048 52.8 / 54.9, with a reader of the result behind it 33.0 / 34.2, 48.9 / 48.5, 90 / 88).
 constexpr bool has_feature_blocks_ar(int log2n) { return feature_ar_log2r(log2n) != 0; }
+constexpr bool feature_blocks_on_ar(int log2n, int L, int m, long long batch)
+{
+    return has_feature_blocks_ar(log2n) && !(log2n == 12 && L == 2 && m < 4096 && batch <= ((m & 31) && m > 3072 ? 1024 : 256));
+}
 hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 // n = 2^12 .. 2^14: the wide geometries flip signs in a layout whose lane masks are no words of the packed format;
 // they follow as a block of their own, [3 diagonals][n / 64 words], word (wave << r) | register (fused_none.hip).
