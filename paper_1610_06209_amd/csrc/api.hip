@@ -802,7 +802,7 @@ static int struct_apply_impl(const float* x, int n, long batch, int kind, const 
         if (!workspace) return SPINNER_ERR_WORKSPACE;
         if (!aligned16(workspace)) return SPINNER_ERR_ALIGNMENT;
     }
-    if (spinner::struct_fft_serves(log2n)) {
+    if (spinner::struct_fft_serves(log2n, lp, batch)) {
         const hipError_t e = spinner::launch_struct_fft(x, d1, d2, spec, spec + ((size_t)1 << lp), out, batch, log2n, lp, m,
                                                         kind == SPINNER_STRUCT_HANKEL ? 1 : 0, (float)factor,
                                                         static_cast<hipStream_t>(stream));

@@ -252,7 +252,13 @@ hipError_t launch_struct_conv(const float* x, const float* d1, const float* d2, 
                               long long batch, int n, int log2n, int log2p, int m, int reverse, float factor, hipStream_t s);
 
 // the same with every stage between registers, n points at a time (struct_fft.hip): P = n or 2n
-constexpr bool struct_fft_serves(int log2n) { return log2n >= 9 && log2n <= 14; }
+// At n = 2^14 a padded kind of a few vectors leaves most compute units idle (a workgroup takes two vectors through both
+// convolutions, 34 us): up to 64 vectors the passes through global memory, which share a vector among workgroups, are ahead
+// (batch 1 19.6 against 34.3 us, 32 25.4 / 35.5, 64 33.0 / 36.0, 96 40 / 36, 256 58 / 41).
+constexpr bool struct_fft_serves(int log2n, int log2p, long long batch)
+{
+    return log2n >= 9 && log2n <= 14 && !(log2p == 15 && batch <= 64);
+}
 hipError_t launch_struct_fft(const float* x, const float* d1, const float* d2, const float2* spec, const float2* tw, float* out,
                              long long batch, int log2n, int log2p, int m, int reverse, float factor, hipStream_t s);
 

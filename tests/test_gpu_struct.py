@@ -167,3 +167,19 @@ def test_struct_register_transforms_at_the_edges_of_their_range(gpu, oracle, kin
         assert rel_l2_per_vector(got[:, rows], want).max() <= REL_L2_TOL
         for m in (1, n - 1):
             assert np.array_equal(gpu.b.spinner_struct_apply_ws(*args, m, 0.75).cpu().numpy(), got[:, :m])
+
+
+@pytest.mark.parametrize("kind,n,batch", [(k, 1 << 14, 64) for k in KINDS if k != "circulant"])
+def test_struct_on_both_sides_of_a_batch_limit(gpu, oracle, kind, n, batch):
+    # `batch` vectors and one more go to different kernels; each is compared with the oracle on sampled rows of its first
+    # and last vectors, and the two with each other (fp32 transforms of 2^15 points at most in another order: the errors of both)
+    x, d, params = _case(kind, n, batch + 1, 10700)
+    spec = gpu.b.spinner_struct_prepare(kind, _to(gpu, params), n)
+    rows = np.unique(np.concatenate([[0, 1, n - 1], np.random.default_rng(2).integers(0, n, 24)]))
+    got = []
+    for b in (batch, batch + 1):
+        got.append(gpu.b.spinner_struct_apply_ws(_to(gpu, x[:b]), kind, spec, _to(gpu, d[0]), _to(gpu, d[1]), n, 0.75).cpu().numpy())
+        some = [0, b - 2, b - 1]
+        want = oracle.struct_apply_rows(x[some], kind, params, d[0], d[1], rows, 0.75)
+        assert rel_l2_per_vector(got[-1][np.ix_(some, rows)], want).max() <= REL_L2_TOL
+    assert rel_l2_per_vector(got[0], got[1][:batch].astype(np.float64)).max() <= 2e-6
