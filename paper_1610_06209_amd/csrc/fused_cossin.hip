@@ -218,6 +218,11 @@ spinner_feature_ar_kernel(TileParams p, int L)
 constexpr int kFeatureArWaves = 1;
 template <int NT>
 static bool feature_ar_streams(int m) { return NT != 10 || (m & 31) == 0 || m < (1 << NT) / 2; }
+// n = 2^13, 2^14 without the limit of 128 registers (launch.hpp), for batches whose tiles are all on the chip without it (three
+// and one per compute unit): nothing is gained from more of them, and the spills cost (fp32 diagonals, with / without the
+// limit, in us: 2^13, m = 500, batch 256 13.6 / 12.5, 768 24.7 / 22.5, m = n, 768 25.4 / 23.2; 2^14, m = 1001, 256 21.1 / 18.7; sign
+// words: 2^14, m = 1001, 256 20.4 / 19.0, 2^13 alike)
+struct FeatureFewTuning : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 template <int NT, bool SIGNS>
 static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_t s)
 {
@@ -229,6 +234,10 @@ static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_
         const auto kernel = feature_ar_streams<NT>(p.m) ? spinner_feature_ar_kernel<GA, SIGNS, true> : spinner_feature_ar_kernel<GA, SIGNS, NT != 10>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p, 1);
         return hipGetLastError();
+    }
+    if constexpr (NT == 14 || (NT == 13 && !SIGNS)) {
+        if (tiles <= (NT == 13 ? 3 : 1) * kComputeUnits)
+            return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS, 0, true, GeomFrom<FeatureFewTuning, NT>>(p, tiles, s);
     }
     return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
 }

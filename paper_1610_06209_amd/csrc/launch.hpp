@@ -84,7 +84,7 @@ constexpr int xcd_group_log_for()
     return G::NT > 14 ? -1 : (target > wg_bytes_log ? target - wg_bytes_log : 0);
 }
 
-template <typename T, int NT, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS = false, int PRUNE = 0, bool RAGGED = true>
+template <typename T, int NT, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS = false, int PRUNE = 0, bool RAGGED = true, typename GEOM = void>
 inline hipError_t launch_tile(const TileParams& p, long long total_tiles, hipStream_t stream)
 {
     // wide exchanges pay with packed sign words only: fp32 diagonals read in layout 1 come in 256-byte runs,
@@ -94,10 +94,11 @@ inline hipError_t launch_tile(const TileParams& p, long long total_tiles, hipStr
     constexpr bool kWidePruned = PRUNE > 0 && SIGNS && C >= NT && NSTEPS == 3 && EPI == EPI_STORE_NONE && std::is_same<T, float>::value &&
                                  has_wide_words(NT);
     constexpr bool kFusedF32Diag = PRUNE == 0 && !SIGNS && C >= NT && NSTEPS == 3 && EPI == EPI_STORE_NONE && std::is_same<T, float>::value;
-    using G = std::conditional_t<(PRUNE > 0 && !kWidePruned), PrunedGeomFor<T, NT>,
+    using TableG = std::conditional_t<(PRUNE > 0 && !kWidePruned), PrunedGeomFor<T, NT>,
                                  std::conditional_t<(C >= NT && SIGNS && NSTEPS == 3), ContigGeomFor<T, NT>,
                                                     std::conditional_t<(SIGNS && NSTEPS < 3 && NT == 11), GeomFrom<RowSigns11, NT>,
                                                                        std::conditional_t<kFusedF32Diag, GeomFrom<FusedF32DiagTuning<NT>, NT>, GeomFor<T, NT>>>>>;
+    using G = std::conditional_t<std::is_void<GEOM>::value, TableG, GEOM>;
     const long long blocks = (total_tiles + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;

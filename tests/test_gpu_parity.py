@@ -737,6 +737,20 @@ def test_stacked_features_on_both_sides_of_a_batch_limit(gpu, n, m, L, batch):
         assert float((both - one).abs().max()) <= 2.0 * tol
 
 
+@pytest.mark.parametrize("n,m,batch", [(1 << 13, 1 << 13, 768), (1 << 13, 501, 768), (1 << 14, 1 << 14, 256), (1 << 14, 8196, 256)])
+def test_features_on_both_sides_of_a_batch_limit(gpu, n, m, batch):
+    # `batch` vectors and one more go to kernels that differ in nothing but the registers they may take: the same bits
+    t = gpu.torch
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + m)
+    x = t.randn((batch + 1, n), generator=g, device=gpu.dev)
+    d = t.randint(0, 2, (3, n), generator=g, device=gpu.dev).float() * 2.0 - 1.0
+    words = gpu.b.spinner_pack_signs(d[None])
+    for f in (lambda v: gpu.b.spinner_apply(v, d[0], d[1], d[2], m, "cossin", 64.0),
+              lambda v: gpu.b.spinner_apply_signs(v, words, m, "cossin", 64.0)):
+        assert t.equal(f(x)[:batch], f(x[:batch]))
+
+
 def test_stacked_feature_blocks_in_slices(gpu):
     # n = 1024: one wave per pair of vectors and block, at most 2^24 workgroups per launch; with 2^18 blocks a launch takes
     # 128 vectors, so the last three rows of 131 come from a second one
