@@ -234,12 +234,13 @@ static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_
         const auto kernel = feature_ar_streams<NT>(p.m) ? spinner_feature_ar_kernel<GA, SIGNS, true> : spinner_feature_ar_kernel<GA, SIGNS, NT != 10>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p, 1);
         return hipGetLastError();
+    } else {
+        if constexpr (NT == 14 || (NT == 13 && !SIGNS)) {
+            if (tiles <= (NT == 13 ? 3 : 1) * kComputeUnits)
+                return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS, 0, true, GeomFrom<FeatureFewTuning, NT>>(p, tiles, s);
+        }
+        return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
     }
-    if constexpr (NT == 14 || (NT == 13 && !SIGNS)) {
-        if (tiles <= (NT == 13 ? 3 : 1) * kComputeUnits)
-            return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS, 0, true, GeomFrom<FeatureFewTuning, NT>>(p, tiles, s);
-    }
-    return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
 }
 
 // p as for one block (out_stride = the whole row, sin_off = L m, inv_sqrt_m = 1 / sqrt(L m))

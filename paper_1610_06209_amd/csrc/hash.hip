@@ -266,13 +266,13 @@ static hipError_t launch_hash_nt(const HashParams& p, hipStream_t s)
         if (blocks <= 0) return hipSuccess;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
         hipLaunchKernelGGL((spinner_hash_ar_kernel<GA>), dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p);
-        return hipGetLastError();
+    } else {
+        using G = TileGeom<NT, clamp_rmax(NT, kHashRmax)>;
+        const long long blocks = (p.batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
+        if (blocks <= 0) return hipSuccess;
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((spinner_hash_kernel<G, SIGNS>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     }
-    using G = TileGeom<NT, clamp_rmax(NT, kHashRmax)>;
-    const long long blocks = (p.batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
-    if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((spinner_hash_kernel<G, SIGNS>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     return hipGetLastError();
 }
 // n = 2^15, 2^16: a vector fills the registers of a whole workgroup, so no copy of x can stay resident beside the
