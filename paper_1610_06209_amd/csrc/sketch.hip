@@ -82,6 +82,26 @@ __device__ __forceinline__ void upper_tile(int t, int& ta, int& tb)
     ta = t - tb * (tb + 1) / 2;
 }
 
+// A tile put together in LDS goes to rows a0 .. and columns b0 .. of G, and once more turned over
+constexpr int kGramTilePitch = 65;
+__device__ __forceinline__ void store_gram_tile(const float* T, float* __restrict__ G, int d, int a0, int b0, int wave, int lane, bool mirror)
+{
+    if (b0 + lane < d) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = wave * 16 + i;
+            if (a0 + r < d) G[(long long)(a0 + r) * d + b0 + lane] = T[r * kGramTilePitch + lane];
+        }
+    }
+    if (mirror && a0 + lane < d) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = wave * 16 + i;
+            if (b0 + r < d) G[(long long)(b0 + r) * d + a0 + lane] = T[lane * kGramTilePitch + r];
+        }
+    }
+}
+
 // Slab z handles rows [z * kchunk, (z + 1) * kchunk) of B and writes its own d x d matrix of `out`, tiles on and above the
 // diagonal only (gram_reduce_kernel adds the slabs up and mirrors); with a single slab `out` is G, mirrored here.
 template <bool EVEN>
@@ -146,9 +166,9 @@ __global__ void __launch_bounds__(256, 2) sketch_gram_kernel(const float* __rest
 #pragma unroll
                 for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(g.a[i][t], g.b[i][u], acc[t][u], 0, 0, 0);
     };
-    if (k_begin < k_end) {
-        constexpr int STEP = 2 * UNROLL;
-        Group g0, g1;
+    constexpr int STEP = 2 * UNROLL;
+    Group g0, g1;
+    if (k_end - k_begin > STEP) {
         load(g0, k_begin);
         int k0 = k_begin;
         do {
@@ -158,6 +178,9 @@ __global__ void __launch_bounds__(256, 2) sketch_gram_kernel(const float* __rest
             if (k0 + STEP < k_end) multiply(g1, k0 + STEP);
             k0 += 2 * STEP;
         } while (k0 < k_end);
+    } else if (k_begin < k_end) {            // one group: no load that is not multiplied (m = 1000, d = 129 13.2 -> 12.8 us)
+        load(g0, k_begin);
+        multiply(g0, k_begin);
     }
 
     // wave w ends up with quadrant (w / 2, w % 2): the others hand it theirs
@@ -188,29 +211,62 @@ __global__ void __launch_bounds__(256, 2) sketch_gram_kernel(const float* __rest
     }
 
     // Result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its quadrant (i, j) = (wave / 2,
-    // wave % 2), which stand for row 2 row + i and column 2 column + j of the tile.  The tile is put together in LDS (64 rows
-    // of 65) and stored from there, once more turned over.
+    // wave % 2), which stand for row 2 row + i and column 2 column + j of the tile.
     __syncthreads();
     float* T = &red[0][0][0][0];
-    static_assert(sizeof(red) >= 64 * 65 * sizeof(float), "the tile fits the exchange buffer");
+    static_assert(sizeof(red) >= kGramTile * kGramTilePitch * sizeof(float), "the tile fits the exchange buffer");
 #pragma unroll
-    for (int v = 0; v < 16; ++v) T[(2 * (8 * (v >> 2) + 4 * half + (v & 3)) + (wave >> 1)) * 65 + 2 * l32 + (wave & 1)] = sum[v];
+    for (int v = 0; v < 16; ++v)
+        T[(2 * (8 * (v >> 2) + 4 * half + (v & 3)) + (wave >> 1)) * kGramTilePitch + 2 * l32 + (wave & 1)] = sum[v];
     __syncthreads();
-    float* G = out + (long long)blockIdx.y * d * d;
-    if (b0 + lane < d) {
+    store_gram_tile(T, out + (long long)blockIdx.y * d * d, d, a0, b0, wave, lane, mirror && ta < tb);
+}
+
+// The same with a quadrant of the tile per wave, through all rows (one slab): nothing is added up between waves and no group
+// of rows is mostly empty, at the price of every operand being loaded by two waves.  Four sums per entry, every fourth row pair
+// each, keep an entry's chain of additions as short as the rows split over the waves do.
+// For up to 64 rows, for up to 128 where one slab fills the chip, and there for every odd d, whose 8-byte loads the other kernel
+// has to do without.  Former 128 x 128 tiles / rows split over the waves / this kernel, in us:
+// m = 16, d = 129 5.1 / 7.2 / 3.9, 1000 5.8 / 6.8 / 4.6, 3001 13.6 / 24.7 / 11.7; m = 64, 64 9.2 / 5.1 / 4.4, 4096 35 / 29.8 / 26;
+// m = 128, 4096 57 / 46 / 40; m = 300, 4001 104 / 111 / 77, 4096 105 / 86 / - ; m = 2048, 1921 210 / 127 / 117, 4001 623 / 598 / 454.
+__global__ void __launch_bounds__(256) sketch_gram_quadrants_kernel(const float* __restrict__ B, int m, int d, float* __restrict__ G)
+{
+    __shared__ float T[kGramTile * kGramTilePitch];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    int ta, tb;
+    upper_tile((int)blockIdx.x, ta, tb);
+    const int a0 = ta * kGramTile, b0 = tb * kGramTile;
+    const int qa = 32 * (wave >> 1), qb = 32 * (wave & 1);      // the quadrant's first row and column of the tile
+    // columns past the last one are read from it: they only reach entries that are not stored
+    const int ca = a0 + qa + l32 < d ? a0 + qa + l32 : d - 1, cb = b0 + qb + l32 < d ? b0 + qb + l32 : d - 1;
+    floatx16 acc[4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = wave * 16 + i;
-            if (a0 + r < d) G[(long long)(a0 + r) * d + b0 + lane] = T[r * 65 + lane];
-        }
-    }
-    if (mirror && ta < tb && a0 + lane < d) {
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = wave * 16 + i;
-            if (b0 + r < d) G[(long long)(b0 + r) * d + a0 + lane] = T[lane * 65 + r];
+        for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
+    constexpr int UNROLL = 8;
+    for (int k0 = 0; k0 < m; k0 += 2 * UNROLL) {
+        float fa[UNROLL], fb[UNROLL];
+#pragma unroll
+        for (int i = 0; i < UNROLL; ++i) {
+            const int row = k0 + 2 * i + half;
+            const float* r = B + (long long)(row < m ? row : m - 1) * d;      // clamped: no load under a condition
+            fa[i] = r[ca]; fb[i] = r[cb];
         }
+        if (k0 + 2 * UNROLL > m) {                   // rows past the end count as zero in both operands
+#pragma unroll
+            for (int i = 0; i < UNROLL; ++i)
+                if (k0 + 2 * i + half >= m) fa[i] = fb[i] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < UNROLL; ++i)
+            if (k0 + 2 * i < m) acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[i], acc[i & 3], 0, 0, 0);
     }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) T[(qa + 8 * (v >> 2) + 4 * half + (v & 3)) * kGramTilePitch + qb + l32] = ((acc[0][v] + acc[1][v]) + acc[2][v]) + acc[3][v];
+    __syncthreads();
+    store_gram_tile(T, G, d, a0, b0, wave, lane, ta < tb);
 }
 
 // G from the slabs: a block adds up one 32 x 32 tile on or above the diagonal (fixed order) and stores it twice
@@ -303,6 +359,10 @@ hipError_t launch_sketch_gram(const float* B, int m, int d, float* G, float* sla
     if (m <= 0 || d <= 0) return hipSuccess;
     const long long g = (d + kGramTile - 1) / kGramTile, tiles = g * (g + 1) / 2;
     if (tiles > 0x1fffffffLL) return hipErrorInvalidConfiguration;
+    if (m <= 64 || ((m <= 128 || (d & 1)) && sketch_gram_slabs(m, d) == 1)) {
+        hipLaunchKernelGGL(sketch_gram_quadrants_kernel, dim3((unsigned)tiles), dim3(256), 0, s, B, m, d, G);
+        return hipGetLastError();
+    }
     // slabs: the fewest that bring the busiest compute unit's share of the rows within 10 % of the least, as far as the
     // scratch goes
     const int room = sketch_gram_slabs(m, d);

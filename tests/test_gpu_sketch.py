@@ -144,6 +144,13 @@ def test_gram_tiles_at_their_edges(gpu, oracle, m, d):
     assert np.array_equal(H[np.ix_(keep, keep)], G[np.ix_(keep, keep)]) and not np.isfinite(H[c]).any()
 
 
+@pytest.mark.parametrize("m,d", [(5, 64), (17, 200), (64, 1), (64, 130), (65, 130), (128, 1924), (129, 1924), (700, 1923)])
+def test_gram_by_quadrants_and_by_rows(gpu, oracle, m, d):
+    # a quadrant of the tile per wave: up to 64 rows, with one slab (d > 1920) up to 128, for odd d any number; the waves split
+    # the rows beyond
+    test_gram_tiles_at_their_edges(gpu, oracle, m, d)
+
+
 def test_full_sketch_gives_the_exact_hessian(gpu):
     # m = n, scale 1: S is orthogonal, so the sketched Hessian equals A^T W A
     n, d = 2048, 96
