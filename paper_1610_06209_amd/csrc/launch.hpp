@@ -140,15 +140,15 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
 // p as for one block (out_stride = the whole row, sin_off = L m, inv_sqrt_m = 1 / sqrt(L m))
 constexpr int kBlocksMaxLog = 14;
 // The feature blocks at n = 2^14: with x resident beside the fp64 values the kernel takes 248 registers, two waves per SIMD,
-// one vector per compute unit.  While every vector has a compute unit of its own (short rows: up to two rounds of that) it is
-// the shortest way; larger batches take one launch of the feature kernel per block, whose vectors share a compute unit in
-// twos.  One launch / one per block, in us: m = n, L = 2, batch 128 34.7 / 38.7, 256 42.6 / 48.7, 384 75.5 / 68.1, 1024 153 /
-// 134; L = 8, 256 142 / 187, 512 270 / 290 (with a reader of the result behind it 511 / 470), 1024 521 / 530 (943 / 876);
-// L = 4, 2048 562 / 500; m = 1000, L = 4, 256 60 / 83, 512 116 / 131, 1024 232 / 235 (255 / 247).
+// one vector per compute unit.  While every vector has a compute unit of its own it is the shortest way; larger batches take
+// one launch of the feature kernel per block, whose vectors share a compute unit in twos.  One launch / one per block, in us:
+// m = n, L = 2, batch 128 34.7 / 38.7, 256 42.6 / 48.7, 384 75.5 / 68.1, 1024 153 / 134; L = 8, 256 142 / 187, 512 270 / 290 (with a
+// reader of the result behind it 511 / 470), 1024 521 / 530 (943 / 876); L = 4, 2048 562 / 500; m = 1000, L = 4, 256 69 / 85, with
+// inputs that change from call to call 384 125 / 128, L = 2 65.5 / 64.7.
 constexpr int kComputeUnits = 256;
-constexpr bool blocks_in_one_launch(int log2n, bool cossin, long long batch, int m)
+constexpr bool blocks_in_one_launch(int log2n, bool cossin, long long batch)
 {
-    return log2n <= (cossin && batch > (m <= 1 << (kBlocksMaxLog - 2) ? 2 : 1) * kComputeUnits ? 13 : kBlocksMaxLog);
+    return log2n <= (cossin && batch > kComputeUnits ? 13 : kBlocksMaxLog);
 }
 hipError_t launch_blocks(int log2n, bool cossin, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 
