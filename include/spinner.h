@@ -355,7 +355,7 @@ int spinner_sketch_gram_static(const float *B, int m, int d, float *G, void *str
  * the call is one kernel that needs no scratch memory; spinner_struct_apply returns
  * SPINNER_ERR_UNSUPPORTED above that.  spinner_struct_apply_ws takes a workspace of
  * spinner_struct_workspace_bytes(kind, n, batch) bytes (0 for the sizes above) and also
- * serves P = 2^15 .. 2^22 (n up to 2^22 / 2^21): one kernel at n = 2^14 for more than 64
+ * serves P = 2^15 .. 2^22 (n up to 2^22 / 2^21): one kernel at n = 2^14 for more than 96
  * vectors (the workspace is asked for but not touched); otherwise H D1 x by a pass over
  * rows and a pass over columns, then the transform in three passes through global memory (its top
  * stages over column tiles, blocks of 2^12 points with the spectrum product, the top

@@ -169,8 +169,8 @@ def test_struct_register_transforms_at_the_edges_of_their_range(gpu, oracle, kin
             assert np.array_equal(gpu.b.spinner_struct_apply_ws(*args, m, 0.75).cpu().numpy(), got[:, :m])
 
 
-@pytest.mark.parametrize("kind,n,batch", [(k, 1 << 14, 64) for k in KINDS if k != "circulant"] +
-                         [(k, 1 << 13, 512) for k in KINDS if k != "circulant"])
+@pytest.mark.parametrize("kind,n,batch", [(k, 1 << 14, 96) for k in KINDS if k != "circulant"] +
+                         [(k, 1 << 13, 32) for k in KINDS if k != "circulant"])
 def test_struct_on_both_sides_of_a_batch_limit(gpu, oracle, kind, n, batch):
     # `batch` vectors and one more go to different kernels; each is compared with the oracle on sampled rows of its first
     # and last vectors, and the two with each other (fp32 transforms of 2^15 points at most in another order: the errors of both)
