@@ -166,14 +166,19 @@ constexpr int hash_ar_log2r(int log2n)      // values per thread (log2) at n = 2
 constexpr int feature_ar_log2r(int log2n) { return log2n == 10 ? 5 : (log2n == 12 ? 6 : 0); }
 constexpr int ar_log2r(int log2n) { return hash_ar_log2r(log2n) ? hash_ar_log2r(log2n) : feature_ar_log2r(log2n); }
 // The cos / sin blocks of the sizes of the all-register feature kernel run on it, one wave per block (fused_cossin.hip), but
-// for two blocks at n = 2^12 with a row limit: the kernel of blocks.hip is ahead while its workgroups of one vector have a
-// compute unit each (batch 256, in us: m = 1000 13.5 against 14.3, 2560 14.0 / 15.3, 4072 14.8 / 16.5; 512: 18.0 / 16.2, 18.1 /
-// 17.2), and up to 1024 with long rows that are no whole 128-byte lines, which cost its 16-byte stores less (m = 3588, 512 19.3 /
-// 21.0, 1024 26.5 / 30.1, 2048 52.8 / 54.9, with a reader of the result behind it 33.0 / 34.2, 48.9 / 48.5, 90 / 88).
+// for a few blocks at n = 2^12 with a row limit.  Two blocks: the kernel of blocks.hip is ahead while its workgroups of one vector
+// have a compute unit each (batch 256, in us: m = 1000 13.5 against 14.3, 2560 14.0 / 15.3, 4072 14.8 / 16.5; 512: 18.0 / 16.2, 18.1 /
+// 17.2).  Long rows that are no whole 128-byte lines cost its 16-byte stores less: two blocks up to 3072 vectors (m = 4072, 1024
+// 28.8 / 33.2, 1280 37.5 / 45.9, 2176 59.9 / 64.8, 3072 77.9 / 78.6, 4120 114 / 103), three where the other kernel's workgroups
+// fill the chip once and a little more (512 27.3 / 28.1, 704 34.3 / 43.7, 1024 42.2 / 46.3, 1365 61.0 / 62.5 but with a reader of
+// the result behind it 109 / 103; 256 20.7 / 18.3).
 constexpr bool has_feature_blocks_ar(int log2n) { return feature_ar_log2r(log2n) != 0; }
 constexpr bool feature_blocks_on_ar(int log2n, int L, int m, long long batch)
 {
-    return has_feature_blocks_ar(log2n) && !(log2n == 12 && L == 2 && m < 4096 && batch <= ((m & 31) && m > 3072 ? 1024 : 256));
+    if (log2n != 12 || m == 4096 || L > 3) return has_feature_blocks_ar(log2n);
+    const bool long_pieces = (m & 31) != 0 && m > 3072;
+    if (L == 3) return !long_pieces || batch <= 512 || batch > 1024;
+    return batch > (long_pieces ? 3072 : 256);
 }
 hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 // n = 2^12 .. 2^14: the wide geometries flip signs in a layout whose lane masks are no words of the packed format;

@@ -717,7 +717,8 @@ def test_stacked_blocks_every_one_launch_size(gpu, oracle, log2n):
 
 
 @pytest.mark.parametrize("n,m,L,batch", [(1 << 14, 1 << 14, 2, 256), (1 << 14, 4100, 3, 256),
-                                             (1 << 12, 2560, 2, 256), (1 << 12, 4092, 2, 1024)])
+                                             (1 << 12, 2560, 2, 256), (1 << 12, 4092, 2, 3072),
+                                             (1 << 12, 4092, 3, 512), (1 << 12, 4092, 3, 1024)])
 def test_stacked_features_on_both_sides_of_a_batch_limit(gpu, n, m, L, batch):
     # `batch` vectors and one more go to different kernels: fp64 butterflies in another order, so the features of the same
     # vectors agree to the rounding of their last two fp32 operations (a feature is at most 1 / sqrt(L m)), and the vector
