@@ -184,10 +184,12 @@ int spinner_hash_signs_ws(const float *x, int n, long batch, int L,
  *   diag_sets  in   device fp32 [L][3][n], order d1, d2, d3 within a triple
  *   workspace  in   spinner_blocks_workspace_bytes(n, batch, m, epilogue) bytes
  * For L > 1, m must be a multiple of 4.  Up to n = 2^14 the L blocks come from one
- * kernel launch that reads x once (the feature blocks in fp64 as in spinner_apply, at
- * n = 2^14 one launch per block); above
- * that size every block runs the four-pass path and reads x again.  Otherwise as
- * spinner_apply (which is the case L = 1).
+ * kernel launch that reads x once, with these exceptions among the feature blocks (fp64
+ * as in spinner_apply): at n = 2^10 and, but for some small batches of two or three
+ * blocks, 2^12 every block reads x (all blocks of a vector through one L2; one launch for
+ * up to 2^24 workgroups); at n = 2^14 batches of more than 256 vectors take one launch per
+ * block.  Above that size every block runs the four-pass path and reads x again.
+ * Otherwise as spinner_apply (which is the case L = 1).
  */
 size_t spinner_blocks_workspace_bytes(int n, long batch, int m, int epilogue);
 int spinner_apply_blocks(const float *x, int n, long batch, int L,

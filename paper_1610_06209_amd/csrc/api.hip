@@ -696,7 +696,8 @@ int spinner_apply_blocks(const float* x, int n, long batch, int L, const float* 
     if (!aligned16(diag_sets)) return SPINNER_ERR_ALIGNMENT;
     if (spinner_blocks_workspace_bytes(n, batch, m, epilogue) && !workspace) return SPINNER_ERR_WORKSPACE;
     if (L > 1 && spinner::blocks_in_one_launch(log2n, epilogue == SPINNER_EPI_COSSIN, batch)) {
-        // one launch: x is read once and stays in registers while the L triples are applied
+        // one call of launch_blocks: x stays in registers while the L triples are applied, or (feature blocks of the
+        // all-register kernel) is read once per block
         if (batch > 0x7fffffffLL) return SPINNER_ERR_BAD_BATCH;
         const double factor_d = (double)scale / ((double)n * sqrt((double)n));
         spinner::TileParams p;

@@ -116,6 +116,7 @@ __device__ __forceinline__ intx8 spread_bits_fp4(unsigned w, unsigned sign, unsi
     return f;
 }
 
+// Three workgroups per compute unit cost 20 bytes of scratch per thread.
 // LINES: rows of `out` are whole 128-byte lines (nb a multiple of 32) and bypass cache retention (4096 x 4096, m = 1024 18.2 ->
 // 16.4 us; 16384 x 16384, m = 4096 625 -> 607); the pieces of other rows' lines have to meet in the L2 (16384 x 10007, m = 256:
 // 152 us, with the hint 338)

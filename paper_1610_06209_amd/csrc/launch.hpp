@@ -18,9 +18,10 @@ constexpr int kFusedMaxLogOther = 14;     // fp64 feature map, hash
 struct NotWide { static constexpr int wide = 0, start = 0, chunk = kLaneChunk; };
 template <typename T, int NT> struct Tuning : NotWide { static constexpr int rmax = std::is_same<T, double>::value ? clamp_rmax(NT, 5) : 6, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<double, 12> : NotWide { static constexpr int rmax = 4, waves = 4, min_waves = 0, trips = 0; };
-// held to 128 registers (they take 133 .. 147 otherwise): four and two tiles per compute unit instead of three and one.
+// held to 128 registers (they take 133 .. 147 otherwise; 2^14 spills 60 bytes per thread): four and two tiles per compute unit
+// instead of three and one, for batches that need them (fused_cossin.hip).
 // Measured on 2^27 elements, sign words / fp32 diagonals, in us: 2^13 428 -> 405 / 461 -> 439, 2^14 581 -> 472 / 619 -> 504
-// (no gain for 2^7 .. 2^11, where the same limit spills)
+// (no gain for 2^7 .. 2^11, where the same limit spills more than it helps)
 template <> struct Tuning<double, 13> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
 template <> struct Tuning<double, 14> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
 template <> struct Tuning<float, 4> : NotWide { static constexpr int rmax = 2, waves = 4, min_waves = 0, trips = 0; };

@@ -884,7 +884,10 @@ spinner_tile_kernel(TileParams p)
     // x read by the first pass and what the last pass reads and writes (what lies between is read again soon)
     constexpr bool FIRST_PASS = NSTEPS == 1 && FIRST_DIAG && C >= NT, LAST_PASS = NSTEPS == 1 && !FIRST_DIAG && C < NT;
     // (feature rows, 2^22 .. 2^27 elements: the hint on the stores 2^9 15.6 -> 12.2 us .. +0 %, 2^11 19.9 -> 15.7 .. +5 %, 2^13
-    // 21.5 -> 16.9 .. +5 %, 2^14 25.5 -> 21.4 .. +4 %, 2^15 +0 .. 10 %)
+    // 21.5 -> 16.9 .. +5 %, 2^14 25.5 -> 21.4 .. +4 %, 2^15 +0 .. 10 %.  With a reader that follows at once, call and
+    // reader together: -14 .. +4 % at 16 MiB of results, -1 .. +5 % at 64 MiB, -7 .. -1 % at 256 MiB.  First m rows in whole 16-byte
+    // pieces, 2^22 / 2^24 / 2^26 elements of x: the call alone 5 .. 10, 9 .. 18, 0 .. 8 % less; with the reader 1 .. 4 % less, 0 .. 5 %
+    // more, -2 .. +3 %; n = 2^16 at 2^26 13 and 8 % less)
     // (measured on the four-pass schedule: the hint on the first pass alone +2-3 % at n = 2^17 .. 2^20, on the last pass too +0.4 .. 4 %)
     constexpr bool STREAM_LD = NSTEPS == 3 || FIRST_PASS || LAST_PASS;
     constexpr bool STREAM = NSTEPS == 3 || LAST_PASS;

@@ -16,7 +16,9 @@
 // writes the same positions, so an exchange is: write, one barrier, read.  Hadamard phases run middle, low, top and the
 // top one goes straight into the transform's top phase; the low phase holds the forward stages, the spectrum product
 // and the inverse stages.  Six exchanges for a circulant block, ten for the others (the general kernel in
-// structured.hip: ten and sixteen round trips of twice the points for the padded kinds).
+// structured.hip took ten and sixteen round trips at these sizes, of twice the points for the padded kinds: n = 4096,
+// batch 16383, Toeplitz 315 -> 251 us).  n = 2^13 and 2^14 are held to two waves per SIMD and the padded kinds spill 100 and 72
+// bytes per thread there (2^10 and 2^11: 16 and 20).
 #include "launch.hpp"
 namespace spinner {
 
@@ -328,7 +330,10 @@ struct_fft_kernel(StructFftParams p)
         fft::convolve<G, false>(v, X, p.spec, p.tw, LOGP, t);
     }
     const int e = G::base_index(0, t);
-    // (the non-temporal hint on the stores: 1-3 % at 2^27 elements, up to 14 % at 2^22)
+    // The non-temporal hint on the stores, without / with it, Toeplitz, in us: n = 4096, 2^22 elements 20.6 / 18.3, 2^24 61.3 /
+    // 59.5, 2^26 280 / 243; rows that are no whole lines, m = 4095 21.0 / 18.6, 64.2 / 64.2, 258 / 231, m = 2561 19.2 / 18.6,
+    // 61.4 / 63.5, 246 / 214, n = 2^14, m = 16383 41.9 / 41.3, 89.7 / 94.8, 359 / 344.  With a reader of the result behind it the
+    // two differ by less than 5 % either way.
     float* o0 = p.out + v0 * p.m;
     float* o1 = o0 + p.m;
     static_for<0, R>([&](auto k) {

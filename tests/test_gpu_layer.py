@@ -131,8 +131,9 @@ def test_layer_backward_many_vectors_per_slot(gpu, oracle, n, batch):
 
 @pytest.mark.parametrize("n", [16, 256, 2048, 1 << 14])
 def test_layer_of_large_batches(gpu, n):
-    # from 2^24 elements on the backward kernels carry the non-temporal hint: the same bits per vector as for a small batch, and diagonal gradients that are the sum of those of parts below the limit (fp32 running sums
-    # over at most batch / 8192 .. batch / 512 vectors per slot, slots added in fp64: 1e-6 of the norm leaves a factor of five)
+    # from 2^24 elements on the backward kernels carry the non-temporal hint: the same bits per vector as for a small batch, and
+    # diagonal gradients that are the sum of those of parts below the limit (fp32 running sums over at most batch / 8192 ..
+    # batch / 512 vectors per slot, slots added in fp64: 1e-6 of the norm leaves a factor of five)
     t = gpu.torch
     batch = (1 << 25) // n + 3
     g = t.Generator(device=gpu.dev)

@@ -688,9 +688,9 @@ def test_stacked_blocks(gpu, oracle, n, m, L, epilogue, scale, batch):
 
 @pytest.mark.parametrize("log2n", list(range(4, 15)))
 def test_stacked_blocks_every_one_launch_size(gpu, oracle, log2n):
-    # n <= 2^14: one kernel keeps x in registers and applies the L triples one after the other; both epilogues,
-    # all coordinates and a row limit that cuts through a tile (m a multiple of 4), batches that leave part of a
-    # workgroup without a vector
+    # n <= 2^14: one kernel keeps x in registers and applies the L triples one after the other (features at 2^10 and 2^12: one
+    # wave per block); both epilogues, all coordinates and a row limit that cuts through a tile (m a multiple of 4), batches
+    # that leave part of a workgroup without a vector
     n = 1 << log2n
     batch = {4: 203, 5: 131, 6: 67}.get(log2n, 21 if log2n < 12 else 5)
     L = 3

@@ -155,7 +155,8 @@ def test_struct_argument_errors(gpu):
 @pytest.mark.parametrize("log2n", [8, 9, 10, 14])
 def test_struct_register_transforms_at_the_edges_of_their_range(gpu, oracle, kind, log2n):
     # n = 2^9 .. 2^14 run every stage between registers (2^8 is the last size of the general kernel below); one vector
-    # and a full pair, one row, all but one row; at 2^14 sampled rows, the padded kinds through the call with a workspace
+    # and a full pair, one row, all but one row; at 2^14 sampled rows (so few vectors of the padded kinds go through global
+    # memory there: see the batch limits below)
     n = 1 << log2n
     rows = np.arange(n) if log2n < 14 else np.unique(np.concatenate([np.arange(8), np.arange(n - 8, n), np.random.default_rng(1).integers(0, n, 48)]))
     for batch in (1, 2):
