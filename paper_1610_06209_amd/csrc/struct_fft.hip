@@ -20,6 +20,7 @@
 // batch 16383, Toeplitz 315 -> 251 us).  n = 2^13 and 2^14 are held to two waves per SIMD and the padded kinds spill 100 and 72
 // bytes per thread there (2^10 and 2^11: 16 and 20).
 #include "launch.hpp"
+#include "allreg.hpp"
 namespace spinner {
 
 struct StructFftParams {
@@ -90,10 +91,17 @@ struct Geo {
         return ((k & ((1 << b) - 1)) << lo(g)) | ((k >> b) << (LOGN - e));
     }
     // the part that the thread contributes
-    static __device__ __forceinline__ int base_index(int g, int t) { return (t & ((1 << lo(g)) - 1)) | ((t >> lo(g)) << (lo(g) + bits(g))); }
+    static constexpr __host__ __device__ __forceinline__ int base_index(int g, int t) { return (t & ((1 << lo(g)) - 1)) | ((t >> lo(g)) << (lo(g) + bits(g))); }
     // one unused 8-byte slot after every 16 points keeps the strided accesses of a phase on different banks; index
     // parts with disjoint bits add up, so a register's part of the address is a constant
     static constexpr __host__ __device__ int pad(int i) { return i + (i >> 4); }
+    // the wave id stands for the same index bits in both phases: a wave then reads what it wrote itself
+    static constexpr bool within_waves(int from, int to)
+    {
+        for (int bit = 64; bit < T; bit <<= 1)
+            if (base_index(from, bit) != base_index(to, bit)) return false;
+        return true;
+    }
     static constexpr int LDS_POINTS = N + N / 16;
 };
 
@@ -199,13 +207,15 @@ struct JoinFactors {
     }
 };
 
-// registers of group FROM's phase to those of group TO's
+// Registers of group FROM's phase to those of group TO's.  A thread writes the positions that it read in the exchange before, so
+// one barrier is enough, and none where the data stay within the waves.
 template <typename G, int FROM, int TO>
 __device__ __forceinline__ void exchange(C (&v)[G::R], C* X, int t)
 {
     C* a = X + G::pad(G::base_index(FROM, t));
     static_for<0, G::R>([&](auto k) { a[G::pad(G::reg_index(FROM, k.value))] = v[k.value]; });
-    __syncthreads();
+    if constexpr (G::within_waves(FROM, TO)) wave_lds_fence();
+    else __syncthreads();
     const C* c = X + G::pad(G::base_index(TO, t));
     static_for<0, G::R>([&](auto k) { v[k.value] = c[G::pad(G::reg_index(TO, k.value))]; });
     __builtin_amdgcn_sched_barrier(0);
