@@ -10,6 +10,7 @@ struct BlockParams {
     TileParams t;             // x, out, batch, m, out_stride, factor, factor_rev, inv_sqrt_m, sin_off as for one block
     const float* diag_sets;   // [L][3][n]
     int L;
+    int per_slice;            // blocks that one workgroup applies: blockIdx.y takes [y per_slice, (y + 1) per_slice)
 };
 
 // EPI_STORE_NONE:   out[vec][l m + i]              = factor * y_l[i]
@@ -57,7 +58,8 @@ spinner_blocks_kernel(BlockParams p)
     float* row = p.t.out + (active ? vec : 0) * p.t.out_stride;
     const int m = active ? p.t.m : 0;
 
-    for (int l = 0; l < p.L; ++l) {
+    const int first = blockIdx.y * p.per_slice, last = p.L - first < p.per_slice ? p.L : first + p.per_slice;
+    for (int l = first; l < last; ++l) {
         const float* d = p.diag_sets + (long long)l * 3 * n;
         T v[R];
 #pragma unroll
@@ -102,14 +104,16 @@ template <> struct BlocksTuning<float, 13> : NotWide { static constexpr int rmax
 template <> struct BlocksTuning<float, 14> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 
 template <typename T, int NT, int EPI>
-static hipError_t launch_blocks_nt(const BlockParams& p, hipStream_t s)
+static hipError_t launch_blocks_nt(const BlockParams& p0, hipStream_t s)
 {
+    BlockParams p = p0;
     using G = GeomFrom<BlocksTuning<T, NT>, NT>;
     static_assert(G::R <= 32, "resident x beside the working values");
     const long long blocks = (p.t.batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((spinner_blocks_kernel<T, G, EPI>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
+    const unsigned slices = block_slices(NT, EPI == EPI_STORE_COSSIN, blocks * G::WAVES, p.L, p.per_slice);
+    hipLaunchKernelGGL((spinner_blocks_kernel<T, G, EPI>), dim3((unsigned)blocks, slices), dim3(G::THREADS), 0, s, p);
     return hipGetLastError();
 }
 

@@ -200,7 +200,8 @@ __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams 
     }
 
     constexpr int W = n / 64 < 4 ? 4 : n / 64;
-    for (int t = 0; t < p.L; ++t) {
+    const int first = blockIdx.y * p.per_slice, last = p.L - first < p.per_slice ? p.L : first + p.per_slice;
+    for (int t = first; t < last; ++t) {
         const unsigned long long* hw = p.signs + (long long)t * p.triple_words + 3 * W;   // [3][2][R]: diagonal, layout
         float v[R];
         hash_ar_flip_from<G>(v, x0, hw);            // D1 in layout A
@@ -258,20 +259,23 @@ hipError_t launch_pack_hash_words(const float* diag_sets, int log2n, int L, unsi
 }
 
 template <int NT, bool SIGNS>
-static hipError_t launch_hash_nt(const HashParams& p, hipStream_t s)
+static hipError_t launch_hash_nt(const HashParams& p0, hipStream_t s)
 {
+    HashParams p = p0;
     if constexpr (SIGNS && hash_ar_log2r(NT) != 0) {
         using GA = HashArGeom<NT, hash_ar_log2r(NT)>;
         const long long blocks = (p.batch + GA::VECS_PER_WG - 1) / GA::VECS_PER_WG;
         if (blocks <= 0) return hipSuccess;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((spinner_hash_ar_kernel<GA>), dim3((unsigned)blocks), dim3(GA::THREADS), 0, s, p);
+        const unsigned slices = hash_slices(NT, blocks * GA::WAVES, p.L, p.per_slice);
+        hipLaunchKernelGGL((spinner_hash_ar_kernel<GA>), dim3((unsigned)blocks, slices), dim3(GA::THREADS), 0, s, p);
     } else {
         using G = TileGeom<NT, clamp_rmax(NT, kHashRmax)>;
         const long long blocks = (p.batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG;
         if (blocks <= 0) return hipSuccess;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((spinner_hash_kernel<G, SIGNS>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
+        const unsigned slices = hash_slices(NT, blocks * G::WAVES, p.L, p.per_slice);
+        hipLaunchKernelGGL((spinner_hash_kernel<G, SIGNS>), dim3((unsigned)blocks, slices), dim3(G::THREADS), 0, s, p);
     }
     return hipGetLastError();
 }

@@ -151,6 +151,39 @@ constexpr bool blocks_in_one_launch(int log2n, bool cossin, long long batch)
 {
     return log2n <= (cossin && batch > kComputeUnits ? 13 : kBlocksMaxLog);
 }
+// A workgroup that applies L triples to its vectors one after the other takes as long as L of them, however empty the chip is.
+// Launches of few waves are therefore cut along the triples as well: slices of per_slice triples each (blockIdx.y), up to
+// `most_waves` waves in all and at least `least` triples in a slice, each slice reading x for itself.
+inline unsigned triple_slices(long long waves, int L, long long most_waves, int least, int& per_slice)
+{
+    long long slices = most_waves / (waves > 0 ? waves : 1);
+    if (slices > L / least) slices = L / least;
+    if (slices < 1) slices = 1;
+    const long long per = (L + slices - 1) / slices;
+    per_slice = (int)per;
+    return (unsigned)((L + per - 1) / per);
+}
+// Hash: bound by the vector ALU, so many short slices also even out the last round of workgroups; what a slice reads again
+// shows once there are four waves per SIMD.  One slice / as cut here, in us, L = 16: n = 64, batch 16384 24 / 11; n = 256, 4096
+// vectors 36 / 14; n = 1024, 512 vectors 68 / 10, 4096 68 / 49; n = 4096, 16 vectors 96 / 8, 256 97 / 26, 1024 113 / 86, 4096 369 /
+// 322; n = 2^14, 128 vectors 132 / 50, 1024 394 / 372.  A batch of n = 2^12 that fills the chip just once is left whole (2048
+// vectors, L = 12, fp32 diagonals, inputs that change from call to call: 140 / 149).
+inline unsigned hash_slices(int log2n, long long waves, int L, int& per_slice)
+{
+    if (log2n == 12 && waves >= 4096 && waves < 6144) { per_slice = L; return 1; }
+    return triple_slices(waves, L, 32768, waves >= 4096 ? 4 : (waves >= 2048 ? 2 : 1), per_slice);
+}
+// Stacked blocks: memory comes in earlier.  One slice / as cut here, in us, L = 4: n = 512, features, batch 1024 22.4 / 8.9;
+// n = 2048, projections, 256 21.4 / 7.9, 2048 27.4 / 24.0, features 1024 36.8 / 29.1; n = 4096, projections, 512 26.1 / 15.1; n = 2^13,
+// features, 128 36.3 / 18.4, projections, 512 32.6 / 27.1; n = 2^14, features, 64 63.4 / 22.7, projections, 128 34.5 / 21.5.  With
+// twice the waves and more it loses (n = 2048, projections, 4096 44.6 / 51.3, features, 2048 50.8 / 52.0; n = 2^14, projections, 256
+// 37.8 / 40.4).
+inline unsigned block_slices(int log2n, bool cossin, long long waves, int L, int& per_slice)
+{
+    const bool wide = log2n >= 11 && log2n <= 13;
+    if (waves > (wide && !cossin ? 2048 : 1024)) { per_slice = L; return 1; }
+    return triple_slices(waves, L, wide ? 4096 : 2048, 1, per_slice);
+}
 hipError_t launch_blocks(int log2n, bool cossin, const TileParams& p, const float* diag_sets, int L, hipStream_t s);
 
 // sign words per diagonal in the packed format

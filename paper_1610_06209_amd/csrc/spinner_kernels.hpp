@@ -1122,6 +1122,7 @@ struct HashParams {
     int* out_idx;             // [batch][L]
     long long batch;
     int L;
+    int per_slice;            // triples that one workgroup applies: blockIdx.y takes [y per_slice, (y + 1) per_slice)
 };
 
 template <typename G, bool SIGNS>
@@ -1164,7 +1165,8 @@ spinner_hash_kernel(HashParams p)
         }
     }
 
-    for (int l = 0; l < p.L; ++l) {
+    const int first = blockIdx.y * p.per_slice, last = p.L - first < p.per_slice ? p.L : first + p.per_slice;
+    for (int l = first; l < last; ++l) {
         const float* d = p.diag_sets + (long long)l * 3 * n;
         constexpr int W = n / 64 < 4 ? 4 : n / 64;              // sign words per diagonal
         const unsigned long long* sw = p.signs + (long long)l * p.triple_words;

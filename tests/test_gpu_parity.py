@@ -752,6 +752,42 @@ def test_features_on_both_sides_of_a_batch_limit(gpu, n, m, batch):
         assert t.equal(f(x)[:batch], f(x[:batch]))
 
 
+@pytest.mark.parametrize("n", [16, 64, 256, 1024, 4096, 1 << 13, 1 << 14])
+@pytest.mark.parametrize("L", [2, 5, 16])
+def test_hash_of_few_vectors_cut_along_the_triples(gpu, n, L):
+    # a launch of few waves applies the triples in several workgroups: the buckets of the same vectors in a batch that fills the
+    # chip (4096 waves and five triples: one slice; 8192 waves and 16: four)
+    t = gpu.torch
+    batch = max(512, (1 << 22) // n)
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + L)
+    x = t.randn((batch, n), generator=g, device=gpu.dev)
+    d = t.randint(0, 2, (L, 3, n), generator=g, device=gpu.dev).float() * 2 - 1
+    words = gpu.b.spinner_pack_signs(d)
+    for call in (lambda v: gpu.b.spinner_hash(v, d), lambda v: gpu.b.spinner_hash_signs(v, words, L)):
+        want = call(x)
+        for few in (1, 19, 130):
+            assert t.equal(call(x[:few]), want[:few]), few
+
+
+@pytest.mark.parametrize("epilogue", ["none", "cossin"])
+@pytest.mark.parametrize("n, m", [(16, 16), (512, 512), (2048, 1000), (4096, 2560), (1 << 13, 1 << 13), (1 << 14, 4000)])
+def test_stacked_blocks_of_few_vectors_cut_along_the_blocks(gpu, n, m, epilogue):
+    # the same for stacked blocks: rows as in a batch of more than 2048 waves, which one workgroup takes through all blocks
+    # (features of 2^14 from 257 vectors on run in another kernel with the same arithmetic)
+    t, L = gpu.torch, 5
+    batch = max(260, (1 << 24) // n)
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + m)
+    x = t.randn((batch, n), generator=g, device=gpu.dev)
+    d = t.randint(0, 2, (L, 3, n), generator=g, device=gpu.dev).float() * 2 - 1
+    want = gpu.b.spinner_apply_blocks(x, d, m, epilogue, 1.5)
+    for few in (1, 19, 130):
+        got = gpu.b.spinner_apply_blocks(x[:few], d, m, epilogue, 1.5)
+        # (other kernels serve some batches of features: sums in another order, a last place in the hardware's sine)
+        assert float((got - want[:few]).abs().max()) <= (0.0 if epilogue == "none" else 1e-6 / (L * m) ** 0.5), few
+
+
 def test_stacked_feature_blocks_in_slices(gpu):
     # n = 1024: one wave per pair of vectors and block, at most 2^24 workgroups per launch; with 2^18 blocks a launch takes
     # 128 vectors, so the last three rows of 131 come from a second one
