@@ -587,11 +587,9 @@ int spinner_layer_backward(const float* dy, const float* x, const void* saved, i
     p.dx = dx;
     p.partial = static_cast<float*>(workspace);
     p.batch = batch;
-    p.slots = spinner::layer_backward_slots(log2n, batch);
+    p.slots = 0;              // the launch knows its workgroups
     p.factor = (float)factor;
-    hipError_t e = spinner::launch_layer_backward(log2n, p, s);
-    if (e != hipSuccess) return hip_fail(e);
-    e = spinner::launch_layer_reduce(p.partial, p.slots, 3LL * n, factor, dd, s);
+    const hipError_t e = spinner::launch_layer_backward(log2n, p, factor, dd, s);
     return e == hipSuccess ? SPINNER_OK : hip_fail(e);
 }
 

@@ -255,9 +255,9 @@ struct LayerForwardParams;
 struct LayerBackwardParams;
 constexpr int kLayerMaxLog = 14;
 hipError_t launch_layer_forward(int log2n, const LayerForwardParams& p, hipStream_t s);
-long long layer_backward_slots(int log2n, long long batch);      // partial-sum rows the backward kernel writes
-hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, hipStream_t s);
-hipError_t launch_layer_reduce(const float* partial, long long slots, long long len, double factor, float* dd, hipStream_t s);
+long long layer_backward_slots(int log2n, long long batch);      // rows of 3 n floats of workspace that the partial sums are given
+// the backward kernel and the sum of its partial rows: dd = factor * sums
+hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, double factor, float* dd, hipStream_t s);
 // n > 2^14: dd[i] = sum over the batch of g[b][i] a[b][i] (partial: layer_large_slabs(log2n, batch) rows of n floats);
 // with d1 != null the same sweep writes dx = d1 .* g
 long long layer_large_slabs(int log2n, long long batch);

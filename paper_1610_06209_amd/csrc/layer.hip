@@ -8,32 +8,50 @@ constexpr int layer_rmax(int nt) { return nt <= 5 ? 2 : (nt <= 9 ? 3 : (nt <= 12
 template <int NT>
 using LayerGeom = TileGeom<NT, layer_rmax(NT), 4>;
 
-// dd[i] = factor * sum over slots of partial[slot][i], summed in fp64 in a fixed order.  A block owns 16
-// columns; its 16 slot lanes walk the slots with stride 16 and are then added up through LDS.
-__global__ void __launch_bounds__(256) layer_reduce_kernel(const float* __restrict__ partial, long long slots, long long len,
-                                                           double factor, float* __restrict__ dd)
+// dd[i] = factor * sum over the rows of partial[row][i], summed in fp64 in a fixed order.  A block owns one 128-byte line of
+// columns; its row lanes walk the rows and are then added up through LDS.  Bound by the latency of a row lane's loads one behind
+// the other, so a block takes 1024 threads unless there are few rows (whole backward pass with 256 / 1024 threads, in us:
+// n = 2048, batch 500 14.9 / 13.3, n = 2^14, 500 91 / 81, 20 17.0 / 17.9).
+template <typename T, int THREADS>
+__global__ void __launch_bounds__(THREADS) layer_reduce_kernel(const T* __restrict__ partial, long long rows, long long len,
+                                                            double factor, float* __restrict__ dd)
 {
-    __shared__ double sh[16][17];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const long long i = (long long)blockIdx.x * 16 + tx;
+    constexpr int COLS = 128 / sizeof(T), LANES = THREADS / COLS;
+    __shared__ double sh[LANES][COLS + 1];
+    const int tx = threadIdx.x % COLS, ty = threadIdx.x / COLS;
+    const long long i = (long long)blockIdx.x * COLS + tx;
     double s = 0.0;
     if (i < len) {
         long long k = ty;
-        for (; k + 48 < slots; k += 64) {        // four independent loads in flight per thread
-            const float a0 = partial[k * len + i], a1 = partial[(k + 16) * len + i];
-            const float a2 = partial[(k + 32) * len + i], a3 = partial[(k + 48) * len + i];
+        for (; k + 3 * LANES < rows; k += 4 * LANES) {        // four independent loads in flight per thread
+            const T a0 = partial[k * len + i], a1 = partial[(k + LANES) * len + i];
+            const T a2 = partial[(k + 2 * LANES) * len + i], a3 = partial[(k + 3 * LANES) * len + i];
             s += ((double)a0 + (double)a1) + ((double)a2 + (double)a3);
         }
-        for (; k < slots; k += 16) s += (double)partial[k * len + i];
+        for (; k < rows; k += LANES) s += (double)partial[k * len + i];
     }
     sh[ty][tx] = s;
     __syncthreads();
-    if (ty == 0 && i < len) {
-        double t = 0.0;
+    if (ty < 8) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t += sh[r][tx];
-        dd[i] = (float)(factor * t);
+        for (int r = 8; r < LANES; r += 8) s += sh[ty + r][tx];
+        sh[ty][tx] = s;
     }
+    __syncthreads();
+    if (ty == 0 && i < len) {
+#pragma unroll
+        for (int r = 1; r < 8; ++r) s += sh[r][tx];
+        dd[i] = (float)(factor * s);
+    }
+}
+
+template <typename T>
+static hipError_t launch_reduce(const T* partial, long long rows, long long len, double factor, float* dd, hipStream_t s)
+{
+    const long long cols = 128 / sizeof(T), blocks = (len + cols - 1) / cols;
+    if (rows > 32) hipLaunchKernelGGL((layer_reduce_kernel<T, 1024>), dim3((unsigned)blocks), dim3(1024), 0, s, partial, rows, len, factor, dd);
+    else hipLaunchKernelGGL((layer_reduce_kernel<T, 256>), dim3((unsigned)blocks), dim3(256), 0, s, partial, rows, len, factor, dd);
+    return hipGetLastError();
 }
 
 // Above the fused range the backward pass materialises the signal that arrives at each diagonal; the gradient of
@@ -80,7 +98,7 @@ hipError_t launch_layer_large_dd(const float* g, const float* a, int log2n, long
     hipLaunchKernelGGL(layer_large_dd_kernel, dim3((unsigned)per_row, (unsigned)slabs), dim3(256), 0, s, g, a, n, batch, partial, d1, dx);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_layer_reduce(partial, slabs, n, 1.0, dd, s);
+    return launch_reduce(partial, slabs, n, 1.0, dd, s);
 }
 
 // The backward pass of a large batch bypasses cache retention (non-temporal hint on dy, x, the saved activations and dx);
@@ -117,15 +135,36 @@ static long long slots_nt(long long batch)
     return wgs * G::TILES_PER_WG;
 }
 
+// Workgroups of the backward kernel.  Where a workgroup holds several tiles it adds them up itself and leaves one row of doubles,
+// which the workspace (sized for a row of floats per tile and at most 8192 of them) holds for 2048 workgroups and more.  Against
+// a row of floats per tile, which let n = 16 have 128 workgroups and n = 256 write 8192 rows, in us: n = 16, batch 20000 50 -> 7,
+// 337332 143 -> 27; n = 64, 65536 vectors 66 -> 20; n = 256, 1024 vectors 12.4 -> 7.4, 52357 101 -> 57; n = 512, 8000 45 -> 22; n = 1024,
+// 16384 96 -> 74.  768 / 1024 / 1280 / 1536 workgroups: n = 16, batch 10^6 80 / 69 / 65 / 63; n = 64, 500000 112 / 109 / 111 / 133; n = 256,
+// 200000 182 / 173 / 174 / 220; n = 1024, 65536 257 / 242 / 298 / 273 (four waves per SIMD are what 126 registers leave there).
 template <int NT>
-static hipError_t backward_nt(const LayerBackwardParams& p, hipStream_t s)
+static long long workgroups_nt(long long batch)
 {
     using G = LayerGeom<NT>;
-    const long long blocks = p.slots / G::TILES_PER_WG;
+    if (G::WB > 0) return slots_nt<NT>(batch);
+    const long long need = (batch + G::TILES_PER_WG - 1) / G::TILES_PER_WG, most = NT <= 5 ? 1536 : 1024;
+    static_assert(G::WB > 0 || (G::TILES_PER_WG >= 4 && G::TILES_PER_WG <= 64), "a workgroup's doubles fit its tiles' floats");
+    return need < most ? need : most;
+}
+
+template <int NT>
+static hipError_t backward_nt(const LayerBackwardParams& p0, double factor, float* dd, hipStream_t s)
+{
+    using G = LayerGeom<NT>;
+    LayerBackwardParams p = p0;
+    const long long blocks = workgroups_nt<NT>(p.batch);
+    p.slots = blocks * G::TILES_PER_WG;
     if (blocks <= 0) return hipSuccess;
     if (layer_streams(NT, p.batch)) hipLaunchKernelGGL((layer_backward_kernel<G, true>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
     else hipLaunchKernelGGL((layer_backward_kernel<G, false>), dim3((unsigned)blocks), dim3(G::THREADS), 0, s, p);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if constexpr (G::WB > 0) return launch_reduce(p.partial, blocks, 3LL << NT, factor, dd, s);
+    else return launch_reduce(reinterpret_cast<const double*>(p.partial), blocks, 3LL << NT, factor, dd, s);
 }
 
 #define CASES(F, ...) switch (log2n) { case 4: return F<4>(__VA_ARGS__); case 5: return F<5>(__VA_ARGS__); case 6: return F<6>(__VA_ARGS__); \
@@ -143,16 +182,10 @@ long long layer_backward_slots(int log2n, long long batch)
     CASES(slots_nt, batch)
     return 0;
 }
-hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, hipStream_t s)
+hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, double factor, float* dd, hipStream_t s)
 {
-    CASES(backward_nt, p, s)
+    CASES(backward_nt, p, factor, dd, s)
     return hipErrorInvalidValue;
-}
-hipError_t launch_layer_reduce(const float* partial, long long slots, long long len, double factor, float* dd, hipStream_t s)
-{
-    const long long blocks = (len + 15) / 16;
-    hipLaunchKernelGGL(layer_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, partial, slots, len, factor, dd);
-    return hipGetLastError();
 }
 #undef CASES
 }  // namespace spinner

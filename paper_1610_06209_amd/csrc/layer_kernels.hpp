@@ -95,6 +95,42 @@ __device__ __forceinline__ void layer_ctx(ThreadCtx<G>& c, long long& slot)
     for (int b = 0; b < 6; ++b) c.sg[b] = ((c.lit >> b) & 1) ? -1.0f : 1.0f;
 }
 
+// Sums of a workgroup's tiles (one wave or less each), per coordinate, in fp64 and in a fixed order: part[i] = sum over the
+// tiles of f * acc.  The tiles go through LDS; vectors shorter than the workgroup have their tiles shared out among its threads
+// first.  One fp64 row per workgroup instead of an fp32 row per tile: see slots_nt in layer.hip.
+template <typename G>
+__device__ __forceinline__ void sum_tiles(const float (&acc)[G::R], const ThreadCtx<G>& c, float f, double* part)
+{
+    constexpr int n = 1 << G::NT, TILES = G::TILES_PER_WG, THREADS = G::THREADS;
+    constexpr int SHARES = n < THREADS ? THREADS / n : 1, PER = TILES / SHARES;
+    static_assert(TILES % SHARES == 0 && (n >= THREADS || SHARES * n == THREADS), "tiles fall into equal shares");
+    __shared__ float4 tiles[TILES * n / 4];
+    __shared__ double shares[SHARES > 1 ? THREADS : 1];
+    const int tile = (threadIdx.x >> 6) * G::TPW + ((threadIdx.x & 63) >> G::LB);
+    float* all = reinterpret_cast<float*>(tiles);
+    __syncthreads();
+    tile_store<G, 0, false>(acc, c, all + tile * n, f);
+    __syncthreads();
+#pragma unroll
+    for (int i0 = 0; i0 < n; i0 += THREADS) {
+        const int i = SHARES > 1 ? threadIdx.x & (n - 1) : i0 + threadIdx.x, first = SHARES > 1 ? threadIdx.x / n * PER : 0;
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) s += (double)all[(first + k) * n + i];
+        if constexpr (SHARES == 1) {
+            part[i] = s;
+        } else {
+            shares[threadIdx.x] = s;
+            __syncthreads();
+            if (threadIdx.x < n) {
+#pragma unroll
+                for (int k = 1; k < SHARES; ++k) s += shares[k * n + i];
+                part[i] = s;
+            }
+        }
+    }
+}
+
 // One vector per tile.  The held values carry the tracked lane sign after an odd number of
 // transforms (see lane_stage_fmac_dpp); it is folded into the factors of what is stored.
 template <typename G>
@@ -122,7 +158,8 @@ __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardP
 }
 
 // Slot s (one tile position of one workgroup) handles vectors s, s + slots, s + 2 slots, ... and
-// keeps its three per-coordinate sums in registers; they are written once at the end.
+// keeps its three per-coordinate sums in registers; they are written once at the end: a row of floats per slot where a
+// tile spans several waves, else a row of doubles per workgroup.
 template <typename G, bool STREAM>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu((G::R == 16 && G::WB > 0) ? kLayerBackwardWaves : (G::R == 32 ? 2 : 1))))
 layer_backward_kernel(LayerBackwardParams p)
@@ -216,11 +253,19 @@ layer_backward_kernel(LayerBackwardParams p)
             }
         }
     }
-    if (slot < p.slots) {
-        float* part = p.partial + slot * 3LL * n;
-        tile_store<G, L3, false>(acc1, c, part, sgn);            // t3 carries the tracked sign (three transforms)
-        tile_store<G, L2, false>(acc2, c, part + n, 1.0f);       // t2: two transforms
-        tile_store<G, L1, false>(acc3, c, part + 2 * n, sgn);    // t1: one transform
+    // t3 carries the tracked sign (three transforms), t2 does not (two), t1 does (one)
+    if constexpr (G::WB > 0) {
+        if (slot < p.slots) {
+            float* part = p.partial + slot * 3LL * n;
+            tile_store<G, L3, false>(acc1, c, part, sgn);
+            tile_store<G, L2, false>(acc2, c, part + n, 1.0f);
+            tile_store<G, L1, false>(acc3, c, part + 2 * n, sgn);
+        }
+    } else {
+        double* part = reinterpret_cast<double*>(p.partial) + blockIdx.x * 3LL * n;
+        sum_tiles<G>(acc1, c, sgn, part);
+        sum_tiles<G>(acc2, c, 1.0f, part + n);
+        sum_tiles<G>(acc3, c, sgn, part + 2 * n);
     }
 }
 

@@ -20,7 +20,8 @@ struct LayerBackwardParams {
     const float* saved2;
     const float* d[3];
     float* dx;
-    float* partial;          // [slots][3][n]: per-slot sums over the vectors of that slot (unscaled)
+    float* partial;          // sums over the vectors of a slot or of a workgroup (unscaled): floats [slots][3][n] where a tile
+                             // spans several waves, else doubles [workgroups][3][n]
     long long batch;
     long long slots;         // number of (workgroup, tile slot) pairs = stride between the vectors of one slot
     float factor;            // scale * n^{-3/2}

@@ -3,6 +3,7 @@ called through the C ABI, against the fp64 oracle on the same fp32 inputs.
 
 Tolerance: relative L2 error <= 1e-5 per vector for y and dx, and per diagonal for the three parameter
 gradients (which sum over the batch)."""
+import math
 import sys
 
 import numpy as np
@@ -127,6 +128,39 @@ def test_layer_backward_many_vectors_per_slot(gpu, oracle, n, batch):
     assert gpu.b.spinner_layer_workspace_bytes(n, batch) < batch * 3 * n * 4
     y, dx, dd = _run(gpu, x, d, dy, 1.0)
     _check(oracle, x, d, dy, 1.0, y, dx, dd)
+
+
+@pytest.mark.parametrize("n,batch", [(16, 1), (16, 65), (16, 98305), (32, 33), (32, 50001), (64, 8000), (128, 17), (256, 8193), (512, 5),
+                                     (512, 4097), (1024, 3), (1024, 4099), (2048, 33), (8192, 20)])
+def test_layer_diagonal_gradients_of_whole_workgroups(gpu, n, batch):
+    # up to n = 1024 a workgroup adds up its tiles in fp64 and writes one row (edges: a workgroup that is not full, one vector more
+    # than all workgroups hold at once), above it writes a row per tile and few rows are added by smaller blocks: the gradients
+    # against fp64 matrix products, and nothing written past the documented workspace
+    t, b = gpu.torch, gpu.b
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + batch)
+    x, dy = (t.randn((batch, n), generator=g, device=gpu.dev) for _ in range(2))
+    d = 1.0 + 0.5 * t.randn((3, n), generator=g, device=gpu.dev)
+    _, saved = b.spinner_layer_forward(x, d[0], d[1], d[2])
+    need = b.spinner_layer_workspace_bytes(n, batch)
+    ws = t.full((need + 4096,), 0xA5, dtype=t.uint8, device=gpu.dev)
+    dx, dd = b.spinner_layer_backward(dy, x, saved, d[0], d[1], d[2], workspace=ws)
+    assert bool((ws[need:] == 0xA5).all())
+    H = t.ones((1, 1), dtype=t.float64, device=gpu.dev)
+    while H.shape[0] < n:
+        H = t.cat((t.cat((H, H), 1), t.cat((H, -H), 1)), 0)
+    H /= math.sqrt(n)
+    a, D = [x.double()], d.double()
+    for k in range(2):
+        a.append((a[-1] * D[k]) @ H)
+    s, want = dy.double() @ H, [None] * 3
+    for k in (2, 1, 0):
+        want[k] = (s * a[k]).sum(0)
+        s = (s * D[k]) @ H if k else s * D[0]
+    want = t.stack(want)
+    # 3 log2(n) rounded stages per factor of a product (2^-24 each, independent) leave some 4e-7 of the norm at n = 2^13
+    assert float(((dd.double() - want).norm(dim=1) / want.norm(dim=1)).max()) <= 1.5e-6
+    assert float((dx.double() - s).norm() / s.norm()) <= 1.5e-6
 
 
 @pytest.mark.parametrize("n", [16, 256, 2048, 1 << 14])
