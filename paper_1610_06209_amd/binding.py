@@ -1,4 +1,4 @@
-"""Thin ctypes binding of ``libspinner.so`` (the C ABI in ``include/spinner.h``).
+"""Thin binding of ``libspinner.so`` (the C ABI in ``include/spinner.h``): ctypes, with the usual calls in native code.
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  PyTorch is used for device memory and streams, nothing else.  There
@@ -42,9 +42,9 @@ EXPORTS = ["spinner_apply", "spinner_hash", "spinner_workspace_bytes", "spinner_
            "spinner_struct_params", "spinner_struct_spectrum_bytes", "spinner_struct_prepare", "spinner_struct_apply",
            "spinner_struct_workspace_bytes", "spinner_struct_apply_ws"]
 
-if not os.path.exists(LIB_PATH):
+if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_native.so")):
     raise ImportError(
-        "libspinner.so is not built: run `python -m paper_1610_06209_amd.build` "
+        "libspinner.so or _native.so is not built: run `python -m paper_1610_06209_amd.build` "
         "(or __graft_entry__.build()); there is no fallback path")
 
 # PyTorch ships its own HIP runtime and loads it by path; the library must bind to that same copy (it owns
@@ -53,6 +53,10 @@ if not os.path.exists(LIB_PATH):
 import torch  # noqa: E402
 
 lib = ctypes.CDLL(LIB_PATH)
+# The usual calls, checks and allocations included, in native code (csrc/binding_native.cpp); each answers None, before anything is
+# launched, to a call that is out of the ordinary, which then goes the long way below.
+from . import _native  # noqa: E402
+
 _vp = ctypes.c_void_p
 lib.spinner_apply.restype = ctypes.c_int
 lib.spinner_apply.argtypes = [_vp, ctypes.c_int, ctypes.c_long, _vp, _vp, _vp, ctypes.c_int, ctypes.c_int,
@@ -201,6 +205,9 @@ def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, w
     ``out`` (and the workspace when one is needed) unless given.  Asynchronous
     on ``stream`` (default: torch's current stream).
     """
+    r = _native.apply(x, d1, d2, d3, m, epilogue, scale, out, workspace, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -232,6 +239,9 @@ def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, w
 
 def spinner_hash(x, diag_sets, out_idx=None, stream=None):
     """Cross-polytope buckets, int32 [batch][L], for L diagonal triples diag_sets fp32 [L][3][n]."""
+    r = _native.hash(x, diag_sets, out_idx, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     batch, n = x.shape
@@ -328,6 +338,9 @@ def spinner_pack_signs(diag_sets, stream=None):
 def spinner_apply_signs(x, signs, m=None, epilogue="none", scale=1.0, out=None, workspace=None, stream=None,
                         triple=0):
     """spinner_apply for +-1 diagonals given as packed sign words (see spinner_pack_signs)."""
+    r = _native.apply_signs(x, signs, m, epilogue, scale, out, workspace, stream, triple)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     m = n if m is None else int(m)
@@ -357,6 +370,9 @@ def spinner_apply_signs(x, signs, m=None, epilogue="none", scale=1.0, out=None, 
 
 def spinner_hash_signs(x, signs, L, out_idx=None, stream=None):
     """spinner_hash for +-1 diagonals given as packed sign words of L triples."""
+    r = _native.hash_signs(x, signs, L, out_idx, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     if signs.numel() < spinner_signs_bytes(n, L):
@@ -428,6 +444,9 @@ def _codes_workspace(x, workspace):
 
 def spinner_sign_codes(x, d1, d2, d3, m=None, codes=None, workspace=None, stream=None):
     """Sign bits of the first m coordinates of H D3 H D2 H D1 x, int64 CUDA tensor [batch][m/64]."""
+    r = _native.sign_codes(x, d1, d2, d3, m, codes, workspace, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -444,6 +463,9 @@ def spinner_sign_codes(x, d1, d2, d3, m=None, codes=None, workspace=None, stream
 
 def spinner_sign_codes_signs(x, signs, m=None, codes=None, workspace=None, stream=None, triple=0):
     """spinner_sign_codes for +-1 diagonals given as packed sign words (see spinner_pack_signs)."""
+    r = _native.sign_codes_signs(x, signs, m, codes, workspace, stream, triple)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
     m = n if m is None else int(m)
@@ -461,6 +483,9 @@ def spinner_sign_codes_signs(x, signs, m=None, codes=None, workspace=None, strea
 
 def spinner_angular_gram(codes_a, codes_b, m, out=None, stream=None):
     """out[i][j] = 1 - Hamming(codes_a[i], codes_b[j]) / m, fp32 CUDA tensor [na][nb]."""
+    r = _native.angular_gram(codes_a, codes_b, m, out, stream)
+    if r is not None:
+        return r
     _check_tensor(codes_a, "codes_a", torch.int64)
     _check_tensor(codes_b, "codes_b", torch.int64)
     words = spinner_code_bytes(m) // 8
@@ -492,6 +517,9 @@ def spinner_layer_workspace_bytes(n: int, batch: int) -> int:
 
 def spinner_layer_forward(x, d1, d2, d3, scale=1.0, y=None, saved=None, stream=None):
     """y = scale * H D3 H D2 H D1 x and the opaque activations the backward pass needs: returns (y, saved)."""
+    r = _native.layer_forward(x, d1, d2, d3, scale, y, saved, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(d, name, torch.float32)
@@ -515,6 +543,9 @@ def spinner_layer_forward(x, d1, d2, d3, scale=1.0, y=None, saved=None, stream=N
 
 def spinner_layer_backward(dy, x, saved, d1, d2, d3, scale=1.0, dx=None, dd=None, workspace=None, stream=None):
     """Gradients for x ([batch][n]) and for the three diagonals ([3][n], summed over the batch): returns (dx, dd)."""
+    r = _native.layer_backward(dy, x, saved, d1, d2, d3, scale, dx, dd, workspace, stream)
+    if r is not None:
+        return r
     for name, t in (("dy", dy), ("x", x), ("saved", saved), ("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(t, name, torch.float32)
     batch, n = x.shape
@@ -543,6 +574,9 @@ def spinner_sketch_workspace_bytes(n: int, d: int, m: int) -> int:
 
 def spinner_sketch(A, w, d1, d2, d3, m, scale=1.0, out=None, workspace=None, stream=None):
     """B = scale * (first m rows of H D3 H D2 H D1) diag(w) A for A fp32 [n][d]; w may be None.  Returns B [m][d]."""
+    r = _native.sketch(A, w, d1, d2, d3, m, scale, out, workspace, stream)
+    if r is not None:
+        return r
     _check_tensor(A, "A", torch.float32)
     for name, t in (("d1", d1), ("d2", d2), ("d3", d3)):
         _check_tensor(t, name, torch.float32)
@@ -591,6 +625,9 @@ def spinner_sketch_gram_workspace_bytes(m: int, d: int) -> int:
 
 def spinner_sketch_gram(B, out=None, workspace=None, stream=None):
     """G = B^T B, fp32 CUDA tensor [d][d]."""
+    r = _native.sketch_gram(B, out, workspace, stream)
+    if r is not None:
+        return r
     _check_tensor(B, "B", torch.float32)
     m, d = B.shape
     if out is None:
@@ -614,6 +651,9 @@ def spinner_sketch_gram(B, out=None, workspace=None, stream=None):
 def spinner_apply_blocks(x, diag_sets, m=None, epilogue="none", scale=1.0, out=None, workspace=None, stream=None):
     """L independent triples (diag_sets fp32 [L][3][n]) applied to the same x, their m-row blocks side by side:
     out [batch][L m] (epilogue none) or [batch][2 L m] (cos block | sin block)."""
+    r = _native.apply_blocks(x, diag_sets, m, epilogue, scale, out, workspace, stream)
+    if r is not None:
+        return r
     _check_tensor(x, "x", torch.float32)
     _check_tensor(diag_sets, "diag_sets", torch.float32)
     batch, n = x.shape
@@ -685,6 +725,9 @@ def spinner_struct_workspace_bytes(kind, n: int, batch: int) -> int:
 
 def spinner_struct_apply_ws(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=None, workspace=None, stream=None):
     """spinner_struct_apply for every supported n (a workspace tensor is made when none is given and one is needed)."""
+    r = _native.struct_apply_ws(x, kind, spectrum, d1, d2, m, scale, out, workspace, stream)
+    if r is not None:
+        return r
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
     for name, t in (("x", x), ("d1", d1), ("d2", d2)):
         _check_tensor(t, name, torch.float32)

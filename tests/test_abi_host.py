@@ -194,6 +194,27 @@ def test_layer_entry_points_host_side(b):
     assert g(None, None, None, 1024, 0, None, None, None, one, None, None, None, None) == b.SPINNER_OK
 
 
+def test_native_calls_leave_host_tensors_to_the_long_way(b):
+    # every native call answers None, having done nothing, to tensors that are not on a GPU, and takes all its arguments
+    import torch
+
+    x = torch.zeros(2, 16)
+    one = torch.zeros(16)
+    none = [None] * 3
+    calls = {"apply": (x, one, one, one, None, "none", 1.0, *none), "apply_signs": (x, one, None, "none", 1.0, *none, 0),
+             "apply_blocks": (x, x, None, "none", 1.0, *none), "hash": (x, x, None, None), "hash_signs": (x, one, 1, None, None),
+             "sign_codes": (x, one, one, one, None, *none), "sign_codes_signs": (x, one, None, *none, 0),
+             "angular_gram": (x, x, 256, None, None), "layer_forward": (x, one, one, one, 1.0, *none),
+             "layer_backward": (x, x, x, one, one, one, 1.0, *none, None), "sketch": (x, None, one, one, one, 2, 1.0, *none),
+             "sketch_gram": (x, *none), "struct_apply_ws": (x, "toeplitz", one, one, one, None, 1.0, *none)}
+    for name, args in calls.items():
+        assert getattr(b._native, name)(*args) is None, name
+        with pytest.raises(TypeError):
+            getattr(b._native, name)(*args[:-1])
+    with pytest.raises(ValueError, match="CUDA tensor"):
+        b.spinner_apply(x, one, one, one)
+
+
 def test_stream_copy_rejects_bad_arguments(b):
     c = b.lib.spinner_stream_copy
     assert c(None, 64, 16, None) == b.SPINNER_ERR_NULL_PTR
