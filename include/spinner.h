@@ -80,17 +80,18 @@ typedef enum {
  *                  NULL when that is 0
  *   stream         hipStream_t
  *
- * Up to the fused limit (n <= 2^16 for SPINNER_EPI_NONE, n <= 2^14 for
- * SPINNER_EPI_COSSIN) one kernel keeps the vector on chip for all three sign-flip +
- * transform rounds.  Above it the call makes four passes over HBM using the
- * Kronecker structure H_{ab} = H_a (x) H_b of the Sylvester matrix; intermediate
- * passes run in place in `out` when m == n, else in `workspace`.
+ * Up to the fused limit of n = 2^16 one kernel keeps the vector on chip for all three
+ * sign-flip + transform rounds.  Above it, and at n = 2^15 and 2^16 for batches of up to
+ * 32 vectors (features at 2^16: 48) that have a buffer, the call makes four passes over HBM
+ * using the Kronecker structure H_{ab} = H_a (x) H_b of the Sylvester matrix; intermediate
+ * passes run in place in `out` when m == n and the epilogue is NONE, else in `workspace`,
+ * which features ask for from n = 2^15 on.
  *
  * Accuracy: outputs of SPINNER_EPI_NONE carry the rounding of 3 log2 n fp32
  * butterfly stages (relative L2 error of a few 1e-7 per vector).  The fused
  * feature kernels (SPINNER_EPI_COSSIN, n <= 2^14) run their butterflies and the
  * reduction of w in fp64, so the unit-norm feature vector is good to 1e-5
- * relative at any scale.  Above 2^14 the four passes are fp32: each angle w
+ * relative at any scale.  Above 2^14 the butterflies are fp32: each angle w
  * then carries an error of about 3.4e-8 * sqrt(3 log2 n) * rms(w) radians,
  * which is also the relative L2 error of the feature vector, i.e. at most
  * max(1e-5, 5e-7 * rms(w)); with scale = sqrt(n) / sigma that exceeds 1e-5
@@ -188,7 +189,7 @@ int spinner_hash_signs_ws(const float *x, int n, long batch, int L,
  * as in spinner_apply): at n = 2^10 and, but for some small batches of two or three
  * blocks, 2^12 every block reads x (all blocks of a vector through one L2; one launch for
  * up to 2^24 workgroups); at n = 2^14 batches of more than 256 vectors take one launch per
- * block.  Above that size every block runs the four-pass path and reads x again.
+ * block.  Above that size every block runs as a call of its own and reads x again.
  * Otherwise as spinner_apply (which is the case L = 1).
  */
 size_t spinner_blocks_workspace_bytes(int n, long batch, int m, int epilogue);

@@ -136,7 +136,11 @@ static int apply_impl(const float* x, int n, int log2n, long batch, const float*
     p.factor_rev = factor_d / 6.283185307179586476925286766559;
     p.xcd_group_log = -1;
 
-    if (log2n <= fused_max_log(epilogue)) {
+    // n = 2^15, 2^16: few vectors take the four passes where there is a buffer for them (the output itself, or a workspace)
+    const bool cossin = epilogue == SPINNER_EPI_COSSIN;
+    const bool passes = log2n > kFusedMaxLogOther && batch <= few_wide_vectors(log2n, !cossin) &&
+                        (ws || (epilogue == SPINNER_EPI_NONE && m == n && blocks == 1));
+    if (!passes && log2n <= (cossin ? kFusedMaxLogFeatures : fused_max_log(epilogue))) {
         if (batch > 0x7fffffffLL) return SPINNER_ERR_BAD_BATCH;
         p.x = x; p.out = out;
         p.d[0] = d1; p.d[1] = d2; p.d[2] = d3;
@@ -280,7 +284,7 @@ int spinner_apply_signs(const float* x, int n, long batch, const void* signs, in
     if (rc != SPINNER_OK || batch == 0) return rc;
     if (!signs) return SPINNER_ERR_NULL_PTR;
     if (!aligned16(signs)) return SPINNER_ERR_ALIGNMENT;
-    if (log2n > fused_max_log(epilogue) && spinner::has_fp32_copy(log2n)) {      // four passes whose row passes multiply by the fp32 diagonals behind the words
+    if (spinner::has_fp32_copy(log2n)) {      // for the four passes, whose row passes multiply by the fp32 diagonals behind the words
         const unsigned long long* w = static_cast<const unsigned long long*>(signs);
         const float* d = reinterpret_cast<const float*>(w + spinner::fp32_copy_offset(n, log2n));
         return apply_impl(x, n, log2n, batch, d, d + n, d + 2 * (size_t)n, w, m, epilogue, scale, out, workspace, stream);

@@ -1,5 +1,5 @@
-// Fused three-round kernels, cos/sin random-feature epilogue, n = 2^4 .. 2^14.
-// The butterflies run in fp64: with w = scale * y of magnitude ~10^2 the rounding
+// Fused three-round kernels, cos/sin random-feature epilogue, n = 2^4 .. 2^16.
+// Up to 2^14 the butterflies run in fp64: with w = scale * y of magnitude ~10^2 the rounding
 // of 3 log2(n) fp32 stages alone would exceed a 1e-5 relative feature error.
 #include "launch.hpp"
 #include "allreg.hpp"
@@ -277,12 +277,17 @@ hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float*
 }
 
 #define CASE(NT) case NT: return signs ? launch_cossin<NT, true>(p, tiles, s) : launch_cossin<NT, false>(p, tiles, s);
+// n = 2^15, 2^16: fp64 values do not fit a compute unit; fp32 butterflies on the plain kernels' geometries
+#define WIDECASE(NT) case NT: return signs ? launch_tile<float, NT, NT, 3, true, EPI_STORE_COSSIN, true>(p, tiles, s) \
+                                           : launch_tile<float, NT, NT, 3, true, EPI_STORE_COSSIN, false>(p, tiles, s);
 hipError_t launch_fused_cossin(int log2n, bool signs, const TileParams& p, long long tiles, hipStream_t s)
 {
     switch (log2n) {
         CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
+        WIDECASE(15) WIDECASE(16)
     default: return hipErrorInvalidValue;
     }
 }
+#undef WIDECASE
 #undef CASE
 }  // namespace spinner

@@ -10,6 +10,17 @@ constexpr int clamp_rmax(int nt, int want) { return (nt - 3) / 2 > want ? (nt - 
 // largest n (log2) that a single fused kernel handles, per epilogue / entry point
 constexpr int kFusedMaxLogPlain = 16;     // fp32 butterflies, first-m-rows epilogue
 constexpr int kFusedMaxLogOther = 14;     // fp64 feature map, hash
+constexpr int kFusedMaxLogFeatures = 16;  // feature map on fp32 butterflies above that: one fused pass, the workspace that its callers
+                                          // have to bring stays unused but for few vectors
+// n = 2^15, 2^16: up to so many vectors the passes through global memory are ahead, which share a vector among 32 workgroups and
+// more; one workgroup that takes a vector through all rounds leaves the other compute units idle.  Passes / fused, in us, fp32
+// diagonals: plain 2^15, 1 vector 11.7 / 17.4, 32 17.5 / 18.7, 48 21.7 / 20.0, 256 53 / 25; 2^16, 1 12.8 / 28.3, 32 26.0 / 30.9, 48 33.9 /
+// 30.9, 256 90 / 45; features 2^15, 32 19.5 / 21.6, 48 23.7 / 21.7, 256 55 / 32, 1000 179 / 82; 2^16, 48 36.4 / 37.8, 64 42.4 / 38.4,
+// 256 98 / 72; layer forward and backward 2^15, 24 69 / 67, 48 87 / 80, 256 206 / 136; 2^16, 48 104 / 108, 64 124 / 113, 256 361 / 235.
+constexpr long long few_wide_vectors(int log2n, bool plain)
+{
+    return log2n < 15 || log2n > 16 ? 0 : (plain || log2n == 15 ? 32 : 48);
+}
 
 // Registers per thread (2^rmax values) and waves per workgroup for each tile
 // size, from timing sweeps on MI355X: fewer registers per thread buy occupancy

@@ -842,16 +842,21 @@ __device__ __forceinline__ void feature_sincos(float y, const TileParams&, float
 {
     sincosf(y * lane_factor, &s, &c);
 }
+// fp32 values of a kernel that runs all three rounds (n = 2^15, 2^16): the angle in fp64 as below.  Sixty-four library calls
+// per thread take registers and instruction cache that such a kernel does not have, and the product's rounding goes away.
+__device__ __forceinline__ void feature_sincos(double y, double revolutions, float& s, float& c)
+{
+    const float fr = (float)__builtin_amdgcn_fract(y * revolutions);
+    s = __builtin_amdgcn_sinf(fr);
+    c = __builtin_amdgcn_cosf(fr);
+}
 // fp64 values: w / (2 pi) is formed in fp64 and reduced to its fractional part in fp64
 // (exact), then the hardware sine / cosine, which take their argument in revolutions,
 // evaluate it in fp32.  On reduced arguments they are accurate to 1.2e-7 absolute
 // (measured over 4M points), far inside the 1e-5 feature tolerance.
 __device__ __forceinline__ void feature_sincos(double y, const TileParams& p, float, float& s, float& c)
 {
-    const double t = y * p.factor_rev;
-    const float fr = (float)__builtin_amdgcn_fract(t);
-    s = __builtin_amdgcn_sinf(fr);
-    c = __builtin_amdgcn_cosf(fr);
+    feature_sincos(y, p.factor_rev, s, c);
 }
 
 // ------------------------------------------------------------------ the tile kernel
@@ -1084,13 +1089,16 @@ spinner_tile_kernel(TileParams p)
             } else {
                 // dst row is [cos block | sin block]; the sin entry of coordinate i sits sin_off floats after its cos entry
                 const long long so = p.sin_off;
+                constexpr bool WIDE_ANGLE = std::is_same<T, float>::value && NSTEPS == 3;
+                const double revolutions = WIDE_ANGLE ? p.factor_rev * (double)tracked_sign<G, CB, T>(c) : 0.0;
         #pragma unroll
                 for (int jh = 0; jh < RF / 4; ++jh) {
                     const long long i = tile_first + tile_offset<NT, C>(ebase | G::reg_index(LAYF, jh * 4), p.sl);
                     float sn[4], cs[4];
         #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        feature_sincos(v[jh * 4 + k], p, lane_factor, sn[k], cs[k]);
+                        if constexpr (WIDE_ANGLE) feature_sincos((double)v[jh * 4 + k], revolutions, sn[k], cs[k]);
+                        else feature_sincos(v[jh * 4 + k], p, lane_factor, sn[k], cs[k]);
                         sn[k] *= p.inv_sqrt_m;
                         cs[k] *= p.inv_sqrt_m;
                     }

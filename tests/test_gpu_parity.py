@@ -514,6 +514,41 @@ def test_features_above_the_fused_range_at_the_kernel_scale(gpu, oracle):
     assert rel_l2_per_vector(got, oracle.epilogue_cossin(y, n, scale / 22.6)).max() <= REL_L2_TOL
 
 
+@pytest.mark.parametrize("log2n,few", [(15, 32), (16, 48)])
+def test_few_and_many_vectors_of_the_widest_fused_sizes(gpu, oracle, log2n, few):
+    # n = 2^15, 2^16: up to 32 vectors (features at 2^16: 48) go through the four passes, more through one fused kernel.  The
+    # same vectors on both sides of the limit, some against the oracle, in place, on both diagonal forms, and features of rows
+    # of whole 16-byte pieces and others, alone and in stacked blocks
+    t, n = gpu.torch, 1 << log2n
+    x, d = _rng_case(n, 2, 1600 + log2n)
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(log2n)
+    xd = t.randn((few + 1, n), generator=g, device=gpu.dev)
+    xd[:2] = _to(gpu, x)
+    dd = [_to(gpu, d[k]) for k in range(3)]
+    signs = gpu.b.spinner_pack_signs(_to(gpu, d[None]))
+    y = oracle.spinner(x, d[0], d[1], d[2])
+    for f in (lambda v, m, e, c: gpu.b.spinner_apply(v, *dd, m, e, c), lambda v, m, e, c: gpu.b.spinner_apply_signs(v, signs, m, e, c)):
+        for k in (1, 32, 33):
+            got = f(xd[:k], n, "none", 1.5)
+            assert rel_l2_per_vector(got[:1].cpu().numpy(), oracle.epilogue_none(y[:1], n, 1.5)).max() <= 1e-6
+            # two roundings of each of 3 log2(n) stages, in another order
+            assert float((got - f(xd, n, "none", 1.5)[:k]).norm() / got.norm()) <= 1e-6
+        for m in (n, 4096, 1001):
+            many, less = f(xd, m, "cossin", 8.0), f(xd[:few], m, "cossin", 8.0)
+            assert rel_l2_per_vector(many[:2].cpu().numpy(), oracle.epilogue_cossin(y, m, 8.0)).max() <= REL_L2_TOL
+            # angles of rms 8 carry 3.4e-8 sqrt(3 log2 n) of it on either side
+            assert float((many[:few] - less).norm() / less.norm()) <= 2 * 3.4e-8 * math.sqrt(3 * log2n) * 8.0
+    here = xd[:5].clone()
+    gpu.b.spinner_apply(here, *dd, n, "none", 1.5, out=here)
+    assert t.equal(here, gpu.b.spinner_apply(xd[:5], *dd, n, "none", 1.5))
+    sets = t.stack([t.stack(dd), t.stack((dd[2], dd[0], dd[1]))])
+    both = gpu.b.spinner_apply_blocks(xd, sets, 512, "cossin", 8.0).reshape(few + 1, 2, 2, 512)
+    for l in range(2):
+        one = gpu.b.spinner_apply(xd, *sets[l], 512, "cossin", 8.0).reshape(few + 1, 2, 512) / math.sqrt(2.0)
+        assert float((both[:, :, l] - one).abs().max()) <= 2.0 ** -22 / math.sqrt(2 * 512)
+
+
 # ------------------------------------------------------------------ +-1 diagonals as packed sign words
 @pytest.mark.parametrize("log2n", list(range(4, 15)))
 def test_sign_word_path_every_fused_size(gpu, oracle, log2n):
