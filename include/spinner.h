@@ -266,7 +266,10 @@ int spinner_angular_gram(const void *codes_a, long na, const void *codes_b, long
  *                   above 2^14 also two signal buffers of batch * n floats)
  *
  * n = 2^4 .. 2^24, batch < 2^31.  Up to 2^14 each call is one fused kernel (plus the
- * reduction of the partial sums).  Above, every one of the three transforms is a pass
+ * reduction of the partial sums).  At 2^15 and 2^16, for more than 32 and 48 vectors, the
+ * forward pass is one kernel, the backward pass one that leaves the signals arriving at D3
+ * and D2 in the workspace, one that leaves the signal arriving at D1, and the three batch
+ * sums.  Above, every one of the three transforms is a pass
  * over the rows and a pass over the columns of the matrix view of the vector (the
  * saved activations arise between transforms), the backward pass writes the signal
  * arriving at each diagonal to the workspace and sums signal times activation over

@@ -527,7 +527,7 @@ int spinner_layer_forward(const float* x, int n, long batch, const float* d1, co
     if (!x || !d1 || !d2 || !d3 || !y || !saved) return SPINNER_ERR_NULL_PTR;
     if (!aligned16(x) || !aligned16(d1) || !aligned16(d2) || !aligned16(d3) || !aligned16(y) || !aligned16(saved))
         return SPINNER_ERR_ALIGNMENT;
-    if (log2n > spinner::kLayerMaxLog) {
+    if (log2n > spinner::kLayerWideMaxLog || batch <= spinner::few_wide_vectors(log2n, false)) {
         // three single transforms; the activations entering D2 and D3 are kept normalised
         hipStream_t s = static_cast<hipStream_t>(stream);
         float* a2 = static_cast<float*>(saved);
@@ -544,6 +544,7 @@ int spinner_layer_forward(const float* x, int n, long batch, const float* d1, co
     p.saved2 = p.saved1 + (size_t)batch * n;
     p.batch = batch;
     p.factor = (float)((double)scale / ((double)n * sqrt((double)n)));
+    p.norm = (float)(1.0 / sqrt((double)n));
     const hipError_t e = spinner::launch_layer_forward(log2n, p, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SPINNER_OK : hip_fail(e);
 }
@@ -570,6 +571,16 @@ int spinner_layer_backward(const float* dy, const float* x, const void* saved, i
         float* w0 = static_cast<float*>(workspace);
         float* w1 = w0 + (size_t)batch * n;
         float* partial = w1 + (size_t)batch * n;
+        if (log2n <= spinner::kLayerWideMaxLog && batch > spinner::few_wide_vectors(log2n, false)) {
+            // signals unnormalised, activations as saved; dx is not written before x and dy are used up
+            const double c = scale, nn = (double)n, h1 = sqrt(nn);
+            hipError_t e = spinner::launch_layer_signals(log2n, dy, nullptr, d3, w0, w1, batch, s);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, a3, log2n, batch, partial, dd + 2 * (size_t)n, nullptr, nullptr, s, c / h1);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w1, a2, log2n, batch, partial, dd + (size_t)n, nullptr, nullptr, s, c / nn);
+            if (e == hipSuccess) e = spinner::launch_layer_signals(log2n, w1, d2, nullptr, w0, nullptr, batch, s);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, x, log2n, batch, partial, dd, d1, dx, s, c / (nn * h1));
+            return e == hipSuccess ? SPINNER_OK : hip_fail(e);
+        }
         const double h = 1.0 / sqrt((double)n);
         int r = large_round(dy, nullptr, w0, n, log2n, batch, h * (double)scale, s);
         if (r != SPINNER_OK) return r;

@@ -264,16 +264,20 @@ hipError_t launch_pack_hash_words(const float* diag_sets, int log2n, int L, unsi
 // adaptive layer (forward with saved activations, backward); the parameter structs are in layer_kernels.hpp
 struct LayerForwardParams;
 struct LayerBackwardParams;
-constexpr int kLayerMaxLog = 14;
+constexpr int kLayerMaxLog = 14;          // backward pass in one kernel
+constexpr int kLayerWideMaxLog = 16;      // forward pass in one kernel, backward pass with one vector per workgroup and signals in memory
 hipError_t launch_layer_forward(int log2n, const LayerForwardParams& p, hipStream_t s);
 long long layer_backward_slots(int log2n, long long batch);      // rows of 3 n floats of workspace that the partial sums are given
 // the backward kernel and the sum of its partial rows: dd = factor * sums
 hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, double factor, float* dd, hipStream_t s);
 // n > 2^14: dd[i] = sum over the batch of g[b][i] a[b][i] (partial: layer_large_slabs(log2n, batch) rows of n floats);
-// with d1 != null the same sweep writes dx = d1 .* g
+// with d1 != null the same sweep writes dx = factor d1 .* g, and dd is factor times the sum
 long long layer_large_slabs(int log2n, long long batch);
 hipError_t launch_layer_large_dd(const float* g, const float* a, int log2n, long long batch, float* partial, float* dd,
-                                 const float* d1, float* dx, hipStream_t s);
+                                 const float* d1, float* dx, hipStream_t s, double factor = 1.0);
+// n = 2^15, 2^16, unnormalised: first = H in and second = H (db .* first), or (db null) first = H (da .* in)
+hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, long long batch,
+                                hipStream_t s);
 
 // Newton sketch: transposition with optional row weights, Gram matrix on the matrix pipe
 hipError_t launch_transpose_scale(const float* src, long long rows, long long cols, const float* row_scale, float* dst,

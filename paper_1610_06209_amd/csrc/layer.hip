@@ -58,16 +58,19 @@ static hipError_t launch_reduce(const T* partial, long long rows, long long len,
 // that diagonal is then a sum over the batch of (signal x activation), per coordinate.  Block (bx, by) owns four
 // coordinates per thread and the vectors by, by + S, by + 2S, ... (S = gridDim.y) and writes row `by` of `partial`
 // (fp64 sums, rounded once); layer_reduce_kernel adds the S rows in fp64 in a fixed order.  With d1 != null the same
-// sweep also writes dx = d1 .* g (the last step of the backward pass).
+// sweep also writes dx = factor d1 .* g (the last step of the backward pass).
 __global__ void __launch_bounds__(256) layer_large_dd_kernel(const float* __restrict__ g, const float* __restrict__ a, long long n,
                                                              long long batch, float* __restrict__ partial,
-                                                             const float* __restrict__ d1, float* __restrict__ dx)
+                                                             const float* __restrict__ d1, float* __restrict__ dx, float factor)
 {
     const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= n) return;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     float4 dv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (d1) dv = *reinterpret_cast<const float4*>(d1 + i);
+    if (d1) {
+        dv = *reinterpret_cast<const float4*>(d1 + i);
+        dv.x *= factor; dv.y *= factor; dv.z *= factor; dv.w *= factor;
+    }
     for (long long b = blockIdx.y; b < batch; b += gridDim.y) {
         const float4 gv = *reinterpret_cast<const float4*>(g + b * n + i);
         const float4 av = *reinterpret_cast<const float4*>(a + b * n + i);
@@ -89,16 +92,16 @@ long long layer_large_slabs(int log2n, long long batch)
 }
 
 hipError_t launch_layer_large_dd(const float* g, const float* a, int log2n, long long batch, float* partial, float* dd,
-                                 const float* d1, float* dx, hipStream_t s)
+                                 const float* d1, float* dx, hipStream_t s, double factor)
 {
     const long long n = 1LL << log2n;
     const long long per_row = (n / 4 + 255) / 256;
     const long long slabs = layer_large_slabs(log2n, batch);
     if (per_row > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(layer_large_dd_kernel, dim3((unsigned)per_row, (unsigned)slabs), dim3(256), 0, s, g, a, n, batch, partial, d1, dx);
+    hipLaunchKernelGGL(layer_large_dd_kernel, dim3((unsigned)per_row, (unsigned)slabs), dim3(256), 0, s, g, a, n, batch, partial, d1, dx, (float)factor);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce(partial, slabs, n, 1.0, dd, s);
+    return launch_reduce(partial, slabs, n, factor, dd, s);
 }
 
 // The backward pass of a large batch bypasses cache retention (non-temporal hint on dy, x, the saved activations and dx);
@@ -172,8 +175,37 @@ static hipError_t backward_nt(const LayerBackwardParams& p0, double factor, floa
     case 11: return F<11>(__VA_ARGS__); case 12: return F<12>(__VA_ARGS__); case 13: return F<13>(__VA_ARGS__); case 14: return F<14>(__VA_ARGS__); \
     default: break; }
 
+// n = 2^15, 2^16 on the geometries of the fused plain kernels
+template <typename G>
+static hipError_t forward_wide(const LayerForwardParams& p, hipStream_t s)
+{
+    if (p.batch <= 0) return hipSuccess;
+    if (p.batch > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((layer_forward_kernel<G, true>), dim3((unsigned)p.batch), dim3(G::THREADS), 0, s, p);
+    return hipGetLastError();
+}
+// first = H (da .* in) (da null: H in), and with db second = H (db .* first)
+template <typename G>
+static hipError_t signals_wide(const float* in, const float* da, const float* db, float* first, float* second, long long batch, hipStream_t s)
+{
+    if (batch <= 0) return hipSuccess;
+    if (batch > 0x7fffffffLL || (da && db)) return hipErrorInvalidConfiguration;
+    if (da) hipLaunchKernelGGL((layer_signals_kernel<G, true, false>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second);
+    else hipLaunchKernelGGL((layer_signals_kernel<G, false, true>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second);
+    return hipGetLastError();
+}
+hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, long long batch,
+                                hipStream_t s)
+{
+    if (log2n == 15) return signals_wide<GeomFor<float, 15>>(in, da, db, first, second, batch, s);
+    if (log2n == 16) return signals_wide<GeomFor<float, 16>>(in, da, db, first, second, batch, s);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_layer_forward(int log2n, const LayerForwardParams& p, hipStream_t s)
 {
+    if (log2n == 15) return forward_wide<GeomFor<float, 15>>(p, s);
+    if (log2n == 16) return forward_wide<GeomFor<float, 16>>(p, s);
     CASES(forward_nt, p, s)
     return hipErrorInvalidValue;
 }

@@ -95,6 +95,30 @@ __device__ __forceinline__ void layer_ctx(ThreadCtx<G>& c, long long& slot)
     for (int b = 0; b < 6; ++b) c.sg[b] = ((c.lit >> b) & 1) ? -1.0f : 1.0f;
 }
 
+// One or two transforms of the backward pass of vectors of 2^15 and 2^16 elements, one vector per workgroup, unnormalised:
+// first = H (da .* in), or H in without FIRST_DIAG; TWO: second = H (db .* first) as well.  A compute unit has no room for
+// running sums beside such a vector: the signals go to memory, where layer_large_dd_kernel meets them.
+template <typename G, bool FIRST_DIAG, bool TWO>
+__global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
+layer_signals_kernel(const float* in, const float* da, const float* db, float* first, float* second)
+{
+    static_assert(G::WB > 0, "a workgroup holds one vector");
+    ThreadCtx<G> c;
+    long long vec;
+    layer_ctx(c, vec);
+    const long long off = vec << G::NT;
+    __shared__ float4 lds_store[G::LDS_FLOAT4];
+    float4* lds = lds_store;
+    float v[G::R];
+    tile_load<G, G::layout_after(0), false>(v, c, in + off);
+    spinner_step<G, G::NT, 0, G::layout_after(0), FIRST_DIAG, true, false, false>(v, c, da, nullptr, 0, lds);
+    tile_store<G, G::layout_after(1), false>(v, c, first + off, tracked_sign<G, 0, float>(c));
+    if constexpr (TWO) {
+        spinner_step<G, G::NT, 0, G::layout_after(1), true, false, true, false>(v, c, db, nullptr, 0, lds);
+        tile_store<G, G::layout_after(2), false>(v, c, second + off, 1.0f);
+    }
+}
+
 // Sums of a workgroup's tiles (one wave or less each), per coordinate, in fp64 and in a fixed order: part[i] = sum over the
 // tiles of f * acc.  The tiles go through LDS; vectors shorter than the workgroup have their tiles shared out among its threads
 // first.  One fp64 row per workgroup instead of an fp32 row per tile: see slots_nt in layer.hip.
@@ -133,8 +157,10 @@ __device__ __forceinline__ void sum_tiles(const float (&acc)[G::R], const Thread
 
 // One vector per tile.  The held values carry the tracked lane sign after an odd number of
 // transforms (see lane_stage_fmac_dpp); it is folded into the factors of what is stored.
-template <typename G>
-__global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardParams p)
+// NORMALISED: the activations are saved times n^-1/2 and n^-1, as the passes through global memory leave and read them.
+template <typename G, bool NORMALISED = false>
+__global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
+layer_forward_kernel(LayerForwardParams p)
 {
     constexpr int NT = G::NT;
     constexpr int n = 1 << NT;
@@ -150,9 +176,9 @@ __global__ void __launch_bounds__(G::THREADS) layer_forward_kernel(LayerForwardP
     float v[G::R];
     tile_load<G, G::layout_after(0), false>(v, c, p.x + off);
     spinner_step<G, NT, 0, G::layout_after(0), true, true, false, false>(v, c, p.d[0], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(1), false>(v, c, p.saved1 + off, sgn);
+    if (active) tile_store<G, G::layout_after(1), false>(v, c, p.saved1 + off, NORMALISED ? sgn * p.norm : sgn);
     spinner_step<G, NT, 0, G::layout_after(1), true, false, true, false>(v, c, p.d[1], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(2), false>(v, c, p.saved2 + off, 1.0f);
+    if (active) tile_store<G, G::layout_after(2), false>(v, c, p.saved2 + off, NORMALISED ? 1.0f / (1 << G::NT) : 1.0f);
     spinner_step<G, NT, 0, G::layout_after(2), true, false, false, false>(v, c, p.d[2], nullptr, 0, lds);
     if (active) tile_store<G, G::layout_after(3), false>(v, c, p.y + off, p.factor * sgn);
 }

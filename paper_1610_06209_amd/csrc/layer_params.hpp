@@ -11,6 +11,7 @@ struct LayerForwardParams {
     float* saved2;
     long long batch;
     float factor;            // scale * n^{-3/2}
+    float norm;              // n^{-1/2}
 };
 
 struct LayerBackwardParams {

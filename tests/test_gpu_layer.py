@@ -97,6 +97,35 @@ def test_layer_above_the_fused_range(gpu, oracle, log2n, batch):
     assert rel_l2_per_vector(y1.cpu().numpy(), y3.cpu().numpy().astype(np.float64)).max() <= 2e-6
 
 
+@pytest.mark.parametrize("n,batch", [(1 << 15, 33), (1 << 15, 300), (1 << 16, 49)])
+def test_layer_of_the_widest_sizes_on_both_sides_of_the_batch_limit(gpu, n, batch):
+    # more than 32 (2^16: 48) vectors go through one kernel per pass, fewer through global memory; what the one saves the other
+    # reads: the forward pass of the whole batch, then backward passes of the whole and of its first five vectors
+    t, b = gpu.torch, gpu.b
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + batch)
+    x, dy = (t.randn((batch, n), generator=g, device=gpu.dev) for _ in range(2))
+    d = 1.0 + 0.5 * t.randn((3, n), generator=g, device=gpu.dev)
+    y, saved = b.spinner_layer_forward(x, d[0], d[1], d[2], 0.8)
+    dx, dd = b.spinner_layer_backward(dy, x, saved, d[0], d[1], d[2], 0.8)
+    few = b.spinner_layer_forward(x[:5], d[0], d[1], d[2], 0.8)
+    # fp32 rounding of 3 log2(n) stages in two orders
+    assert float((few[0] - y[:5]).norm() / y[:5].norm()) <= 1e-6
+    part = saved.view(2, batch, n)[:, :5].contiguous()
+    assert float((few[1] - part).norm() / part.norm()) <= 1e-6
+    a = b.spinner_layer_backward(dy[:5], x[:5], part, d[0], d[1], d[2], 0.8)
+    assert float((a[0] - dx[:5]).norm() / dx[:5].norm()) <= 1e-6
+    rest = saved.view(2, batch, n)[:, 5:].contiguous()
+    c = b.spinner_layer_backward(dy[5:], x[5:], rest, d[0], d[1], d[2], 0.8)
+    assert float(((a[1].double() + c[1].double() - dd.double()).norm(dim=1) / dd.double().norm(dim=1)).max()) <= 2e-6
+    inner = float((dy.double() * y.double()).sum())
+    for k in range(3):
+        assert abs(float((d[k].double() * dd[k].double()).sum()) - inner) <= 1e-5 * abs(inner) + 1e-2
+    over = dy.clone()
+    dx2, dd2 = b.spinner_layer_backward(over, x, saved, d[0], d[1], d[2], 0.8, dx=over)
+    assert t.equal(dx2, dx) and t.equal(dd2, dd)
+
+
 def test_layer_above_the_fused_range_in_several_slices(gpu):
     # n = 2^17: the passes walk the batch in slices of 512 vectors; 513 vectors leave a second, shorter slice (257 + 256).
     # Vectors are independent, so y and dx of any row must have the bits of a run on that row alone; each diagonal
