@@ -308,15 +308,11 @@ hipError_t launch_struct_conv(const float* x, const float* d1, const float* d2, 
 
 // the same with every stage between registers, n points at a time (struct_fft.hip): P = n or 2n
 // At n = 2^14 a padded kind of a few vectors leaves most compute units idle (a workgroup takes two vectors through both
-// convolutions, 34 us): up to 96 vectors the passes through global memory, which share a vector among workgroups, are ahead
-// (batch 1 19.6 against 34.3 us, 32 25.4 / 35.5, 64 33.0 / 36.0; 96 38.2 / 35.9, with inputs that change from call to call 33.9 /
-// 37.8; 256 58 / 41).  At n = 2^13 the 512 threads
-// of the general kernel are done with a pair sooner than 256 of this one, but read twice the points and twiddles: up to 32 vectors
-// (Toeplitz, batch 1 25.0 against 27.1, 32 25.6 / 27.8; with spectra and inputs that change from call to call 48 28.9 / 28.5,
-// 128 30.5 / 29.0, 512 34.9 / 35.3, with the same ones 128 26.4 / 28.3, 512 31.9 / 34.0; 513 54 / 34).
+// convolutions, 33 us): up to 96 vectors the passes through global memory, which share a vector among workgroups, are ahead
+// (with inputs that change from call to call, 33 vectors 24.5 / 32.7 us, 64 27.4 / 32.9, 96 32.9 / 33.7, 97 36.8 / 33.6).
 constexpr bool struct_fft_serves(int log2n, int log2p, long long batch)
 {
-    return log2n >= 9 && log2n <= 14 && !(log2p == 15 && batch <= 96) && !(log2p == 14 && log2n == 13 && batch <= 32);
+    return log2n >= 9 && log2n <= 14 && !(log2p == 15 && batch <= 96);
 }
 hipError_t launch_struct_fft(const float* x, const float* d1, const float* d2, const float2* spec, const float2* tw, float* out,
                              long long batch, int log2n, int log2p, int m, int reverse, float factor, hipStream_t s);

@@ -229,13 +229,14 @@ __device__ __forceinline__ void turned_stage(C (&v)[R], C w)
     constexpr int D = INVERSE ? s : B - 1 - s, HALF = D ? 1 << (D - 1) : 1;
     static_for<0, HALF>([&](auto q) {
         const C u = rot64<(q.value << 5 >> D), false>(w);
-        static_for<0, (1 << (B - 1 - D))>([&](auto m) {
-            static_for<0, (D ? 2 : 1)>([&](auto second) {
-                constexpr int turn = q.value + (second.value ? HALF : 0);
-                constexpr int k = FIRST + (INVERSE ? turn | m.value << (s + 1) : bit_reverse(turn, D) << (s + 1) | m.value);
-                butterfly<INVERSE, APART>(v[k], v[k | (1 << s)], second.value ? C{u.y, -u.x} : u);
-            });
-        });
+        constexpr int first = FIRST + (INVERSE ? q.value : bit_reverse(q.value, D) << (s + 1));
+        constexpr int second = FIRST + (INVERSE ? q.value + HALF : bit_reverse(q.value + HALF, D) << (s + 1));
+#pragma unroll
+        for (int m = 0; m < (1 << (B - 1 - D)); ++m) {
+            const int k = m << (INVERSE ? s + 1 : 0);
+            butterfly<INVERSE, APART>(v[first + k], v[(first + k) | (1 << s)], u);
+            if constexpr (D > 0) butterfly<INVERSE, APART>(v[second + k], v[(second + k) | (1 << s)], C{u.y, -u.x});
+        }
     });
 }
 

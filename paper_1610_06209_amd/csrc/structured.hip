@@ -227,10 +227,8 @@ __device__ __forceinline__ void wht_trip(float2* X, int top, int log2n, Load loa
 // H D1 x of two vectors, times D2 (reversed for a Hankel block), zero-padded to P; forward transform, product with
 // the spectrum, inverse transform.  The first trip of the Hadamard stages reads x from global memory, the last
 // inverse trip writes the result there; everything between stays in LDS.
-// THREADS: 64 for transforms of up to 2^9 points (n = 2^5 .. 2^8), 512 for those of 2^14 (a few vectors of n = 2^13, padded
-// kinds); else struct_fft.hip
-template <int THREADS>
-__global__ void __launch_bounds__(THREADS) struct_conv_kernel(StructParams p)
+// Transforms of up to 2^9 points (n = 2^5 .. 2^8); else struct_fft.hip
+__global__ void __launch_bounds__(64) struct_conv_kernel(StructParams p)
 {
     extern __shared__ float2 X[];
     const int L = p.log2p, N = p.log2n;
@@ -528,15 +526,8 @@ hipError_t launch_struct_conv(const float* x, const float* d1, const float* d2, 
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const size_t lds = fft_lds_bytes(log2p);
     StructParams p{x, d1, d2, spec, tw, out, batch, n, log2p, m, reverse, factor, log2n};
-    if (log2p <= 9) {
-        hipLaunchKernelGGL(struct_conv_kernel<64>, dim3((unsigned)blocks), dim3(64), lds, s, p);
-    } else if (log2p == 14) {
-        const hipError_t e = allow_lds(reinterpret_cast<const void*>(struct_conv_kernel<512>), lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(struct_conv_kernel<512>, dim3((unsigned)blocks), dim3(512), lds, s, p);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (log2p > 9) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(struct_conv_kernel, dim3((unsigned)blocks), dim3(64), lds, s, p);
     return hipGetLastError();
 }
 
