@@ -1093,6 +1093,12 @@ spinner_tile_kernel(TileParams p)
                 const double revolutions = WIDE_ANGLE ? p.factor_rev * (double)tracked_sign<G, CB, T>(c) : 0.0;
         #pragma unroll
                 for (int jh = 0; jh < RF / 4; ++jh) {
+                    // four registers whose first coordinate in this wave is past the kept rows: nothing to evaluate.  Sign words, 2^24
+                    // elements, without / with the test, in us: n = 512, m = 256 33.5 / 31.0, m = 64 31.6 / 25.6; n = 2048, m = 1024 43.2 /
+                    // 40.7, m = 256 42.5 / 37.1; n = 2^13, m = 1024 46.2 / 41.2; all rows alike, but n = 2^14 61.4 / 63.0
+                    if constexpr (C >= NT && NT <= 13 && RF > 4) {
+                        if ((wave_index_bits<G, LAYF>(c) | G::reg_index(LAYF, jh * 4)) >= m) continue;
+                    }
                     const long long i = tile_first + tile_offset<NT, C>(ebase | G::reg_index(LAYF, jh * 4), p.sl);
                     float sn[4], cs[4];
         #pragma unroll
