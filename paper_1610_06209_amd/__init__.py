@@ -1,8 +1,9 @@
 """MI355X-native structured spinner (H D3 H D2 H D1 x) hot path.
 
-``workloads`` holds seeded input recipes only.  ``binding`` is the thin ctypes
-face of the C-ABI library built from ``csrc/`` (it is imported lazily so that
-the input recipes stay importable on machines without the built library).
+``workloads`` holds seeded input recipes only.  ``binding`` is the thin face
+(native code for the usual calls, ctypes for the rest) of the C-ABI library
+built from ``csrc/`` (it is imported lazily so that the input recipes stay
+importable on machines without the built library).
 """
 
 __all__ = ["workloads", "binding"]

@@ -105,7 +105,7 @@ size_t spinner_workspace_bytes(int n, long batch, int m, int epilogue)
     return (size_t)batch * (size_t)n * sizeof(float);
 }
 
-// Shared body of spinner_apply / spinner_apply_signs.  For n <= 2^14 `signs`
+// Shared body of spinner_apply / spinner_apply_signs.  Up to the fused limit `signs`
 // (if non-null) replaces d1..d3; above that size the caller passes fp32 diagonals.
 // blocks > 1: this call writes block `block` of a row that stacks `blocks` independent m-row blocks
 // (out already points at the block's first column; see spinner_apply_blocks).

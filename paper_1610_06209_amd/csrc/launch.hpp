@@ -306,7 +306,7 @@ hipError_t launch_struct_prepare(const float* params, int kind, int n, int log2p
 hipError_t launch_struct_conv(const float* x, const float* d1, const float* d2, const float2* spec, const float2* tw, float* out,
                               long long batch, int n, int log2n, int log2p, int m, int reverse, float factor, hipStream_t s);
 
-// the same with every stage between registers, n points at a time (struct_fft.hip): P = n or 2n
+// the same with every stage between registers, n points at a time (struct_fft_kernels.hpp): P = n or 2n
 // At n = 2^14 a padded kind of a few vectors leaves most compute units idle (a workgroup takes two vectors through both
 // convolutions, 33 us): up to 96 vectors the passes through global memory, which share a vector among workgroups, are ahead
 // (with inputs that change from call to call, 33 vectors 24.5 / 32.7 us, 64 27.4 / 32.9, 96 32.9 / 33.7, 97 36.8 / 33.6).

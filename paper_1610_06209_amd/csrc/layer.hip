@@ -1,4 +1,5 @@
-// Adaptive-layer kernels: forward with saved activations, backward, n = 2^4 .. 2^14; batch sums of the backward pass above that.
+// Adaptive-layer kernels: forward with saved activations, backward, n = 2^4 .. 2^14; n = 2^15 and 2^16 in one kernel forward and with
+// the signals in memory backward; batch sums of the backward pass above 2^14.
 #include "launch.hpp"
 #include "layer_kernels.hpp"
 namespace spinner {
@@ -123,6 +124,7 @@ static hipError_t forward_nt(const LayerForwardParams& p, hipStream_t s)
     return hipGetLastError();
 }
 
+// Rows of 3 n floats that the workspace holds; where a tile spans several waves, also the tiles that the backward kernel runs.
 template <int NT>
 static long long slots_nt(long long batch)
 {

@@ -227,7 +227,7 @@ __device__ __forceinline__ void wht_trip(float2* X, int top, int log2n, Load loa
 // H D1 x of two vectors, times D2 (reversed for a Hankel block), zero-padded to P; forward transform, product with
 // the spectrum, inverse transform.  The first trip of the Hadamard stages reads x from global memory, the last
 // inverse trip writes the result there; everything between stays in LDS.
-// Transforms of up to 2^9 points (n = 2^5 .. 2^8); else struct_fft.hip
+// Transforms of up to 2^9 points (n = 2^5 .. 2^8); else struct_fft_kernels.hpp
 __global__ void __launch_bounds__(64) struct_conv_kernel(StructParams p)
 {
     extern __shared__ float2 X[];
