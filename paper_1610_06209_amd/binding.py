@@ -53,8 +53,8 @@ if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_nati
 import torch  # noqa: E402
 
 lib = ctypes.CDLL(LIB_PATH)
-# The usual calls, checks and allocations included, in native code (csrc/binding_native.cpp); each answers None, before anything is
-# launched, to a call that is out of the ordinary, which then goes the long way below.
+# The usual calls, checks and allocations included, in native code (csrc/binding_native.cpp); each answers None to a call
+# that is out of the ordinary or that the library refuses, which then goes the long way below.
 from . import _native  # noqa: E402
 
 _vp = ctypes.c_void_p

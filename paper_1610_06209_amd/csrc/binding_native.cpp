@@ -5,7 +5,8 @@
 // Each function takes the arguments of its namesake in binding.py, all of them, by position, and returns its result, or
 // None when anything about the call is out of the ordinary: a tensor that is no plain contiguous CUDA tensor of the
 // type and size expected, a number that is no Python number, an explicit stream, a status other than SPINNER_OK.
-// Nothing has been launched then, and binding.py takes the call its long way, which knows every check and error.
+// binding.py then takes the call its long way, which knows every check and error.  But for a launch that HIP itself refuses, which
+// the long way meets again and reports, nothing has been launched by then.
 #include <Python.h>
 
 #include <ATen/ATen.h>
