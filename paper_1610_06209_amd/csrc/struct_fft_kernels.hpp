@@ -154,6 +154,20 @@ struct Geo {
     static constexpr int LDS_POINTS = N + N / 16;
 };
 
+// Where the two results of a butterfly are formed apart (eight fused operations), so that the sum's rounding does not enter the
+// difference: as far as it takes for the convolution's error to be no larger than with one factor per point between the phases.
+// Error over 2^26 values in units of 1e-7 of the norm, that form / this one / this one without any phase apart but, of a
+// circulant, the last (512: the middle too, and a factor by squaring): circulant 2^9 1.735 / 1.728 / 1.789, 2^10 1.945 / 1.935 / 1.983, 2^11 2.129 /
+// 2.112 / 2.112, 2^12 2.210 / 2.202 / 2.238, 2^13 2.408 / 2.399 / 2.451, 2^14 2.594 / 2.593 / 2.599; Toeplitz 2^9 1.919 / 1.913 / 1.946, 2^10 2.150 /
+// 2.146 / 2.167, 2^11 2.325 / 2.316 / 2.316, 2^12 2.388 / 2.385 / 2.392, 2^13 2.625 / 2.529 / 2.529.
+template <typename G, bool PADDED>
+struct Apart {
+    static constexpr int n = G::LOGN_;
+    static constexpr bool forward = !PADDED && (n == 9 || n == 10 || n == 13);                              // forward, middle phase
+    static constexpr bool low = PADDED ? n == 9 || n == 12 : n == 12 || n == 14;                            // forward, last stage of all
+    static constexpr bool middle = PADDED ? n <= 10 : n != 11 && n != 14, last = !PADDED;                   // backward
+};
+
 template <int B, int R>
 __device__ __forceinline__ void hadamard_regs(C (&v)[R])
 {
@@ -178,9 +192,9 @@ template <typename G, int g, bool SKEW, bool PADDED>
 struct ForwardTwiddles {
     static constexpr int b = G::bits(g), lo = G::lo(g), above = G::LOGN_ - lo - b, e = G::r - b;
     static_assert(g > 0 && e <= 1, "constants in the top group; at most one more index bit in the registers");
-    // three bits in the low phase: the middle stage's factor is the last one's square, a scattered read less (n = 512, batch 65536,
-    // Toeplitz 110 -> 102 us, circulant 70 -> 67; with four bits and two squares the result's error would grow by 3 to 6 %)
-    static constexpr bool SQUARE = g == 2 && b == 3 && (PADDED || G::LOGN_ == 9);
+    // three bits in the low phase, padded kinds: the middle stage's factor is the last one's square, a scattered read less (n = 512,
+    // batch 65536, Toeplitz 110 -> 102 us; with four bits and two squares the result's error would grow by 3 to 6 %, a circulant's by 2 %)
+    static constexpr bool SQUARE = g == 2 && b == 3 && PADDED;
     C w[b];
     __device__ __forceinline__ void load(const float2* __restrict__ tw, int log2p, int t)
     {
@@ -254,20 +268,21 @@ __device__ __forceinline__ void forward_top(C (&v)[R])
         if constexpr (R > 16) __builtin_amdgcn_sched_barrier(0);
     });
 }
-template <typename G, int g, bool SKEW, bool PADDED>
+// APART: from this stage of the group on
+template <int APART, typename G, int g, bool SKEW, bool PADDED>
 __device__ __forceinline__ void forward_group(C (&v)[G::R], ForwardTwiddles<G, g, SKEW, PADDED>& f)
 {
     constexpr int B = G::bits(g), above = ForwardTwiddles<G, g, SKEW, PADDED>::above;
     if constexpr (ForwardTwiddles<G, g, SKEW, PADDED>::SQUARE) f.w[1] = mul(f.w[2], f.w[2]);
     static_for<0, B>([&](auto st) {
         constexpr int s = B - 1 - st.value;
-        turned_stage<false, false, s, B, 0>(v, f.w[st.value]);
+        turned_stage<false, (st.value >= APART), s, B, 0>(v, f.w[st.value]);
         // the top index bit, where the registers hold it, turns the factors of its half by 2 pi / 2^(above + st + 1)
         if constexpr (G::R >> B == 2) {
             constexpr double a = 6.283185307179586476925286766559 / (double)(2 << (above + st.value));
             constexpr float less = (float)cosm1_near_0(a), sine = (float)sin_near_0(a);
             const C w = f.w[st.value];      // one rounding: what the turn adds is small
-            turned_stage<false, false, s, B, (1 << B)>(v, C{w.x + __builtin_fmaf(w.x, less, w.y * sine), w.y + __builtin_fmaf(w.y, less, w.x * -sine)});
+            turned_stage<false, (st.value >= APART), s, B, (1 << B)>(v, C{w.x + __builtin_fmaf(w.x, less, w.y * sine), w.y + __builtin_fmaf(w.y, less, w.x * -sine)});
         }
         if constexpr (G::R > 16) __builtin_amdgcn_sched_barrier(0);
     });
@@ -317,13 +332,11 @@ __device__ __forceinline__ void exchange(C (&v)[G::R], C* X, int t)
 
 // v (natural order, top phase) convolved with the part of the spectrum at `spec`: cyclic, or skew-cyclic, whose results take
 // exp(+i pi k / n) on point k = j + q0 2^lo0: a constant power of exp(i pi / 2^B0) per register times the conjugate of exp(-i pi j / n).
-// PADDED: one of the two halves of a padded kind.  A circulant block, where less is added up, keeps the butterflies of the last
-// phase apart: with that its error is what it was with a factor for every point between the phases (measured over 2^19
-// values: n = 512 2.6e-7 of the norm, 1024 2.7e-7, 2^12 3.0e-7, 2^13 3.45e-7; 1 % above it without; the padded kinds are 1 .. 4 % below).
+// PADDED: one of the two halves of a padded kind.
 template <typename G, bool SKEW, bool PADDED>
 __device__ __forceinline__ void convolve(C (&v)[G::R], C* X, const float2* __restrict__ spec, const float2* __restrict__ tw, int log2p, int t)
 {
-    constexpr int B0 = G::bits(0), B2 = G::bits(2);
+    constexpr int B0 = G::bits(0), B1 = G::bits(1), B2 = G::bits(2);
     {
         ForwardTwiddles<G, 1, SKEW, PADDED> f1;
         ForwardTwiddles<G, 2, SKEW, PADDED> f2;
@@ -331,9 +344,9 @@ __device__ __forceinline__ void convolve(C (&v)[G::R], C* X, const float2* __res
         forward_top<B0, SKEW>(v);
         exchange<G, 0, 1>(v, X, t);
         f2.load(tw, log2p, t);
-        forward_group<G, 1, SKEW, PADDED>(v, f1);
+        forward_group<(Apart<G, PADDED>::forward ? 0 : B1), G, 1, SKEW, PADDED>(v, f1);
         exchange<G, 1, 2>(v, X, t);
-        forward_group<G, 2, SKEW, PADDED>(v, f2);
+        forward_group<(Apart<G, PADDED>::low ? B2 - 1 : B2), G, 2, SKEW, PADDED>(v, f2);
     }
     {
         // a thread's points of the low phase are runs of 2^B2 consecutive ones: 16-byte loads of two spectrum points
@@ -351,9 +364,9 @@ __device__ __forceinline__ void convolve(C (&v)[G::R], C* X, const float2* __res
     f1.load(tw, log2p, t);
     exchange<G, 2, 1>(v, X, t);
     f0.load(tw, log2p, t);
-    inverse_group<G, 1, false, !PADDED && ForwardTwiddles<G, 2, SKEW, PADDED>::SQUARE>(v, f1);
+    inverse_group<G, 1, false, Apart<G, PADDED>::middle>(v, f1);
     exchange<G, 1, 0>(v, X, t);
-    inverse_group<G, 0, SKEW, !PADDED>(v, f0);
+    inverse_group<G, 0, SKEW, Apart<G, PADDED>::last>(v, f0);
     if constexpr (SKEW) static_for<0, G::R>([&](auto k) { v[k.value] = rot64<k.value * (32 >> B0), true>(v[k.value]); });
 }
 }  // namespace fft

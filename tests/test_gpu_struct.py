@@ -68,6 +68,51 @@ def test_struct_members_match_oracle(gpu, oracle, kind, log2n):
     assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL
 
 
+# Relative error (2-norm) of the convolution alone, in units of 1e-7, of the form that multiplied every point by one factor between
+# two phases, measured on these very inputs: the butterflies that carry their twiddles must not be further off.
+_ERROR_OF_SEPARATE_FACTORS = {("circulant", 9): 1.738, ("circulant", 10): 1.947, ("circulant", 11): 2.131, ("circulant", 12): 2.209,
+                              ("circulant", 13): 2.408, ("circulant", 14): 2.593, ("toeplitz", 9): 1.925, ("toeplitz", 10): 2.152,
+                              ("toeplitz", 11): 2.328, ("toeplitz", 12): 2.391, ("toeplitz", 13): 2.627}
+
+
+def _convolution_error(g, kind, log2n):
+    """x = H u / n with whole numbers u, which the Hadamard stages give back without rounding, so that what enters the convolution is
+    known to the bit: u times D2, rounded once; a final factor that is a power of two; and as reference the spectrum as the
+    library holds it: what remains is the rounding of the two transforms."""
+    t, n = g.torch, 1 << log2n
+    P = n if kind == "circulant" else 2 * n
+    rng = np.random.default_rng(600 + log2n)
+    at = np.arange(P)
+    rev = t.from_numpy(sum(((at >> b) & 1) << (P.bit_length() - 2 - b) for b in range(P.bit_length() - 1))).to(g.dev)
+    one = t.ones(n, device=g.dev)
+    error = norm = 0.0
+    for _ in range(16):
+        spec = g.b.spinner_struct_prepare(kind, _to(g, rng.standard_normal(n if kind == "circulant" else 2 * n - 1).astype(np.float32)), n)
+        d2 = _to(g, rng.standard_normal(n).astype(np.float32))
+        u = _to(g, rng.integers(-511, 512, ((1 << 19) >> log2n, n)).astype(np.float64))
+        x = u / n
+        for b in range(log2n):
+            y = x.reshape(-1, n >> (b + 1), 2, 1 << b)
+            x = t.stack((y[:, :, 0] + y[:, :, 1], y[:, :, 0] - y[:, :, 1]), 2).reshape(-1, n)
+        got = g.b.spinner_struct_apply(x.float(), kind, spec, one, d2, n, float(np.sqrt(n)))
+        v = (u.float() * d2).double()
+        W = t.view_as_complex(spec.view(t.float32)[:2 * P].view(-1, 2).double())[rev]
+        # a generating vector is real, its spectrum as held only nearly so: the vectors go through in pairs, as complex points
+        z = t.zeros((v.shape[0] // 2, P), dtype=t.complex128, device=g.dev)
+        z[:, :n] = t.complex(v[0::2], v[1::2])
+        z = t.fft.ifft(t.fft.fft(z) * W)[:, :n]
+        want = t.stack((z.real, z.imag), 1).reshape(-1, n)
+        error += float((got.double() - want).square().sum())
+        norm += float(want.square().sum())
+    return (error / norm) ** 0.5
+
+
+@pytest.mark.parametrize("kind,log2n", list(_ERROR_OF_SEPARATE_FACTORS))
+def test_rounding_of_the_convolution(gpu, kind, log2n):
+    # 2^23 values: two forms with the same error differ by 0.1 %
+    assert _convolution_error(gpu, kind, log2n) <= 1.001e-7 * _ERROR_OF_SEPARATE_FACTORS[(kind, log2n)]
+
+
 @pytest.mark.parametrize("kind,log2n,batch", [("circulant", 15, 3), ("toeplitz", 14, 5), ("skew_circulant", 15, 2), ("hankel", 15, 3),
                                                ("circulant", 17, 4), ("toeplitz", 17, 1), ("hankel", 18, 2), ("circulant", 20, 2),
                                                ("toeplitz", 21, 1), ("circulant", 22, 1)])
