@@ -543,8 +543,10 @@ int spinner_layer_forward(const float* x, int n, long batch, const float* d1, co
     p.saved1 = static_cast<float*>(saved);
     p.saved2 = p.saved1 + (size_t)batch * n;
     p.batch = batch;
-    p.factor = (float)((double)scale / ((double)n * sqrt((double)n)));
+    const int shrunk = log2n > spinner::kLayerMaxLog ? spinner::wide_shrink_log(log2n) : 0;
+    p.factor = (float)ldexp((double)scale / ((double)n * sqrt((double)n)), 2 * shrunk);
     p.norm = (float)(1.0 / sqrt((double)n));
+    p.norm2 = (float)ldexp(1.0 / (double)n, shrunk);
     const hipError_t e = spinner::launch_layer_forward(log2n, p, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SPINNER_OK : hip_fail(e);
 }
@@ -572,13 +574,17 @@ int spinner_layer_backward(const float* dy, const float* x, const void* saved, i
         float* w1 = w0 + (size_t)batch * n;
         float* partial = w1 + (size_t)batch * n;
         if (log2n <= spinner::kLayerWideMaxLog && batch > spinner::few_wide_vectors(log2n, false)) {
-            // signals unnormalised, activations as saved; dx is not written before x and dy are used up
-            const double c = scale, nn = (double)n, h1 = sqrt(nn);
-            hipError_t e = spinner::launch_layer_signals(log2n, dy, nullptr, d3, w0, w1, batch, s);
-            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, a3, log2n, batch, partial, dd + 2 * (size_t)n, nullptr, nullptr, s, c / h1);
-            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w1, a2, log2n, batch, partial, dd + (size_t)n, nullptr, nullptr, s, c / nn);
-            if (e == hipSuccess) e = spinner::launch_layer_signals(log2n, w1, d2, nullptr, w0, nullptr, batch, s);
-            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, x, log2n, batch, partial, dd, d1, dx, s, c / (nn * h1));
+            // signals with the power of two in scale n^-1/2, n^-1/2 and n^-1/2, activations as saved; the rest goes into the sums'
+            // factors.  dx is not written before x and dy are used up
+            const int shrink = spinner::wide_shrink_log(log2n);
+            int e2;
+            const double c = 2.0 * frexp((double)scale, &e2), h = ldexp(1.0 / sqrt((double)n), shrink);
+            const float p0 = (float)ldexp(1.0, e2 - 1 - shrink), p1 = (float)ldexp(1.0, -shrink);
+            hipError_t e = spinner::launch_layer_signals(log2n, dy, nullptr, d3, w0, w1, p0, p1, batch, s);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, a3, log2n, batch, partial, dd + 2 * (size_t)n, nullptr, nullptr, s, c * h);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w1, a2, log2n, batch, partial, dd + (size_t)n, nullptr, nullptr, s, c * h * h);
+            if (e == hipSuccess) e = spinner::launch_layer_signals(log2n, w1, d2, nullptr, w0, nullptr, p1, 1.0f, batch, s);
+            if (e == hipSuccess) e = spinner::launch_layer_large_dd(w0, x, log2n, batch, partial, dd, d1, dx, s, c * h * h * h);
             return e == hipSuccess ? SPINNER_OK : hip_fail(e);
         }
         const double h = 1.0 / sqrt((double)n);

@@ -275,9 +275,9 @@ hipError_t launch_layer_backward(int log2n, const LayerBackwardParams& p, double
 long long layer_large_slabs(int log2n, long long batch);
 hipError_t launch_layer_large_dd(const float* g, const float* a, int log2n, long long batch, float* partial, float* dd,
                                  const float* d1, float* dx, hipStream_t s, double factor = 1.0);
-// n = 2^15, 2^16, unnormalised: first = H in and second = H (db .* first), or (db null) first = H (da .* in)
-hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, long long batch,
-                                hipStream_t s);
+// n = 2^15, 2^16, H unnormalised: first = p0 H in and second = p1 H (db .* first), or (db null) first = p0 H (da .* in)
+hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, float p0, float p1,
+                                long long batch, hipStream_t s);
 
 // Newton sketch: transposition with optional row weights, Gram matrix on the matrix pipe
 hipError_t launch_transpose_scale(const float* src, long long rows, long long cols, const float* row_scale, float* dst,

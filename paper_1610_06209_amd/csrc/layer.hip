@@ -186,21 +186,22 @@ static hipError_t forward_wide(const LayerForwardParams& p, hipStream_t s)
     hipLaunchKernelGGL((layer_forward_kernel<G, true>), dim3((unsigned)p.batch), dim3(G::THREADS), 0, s, p);
     return hipGetLastError();
 }
-// first = H (da .* in) (da null: H in), and with db second = H (db .* first)
+// first = p0 H (da .* in) (da null: p0 H in), and with db second = p1 H (db .* first)
 template <typename G>
-static hipError_t signals_wide(const float* in, const float* da, const float* db, float* first, float* second, long long batch, hipStream_t s)
+static hipError_t signals_wide(const float* in, const float* da, const float* db, float* first, float* second, float p0, float p1, long long batch,
+                               hipStream_t s)
 {
     if (batch <= 0) return hipSuccess;
     if (batch > 0x7fffffffLL || (da && db)) return hipErrorInvalidConfiguration;
-    if (da) hipLaunchKernelGGL((layer_signals_kernel<G, true, false>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second);
-    else hipLaunchKernelGGL((layer_signals_kernel<G, false, true>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second);
+    if (da) hipLaunchKernelGGL((layer_signals_kernel<G, true, false>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second, p0, p1);
+    else hipLaunchKernelGGL((layer_signals_kernel<G, false, true>), dim3((unsigned)batch), dim3(G::THREADS), 0, s, in, da, db, first, second, p0, p1);
     return hipGetLastError();
 }
-hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, long long batch,
-                                hipStream_t s)
+hipError_t launch_layer_signals(int log2n, const float* in, const float* da, const float* db, float* first, float* second, float p0, float p1,
+                                long long batch, hipStream_t s)
 {
-    if (log2n == 15) return signals_wide<GeomFor<float, 15>>(in, da, db, first, second, batch, s);
-    if (log2n == 16) return signals_wide<GeomFor<float, 16>>(in, da, db, first, second, batch, s);
+    if (log2n == 15) return signals_wide<GeomFor<float, 15>>(in, da, db, first, second, p0, p1, batch, s);
+    if (log2n == 16) return signals_wide<GeomFor<float, 16>>(in, da, db, first, second, p0, p1, batch, s);
     return hipErrorInvalidValue;
 }
 

@@ -95,12 +95,22 @@ __device__ __forceinline__ void layer_ctx(ThreadCtx<G>& c, long long& slot)
     for (int b = 0; b < 6; ++b) c.sg[b] = ((c.lit >> b) & 1) ? -1.0f : 1.0f;
 }
 
-// One or two transforms of the backward pass of vectors of 2^15 and 2^16 elements, one vector per workgroup, unnormalised:
-// first = H (da .* in), or H in without FIRST_DIAG; TWO: second = H (db .* first) as well.  A compute unit has no room for
-// running sums beside such a vector: the signals go to memory, where layer_large_dd_kernel meets them.
+// Values back by a power of two after a transform of 2^15 or 2^16 elements, once they are stored.  Three transforms raise them by up
+// to n^1.5 = 2^24, which would cost inputs above some 2^100 their range; the power is exact, what is left of n^-1/2 goes into the
+// factors of what is stored.  Behind the stores: ahead of them a step at 2^16 takes 3 to 5 % longer.
+template <int R>
+__device__ __forceinline__ void tile_shrink(float (&v)[R], float power)
+{
+#pragma unroll
+    for (int j = 0; j < R; ++j) v[j] *= power;
+}
+
+// One or two transforms of the backward pass of vectors of 2^15 and 2^16 elements, one vector per workgroup, each followed by
+// its power of two: first = p0 H (da .* in), or p0 H in without FIRST_DIAG; TWO: second = p1 H (db .* first) as well.  A compute unit
+// has no room for running sums beside such a vector: the signals go to memory, where layer_large_dd_kernel meets them.
 template <typename G, bool FIRST_DIAG, bool TWO>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
-layer_signals_kernel(const float* in, const float* da, const float* db, float* first, float* second)
+layer_signals_kernel(const float* in, const float* da, const float* db, float* first, float* second, float p0, float p1)
 {
     static_assert(G::WB > 0, "a workgroup holds one vector");
     ThreadCtx<G> c;
@@ -112,10 +122,11 @@ layer_signals_kernel(const float* in, const float* da, const float* db, float* f
     float v[G::R];
     tile_load<G, G::layout_after(0), false>(v, c, in + off);
     spinner_step<G, G::NT, 0, G::layout_after(0), FIRST_DIAG, true, false, false>(v, c, da, nullptr, 0, lds);
-    tile_store<G, G::layout_after(1), false>(v, c, first + off, tracked_sign<G, 0, float>(c));
+    tile_store<G, G::layout_after(1), false>(v, c, first + off, p0 * tracked_sign<G, 0, float>(c));
     if constexpr (TWO) {
+        tile_shrink(v, p0);
         spinner_step<G, G::NT, 0, G::layout_after(1), true, false, true, false>(v, c, db, nullptr, 0, lds);
-        tile_store<G, G::layout_after(2), false>(v, c, second + off, 1.0f);
+        tile_store<G, G::layout_after(2), false>(v, c, second + off, p1);
     }
 }
 
@@ -157,8 +168,9 @@ __device__ __forceinline__ void sum_tiles(const float (&acc)[G::R], const Thread
 
 // One vector per tile.  The held values carry the tracked lane sign after an odd number of
 // transforms (see lane_stage_fmac_dpp); it is folded into the factors of what is stored.
-// NORMALISED: the activations are saved times n^-1/2 and n^-1, as the passes through global memory leave and read them.
-template <typename G, bool NORMALISED = false>
+// WIDE (2^15, 2^16 elements): the values are shrunk after the first and the second transform, and the activations are saved times
+// n^-1/2 and n^-1, as the passes through global memory leave and read them.
+template <typename G, bool WIDE = false>
 __global__ void __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
 layer_forward_kernel(LayerForwardParams p)
 {
@@ -176,9 +188,12 @@ layer_forward_kernel(LayerForwardParams p)
     float v[G::R];
     tile_load<G, G::layout_after(0), false>(v, c, p.x + off);
     spinner_step<G, NT, 0, G::layout_after(0), true, true, false, false>(v, c, p.d[0], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(1), false>(v, c, p.saved1 + off, NORMALISED ? sgn * p.norm : sgn);
+    constexpr int SH = wide_shrink_log(NT);
+    if (active) tile_store<G, G::layout_after(1), false>(v, c, p.saved1 + off, WIDE ? sgn * p.norm : sgn);
+    if constexpr (WIDE) tile_shrink(v, 1.0f / (1 << SH));
     spinner_step<G, NT, 0, G::layout_after(1), true, false, true, false>(v, c, p.d[1], nullptr, 0, lds);
-    if (active) tile_store<G, G::layout_after(2), false>(v, c, p.saved2 + off, NORMALISED ? 1.0f / (1 << G::NT) : 1.0f);
+    if (active) tile_store<G, G::layout_after(2), false>(v, c, p.saved2 + off, WIDE ? p.norm2 : 1.0f);
+    if constexpr (WIDE) tile_shrink(v, 1.0f / (1 << SH));
     spinner_step<G, NT, 0, G::layout_after(2), true, false, false, false>(v, c, p.d[2], nullptr, 0, lds);
     if (active) tile_store<G, G::layout_after(3), false>(v, c, p.y + off, p.factor * sgn);
 }

@@ -126,6 +126,36 @@ def test_layer_of_the_widest_sizes_on_both_sides_of_the_batch_limit(gpu, n, batc
     assert t.equal(dx2, dx) and t.equal(dd2, dd)
 
 
+@pytest.mark.parametrize("n,batch", [(1 << 15, 32), (1 << 15, 33), (1 << 16, 48), (1 << 16, 49)])
+def test_layer_of_the_widest_sizes_over_the_range_of_fp32(gpu, n, batch):
+    # on both sides of the batch limit the values are normalised on the way: inputs and scales times powers of two, up to where a
+    # transform's own sums come near 2^128, give the same bits times that power (but for the roundings of denormal numbers, which none
+    # of these has); the scale's power counts from the first transform of the backward pass on
+    t, b = gpu.torch, gpu.b
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + batch)
+    x, dy = (t.randn((batch, n), generator=g, device=gpu.dev) for _ in range(2))
+    d = t.randint(0, 2, (3, n), generator=g, device=gpu.dev).float() * 2 - 1
+
+    def step(x, dy, scale, scale_back):
+        y, saved = b.spinner_layer_forward(x, d[0], d[1], d[2], scale)
+        dx, dd = b.spinner_layer_backward(dy, x, saved, d[0], d[1], d[2], scale_back)
+        return y, saved, dx, dd
+
+    want = step(x, dy, 0.75, 0.75)
+    assert all(bool(t.isfinite(r).all()) for r in want)
+    # powers of x, dy, the forward and the backward scale
+    for px, pd, ps, pb in ((110, 0, 0, 0), (0, 110, 0, 0), (-60, 0, 0, 0), (0, -60, 0, 0), (60, -60, 0, 0), (0, 0, 120, 100), (0, 0, -90, -60),
+                           (100, 0, -100, -60), (60, 110, 0, -110)):
+        y, saved, dx, dd = step(x * 2.0 ** px, dy * 2.0 ** pd, 0.75 * 2.0 ** ps, 0.75 * 2.0 ** pb)
+        what = (px, pd, ps, pb)
+        if px + ps <= 120:
+            assert t.equal(y, want[0] * 2.0 ** (px + ps)), what
+        assert t.equal(saved, want[1] * 2.0 ** px), what
+        assert t.equal(dx, want[2] * 2.0 ** (pd + pb)), what
+        assert t.equal(dd, want[3] * 2.0 ** (px + pd + pb)), what
+
+
 def test_layer_above_the_fused_range_in_several_slices(gpu):
     # n = 2^17: the passes walk the batch in slices of 512 vectors; 513 vectors leave a second, shorter slice (257 + 256).
     # Vectors are independent, so y and dx of any row must have the bits of a run on that row alone; each diagonal
