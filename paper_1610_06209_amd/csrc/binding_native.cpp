@@ -4,9 +4,9 @@
 //
 // Each function takes the arguments of its namesake in binding.py, all of them, by position, and returns its result, or
 // None when anything about the call is out of the ordinary: a tensor that is no plain contiguous CUDA tensor of the
-// type and size expected, a number that is no Python number, an explicit stream, a status other than SPINNER_OK.
-// binding.py then takes the call its long way, which knows every check and error.  But for a launch that HIP itself refuses, which
-// the long way meets again and reports, nothing has been launched by then.
+// type and size expected, a number that is no Python number, an explicit stream, a status that the library finds before it
+// launches anything.  binding.py then takes the call its long way, which knows every check and error.  SPINNER_ERR_HIP
+// alone may come with kernels already on their way: that call is not made again, its SpinnerError is raised from here.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -136,6 +136,15 @@ const void* sign_words(PyObject* o, int n, int first, int count)
     return static_cast<const char*>(t->data_ptr()) + first * one;
 }
 
+// a status other than SPINNER_OK: the long way, or the error itself
+PyObject* refused(int rc)
+{
+    if (rc != SPINNER_ERR_HIP) Py_RETURN_NONE;
+    const auto error = pybind11::module_::import("paper_1610_06209_amd.binding").attr("SpinnerError");
+    PyErr_SetObject(error.ptr(), error(rc).ptr());
+    return nullptr;
+}
+
 using Args = PyObject* const*;
 #define LONG_WAY Py_RETURN_NONE
 #define ENTRY(NAME, COUNT)                                                          \
@@ -167,7 +176,7 @@ ENTRY(apply_signs, 9)
         const Tensor ws = w.scratch(need, *x);
         rc = spinner_apply_signs(ptr(x), n, batch, words, m, epi, scale, ptr(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -191,7 +200,7 @@ ENTRY(apply, 10)
         const Tensor ws = w.scratch(need, *x);
         rc = spinner_apply(ptr(x), n, batch, ptr(d1), ptr(d2), ptr(d3), m, epi, scale, ptr(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -216,7 +225,7 @@ ENTRY(apply_blocks, 8)
         const Tensor ws = w.scratch(need, *x);
         rc = spinner_apply_blocks(ptr(x), n, batch, L, ptr(d), m, epi, scale, ptr(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -236,7 +245,7 @@ ENTRY(hash, 4)
         out = o.get({batch, L}, at::kInt, *x);
         rc = spinner_hash(ptr(x), n, batch, L, ptr(d), ptr<int>(out), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -256,7 +265,7 @@ ENTRY(hash_signs, 5)
         out = o.get({batch, L}, at::kInt, *x);
         rc = spinner_hash_signs(ptr(x), n, batch, L, words, ptr<int>(out), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -279,7 +288,7 @@ ENTRY(sign_codes, 8)
         const Tensor ws = w.scratch(need, *x);
         rc = spinner_sign_codes(ptr(x), n, batch, ptr(d1), ptr(d2), ptr(d3), m, ptr<void>(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -302,7 +311,7 @@ ENTRY(sign_codes_signs, 7)
         const Tensor ws = w.scratch(need, *x);
         rc = spinner_sign_codes_signs(ptr(x), n, batch, signs, m, ptr<void>(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -323,7 +332,7 @@ ENTRY(angular_gram, 5)
         out = o.get({na, nb}, at::kFloat, *p);
         rc = spinner_angular_gram(ptr<void>(p), na, ptr<void>(q), nb, m, ptr(out), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -345,7 +354,7 @@ ENTRY(layer_forward, 8)
         saved = s.get({2, batch, n}, at::kFloat, *x);
         rc = spinner_layer_forward(ptr(x), n, batch, ptr(d1), ptr(d2), ptr(d3), scale, ptr(y), ptr<void>(saved), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return Py_BuildValue("(NN)", THPVariable_Wrap(std::move(y)), THPVariable_Wrap(std::move(saved)));
 ENTRY_END
 
@@ -372,7 +381,7 @@ ENTRY(layer_backward, 11)
         rc = spinner_layer_backward(ptr(dy), ptr(x), ptr<void>(saved), n, batch, ptr(d1), ptr(d2), ptr(d3), scale, ptr(dx), ptr(dd),
                                     ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return Py_BuildValue("(NN)", THPVariable_Wrap(std::move(dx)), THPVariable_Wrap(std::move(dd)));
 ENTRY_END
 
@@ -397,7 +406,7 @@ ENTRY(sketch, 10)
         const Tensor ws = w.scratch(need < 16 ? 16 : need, *A);
         rc = spinner_sketch(ptr(A), n, d, ptr(weights), ptr(d1), ptr(d2), ptr(d3), m, scale, ptr(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -419,7 +428,7 @@ ENTRY(sketch_gram, 4)
         const Tensor ws = w.scratch(need, *B);
         rc = spinner_sketch_gram(ptr(B), m, d, ptr(out), ptr<void>(ws), current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 
@@ -443,7 +452,7 @@ ENTRY(struct_apply_ws, 10)
         rc = spinner_struct_apply_ws(ptr(x), n, batch, kind, ptr<void>(spectrum), ptr(d1), ptr(d2), m, scale, ptr(out), ptr<void>(ws),
                                      current_stream());
     }
-    if (rc != SPINNER_OK) LONG_WAY;
+    if (rc != SPINNER_OK) return refused(rc);
     return THPVariable_Wrap(std::move(out));
 ENTRY_END
 

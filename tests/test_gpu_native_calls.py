@@ -1,6 +1,7 @@
 """The native part of the binding against its long way: a call with an explicit stream always goes the long way, so every
 entry point is called both ways on the same inputs and has to give the same bits, with and without the caller's
 buffers; what the native part does not take has to work, or fail, as it does on the long way."""
+import ctypes
 import threading
 
 import numpy as np
@@ -135,6 +136,41 @@ def test_calls_that_the_native_part_leaves_to_the_long_way(gpu):
         t.func.vmap(lambda v: b.spinner_apply(v, d1, d2, d3))(x.reshape(1, 37, 1024))
     empty = b.spinner_apply(x[:0], d1, d2, d3, 100)
     assert tuple(empty.shape) == (0, 100)
+
+
+def test_an_error_of_hip_is_raised_and_the_call_not_made_again(gpu):
+    # an error that an earlier HIP call left behind is met by the check behind the first launch: the kernel is on its way by
+    # then, and a second call on the same buffers would transform x twice.  hipSetDevice refuses a device that is not there.
+    t, b = gpu.torch, gpu.b
+    x, d = _inputs(gpu)
+    want = b.spinner_apply(x, *d[0])
+    t.cuda.synchronize()
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(w[-1] for w in (line.split() for line in f) if "libamdhip64" in w[-1]))
+    native, calls = b._native, []
+
+    class Counting:
+        @staticmethod
+        def apply(*a):
+            calls.append(a)
+            return native.apply(*a)
+
+    for i in range(2):
+        here = x.clone()
+        t.cuda.synchronize()
+        if i == 1:
+            b._native = Counting
+        try:
+            assert hip.hipSetDevice(1 << 20) != 0
+            with pytest.raises(b.SpinnerError) as e:
+                b.spinner_apply(here, *d[0], out=here, stream=None if i else t.cuda.current_stream())
+        finally:
+            b._native = native
+        assert e.value.status == b.SPINNER_ERR_HIP
+        t.cuda.synchronize()
+        assert t.equal(here, want)
+    assert len(calls) == 1
+    assert t.equal(b.spinner_apply(x, *d[0]), want)
 
 
 def test_native_calls_on_side_streams_of_several_threads(gpu):
