@@ -198,6 +198,40 @@ def _check_tensor(t, name, dtype):
         raise ValueError("%s must be a contiguous %s CUDA tensor" % (name, dtype))
 
 
+# Nothing behind the C ABI knows how long a buffer is: a call that could reach past one, or into memory the GPU has no way to, is
+# refused here.
+def _check_device(t, name):
+    if not t.is_cuda and not t.is_pinned():
+        raise ValueError("%s must be in GPU memory" % name)
+
+
+def _check_workspace(t, need):
+    if t is None:
+        return
+    if t.numel() * t.element_size() < need or t.untyped_storage().nbytes() - t.storage_offset() * t.element_size() < need:
+        raise ValueError("workspace too small")
+    _check_device(t, "workspace")
+
+
+def _check_signs(signs, n, triples, first=0):
+    if first < 0 or signs.numel() < (first + triples) * spinner_signs_bytes(n, 1):
+        raise ValueError("signs buffer too small for this n / triple")
+    _check_device(signs, "signs")
+
+
+def _check_diagonals(n, **diagonals):
+    for name, d in diagonals.items():
+        _check_tensor(d, name, torch.float32)
+        if d.numel() < n:
+            raise ValueError("%s is shorter than n" % name)
+
+
+def _check_result(t, name, count):
+    _check_device(t, name)
+    if not t.is_contiguous() or t.numel() * t.element_size() < 4 * count:
+        raise ValueError("%s must be contiguous and hold %d floats" % (name, count))
+
+
 def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, workspace=None, stream=None):
     """out = epilogue(scale * first m coordinates of H D3 H D2 H D1 x) for each row of x.
 
@@ -227,8 +261,7 @@ def spinner_apply(x, d1, d2, d3, m=None, epilogue="none", scale=1.0, out=None, w
     need = spinner_workspace_bytes(n, batch, m, epi)
     if need and workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_apply(x.data_ptr(), n, batch, d1.data_ptr(), d2.data_ptr(), d3.data_ptr(), m, epi,
                            ctypes.c_float(scale), out.data_ptr(),
                            workspace.data_ptr() if workspace is not None else None, _stream_handle(stream))
@@ -268,8 +301,7 @@ def _hash_workspace(x, n, batch, workspace):
     need = spinner_hash_workspace_bytes(n, batch)
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     return workspace
 
 
@@ -299,8 +331,7 @@ def spinner_hash_signs_ws(x, signs, L, out_idx=None, workspace=None, stream=None
     """spinner_hash_signs for every n up to 2^24."""
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
-    if signs.numel() < spinner_signs_bytes(n, L):
-        raise ValueError("signs buffer too small")
+    _check_signs(signs, n, L)
     if out_idx is None:
         out_idx = torch.empty((batch, L), dtype=torch.int32, device=x.device)
     else:
@@ -353,13 +384,11 @@ def spinner_apply_signs(x, signs, m=None, epilogue="none", scale=1.0, out=None, 
         if out.numel() != batch * width:
             raise ValueError("out has the wrong size")
     one = spinner_signs_bytes(n, 1)
-    if signs.numel() < (triple + 1) * one:
-        raise ValueError("signs buffer too small for this n / triple")
+    _check_signs(signs, n, 1, triple)
     need = spinner_workspace_bytes(n, batch, m, epi)
     if need and workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_apply_signs(x.data_ptr(), n, batch, signs.data_ptr() + triple * one, m, epi,
                                  ctypes.c_float(scale), out.data_ptr(),
                                  workspace.data_ptr() if workspace is not None else None, _stream_handle(stream))
@@ -375,8 +404,7 @@ def spinner_hash_signs(x, signs, L, out_idx=None, stream=None):
         return r
     _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
-    if signs.numel() < spinner_signs_bytes(n, L):
-        raise ValueError("signs buffer too small")
+    _check_signs(signs, n, L)
     if out_idx is None:
         out_idx = torch.empty((batch, L), dtype=torch.int32, device=x.device)
     else:
@@ -437,8 +465,7 @@ def _codes_workspace(x, workspace):
     need = spinner_codes_workspace_bytes(n, batch)
     if need and workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     return workspace
 
 
@@ -448,9 +475,8 @@ def spinner_sign_codes(x, d1, d2, d3, m=None, codes=None, workspace=None, stream
     if r is not None:
         return r
     _check_tensor(x, "x", torch.float32)
-    for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
-        _check_tensor(d, name, torch.float32)
     batch, n = x.shape
+    _check_diagonals(n, d1=d1, d2=d2, d3=d3)
     m = n if m is None else int(m)
     codes = _codes_out(x, m, codes)
     workspace = _codes_workspace(x, workspace)
@@ -472,8 +498,7 @@ def spinner_sign_codes_signs(x, signs, m=None, codes=None, workspace=None, strea
     codes = _codes_out(x, m, codes)
     workspace = _codes_workspace(x, workspace)
     one = spinner_signs_bytes(n, 1)
-    if signs.numel() < (triple + 1) * one:
-        raise ValueError("signs buffer too small for this n / triple")
+    _check_signs(signs, n, 1, triple)
     rc = lib.spinner_sign_codes_signs(x.data_ptr(), n, batch, signs.data_ptr() + triple * one, m, codes.data_ptr(),
                                       workspace.data_ptr() if workspace is not None else None, _stream_handle(stream))
     if rc != SPINNER_OK:
@@ -494,6 +519,8 @@ def spinner_angular_gram(codes_a, codes_b, m, out=None, stream=None):
     if codes_a.shape[-1] != words or codes_b.shape[-1] != words:
         raise ValueError("codes do not have m / 64 words per row")
     na, nb = codes_a.shape[0], codes_b.shape[0]
+    if codes_a.numel() < na * words or codes_b.numel() < nb * words:
+        raise ValueError("codes do not have m / 64 words per row")
     if out is None:
         out = torch.empty((na, nb), dtype=torch.float32, device=codes_a.device)
     else:
@@ -521,13 +548,13 @@ def spinner_layer_forward(x, d1, d2, d3, scale=1.0, y=None, saved=None, stream=N
     if r is not None:
         return r
     _check_tensor(x, "x", torch.float32)
-    for name, d in (("d1", d1), ("d2", d2), ("d3", d3)):
-        _check_tensor(d, name, torch.float32)
     batch, n = x.shape
+    _check_diagonals(n, d1=d1, d2=d2, d3=d3)
     if y is None:
         y = torch.empty_like(x)
     else:
         _check_tensor(y, "y", torch.float32)
+        _check_result(y, "y", batch * n)
     if saved is None:
         saved = torch.empty((2, batch, n), dtype=torch.float32, device=x.device)
     else:
@@ -546,20 +573,24 @@ def spinner_layer_backward(dy, x, saved, d1, d2, d3, scale=1.0, dx=None, dd=None
     r = _native.layer_backward(dy, x, saved, d1, d2, d3, scale, dx, dd, workspace, stream)
     if r is not None:
         return r
-    for name, t in (("dy", dy), ("x", x), ("saved", saved), ("d1", d1), ("d2", d2), ("d3", d3)):
+    for name, t in (("dy", dy), ("x", x), ("saved", saved)):
         _check_tensor(t, name, torch.float32)
     batch, n = x.shape
+    _check_diagonals(n, d1=d1, d2=d2, d3=d3)
     if dy.shape != x.shape or saved.numel() != 2 * batch * n:
         raise ValueError("dy / saved do not match x")
     if dx is None:
         dx = torch.empty_like(x)
+    else:
+        _check_result(dx, "dx", batch * n)
     if dd is None:
         dd = torch.empty((3, n), dtype=torch.float32, device=x.device)
+    else:
+        _check_result(dd, "dd", 3 * n)
     need = spinner_layer_workspace_bytes(n, batch)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
-    if workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_layer_backward(dy.data_ptr(), x.data_ptr(), saved.data_ptr(), n, batch, d1.data_ptr(), d2.data_ptr(),
                                     d3.data_ptr(), ctypes.c_float(scale), dx.data_ptr(), dd.data_ptr(), workspace.data_ptr(),
                                     _stream_handle(stream))
@@ -578,11 +609,10 @@ def spinner_sketch(A, w, d1, d2, d3, m, scale=1.0, out=None, workspace=None, str
     if r is not None:
         return r
     _check_tensor(A, "A", torch.float32)
-    for name, t in (("d1", d1), ("d2", d2), ("d3", d3)):
-        _check_tensor(t, name, torch.float32)
-    if w is not None:
-        _check_tensor(w, "w", torch.float32)
     n, d = A.shape
+    _check_diagonals(n, d1=d1, d2=d2, d3=d3)
+    if w is not None:
+        _check_diagonals(n, w=w)
     if out is None:
         out = torch.empty((int(m), d), dtype=torch.float32, device=A.device)
     else:
@@ -592,8 +622,7 @@ def spinner_sketch(A, w, d1, d2, d3, m, scale=1.0, out=None, workspace=None, str
     need = spinner_sketch_workspace_bytes(n, d, m)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=A.device)
-    if workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_sketch(A.data_ptr(), n, d, w.data_ptr() if w is not None else None, d1.data_ptr(), d2.data_ptr(),
                             d3.data_ptr(), int(m), ctypes.c_float(scale), out.data_ptr(), workspace.data_ptr(),
                             _stream_handle(stream))
@@ -639,8 +668,7 @@ def spinner_sketch_gram(B, out=None, workspace=None, stream=None):
     need = spinner_sketch_gram_workspace_bytes(m, d)
     if need and workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=B.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_sketch_gram(B.data_ptr(), m, d, out.data_ptr(), workspace.data_ptr() if workspace is not None else None,
                                  _stream_handle(stream))
     if rc != SPINNER_OK:
@@ -672,8 +700,7 @@ def spinner_apply_blocks(x, diag_sets, m=None, epilogue="none", scale=1.0, out=N
     need = int(lib.spinner_blocks_workspace_bytes(n, batch, m, epi))
     if need and workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_apply_blocks(x.data_ptr(), n, batch, L, diag_sets.data_ptr(), m, epi, ctypes.c_float(scale),
                                   out.data_ptr(), workspace.data_ptr() if workspace is not None else None,
                                   _stream_handle(stream))
@@ -698,12 +725,19 @@ def spinner_struct_prepare(kind, params, n, stream=None):
     return spec
 
 
+def _check_spectrum(spectrum, k, n):
+    _check_device(spectrum, "spectrum")
+    if spectrum.numel() * spectrum.element_size() < int(lib.spinner_struct_spectrum_bytes(k, n)):
+        raise ValueError("spectrum of another kind or a smaller n")
+
+
 def spinner_struct_apply(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=None, stream=None):
     """out [batch][m] = scale * (first m rows of G_struct D2 H D1 x)."""
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
-    for name, t in (("x", x), ("d1", d1), ("d2", d2)):
-        _check_tensor(t, name, torch.float32)
+    _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
+    _check_diagonals(n, d1=d1, d2=d2)
+    _check_spectrum(spectrum, k, n)
     m = n if m is None else int(m)
     if out is None:
         out = torch.empty((batch, m), dtype=torch.float32, device=x.device)
@@ -729,9 +763,10 @@ def spinner_struct_apply_ws(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=No
     if r is not None:
         return r
     k = STRUCT_KINDS[kind] if isinstance(kind, str) else int(kind)
-    for name, t in (("x", x), ("d1", d1), ("d2", d2)):
-        _check_tensor(t, name, torch.float32)
+    _check_tensor(x, "x", torch.float32)
     batch, n = x.shape
+    _check_diagonals(n, d1=d1, d2=d2)
+    _check_spectrum(spectrum, k, n)
     m = n if m is None else int(m)
     if out is None:
         out = torch.empty((batch, m), dtype=torch.float32, device=x.device)
@@ -742,8 +777,7 @@ def spinner_struct_apply_ws(x, kind, spectrum, d1, d2, m=None, scale=1.0, out=No
     need = spinner_struct_workspace_bytes(k, n, batch)
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    if workspace is not None and workspace.numel() * workspace.element_size() < need:
-        raise ValueError("workspace too small")
+    _check_workspace(workspace, need)
     rc = lib.spinner_struct_apply_ws(x.data_ptr(), n, batch, k, spectrum.data_ptr(), d1.data_ptr(), d2.data_ptr(), m,
                                      ctypes.c_float(scale), out.data_ptr(),
                                      workspace.data_ptr() if workspace is not None else None, _stream_handle(stream))

@@ -442,7 +442,7 @@ ENTRY(struct_apply_ws, 10)
     const Tensor *d1 = floats(a[3], n), *d2 = floats(a[4], n);
     const size_t need = spinner_struct_workspace_bytes(kind, n, batch);
     Buffer o, w;
-    if (!d1 || !d2 || !o.usable(a[7], at::kFloat, (int64_t)batch * m) || !w.usable_bytes(a[8], need)) LONG_WAY;
+    if ((size_t)spectrum->nbytes() < spinner_struct_spectrum_bytes(kind, n) || !d1 || !d2 || !o.usable(a[7], at::kFloat, (int64_t)batch * m) || !w.usable_bytes(a[8], need)) LONG_WAY;
     Tensor out;
     int rc;
     {

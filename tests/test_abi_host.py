@@ -215,6 +215,103 @@ def test_native_calls_leave_host_tensors_to_the_long_way(b):
         b.spinner_apply(x, one, one, one)
 
 
+class _Tensor:
+    """What binding.py asks of a device tensor, without a device."""
+
+    def __init__(self, *shape, dtype="float32", cuda=True, whole=True, stored=None):
+        import torch
+
+        self.shape, self.dtype, self.is_cuda, self.whole = torch.Size(shape), getattr(torch, dtype), cuda, whole
+        self.device = torch.device("cpu")
+        self.stored = stored
+
+    numel = lambda self: self.shape.numel()
+    dim = lambda self: len(self.shape)
+    element_size = lambda self: self.dtype.itemsize
+    is_contiguous = lambda self: self.whole
+    is_pinned = lambda self: False
+    data_ptr = lambda self: 4096
+    storage_offset = lambda self: 0
+
+    def untyped_storage(self):
+        stored = self.numel() * self.element_size() if self.stored is None else self.stored
+        return type("Storage", (), {"nbytes": lambda _: stored})()
+
+
+class _NoLaunch:
+    """The library's sizes, and a record of the calls that would have launched something."""
+
+    def __init__(self, lib):
+        self._lib, self.calls = lib, []
+
+    def __getattr__(self, name):
+        if name.endswith(("_bytes", "_params")):
+            return getattr(self._lib, name)
+        return lambda *args: self.calls.append(name) or 0
+
+
+def _buffer_calls(b):
+    """name -> (call of a dictionary of arguments, the arguments that are all right, name -> arguments that are not)"""
+    T, n, B = _Tensor, 1 << 15, 3
+    s = type("Stream", (), {"cuda_stream": 0})()
+    one, signs = b.spinner_signs_bytes(n, 1), dict(dtype="uint8")
+    layer_ws, sketch_ws = b.spinner_layer_workspace_bytes(n, B), b.spinner_sketch_workspace_bytes(n, 20, 64)
+    spec, struct_ws = int(b.lib.spinner_struct_spectrum_bytes(b.STRUCT_KINDS["toeplitz"], n)), b.spinner_struct_workspace_bytes("toeplitz", n, B)
+    d = {k: T(n) for k in ("d1", "d2", "d3")}
+    shorter = [T(n - 1), T(n, cuda=False), T(n, whole=False), T(n, dtype="float64")]
+    bad_d = {k: shorter for k in d}
+    bad_signs = {"signs": [T(2 * one - 1, **signs), T(2 * one, cuda=False, **signs)], "triple": [2, -1]}
+
+    def workspace(need):
+        return [T(need - 1, **signs), T(need, cuda=False, **signs), T(need, stored=64, **signs)]
+
+    def results(name, count):
+        return {name: [T(count - 1), T(count, cuda=False), T(count, whole=False)]}
+
+    return {
+        "spinner_apply_signs": (dict(x=T(B, n), signs=T(2 * one, **signs), m=None, triple=1), bad_signs),
+        "spinner_sign_codes_signs": (dict(x=T(B, n), signs=T(2 * one, **signs), triple=1), bad_signs),
+        "spinner_hash_signs": (dict(x=T(B, n), signs=T(2 * one, **signs), L=2), {"signs": bad_signs["signs"]}),
+        "spinner_hash_signs_ws": (dict(x=T(B, n), signs=T(2 * one, **signs), L=2), {"signs": bad_signs["signs"]}),
+        "spinner_sign_codes": (dict(x=T(B, n), **d), bad_d),
+        "spinner_apply": (dict(x=T(B, n), epilogue="cossin", workspace=T(4 * B * n, **signs), **d), {"workspace": workspace(4 * B * n), **bad_d}),
+        "spinner_angular_gram": (dict(codes_a=T(5, 4, dtype="int64"), codes_b=T(3, 4, dtype="int64"), m=256),
+                                 {"codes_a": [T(4, dtype="int64")], "codes_b": [T(4, dtype="int64")]}),
+        "spinner_layer_forward": (dict(x=T(B, n), y=T(B, n), **d), {**results("y", B * n), **bad_d}),
+        "spinner_layer_backward": (dict(dy=T(B, n), x=T(B, n), saved=T(2, B, n), dx=T(B, n), dd=T(3, n), workspace=T(layer_ws, **signs), **d),
+                                   {**results("dx", B * n), **results("dd", 3 * n), "workspace": workspace(layer_ws), **bad_d}),
+        "spinner_sketch": (dict(A=T(n, 20), w=T(n), m=64, workspace=T(sketch_ws, **signs), **d),
+                           {"w": shorter, "workspace": workspace(sketch_ws), **bad_d}),
+        "spinner_struct_apply": (dict(x=T(B, n), kind="toeplitz", spectrum=T(spec, **signs), d1=T(n), d2=T(n)),
+                                 {"d1": shorter, "d2": shorter, "spectrum": [T(spec - 1, **signs), T(spec, cuda=False, **signs)]}),
+        "spinner_struct_apply_ws": (dict(x=T(B, n), kind="toeplitz", spectrum=T(spec, **signs), d1=T(n), d2=T(n), workspace=T(struct_ws, **signs)),
+                                    {"workspace": workspace(struct_ws), "d1": shorter, "d2": shorter, "spectrum": [T(spec - 1, **signs), T(spec, cuda=False, **signs)]}),
+    }, s
+
+
+def test_buffers_that_a_kernel_would_reach_past_are_refused(b, monkeypatch):
+    # diagonals shorter than n, results and workspaces too small, memory of the host: refused before the library is called, while
+    # the same call with buffers that hold (or more than hold) what is needed reaches it
+    calls, stream = _buffer_calls(b)
+    lib = _NoLaunch(b.lib)
+    monkeypatch.setattr(b, "lib", lib)
+    for name, (good, bad) in calls.items():
+        call = getattr(b, name)
+        call(stream=stream, **good)
+        assert lib.calls == [name]
+        for k in good:
+            if k in ("d1", "d2", "d3", "w", "signs", "spectrum", "dd") and name != "spinner_apply":
+                shape = good[k].shape
+                call(stream=stream, **{**good, k: _Tensor(*shape[:-1], shape[-1] + 4, dtype=str(good[k].dtype)[6:])})
+        for k, wrong in bad.items():
+            for v in wrong:
+                lib.calls.clear()
+                with pytest.raises(ValueError):
+                    call(stream=stream, **{**good, k: v})
+                assert lib.calls == [], (name, k)
+        lib.calls.clear()
+
+
 def test_stream_copy_rejects_bad_arguments(b):
     c = b.lib.spinner_stream_copy
     assert c(None, 64, 16, None) == b.SPINNER_ERR_NULL_PTR
