@@ -65,13 +65,37 @@ def _calls(g, n=1024):
     }
 
 
+class _Recorder:
+    """binding._native with a note of who answered: True for a result, False for None (the long way)."""
+
+    def __init__(self, native):
+        self._native, self.served = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            r = getattr(self._native, name)(*args)
+            self.served.append(r is not None)
+            return r
+
+        return call
+
+
+@pytest.fixture
+def served(gpu, monkeypatch):
+    rec = _Recorder(gpu.b._native)
+    monkeypatch.setattr(gpu.b, "_native", rec)
+    return rec.served
+
+
 def _all(r):
     return r if isinstance(r, tuple) else (r,)
 
 
-def test_native_calls_give_the_bits_of_the_long_way(gpu):
+def test_native_calls_give_the_bits_of_the_long_way(gpu, served):
     t = gpu.torch
-    for name, (f, buffer) in _calls(gpu).items():
+    calls = _calls(gpu)
+    for name, (f, buffer) in calls.items():
+        served.clear()
         long_way = _all(f(stream=t.cuda.current_stream()))
         native = _all(f())
         for p, q in zip(native, long_way):
@@ -79,9 +103,11 @@ def test_native_calls_give_the_bits_of_the_long_way(gpu):
         mine = t.zeros_like(native[0])
         back = _all(f(**{buffer: mine}))
         assert back[0] is mine and t.equal(mine, long_way[0]), name
+        assert served == [False, True, True], name
+    assert {name.split()[0].split(",")[0] for name in calls} == {m.replace("struct_apply_ws", "struct") for m in dir(gpu.b._native._native) if m[0] != "_"}
 
 
-def test_native_calls_with_a_workspace(gpu):
+def test_native_calls_with_a_workspace(gpu, served):
     t, b = gpu.torch, gpu.b
     x, d = _inputs(gpu, 1 << 17, 3, 1)
     need = b.spinner_workspace_bytes(1 << 17, 3, 100, "none")
@@ -89,19 +115,26 @@ def test_native_calls_with_a_workspace(gpu):
     want = b.spinner_apply(x, *d[0], 100, stream=t.cuda.current_stream())
     assert t.equal(b.spinner_apply(x, *d[0], 100), want)
     assert t.equal(b.spinner_apply(x, *d[0], 100, workspace=t.empty(need, dtype=t.uint8, device=gpu.dev)), want)
+    assert served == [False, True, True]
     with pytest.raises(ValueError, match="workspace too small"):
         b.spinner_apply(x, *d[0], 100, workspace=t.empty(need - 1, dtype=t.uint8, device=gpu.dev))
 
 
-def test_calls_that_the_native_part_leaves_to_the_long_way(gpu):
+def test_calls_that_the_native_part_leaves_to_the_long_way(gpu, served):
     t, b = gpu.torch, gpu.b
     x, d = _inputs(gpu)
     d1, d2, d3 = d[0]
     words = b.spinner_pack_signs(d)
     want = b.spinner_apply(x, d1, d2, d3, 100, "none", 2.0)
+    assert served == [True]
+    served.clear()
     # numbers that are no plain Python numbers, a subclass of the tensor, sign words of another type
     assert t.equal(b.spinner_apply(x, d1, d2, d3, np.int64(100), "none", np.float32(2.0)), want)
+    assert served == [False]
+    # (a parameter is a plain tensor)
     assert t.equal(b.spinner_apply(t.nn.Parameter(x), d1, d2, d3, 100, "none", 2.0), want)
+    assert served == [False, True]
+    served.clear()
 
     class Sub(t.Tensor):
         pass
@@ -131,9 +164,15 @@ def test_calls_that_the_native_part_leaves_to_the_long_way(gpu):
     with pytest.raises(b.SpinnerError) as e:          # 4 bytes past a 16-byte boundary
         b.spinner_apply(x.flatten()[1:1025].reshape(1, 1024), d1, d2, d3)
     assert e.value.status == b.SPINNER_ERR_ALIGNMENT
+    # a host tensor or a shorter diagonal where the kernels cannot tell
+    for f in (lambda: b.spinner_apply_signs(x, words.cpu()), lambda: b.spinner_apply_signs(x, words, triple=-1),
+              lambda: b.spinner_layer_forward(x, d1[:512], d2, d3), lambda: b.spinner_sign_codes(x, d1, d2, d3[:1020])):
+        with pytest.raises(ValueError):
+            f()
     # the wrong type of tensor where only a wrapped one can tell: no data pointer to take
     with pytest.raises(RuntimeError):
         t.func.vmap(lambda v: b.spinner_apply(v, d1, d2, d3))(x.reshape(1, 37, 1024))
+    assert len(served) >= 13 and not any(served)
     empty = b.spinner_apply(x[:0], d1, d2, d3, 100)
     assert tuple(empty.shape) == (0, 100)
 
@@ -173,7 +212,7 @@ def test_an_error_of_hip_is_raised_and_the_call_not_made_again(gpu):
     assert t.equal(b.spinner_apply(x, *d[0]), want)
 
 
-def test_native_calls_on_side_streams_of_several_threads(gpu):
+def test_native_calls_on_side_streams_of_several_threads(gpu, served):
     # every thread on a stream of its own that first waits for a long copy: a call on any other stream would read x too early
     t, b = gpu.torch, gpu.b
     x, d = _inputs(gpu, 1024, 4096)
@@ -201,3 +240,4 @@ def test_native_calls_on_side_streams_of_several_threads(gpu):
         th.join()
     for r in got:
         assert t.equal(r, want)
+    assert len(served) == 81 and all(served)
