@@ -177,12 +177,15 @@ inline unsigned triple_slices(long long waves, int L, long long most_waves, int 
 // Hash: bound by the vector ALU, so many short slices also even out the last round of workgroups; what a slice reads again
 // shows once there are four waves per SIMD.  One slice / as cut here, in us, L = 16: n = 64, batch 16384 24 / 11; n = 256, 4096
 // vectors 36 / 14; n = 1024, 512 vectors 68 / 10, 4096 68 / 49; n = 4096, 16 vectors 96 / 8, 256 97 / 26, 1024 113 / 86, 4096 369 /
-// 322; n = 2^14, 128 vectors 132 / 50, 1024 394 / 372.  A batch of n = 2^12 that fills the chip just once is left whole (2048
-// vectors, L = 12, fp32 diagonals, inputs that change from call to call: 140 / 149).
+// 322; n = 2^14, 128 vectors 132 / 50, 1024 394 / 372.  A batch that fills the chip just once (4096 waves) is cut into pairs of triples:
+// n = 4096, inputs that change from call to call, whole / four / two triples in a slice, 2048 vectors, L = 8, 12, 16, fp32 diagonals
+// 98 / 110 / 96, 145 / 149 / 136, 192 / 188 / 175, sign words 95 / 101 / 93, 139 / 140 / 131, 183 / 178 / 170; beyond it slices of four,
+// whole / cut, fp32 diagonals 2049 vectors 130 / 110, 193 / 149, 256 / 188, 3071 154 / 141, 230 / 199, 302 / 255.  (n = 2^11, 2^13 gain 1 to 3 %
+// from the pairs as well; at n = 2^14, where a slice reads 64 KiB a vector again, they cost 1 to 1.7 % with fp32 diagonals.)
 inline unsigned hash_slices(int log2n, long long waves, int L, int& per_slice)
 {
-    if (log2n == 12 && waves >= 4096 && waves < 6144) { per_slice = L; return 1; }
-    return triple_slices(waves, L, 32768, waves >= 4096 ? 4 : (waves >= 2048 ? 2 : 1), per_slice);
+    const bool beyond = log2n < 14 ? waves > 4096 : waves >= 4096;
+    return triple_slices(waves, L, 32768, beyond ? 4 : (waves >= 2048 ? 2 : 1), per_slice);
 }
 // Stacked blocks: memory comes in earlier.  One slice / as cut here, in us, L = 4: n = 512, features, batch 1024 22.4 / 8.9;
 // n = 2048, projections, 256 21.4 / 7.9, 2048 27.4 / 24.0, features 1024 36.8 / 29.1; n = 4096, projections, 512 26.1 / 15.1; n = 2^13,

@@ -805,6 +805,24 @@ def test_hash_of_few_vectors_cut_along_the_triples(gpu, n, L):
             assert t.equal(call(x[:few]), want[:few]), few
 
 
+@pytest.mark.parametrize("n,fills", [(64, 32768), (1024, 4096), (4096, 2048), (1 << 14, 512)])
+@pytest.mark.parametrize("L", [3, 8, 13])
+def test_hash_of_batches_that_fill_the_chip_once(gpu, n, fills, L):
+    # one vector fewer, as many as and one more than give 4096 waves: slices of at least two, two and four triples, the last one
+    # shorter; the buckets of a few vectors from the middle and both ends against those of the vectors alone
+    t = gpu.torch
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(n + L)
+    x = t.randn((fills + 1, n), generator=g, device=gpu.dev)
+    d = t.randint(0, 2, (L, 3, n), generator=g, device=gpu.dev).float() * 2 - 1
+    words = gpu.b.spinner_pack_signs(d)
+    for call in (lambda v: gpu.b.spinner_hash(v, d), lambda v: gpu.b.spinner_hash_signs(v, words, L)):
+        for batch in (fills - 1, fills, fills + 1):
+            got = call(x[:batch])
+            for part in (slice(0, 5), slice(fills // 2, fills // 2 + 5), slice(batch - 5, batch)):
+                assert t.equal(got[part], call(x[:batch][part].contiguous())), batch
+
+
 @pytest.mark.parametrize("epilogue", ["none", "cossin"])
 @pytest.mark.parametrize("n, m", [(16, 16), (512, 512), (2048, 1000), (4096, 2560), (1 << 13, 1 << 13), (1 << 14, 4000)])
 def test_stacked_blocks_of_few_vectors_cut_along_the_blocks(gpu, n, m, epilogue):
