@@ -87,6 +87,12 @@ typedef enum {
  * passes run in place in `out` when m == n and the epilogue is NONE, else in `workspace`,
  * which features ask for from n = 2^15 on.
  *
+ * The kernels of two batch sizes may add in different orders: a vector gives the same bits
+ * in every batch on one side of a limit such as that of 32 (48) vectors, and may differ in
+ * the last places, within the accuracy below, between the two sides.  Limits of that kind:
+ * n = 2^15 and 2^16 here and in spinner_layer_forward / _backward; stacked feature blocks;
+ * spinner_struct_apply_ws at n = 2^14 (96 vectors).  Buckets and sign codes have none.
+ *
  * Accuracy: outputs of SPINNER_EPI_NONE carry the rounding of 3 log2 n fp32
  * butterfly stages (relative L2 error of a few 1e-7 per vector).  The fused
  * feature kernels (SPINNER_EPI_COSSIN, n <= 2^14) run their butterflies and the
@@ -107,7 +113,8 @@ int spinner_apply(const float *x, int n, long batch,
  * independently drawn diagonal triples (Section 3.2: independently constructed
  * blocks), the hash is the signed canonical direction closest to the
  * projection: i* = argmax_i |y_i| (lowest index on exact ties), bucket = i* if
- * y_{i*} >= 0 else i* + n.  x is read once for all L triples.
+ * y_{i*} >= 0 else i* + n.  x is read once for all L triples (few vectors are
+ * applied to some of the triples per workgroup, each of which reads x).
  *
  *   x          in   device fp32 [batch][n]
  *   L          in   number of triples, >= 1

@@ -132,7 +132,7 @@ layer_signals_kernel(const float* in, const float* da, const float* db, float* f
 
 // Sums of a workgroup's tiles (one wave or less each), per coordinate, in fp64 and in a fixed order: part[i] = sum over the
 // tiles of f * acc.  The tiles go through LDS; vectors shorter than the workgroup have their tiles shared out among its threads
-// first.  One fp64 row per workgroup instead of an fp32 row per tile: see slots_nt in layer.hip.
+// first.  One fp64 row per workgroup instead of an fp32 row per tile: see workgroups_nt in layer.hip.
 template <typename G>
 __device__ __forceinline__ void sum_tiles(const float (&acc)[G::R], const ThreadCtx<G>& c, float f, double* part)
 {

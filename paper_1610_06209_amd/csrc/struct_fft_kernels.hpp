@@ -14,8 +14,9 @@
 // and runs its stages between registers, every butterfly with its twiddle in six fused operations (see "Twiddles").  A phase
 // reads and writes the same positions, so an exchange is: write, one barrier, read.  Hadamard phases run middle, low, top and the
 // top one goes straight into the transform's top phase; the low phase holds the forward stages, the spectrum product
-// and the inverse stages.  Six exchanges for a circulant block, ten for the others.  Bound by vector-ALU issue (3200 instructions per
-// thread and pair of vectors at n = 2^12, 0.25 per cycle and SIMD of about 0.4) and what the exchanges leave exposed.
+// and the inverse stages.  Six exchanges for a circulant block, ten for the others.  Bound by vector-ALU issue (3214 instructions per
+// thread and pair of vectors at n = 2^12, padded, 0.24 per cycle and SIMD of about 0.4 with 3.7 waves there) and what the exchanges leave
+// exposed (LDS pipe 38 % busy, a quarter of the waves' time waiting for anything but issue).
 // In us, Toeplitz: the general kernel in structured.hip / twiddles between the groups as factors of every point / this form: n = 4096,
 // batch 16383 315 / 244 / 226; n = 2^13, 8192 - / 306 / 250, 1024 - / 43.5 / 35.2; n = 2^14, 4096 - / 351 / 305; n = 2048, 32768 - / 226 / 201.
 // n = 2^13 and 2^14 are held to two waves per SIMD.
