@@ -16,7 +16,7 @@ constexpr int kFusedMaxLogFeatures = 16;  // feature map on fp32 butterflies abo
 // more; one workgroup that takes a vector through all rounds leaves the other compute units idle.  Passes / fused, in us, fp32
 // diagonals, inputs that change from call to call: plain 2^15, 1 vector 12.3 / 17.3, 32 17.3 / 19.6, 40 19.6 / 19.4, 48 21.5 / 19.7, 256
 // 53 / 25; 2^16, 1 13.1 / 27.7, 32 26.2 / 30.7, 40 29.7 / 31.3, 48 33.8 / 31.4, 256 90 / 46; features 2^15, 32 19.4 / 21.6, 40 22.0 / 21.4, 256
-// 55 / 31; 2^16, 48 36.1 / 37.5, 56 39.6 / 37.8, 256 98 / 70; layer forward and backward 2^15, 24 66.6 / 68.3, 32 69.9 / 70.5, 40 76.5 / 76.5,
+// 55 / 31; 2^16, 48 36.1 / 37.5, 56 39.6 / 37.8, 256 98 / 66; layer forward and backward 2^15, 24 66.6 / 68.3, 32 69.9 / 70.5, 40 76.5 / 76.5,
 // 48 80.1 / 79.0, 256 203 / 132; 2^16, 40 94 / 105, 48 104 / 108, 56 113 / 110, 256 362 / 244.
 constexpr long long few_wide_vectors(int log2n, bool plain)
 {

@@ -443,14 +443,25 @@ __device__ __forceinline__ float tracked_sign(const ThreadCtx<G>& c)
     return s;
 }
 
+// the register bit of the last stage of wave_owned_stages
+template <typename G, int CB>
+constexpr int last_wave_owned(int lay)
+{
+    int last = -1;
+    for (int q = 0; q < G::r; ++q)
+        if (G::reg_pos(lay, q) >= CB && !G::is_reg_pos(1 - lay, G::reg_pos(lay, q))) last = q;
+    return last;
+}
+
 // Register stages, in layout LAY, for exactly those index bits that layout
 // 1-LAY does not keep in registers (the part of a transform left after a transpose).
-template <typename G, int CB, int LAY, typename T>
+// BUT_LAST: the last of them is left to the caller.
+template <typename G, int CB, int LAY, bool BUT_LAST = false, typename T>
 __device__ __forceinline__ void wave_owned_stages(T (&v)[G::R])
 {
     static_for<0, G::r>([&](auto q) {
         constexpr int pos = G::reg_pos(LAY, q.value);
-        if constexpr (pos >= CB && !G::is_reg_pos(1 - LAY, pos)) reg_stage<q.value>(v);
+        if constexpr (pos >= CB && !G::is_reg_pos(1 - LAY, pos) && !(BUT_LAST && q.value == last_wave_owned<G, CB>(LAY))) reg_stage<q.value>(v);
     });
 }
 
@@ -708,8 +719,9 @@ __device__ __forceinline__ void sign_flip(T (&v)[G::R], const ThreadCtx<G>& c, c
 // the bits LAY keeps in the wave id after it.
 // NPF > 0: `pm` holds the first NPF lane masks of this step's sign flips unless this is the first step, and, with
 // PF_NEXT, receives those of the next step (packed words at next_words) before this step's exchange.
+// BUT_LAST (tiles of several waves): the last register stage is left to the caller.
 template <typename G, int C, int CB, int LAY, bool HAS_DIAG, bool FIRST_TRANSPOSE, bool NEGATE, bool SIGNS, typename T, int NPF = 0,
-          bool PF_NEXT = false>
+          bool PF_NEXT = false, bool BUT_LAST = false>
 __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c,
                                              const float* dtile, const unsigned long long* words, int sl, float4* lds,
                                              SignMasks<NPF>* pm = nullptr, const unsigned long long* next_words = nullptr)
@@ -728,7 +740,7 @@ __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c
     if constexpr (G::WB > 0) {
         if constexpr (std::is_same<T, float>::value) transpose<G, LAY, !FIRST_TRANSPOSE, 0, 0, SWAP>(v, c, lds);
         else transpose<G, LAY, !FIRST_TRANSPOSE, SWAP>(v, c, lds);
-        wave_owned_stages<G, CB, 1 - LAY>(v);
+        wave_owned_stages<G, CB, 1 - LAY, BUT_LAST>(v);
     }
 }
 
@@ -844,6 +856,9 @@ __device__ __forceinline__ void feature_sincos(float y, const TileParams&, float
 }
 // fp32 values of a kernel that runs all three rounds (n = 2^15, 2^16): the angle in fp64 as below.  Sixty-four library calls
 // per thread take registers and instruction cache that such a kernel does not have, and the product's rounding goes away.
+// The kernel forms the last butterflies in fp64 as well: with them in fp32 features of 2^16 were 0.7 % further off than those of the
+// four passes, which take their stages in another order (scale 8, relative error 1.50e-6; 2^15 0.65 % closer); so they are 0.35 %
+// closer (1.75 %).  2^16, batch 1024, sign words: 255 -> 231 us, first 4096 coordinates 180 -> 180; 2^15 within 1 %.
 __device__ __forceinline__ void feature_sincos(double y, double revolutions, float& s, float& c)
 {
     const float fr = (float)__builtin_amdgcn_fract(y * revolutions);
@@ -960,11 +975,14 @@ spinner_tile_kernel(TileParams p)
         if constexpr (NSTEPS > 1)
             spinner_step<G, C, CB, G::layout_after(1), true, false, true, SIGNS, T, NPF, (NSTEPS > 2)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2]);
         bool wave_live = true;
+        // features of fp32 values (n = 2^15, 2^16): the last butterflies and the angles in fp64
+        constexpr bool WIDE_ANGLE = EPI == EPI_STORE_COSSIN && std::is_same<T, float>::value && NSTEPS == 3;
+        static_assert(!WIDE_ANGLE || G::WB > 0, "the last stage is one between registers, behind the exchange");
         if constexpr (NSTEPS > 2) {
             if constexpr (PRUNE > 0)
                 spinner_step_pruned<G, C, CB, G::layout_after(2), false, SIGNS, PRUNE, NPF>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm);
             else
-                spinner_step<G, C, CB, G::layout_after(2), true, false, false, SIGNS, T, NPF, false>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
+                spinner_step<G, C, CB, G::layout_after(2), true, false, false, SIGNS, T, NPF, false, WIDE_ANGLE>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
         }
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs
@@ -1089,10 +1107,12 @@ spinner_tile_kernel(TileParams p)
             } else {
                 // dst row is [cos block | sin block]; the sin entry of coordinate i sits sin_off floats after its cos entry
                 const long long so = p.sin_off;
-                constexpr bool WIDE_ANGLE = std::is_same<T, float>::value && NSTEPS == 3;
                 const double revolutions = WIDE_ANGLE ? p.factor_rev * (double)tracked_sign<G, CB, T>(c) : 0.0;
+                constexpr int half = WIDE_ANGLE ? 1 << last_wave_owned<G, CB>(LAYF) : 0;
         #pragma unroll
-                for (int jh = 0; jh < RF / 4; ++jh) {
+                for (int step = 0; step < RF / 4; ++step) {
+                    // the two sides of the last butterflies one after the other
+                    const int jh = WIDE_ANGLE ? (step & 1) * (half / 4) | (step >> 1 & (half / 4 - 1)) | (step >> 1 & ~(half / 4 - 1)) << 1 : step;
                     // four registers whose first coordinate in this wave is past the kept rows: nothing to evaluate.  Sign words, 2^24
                     // elements, without / with the test, in us: n = 512, m = 256 33.5 / 31.0, m = 64 31.6 / 25.6; n = 2048, m = 1024 43.2 /
                     // 40.7, m = 256 42.5 / 37.1; n = 2^13, m = 1024 46.2 / 41.2; all rows alike, but n = 2^14 61.4 / 63.0
@@ -1103,7 +1123,11 @@ spinner_tile_kernel(TileParams p)
                     float sn[4], cs[4];
         #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        if constexpr (WIDE_ANGLE) feature_sincos((double)v[jh * 4 + k], revolutions, sn[k], cs[k]);
+                        if constexpr (WIDE_ANGLE) {
+                            const int j = jh * 4 + k;
+                            const double a = v[j & ~half], b = v[j | half];
+                            feature_sincos((j & half) ? a - b : a + b, revolutions, sn[k], cs[k]);
+                        }
                         else feature_sincos(v[jh * 4 + k], p, lane_factor, sn[k], cs[k]);
                         sn[k] *= p.inv_sqrt_m;
                         cs[k] *= p.inv_sqrt_m;
@@ -1119,6 +1143,7 @@ spinner_tile_kernel(TileParams p)
                         for (int k = 0; k < 4; ++k)
                             if (i + k < m) { dst[i + k] = cs[k]; dst[so + i + k] = sn[k]; }
                     }
+                    if constexpr (WIDE_ANGLE) { if (step & 1) __builtin_amdgcn_sched_barrier(0); }
                 }
             }
         }   // active

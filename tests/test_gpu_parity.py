@@ -549,6 +549,32 @@ def test_few_and_many_vectors_of_the_widest_fused_sizes(gpu, oracle, log2n, few)
         assert float((both[:, :, l] - one).abs().max()) <= 2.0 ** -22 / math.sqrt(2 * 512)
 
 
+@pytest.mark.parametrize("log2n,few", [(15, 32), (16, 48)])
+@pytest.mark.parametrize("scale", [8.0, 5.7])
+def test_features_of_the_widest_fused_sizes_are_no_further_off_than_those_of_the_passes(gpu, log2n, few, scale):
+    # the same vectors through the four passes, few at a time, and through the fused kernel, both against fp64: over these 2^24
+    # values and more two forms with the same error differ by less than 0.1 %.  A scale that is a power of two leaves the passes' angle
+    # of 2^16 without a rounding of its own
+    t, n = gpu.torch, 1 << log2n
+    g = t.Generator(device=gpu.dev)
+    g.manual_seed(log2n)
+    x = t.randn((5 * few, n), generator=g, device=gpu.dev)
+    d = t.randint(0, 2, (3, n), generator=g, device=gpu.dev).float() * 2 - 1
+    w = x.double()
+    for k in range(3):
+        w = w * d[k].double()
+        for b in range(log2n):
+            y = w.reshape(-1, n >> (b + 1), 2, 1 << b)
+            w = t.stack((y[:, :, 0] + y[:, :, 1], y[:, :, 0] - y[:, :, 1]), 2).reshape(-1, n)
+    w *= scale / n ** 1.5
+    want = t.cat((t.cos(w), t.sin(w)), 1) / math.sqrt(n)
+    signs = gpu.b.spinner_pack_signs(d[None].contiguous())
+    for f in (lambda v: gpu.b.spinner_apply(v, *d, n, "cossin", scale), lambda v: gpu.b.spinner_apply_signs(v, signs, n, "cossin", scale)):
+        passes = t.cat([f(x[i:i + few]) for i in range(0, 5 * few, few)])
+        fused = f(x)
+        assert float((fused - want).norm()) <= 1.001 * float((passes - want).norm())
+
+
 # ------------------------------------------------------------------ +-1 diagonals as packed sign words
 @pytest.mark.parametrize("log2n", list(range(4, 15)))
 def test_sign_word_path_every_fused_size(gpu, oracle, log2n):
