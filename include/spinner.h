@@ -91,7 +91,8 @@ typedef enum {
  * in every batch on one side of a limit such as that of 32 (48) vectors, and may differ in
  * the last places, within the accuracy below, between the two sides.  Limits of that kind:
  * n = 2^15 and 2^16 here and in spinner_layer_forward / _backward; stacked feature blocks;
- * spinner_struct_apply_ws at n = 2^14 (96 vectors).  Buckets and sign codes have none.
+ * the padded kinds of spinner_struct_apply_ws at n = 2^13 (32 vectors) and 2^14 (96).
+ * Buckets and sign codes have none.
  *
  * Accuracy: outputs of SPINNER_EPI_NONE carry the rounding of 3 log2 n fp32
  * butterfly stages (relative L2 error of a few 1e-7 per vector).  The fused
