@@ -856,9 +856,10 @@ __device__ __forceinline__ void feature_sincos(float y, const TileParams&, float
 }
 // fp32 values of a kernel that runs all three rounds (n = 2^15, 2^16): the angle in fp64 as below.  Sixty-four library calls
 // per thread take registers and instruction cache that such a kernel does not have, and the product's rounding goes away.
-// The kernel forms the last butterflies in fp64 as well: with them in fp32 features of 2^16 were 0.7 % further off than those of the
-// four passes, which take their stages in another order (scale 8, relative error 1.50e-6; 2^15 0.65 % closer); so they are 0.35 %
-// closer (1.75 %).  2^16, batch 1024, sign words: 255 -> 231 us, first 4096 coordinates 180 -> 180; 2^15 within 1 %.
+// The kernel of 2^16 forms the last butterflies in fp64 as well: with them in fp32 its features were 0.7 % further off than those of
+// the four passes, which take their stages in another order (scale 8, relative error 1.50e-6); so they are 0.35 % closer, and batch
+// 1024 takes 231 instead of 255 us with sign words (first 4096 coordinates 180 and 180).  2^15 is 0.65 % closer than the passes
+// without that, which would cost it up to 1.4 %.
 __device__ __forceinline__ void feature_sincos(double y, double revolutions, float& s, float& c)
 {
     const float fr = (float)__builtin_amdgcn_fract(y * revolutions);
@@ -975,14 +976,15 @@ spinner_tile_kernel(TileParams p)
         if constexpr (NSTEPS > 1)
             spinner_step<G, C, CB, G::layout_after(1), true, false, true, SIGNS, T, NPF, (NSTEPS > 2)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2]);
         bool wave_live = true;
-        // features of fp32 values (n = 2^15, 2^16): the last butterflies and the angles in fp64
+        // features of fp32 values (n = 2^15, 2^16): the angles in fp64, at 2^16 the last butterflies too (see feature_sincos)
         constexpr bool WIDE_ANGLE = EPI == EPI_STORE_COSSIN && std::is_same<T, float>::value && NSTEPS == 3;
-        static_assert(!WIDE_ANGLE || G::WB > 0, "the last stage is one between registers, behind the exchange");
+        constexpr bool WIDE_LAST = WIDE_ANGLE && NT >= 16;
+        static_assert(!WIDE_LAST || G::WB > 0, "the last stage is one between registers, behind the exchange");
         if constexpr (NSTEPS > 2) {
             if constexpr (PRUNE > 0)
                 spinner_step_pruned<G, C, CB, G::layout_after(2), false, SIGNS, PRUNE, NPF>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm);
             else
-                spinner_step<G, C, CB, G::layout_after(2), true, false, false, SIGNS, T, NPF, false, WIDE_ANGLE>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
+                spinner_step<G, C, CB, G::layout_after(2), true, false, false, SIGNS, T, NPF, false, WIDE_LAST>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
         }
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs
@@ -1108,11 +1110,11 @@ spinner_tile_kernel(TileParams p)
                 // dst row is [cos block | sin block]; the sin entry of coordinate i sits sin_off floats after its cos entry
                 const long long so = p.sin_off;
                 const double revolutions = WIDE_ANGLE ? p.factor_rev * (double)tracked_sign<G, CB, T>(c) : 0.0;
-                constexpr int half = WIDE_ANGLE ? 1 << last_wave_owned<G, CB>(LAYF) : 0;
+                constexpr int half = WIDE_LAST ? 1 << last_wave_owned<G, CB>(LAYF) : 0;
         #pragma unroll
                 for (int step = 0; step < RF / 4; ++step) {
                     // the two sides of the last butterflies one after the other
-                    const int jh = WIDE_ANGLE ? (step & 1) * (half / 4) | (step >> 1 & (half / 4 - 1)) | (step >> 1 & ~(half / 4 - 1)) << 1 : step;
+                    const int jh = WIDE_LAST ? (step & 1) * (half / 4) | (step >> 1 & (half / 4 - 1)) | (step >> 1 & ~(half / 4 - 1)) << 1 : step;
                     // four registers whose first coordinate in this wave is past the kept rows: nothing to evaluate.  Sign words, 2^24
                     // elements, without / with the test, in us: n = 512, m = 256 33.5 / 31.0, m = 64 31.6 / 25.6; n = 2048, m = 1024 43.2 /
                     // 40.7, m = 256 42.5 / 37.1; n = 2^13, m = 1024 46.2 / 41.2; all rows alike, but n = 2^14 61.4 / 63.0
@@ -1123,11 +1125,12 @@ spinner_tile_kernel(TileParams p)
                     float sn[4], cs[4];
         #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        if constexpr (WIDE_ANGLE) {
+                        if constexpr (WIDE_LAST) {
                             const int j = jh * 4 + k;
                             const double a = v[j & ~half], b = v[j | half];
                             feature_sincos((j & half) ? a - b : a + b, revolutions, sn[k], cs[k]);
                         }
+                        else if constexpr (WIDE_ANGLE) feature_sincos((double)v[jh * 4 + k], revolutions, sn[k], cs[k]);
                         else feature_sincos(v[jh * 4 + k], p, lane_factor, sn[k], cs[k]);
                         sn[k] *= p.inv_sqrt_m;
                         cs[k] *= p.inv_sqrt_m;
@@ -1143,7 +1146,7 @@ spinner_tile_kernel(TileParams p)
                         for (int k = 0; k < 4; ++k)
                             if (i + k < m) { dst[i + k] = cs[k]; dst[so + i + k] = sn[k]; }
                     }
-                    if constexpr (WIDE_ANGLE) { if (step & 1) __builtin_amdgcn_sched_barrier(0); }
+                    if constexpr (WIDE_LAST) { if (step & 1) __builtin_amdgcn_sched_barrier(0); }
                 }
             }
         }   // active
