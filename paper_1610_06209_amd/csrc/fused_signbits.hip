@@ -77,56 +77,62 @@ hipError_t launch_pack_codes(const float* y, long long y_stride, unsigned long l
     return hipGetLastError();
 }
 
-// out[i][j] = 1 - popcount(a_i xor b_j) / m.  With the code bits as numbers +1 (0) and -1 (1),
-//     popcount(a xor b) = (m - <a, b>) / 2,
-// and the table of inner products <a_i, b_j> is a dense contraction over the m code bits: it runs on the matrix
-// pipe in the narrowest format that holds +-1, fp4 (E2M1, 0x2 = 1.0, bit 3 the sign; v_mfma_scale_f32_32x32x64_f8f6f4 with
-// unit scales; products and fp32 sums of at most 2^24 ones: exact).  A workgroup of four waves owns 128 x 128 pairs
-// (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 16 staged in LDS; the next chunk is already in
-// registers while one is multiplied.  A row is read from LDS 16 bytes per lane (rows padded to 144 bytes: the sixteen
-// lanes of a phase cover all banks once): lane group g = lane / 32 takes the g-th 16 bytes of every 32, that is the operand
-// dwords of four instructions.  An instruction's operand is a dword of code bits spread into nibbles: dword q of the fp4
-// vector holds bits q, q + 4, .., q + 28, each moved to bit 3 of its nibble by doubling and joined with 1.0 by one
-// three-operand logic instruction (shifts and v_and_or issue at half its rate).  Which bit lands in which of the 64
-// k-slots does not matter, as long as both operands are spread the same way.
-// Bound: per code word a wave has four operands to spread at 19 cycles beside four products at 32 (4.9 PFLOP/s of 10.1 for
-// long codes, at the clock the chip holds under them), and the results' way out: rows of `out` that are no multiple of 64
-// bytes long take twice the write requests.  Against bits as 0 / 1 with the rows' weights counted on the way, half words read
-// from LDS and tiles dealt to the XCDs one by one, in us: 16384 x 16384, m = 256 284 -> 191, m = 4096 656 -> 622, m = 16384
-// 1808 -> 1785; 16384 x 10007, m = 256 255 -> 154, m = 4096 479 -> 420; 4096 x 4096, m = 1024 23.3 -> 18.3.  Bands of one or
-// eight tile rows: 435, 428 at 16384 x 10007, m = 4096.
+// out[i][j] = 1 - popcount(a_i xor b_j) / m.  The table of inner products of the code bits is a dense contraction and runs on the
+// matrix pipe in the narrowest format, fp4 (E2M1; v_mfma_scale_f32_32x32x64_f8f6f4).  A nibble of code bits is four planes, and a
+// plane is an operand as it lies: masked with 0x1, 0x2, 0x4 its numbers are 0 or 0.5, 1, 2 (whose weight the scale exponents of
+// the instruction take out: every common bit counts 4), masked with 0x8 and joined with 0x2 they are +1 or -1.  So the four dwords
+// that a lane reads at once are the operands of four instructions at one logic instruction a dword.  With the rows' bits in planes
+// 0 to 2 counted apart (w),
+//     popcount(a xor b) = w(a) + w(b) + m / 8 - S / 2,      S = sum of the four products,
+// where all is whole numbers below 2^24 up to m = 2^22; longer codes (WIDE) take plane 3 as 0 or 2 as well, and then S is a
+// multiple of 4.  Which bit lands in which of the 64 k-slots does not matter, as long as both operands are laid out the same way.
+// A workgroup of four waves owns 128 x 128 pairs (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 8, which
+// loads write to LDS directly, one chunk ahead into the other of two buffers: a barrier a chunk.  The 16-byte pieces of a row lie
+// exchanged by its number, so that the sixteen lanes of a phase cover all banks once.  Lane group g = lane / 32 takes the pieces
+// of parity g.
+// Bound: the matrix pipe, which takes 34 to 37 cycles per product (random codes: the longer) with up to four vector instructions
+// beside it and 2.6 more for each further one, and the results' way out: rows of `out` that are no multiple of 64 bytes long take
+// twice the write requests.  A product takes 49 cycles here for long codes (6.1 PFLOP/s of 10.1).  Against +1 / -1 in all planes
+// (shifts and seven instructions an operand dword), staged through registers, in us: 16384 x 10007, m = 4096 333 -> 294, m = 256
+// 150 -> 147; 16384 x 16384, m = 16384 1700 -> 1450, m = 4096 505 -> 443, m = 256 190 -> 192; 700 x 11000, m = 4096 28 -> 22;
+// 12000 x 300, m = 8192 33 -> 28; 4096 x 4096, m = 1024 16.5 -> 16.3.  Workgroups per compute unit, 16384 x 10007 (m = 256, 4096): two
+// 140, 305, three 147, 298, four 158, 294, but 16384 x 16384 three 443, two 466 and 9001 x 4999, m = 768, 33 and 38: three.  Results put
+// in order through LDS and stored in whole lines: 148, 329.  Bands of one or eight tile rows cost 2 to 4 %.
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-constexpr int kGramRows = 128, kGramCols = 128, kGramChunk = 16;      // chunk: code words per row
-constexpr int kGramPitch = kGramChunk / 2 + 1;                        // LDS row, in 16-byte units
+constexpr int kGramRows = 128, kGramCols = 128, kGramChunk = 8;       // chunk: code words per row
+constexpr int kGramPieces = kGramChunk / 2;                           // 16-byte pieces of a row's chunk
 constexpr unsigned kGramBand = 4;                                     // tile rows per band (see the kernel)
+constexpr unsigned kGramSpareLds = 14 << 10;                          // asked for and not used: three workgroups per compute unit, not four
+constexpr int kGramWide = 1 << 22;                                    // codes longer than this: see above
 
-// the 32 bits of w as 32 fp4 numbers (+1.0 or -1.0) in four dwords
-__device__ __forceinline__ intx8 spread_bits_fp4(unsigned w, unsigned sign, unsigned one)
+// plane P of 128 code bits as 32 fp4 numbers
+template <int P, bool WIDE>
+__device__ __forceinline__ intx8 code_plane(uintx4 w, unsigned sign, unsigned one)
 {
     intx8 f = {0, 0, 0, 0, 0, 0, 0, 0};
-    f[3] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);      // (w & sign) | one
-    w += w;
-    f[2] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
-    w += w;
-    f[1] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
-    w += w;
-    f[0] = (int)__builtin_amdgcn_bitop3_b32(w, sign, one, 0xEA);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (P < 3) f[k] = (int)(w[k] & (0x11111111u << P));
+        else if constexpr (WIDE) f[k] = (int)((w[k] >> 1) & 0x44444444u);
+        else f[k] = (int)__builtin_amdgcn_bitop3_b32(w[k], sign, one, 0xEA);      // (w & sign) | one
+    }
     return f;
 }
 
-// Three workgroups per compute unit cost 20 bytes of scratch per thread.
 // LINES: rows of `out` are whole 128-byte lines (nb a multiple of 32) and bypass cache retention (4096 x 4096, m = 1024 18.2 ->
 // 16.4 us; 16384 x 16384, m = 4096 625 -> 607); the pieces of other rows' lines have to meet in the L2 (16384 x 10007, m = 256:
 // 152 us, with the hint 338)
-template <bool LINES>
+template <bool LINES, bool WIDE>
 __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __restrict__ a, long long na, const uintx4* __restrict__ b,
                                                            long long nb, int words, float inv_m, unsigned gx, unsigned gy, float* __restrict__ out)
 {
-    __shared__ uintx4 sa[kGramRows * kGramPitch];
-    __shared__ uintx4 sb[kGramCols * kGramPitch];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // rows of a, then of b; two arrays, each read and written in code of its own, so that the compiler sees that what is read is
+    // not what the loads in flight write and does not wait for them
+    __shared__ uintx4 even[(kGramRows + kGramCols) * kGramPieces], odd[(kGramRows + kGramCols) * kGramPieces];
+    __shared__ float weights[kGramRows + kGramCols];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, wc = wave & 1, g = lane >> 5, l32 = lane & 31;
     // Tiles in bands of four tile rows, column by column, and an equal run of that order per XCD (workgroups go to the eight
     // XCDs in turn): the tiles in flight on an XCD share their codes in its L2, and the two halves of a 128-byte line of
@@ -144,66 +150,78 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][u][v] = 0.0f;
-    const int scale = 0x7f7f7f7f;                    // scale exponents (E8M0): 2^0
     unsigned sign = 0x88888888u, one = 0x22222222u;
     asm("" : "+v"(sign), "+v"(one));                 // in vector registers: scalar operands halve the issue rate
 
-    // staging: 128 rows of 8 16-byte pieces per operand, four pieces per thread and operand; rows and pieces past the end
-    // are read from the last one (they reach no stored result)
-    const int srow = threadIdx.x >> 3, scol = threadIdx.x & 7;
+    // staging: a wave brings 64 rows, 16 of them an instruction, lane l the piece of its row that lands at l mod 4; rows and
+    // pieces past the end are read from the last one (they reach no stored result)
     const int pieces = words >> 1;                   // 16-byte pieces per row (words is a multiple of 4)
-    const uintx4* ra[4];
-    const uintx4* rb[4];
+    const int swap = (l32 >> 2) & 3;                 // piece p of row r lies at p xor (r / 4 mod 4)
+    const int spiece = (lane & 3) ^ (lane >> 4);
+    const uintx4* rows[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        const long long i = i0 + t * 32 + srow, j = j0 + t * 32 + srow;
-        ra[t] = a + (i < na ? i : na - 1) * pieces;
-        rb[t] = b + (j < nb ? j : nb - 1) * pieces;
+        const int r = (wave & 1) * 64 + t * 16 + (lane >> 2);
+        const long long i = i0 + r, j = j0 + r;
+        rows[t] = wave < 2 ? a + (i < na ? i : na - 1) * pieces : b + (j < nb ? j : nb - 1) * pieces;
     }
-    uintx4 pa[4], pb[4];
-    auto load = [&](int piece0) {
-        const int c = piece0 + scol < pieces ? piece0 + scol : pieces - 1;
+    auto load = [&](int piece0, uintx4* buffer) {
+        const int c = piece0 + spiece < pieces ? piece0 + spiece : pieces - 1;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) { pa[t] = ra[t][c]; pb[t] = rb[t][c]; }
+        for (int t = 0; t < 4; ++t)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(rows[t] + c),
+                                             (__attribute__((address_space(3))) void*)(buffer + (wave * 64 + t * 16) * kGramPieces), 16, 0, 0);
     };
-    load(0);
-    const uintx4* ha = sa + (wr * 64 + l32) * kGramPitch + g;
-    const uintx4* hb = sb + (wc * 64 + l32) * kGramPitch + g;
-    for (int p0 = 0; p0 < pieces; p0 += kGramChunk / 2) {
+    int weight = 0;                                   // of the row that this thread counts
+    auto chunk = [&](int p0, const uintx4* now, uintx4* next) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's rows are in place
+        __syncthreads();                                      // everyone's are, and the other buffer has been read
+        if (p0 + kGramPieces < pieces) load(p0 + kGramPieces, next);
+        const uintx4* ha = now + (wr * 64 + l32) * kGramPieces;
+        const uintx4* hb = now + (kGramRows + wc * 64 + l32) * kGramPieces;
+        const uintx4* hw = now + threadIdx.x * kGramPieces;
+        const int have = pieces - p0 < kGramPieces ? pieces - p0 : kGramPieces;      // 2 or 4
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            sa[(t * 32 + srow) * kGramPitch + scol] = pa[t];
-            sb[(t * 32 + srow) * kGramPitch + scol] = pb[t];
-        }
-        __syncthreads();
-        if (p0 + kGramChunk / 2 < pieces) load(p0 + kGramChunk / 2);
-        const int steps = pieces - p0 < kGramChunk / 2 ? pieces - p0 : kGramChunk / 2;
-        for (int s = 0; s < steps; s += 2) {
+        for (int s = 0; s < kGramPieces; s += 2) {
+            if (s >= have) break;
             uintx4 qa[2], qb[2];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) { qa[t] = ha[t * 32 * kGramPitch + s]; qb[t] = hb[t * 32 * kGramPitch + s]; }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int t = 0; t < 2; ++t) {
+                qa[t] = ha[t * 32 * kGramPieces + ((s + g) ^ swap)];
+                qb[t] = hb[t * 32 * kGramPieces + ((s + g) ^ swap)];
+            }
+            const uintx4 w0 = hw[s ^ swap], w1 = hw[(s + 1) ^ swap];
+            static_for<0, 4>([&](auto plane) {
+                constexpr int P = plane.value;
+                constexpr int scale = (int)(0x01010101u * (P < 2 ? 0x7fu + 2 - P : 0x7fu));      // exponents (E8M0)
                 intx8 fa[2], fb[2];
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    fa[t] = spread_bits_fp4(qa[t][k], sign, one);
-                    fb[t] = spread_bits_fp4(qb[t][k], sign, one);
+                    fa[t] = code_plane<P, WIDE>(qa[t], sign, one);
+                    fb[t] = code_plane<P, WIDE>(qb[t], sign, one);
                 }
+                weight += __popc(w0[P] & (WIDE ? ~0u : 0x77777777u)) + __popc(w1[P] & (WIDE ? ~0u : 0x77777777u));
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
                         acc[t][u] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[t], fb[u], acc[t][u], 4, 4, 0, scale, 0, scale);
-            }
+            });
         }
-        __syncthreads();
+    };
+    load(0, even);
+    for (int p0 = 0; p0 < pieces; p0 += 2 * kGramPieces) {
+        chunk(p0, even, odd);
+        if (p0 + kGramPieces < pieces) chunk(p0 + kGramPieces, odd, even);
     }
+    weights[threadIdx.x] = (float)(weight + (!WIDE && threadIdx.x < kGramRows ? words * 8 : 0));
+    __syncthreads();
     // result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its 32 x 32 tile
-    const int m = words * 64;
     const long long i = i0 + wr * 64 + 4 * g, j = j0 + wc * 64 + l32;
     float* dst = out + i * nb + j;
-    const int rows = na - i < 64 ? (int)(na - i) : 64, cols = nb - j < 64 ? (int)(nb - j) : 64;      // what is left below and right of it
+    const int left = na - i < 64 ? (int)(na - i) : 64, cols = nb - j < 64 ? (int)(nb - j) : 64;      // what is left below and right of it
+    const float* wa = weights + wr * 64 + 4 * g;
+    const float* wb = weights + kGramRows + wc * 64 + l32;
     auto store = [&](auto whole) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -212,9 +230,9 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
                 const int r = t * 32 + 8 * (v >> 2) + (v & 3);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const int dh = (m - (int)acc[t][u][v]) >> 1;
-                    const float k = 1.0f - (float)dh * inv_m;
-                    if (decltype(whole)::value || (r < rows && u * 32 < cols)) {
+                    const float dh = __builtin_fmaf(acc[t][u][v], -0.5f, wa[r] + wb[u * 32]);      // exact
+                    const float k = __builtin_fmaf(-dh, inv_m, 1.0f);
+                    if (decltype(whole)::value || (r < left && u * 32 < cols)) {
                         if constexpr (LINES) __builtin_nontemporal_store(k, dst + r * nb + u * 32);
                         else dst[r * nb + u * 32] = k;
                     }
@@ -232,8 +250,10 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
     const long long gx = (nb + kGramCols - 1) / kGramCols, gy = (na + kGramRows - 1) / kGramRows;
     // one workgroup of 256 threads per tile, and a grid holds fewer than 2^32 threads; the caller keeps gy below 2^16
     if (gx > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;
-    const auto kernel = (nb & 31) == 0 ? hamming_gram_kernel<true> : hamming_gram_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(256), 0, s, reinterpret_cast<const uintx4*>(a), na,
+    const bool lines = (nb & 31) == 0;
+    const auto kernel = m > kGramWide ? (lines ? hamming_gram_kernel<true, true> : hamming_gram_kernel<false, true>)
+                                      : (lines ? hamming_gram_kernel<true, false> : hamming_gram_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(256), kGramSpareLds, s, reinterpret_cast<const uintx4*>(a), na,
                        reinterpret_cast<const uintx4*>(b), nb, m / 64, 1.0f / (float)m, (unsigned)gx, (unsigned)gy, out);
     return hipGetLastError();
 }

@@ -184,6 +184,21 @@ def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
     assert got[-1, 0] == 1.0
 
 
+@pytest.mark.parametrize("m", [256, 512, 768, 1024, 1280, 2**22, 2**22 + 256, 2**23, 2**24])
+def test_angular_gram_over_code_lengths(gpu, m):
+    # chunks of eight words, two buffers in turn: half a chunk, one, one and a half, two ..; up to 2^22 bits three planes of a nibble
+    # are 0 / 1 numbers and one +-1, beyond that all are 0 / 1.  Distances are whole numbers in both: one rounding of the quotient and
+    # one of the difference remain.  All bits set against all set, none and half of them are the largest sums.
+    rng = np.random.default_rng(m)
+    ca = rng.integers(-2**63, 2**63 - 1, (5, m // 64), dtype=np.int64)
+    cb = rng.integers(-2**63, 2**63 - 1, (7, m // 64), dtype=np.int64)
+    ca[0], ca[1], ca[2] = -1, 0, 0x7777777777777777
+    cb[0], cb[1], cb[2], cb[3] = -1, 0, 0x7777777777777777, 0x0F0F0F0F0F0F0F0F
+    got = gpu.b.spinner_angular_gram(_to(gpu, ca), _to(gpu, cb), m).cpu().numpy()
+    dh = np.array([[int(np.unpackbits((a ^ b).view(np.uint8)).sum()) for b in cb] for a in ca])
+    assert np.abs(got.astype(np.float64) - (1.0 - dh / m)).max() <= 2.0 ** -23
+
+
 def test_angular_gram_of_the_most_tiles(gpu):
     # one row of codes against as many as a grid of one workgroup per tile takes (2^24 - 1 tiles, 64 GiB of codes): every tile
     # is computed once, the last and ragged one included
