@@ -76,35 +76,46 @@ __device__ __forceinline__ void feat_ar_b_to_a(double (&v)[G::R], float4* pa, fl
 // through the exchange buffer like x (coalesced 16-byte loads, 16-byte reads in layout A).  In layout B register j of
 // consecutive lanes wants consecutive entries: 4-byte loads, 64 lanes on 256 consecutive bytes (the diagonal is
 // cache-resident).
+// Both are asked for a phase ahead of the use, D1 with x: two waves per SIMD leave the wait for them exposed otherwise (n = 4096, L = 4,
+// batch 32768 1347 -> 1322 us; n = 1024, L = 4, 32768 273 -> 261; n = 1024, one block, 131072 297 -> 292; n = 4096, one block, 131072 1370 and
+// 1375).  Lane masks a phase ahead in the same way gained nothing (n = 4096, 131072 1224 and 1221, m = 1000 68 and 72).
 template <typename G>
-__device__ __forceinline__ void feat_ar_diag_a(double (&v)[G::R], const float* d, float* w, float4* pa, int l)
-{
+struct ArDiagA {
+    v4f t[G::R / 4];
+    __device__ __forceinline__ void load(const float* d, unsigned at)      // at: the lane's first entry, 4 l
+    {
 #pragma unroll
-    for (int k = 0; k < G::R / 4; ++k)
-        *reinterpret_cast<float4*>(w + ar_word_of<G>(4 * (k * G::LANES + l))) = *reinterpret_cast<const float4*>(d + 4 * (k * G::LANES + l));
-    wave_lds_fence();
-#pragma unroll
-    for (int k = 0; k < G::R / 4; ++k) {
-        const float4 t = pa[k];
-        v[4 * k] *= (double)t.x; v[4 * k + 1] *= (double)t.y; v[4 * k + 2] *= (double)t.z; v[4 * k + 3] *= (double)t.w;
-    }
-    wave_lds_fence();
-}
-template <typename G>
-__device__ __forceinline__ void feat_ar_diag_b(double (&v)[G::R], const float* d, int ebase)
-{
-    // a few at a time: with all 2^r entries in flight at once the register allocator runs out
-    constexpr int CH = G::R < 16 ? G::R : 16;
-#pragma unroll
-    for (int j0 = 0; j0 < G::R; j0 += CH) {
-        float t[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) t[j] = d[ebase + ((j0 + j) << G::r)];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) v[j0 + j] *= (double)t[j];
+        for (int k = 0; k < G::R / 4; ++k) t[k] = *reinterpret_cast<const v4f*>(d + 4 * k * G::LANES + at);
         __builtin_amdgcn_sched_barrier(0);
     }
-}
+    __device__ __forceinline__ void multiply(double (&v)[G::R], float* put, const float4* pa) const      // put: where that entry goes
+    {
+#pragma unroll
+        for (int k = 0; k < G::R / 4; ++k) *reinterpret_cast<v4f*>(put + 4 * k * G::STRIDE) = t[k];
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < G::R / 4; ++k) {
+            const float4 f = pa[k];
+            v[4 * k] *= (double)f.x; v[4 * k + 1] *= (double)f.y; v[4 * k + 2] *= (double)f.z; v[4 * k + 3] *= (double)f.w;
+        }
+        wave_lds_fence();
+    }
+};
+template <typename G>
+struct ArDiagB {
+    float t[G::R];
+    __device__ __forceinline__ void load(const float* d, unsigned ebase)
+    {
+#pragma unroll
+        for (int j = 0; j < G::R; ++j) t[j] = (d + (j << G::r))[ebase];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void multiply(double (&v)[G::R]) const
+    {
+#pragma unroll
+        for (int j = 0; j < G::R; ++j) v[j] *= (double)t[j];
+    }
+};
 
 template <bool STREAM>
 __device__ __forceinline__ void store1(float* p, float v)
@@ -157,33 +168,41 @@ spinner_feature_ar_kernel(TileParams p, int L)
         const long long vec = wvec + g;
         const bool active = vec < p.batch;
         double v[R];
+        ArDiagA<G> da;
+        ArDiagB<G> db;
         // x: coalesced 16-byte loads, then through the buffer into layout A
-        const float* src = p.x + (active ? vec : 0) * p.in_stride + 4 * l;
+        const float* src = p.x + (active ? vec : 0) * p.in_stride;
+        const unsigned at = 4 * l;
+        float* put = w + ar_word_of<G>(at);             // a lane's pieces lie 4 LANES floats apart, four rows of the buffer
+        float4 t[R / 4];
 #pragma unroll
-        for (int k = 0; k < R / 4; ++k) {
-            const float4 t = load4<!BLOCKS>(src + 4 * k * G::LANES);      // a vector past the end reads the first one
-            *reinterpret_cast<float4*>(w + ar_word_of<G>(4 * (k * G::LANES + l))) = t;
-        }
+        for (int k = 0; k < R / 4; ++k) t[k] = load4<!BLOCKS>(src + 4 * k * G::LANES + at);      // a vector past the end reads the first one
+        if constexpr (!SIGNS) da.load(p.d[0], at);
+#pragma unroll
+        for (int k = 0; k < R / 4; ++k) *reinterpret_cast<float4*>(put + 4 * k * G::STRIDE) = t[k];
         wave_lds_fence();
 #pragma unroll
         for (int k = 0; k < R / 4; ++k) {
-            const float4 t = pa[k];
-            v[4 * k] = (double)t.x; v[4 * k + 1] = (double)t.y; v[4 * k + 2] = (double)t.z; v[4 * k + 3] = (double)t.w;
+            const float4 f = pa[k];
+            v[4 * k] = (double)f.x; v[4 * k + 1] = (double)f.y; v[4 * k + 2] = (double)f.z; v[4 * k + 3] = (double)f.w;
         }
         wave_lds_fence();
 
-        if constexpr (SIGNS) feat_ar_flip<G>(v, hw);                 // D1 in layout A
-        else feat_ar_diag_a<G>(v, p.d[0], w, pa, l);
+        // D1 in layout A, D2 in layout B, D3 in layout A
+        if constexpr (SIGNS) feat_ar_flip<G>(v, hw);
+        else da.multiply(v, put, pa);
         ar_stages<G>(v);
         feat_ar_a_to_b<G>(v, pa, pb);
+        if constexpr (!SIGNS) db.load(p.d[1], ebase);
         ar_stages<G>(v);
-        if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 3 * R);         // D2 in layout B
-        else feat_ar_diag_b<G>(v, p.d[1], ebase);
+        if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 3 * R);
+        else db.multiply(v);
         ar_stages<G>(v);
         feat_ar_b_to_a<G>(v, pa, pb);
+        if constexpr (!SIGNS) da.load(p.d[2], at);
         ar_stages<G>(v);
-        if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 4 * R);         // D3 in layout A
-        else feat_ar_diag_a<G>(v, p.d[2], w, pa, l);
+        if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 4 * R);
+        else da.multiply(v, put, pa);
         ar_stages<G>(v);
         feat_ar_a_to_b<G>(v, pa, pb);
         ar_stages<G>(v);
