@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspinner.so")
-UNITS = ["api", "fused_none", "fused_cossin", "fused_signbits", "multipass", "hash", "layer", "sketch", "structured", "struct_fft", "struct_fft_13", "struct_fft_14", "blocks", "fused_shared", "sketch_cols"]
+UNITS = ["api", "fused_none", "fused_cossin", "fused_signbits", "multipass", "hash", "layer", "sketch", "structured", "struct_fft", "struct_fft_13", "struct_fft_14", "blocks", "fused_shared", "fused_begun", "sketch_cols"]
 NATIVE = os.path.join(HERE, "_native.so")
 CXX = os.environ.get("CXX", "g++")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

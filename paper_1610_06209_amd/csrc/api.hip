@@ -109,9 +109,10 @@ size_t spinner_workspace_bytes(int n, long batch, int m, int epilogue)
 // (if non-null) replaces d1..d3; above that size the caller passes fp32 diagonals.
 // blocks > 1: this call writes block `block` of a row that stacks `blocks` independent m-row blocks
 // (out already points at the block's first column; see spinner_apply_blocks).
+// begun: x has the first diagonal and the first transform's low kColumnBits stages behind it (fused sizes, fp32 diagonals).
 static int apply_impl(const float* x, int n, int log2n, long batch, const float* d1, const float* d2, const float* d3,
                       const unsigned long long* signs, int m, int epilogue, float scale, float* out,
-                      void* workspace, void* stream, int blocks = 1)
+                      void* workspace, void* stream, int blocks = 1, bool begun = false)
 {
     using namespace spinner;
     // a block of a stacked row never runs its passes in place: its output rows are wider than n
@@ -138,7 +139,7 @@ static int apply_impl(const float* x, int n, int log2n, long batch, const float*
 
     // n = 2^15, 2^16: few vectors take the four passes where there is a buffer for them (the output itself, or a workspace)
     const bool cossin = epilogue == SPINNER_EPI_COSSIN;
-    const bool passes = log2n > kFusedMaxLogOther && batch <= few_wide_vectors(log2n, !cossin) &&
+    const bool passes = !begun && log2n > kFusedMaxLogOther && batch <= few_wide_vectors(log2n, !cossin) &&
                         (ws || (epilogue == SPINNER_EPI_NONE && m == n && blocks == 1));
     if (!passes && log2n <= (cossin ? kFusedMaxLogFeatures : fused_max_log(epilogue))) {
         if (batch > 0x7fffffffLL) return SPINNER_ERR_BAD_BATCH;
@@ -156,7 +157,8 @@ static int apply_impl(const float* x, int n, int log2n, long batch, const float*
         int prune = 0;
         while (prune < log2n && (long long)m <= ((long long)n >> (prune + 1))) ++prune;
         const bool shared_diag = !signs && epilogue == SPINNER_EPI_NONE && m == n && blocks == 1 && has_shared_diag_kernel(log2n);
-        const hipError_t e = shared_diag                ? launch_fused_shared_diag(log2n, p, s)
+        const hipError_t e = begun                      ? launch_fused_begun(log2n, prune, p, batch, s)
+                             : shared_diag              ? launch_fused_shared_diag(log2n, p, s)
                              : epilogue == kEpiSignBits ? launch_fused_signbits(log2n, signs != nullptr, prune, p, batch, s)
                              : epi == EPI_STORE_COSSIN ? launch_fused_cossin(log2n, signs != nullptr, p, batch, s)
                                                        : launch_fused_none(log2n, signs != nullptr, prune, p, batch, s);
@@ -648,10 +650,11 @@ int spinner_sketch(const float* A, int n, int d, const float* w, const float* d1
     float* At = reinterpret_cast<float*>(base);                                             // [d][n]
     float* Ut = reinterpret_cast<float*>(base + align256((size_t)d * n * sizeof(float)));   // [d][m]
     void* ws2 = base + align256((size_t)d * n * sizeof(float)) + align256((size_t)d * m * sizeof(float));
-    hipError_t e = spinner::launch_transpose_scale(A, n, d, w, At, s);
+    const bool begun = spinner::sketch_begun_pays(log2n, m);
+    hipError_t e = begun ? spinner::launch_transpose_transform(A, n, d, w, d1, At, s) : spinner::launch_transpose_scale(A, n, d, w, At, s);
     if (e != hipSuccess) return hip_fail(e);
-    const int rc = apply_impl(At, n, log2n, d, d1, d2, d3, nullptr, m, SPINNER_EPI_NONE, scale, Ut,
-                              spinner_workspace_bytes(n, d, m, SPINNER_EPI_NONE) ? ws2 : nullptr, stream);
+    const int rc = apply_impl(At, n, log2n, d, begun ? nullptr : d1, d2, d3, nullptr, m, SPINNER_EPI_NONE, scale, Ut,
+                              spinner_workspace_bytes(n, d, m, SPINNER_EPI_NONE) ? ws2 : nullptr, stream, 1, begun);
     if (rc != SPINNER_OK) return rc;
     e = spinner::launch_transpose_scale(Ut, d, m, nullptr, B, s);
     return e == hipSuccess ? SPINNER_OK : hip_fail(e);

@@ -97,7 +97,8 @@ constexpr int xcd_group_log_for()
     return G::NT > 14 ? -1 : (target > wg_bytes_log ? target - wg_bytes_log : 0);
 }
 
-template <typename T, int NT, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS = false, int PRUNE = 0, bool RAGGED = true, typename GEOM = void>
+template <typename T, int NT, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS = false, int PRUNE = 0, bool RAGGED = true, typename GEOM = void,
+          int BEGUN = 0>
 inline hipError_t launch_tile(const TileParams& p, long long total_tiles, hipStream_t stream)
 {
     // wide exchanges pay with packed sign words only: fp32 diagonals read in layout 1 come in 256-byte runs,
@@ -117,7 +118,7 @@ inline hipError_t launch_tile(const TileParams& p, long long total_tiles, hipStr
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     TileParams q = p;
     q.xcd_group_log = (SIGNS && NSTEPS == 3 && C >= NT) ? xcd_group_log_for<G>() : -1;
-    hipLaunchKernelGGL((spinner_tile_kernel<T, G, C, NSTEPS, FIRST_DIAG, EPI, SIGNS, PRUNE, RAGGED>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((spinner_tile_kernel<T, G, C, NSTEPS, FIRST_DIAG, EPI, SIGNS, PRUNE, RAGGED, BEGUN>), dim3((unsigned)blocks),
                        dim3(G::THREADS), 0, stream, q);
     return hipGetLastError();
 }
@@ -286,6 +287,22 @@ hipError_t launch_layer_signals(int log2n, const float* in, const float* da, con
 // Newton sketch: transposition with optional row weights, Gram matrix on the matrix pipe
 hipError_t launch_transpose_scale(const float* src, long long rows, long long cols, const float* row_scale, float* dst,
                                   hipStream_t s);
+// the same with the first diagonal and the transform over the low kColumnBits index bits, and the projection of what it leaves
+constexpr int kColumnBits = 8;
+// Where the two are ahead of transposition and whole projection.  Whole call and Gram, in us, without / with: n = 2^16, m = 2048, d = 500 132.5 /
+// 125.9, 256 68.7 / 68.2, 64 45.4 / 44.4, 16 42.4 / 39.2, m = 20000, d = 500 210.6 / 192.4; 2^15, m = 1024, d = 1000 127.9 / 121.2, 128 37.0 / 34.2,
+// m = 10000, d = 1000 300.6 / 293.7, m = 2000, d = 17 33.4 / 30.8; 2^14, m = 1000, d = 1999 188 / 177, 300 41.3 / 38.1; 2^13, m = 500, d = 1999 92.2 /
+// 90.0, 333 26.4 / 26.3; 2^11, m = 1000, d = 300 31.2 / 29.3, m = 128, d = 1999 36.2 / 34.4.  Where more than n / 16 rows are kept at 2^13 and 2^14 the
+// kernels of the whole projection have a better split of their own (m = 3000: 2^14, d = 40 30.2 / 31.2, 2^13, d = 100 31.4 / 32.2), as they do at
+// 2^12 (m = 256, d = 500 22.6 / 22.9, m = 2000, d = 25 22.9 / 23.6), at 2^10 (d = 1999 63.1 / 64.0) and where all rows are kept.
+inline bool sketch_begun_pays(int log2n, int m)
+{
+    const int n = 1 << log2n;
+    return log2n == 13 || log2n == 14 ? m <= n >> 4 : (log2n == 11 || log2n == 15 || log2n == 16) && m < n;
+}
+hipError_t launch_transpose_transform(const float* src, long long rows, long long cols, const float* row_scale, const float* diag,
+                                      float* dst, hipStream_t s);
+hipError_t launch_fused_begun(int log2n, int prune, const TileParams& p, long long tiles, hipStream_t s);
 // the sketch on the columns as they lie (sketch_cols.hip): n = 2^4 .. 2^kSketchColsMaxLog, d a multiple of 4; factor = n^{-3/2} scale
 constexpr int kSketchColsMaxLog = 12;
 // Shapes for which that form is the faster one.  Measured against transposition + projection + transposition (ms):

@@ -59,6 +59,87 @@ hipError_t launch_transpose_scale(const float* src, long long rows, long long co
     return hipGetLastError();
 }
 
+// dst[c][r] = src[r][c] * (row_scale ? row_scale[r] : 1) * diag[r], with the transform over the low kColumnBits index bits of r
+// done on the way (unnormalised).  rows: a multiple of 2^kColumnBits.
+// A tile is 256 rows of 32 columns, 32 KiB of LDS.  On the way in lanes 0 .. 31 are the columns and a thread holds 32 rows: row bits
+// 0, 1, 4, 6, 7 are transformed between its registers; the wave is row bits 2, 3 and the upper half of the lanes row bit 5.
+// On the way out a lane is four rows, so those three are lane bits 0, 1, 3 and take one DPP instruction each; the factor that
+// such stages leave on a lane (-1 to the number of the three that are set) is taken from the rows when they are scaled.
+// A column of the tile is 64 pieces of 16 bytes, piece q in place q ^ column: both sides touch 64 different pieces of all banks.
+// Bound: memory, as the transposition alone (46 us for 2 x 131 MB at n = 2^16, d = 500, where that takes 44): the arithmetic hides behind it,
+// and the projection that follows has eight stages and a diagonal less (68 -> 62 us there).  With tiles of 64 columns, whose 64 KiB leave two
+// of them on a compute unit, 51 us; with the non-temporal hint on the loads a line that two tiles share comes twice (131 for 126 us in all).
+// Runs of 4 / 8 / 16 / 32 tiles per XCD, d = 500: 127.5 / 127.2 / 125.9 / 125.5 us in all, n = 2^13, d = 333: 27.0 / 27.0 / 26.3 / 26.8.
+constexpr int kColumnRows = 1 << kColumnBits, kColumnTile = 32, kColumnXcdLog = 4;
+static_assert(kColumnBits == 8, "rows of a tile: five bits in registers, two in the wave, one in the lanes");
+template <bool SCALED>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+transpose_transform_kernel(const float* __restrict__ src, long long rows, long long cols, unsigned gx, const float* __restrict__ row_scale,
+                           const float* __restrict__ diag, float* __restrict__ dst)
+{
+    __shared__ float4 tile[kColumnTile * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lc = lane & 31, up = lane >> 5;
+    const unsigned tl = (unsigned)xcd_tile(blockIdx.x, gridDim.x, kColumnXcdLog);
+    const long long r0 = (long long)(tl / gx) * kColumnRows, c0 = (long long)(tl % gx) * kColumnTile;
+    const long long cc = c0 + lc < cols ? lc : cols - 1 - c0;      // columns past the last one read it and are not stored
+    float v[32];
+    // register 4 a + i: row 4 wave + 32 up + i + 16 (a & 1) + 64 (a >> 1)
+    {
+        const float* in = src + (r0 + 4 * wave) * cols + c0;
+        const long long own = 32 * up * cols + cc;
+#pragma unroll
+        for (int a = 0; a < 8; ++a)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[4 * a + i] = in[(16 * (a & 1) + 64 * (a >> 1) + i) * cols + own];
+        const unsigned sign = (unsigned)((__builtin_popcount(wave) + up) & 1) << 31;
+        const float *w = row_scale + r0 + 4 * wave + 32 * up, *d = diag + r0 + 4 * wave + 32 * up;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const int r = 16 * (a & 1) + 64 * (a >> 1);
+            if constexpr (SCALED) {
+                const float4 t = *reinterpret_cast<const float4*>(w + r);
+                v[4 * a] *= t.x; v[4 * a + 1] *= t.y; v[4 * a + 2] *= t.z; v[4 * a + 3] *= t.w;
+            }
+            const float4 t = *reinterpret_cast<const float4*>(d + r);
+            v[4 * a] *= __uint_as_float(__float_as_uint(t.x) ^ sign); v[4 * a + 1] *= __uint_as_float(__float_as_uint(t.y) ^ sign);
+            v[4 * a + 2] *= __uint_as_float(__float_as_uint(t.z) ^ sign); v[4 * a + 3] *= __uint_as_float(__float_as_uint(t.w) ^ sign);
+        }
+    }
+    static_for<0, 5>([&](auto q) { reg_stage<q.value>(v); });
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        tile[lc * 64 + ((wave + 8 * up + 4 * (a & 1) + 16 * (a >> 1)) ^ lc)] = make_float4(v[4 * a], v[4 * a + 1], v[4 * a + 2], v[4 * a + 3]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int col = 8 * wave + k;
+        const float4 t = tile[col * 64 + (lane ^ col)];
+        v[4 * k] = t.x; v[4 * k + 1] = t.y; v[4 * k + 2] = t.z; v[4 * k + 3] = t.w;
+    }
+    lane_stage_fmac_dpp<0>(v, lane & 1 ? 1.0f : -1.0f);
+    lane_stage_fmac_dpp<1>(v, lane & 2 ? 1.0f : -1.0f);
+    lane_stage_fmac_dpp<3>(v, lane & 8 ? 1.0f : -1.0f);
+    float* out = dst + (c0 + 8 * wave) * rows + r0;
+    const int left = (int)(cols - c0 < kColumnTile ? cols - c0 : kColumnTile) - 8 * wave;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k < left) *reinterpret_cast<float4*>(out + k * rows + 4 * lane) = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+}
+
+hipError_t launch_transpose_transform(const float* src, long long rows, long long cols, const float* row_scale, const float* diag,
+                                      float* dst, hipStream_t s)
+{
+    if (rows <= 0 || cols <= 0) return hipSuccess;
+    if (rows % kColumnRows) return hipErrorInvalidValue;
+    const long long gx = (cols + kColumnTile - 1) / kColumnTile, gy = rows / kColumnRows;
+    if (gx > 0xffffffLL || gy > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;      // 2^32 threads per grid
+    const dim3 grid((unsigned)(gx * gy));
+    if (row_scale) hipLaunchKernelGGL(transpose_transform_kernel<true>, grid, dim3(256), 0, s, src, rows, cols, (unsigned)gx, row_scale, diag, dst);
+    else hipLaunchKernelGGL(transpose_transform_kernel<false>, grid, dim3(256), 0, s, src, rows, cols, (unsigned)gx, row_scale, diag, dst);
+    return hipGetLastError();
+}
+
 // G = B^T B for B [m][d] row-major: G[a][b] = sum_k B[k][a] B[k][b], on the fp32 matrix pipe (v_mfma_f32_32x32x2_f32).
 // G is symmetric, so only the 64 x 64 tiles on and above the diagonal are computed and each is stored twice.  A
 // workgroup owns one tile (of one slab of rows); its four waves take a quarter of the rows each, hold the whole tile

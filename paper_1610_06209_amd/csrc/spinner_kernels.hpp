@@ -888,7 +888,9 @@ __device__ __forceinline__ void feature_sincos(double y, const TileParams& p, fl
 //         are 16-byte aligned (EPI_STORE_NONE only); the kernel then has no per-store row-limit test at all.  With the
 //         tests compiled in, the compiler forms their predicates before the rounds and carries them through the
 //         whole kernel (dozens of scalar register pairs, spilled to vector-register lanes and read back at the end).
-template <typename T, typename G, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS, int PRUNE = 0, bool RAGGED = true>
+// BEGUN   low index bits that the first transform has behind it, and the first diagonal before it (a three-step kernel whose
+//         input another kernel prepared): the first step then does the bits above, and no lane carries a tracked sign after it
+template <typename T, typename G, int C, int NSTEPS, bool FIRST_DIAG, int EPI, bool SIGNS, int PRUNE = 0, bool RAGGED = true, int BEGUN = 0>
 __global__ void __launch_bounds__(G::THREADS)
 __attribute__((amdgpu_waves_per_eu(G::MIN_WAVES > 0 ? G::MIN_WAVES : 1)))
 spinner_tile_kernel(TileParams p)
@@ -901,6 +903,10 @@ spinner_tile_kernel(TileParams p)
     constexpr int NT = G::NT;
     constexpr int R = G::R;
     constexpr int CB = C >= NT ? 0 : C;          // index bits below CB are not transformed
+    static_assert(BEGUN == 0 || (NSTEPS == 3 && !FIRST_DIAG && C >= NT && !SIGNS && EPI == EPI_STORE_NONE && std::is_same<T, float>::value),
+                  "an input that is begun: fused fp32 kernels with fp32 diagonals");
+    constexpr bool ODD = BEGUN == 0;             // the first transform leaves tracked signs
+    static_assert(BEGUN == 0 || BEGUN >= G::lane_pos(0, 3) + 1, "the bits of the DPP stages are all done or none is");
     // data touched once bypass cache retention: x and out of the fused kernels, and, in the four-pass schedule,
     // x read by the first pass and what the last pass reads and writes (what lies between is read again soon)
     constexpr bool FIRST_PASS = NSTEPS == 1 && FIRST_DIAG && C >= NT, LAST_PASS = NSTEPS == 1 && !FIRST_DIAG && C < NT;
@@ -972,9 +978,9 @@ spinner_tile_kernel(TileParams p)
         const unsigned long long* sw1 = p.sw[1];
         if constexpr (SIGNS && NSTEPS < 3) { sw0 += q << (NT - 6); sw1 += q << (NT - 6); }
         // steps (layout alternates only when a tile spans several waves)
-        spinner_step<G, C, CB, G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1)>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1);
+        spinner_step<G, C, (BEGUN ? BEGUN : CB), G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1)>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1);
         if constexpr (NSTEPS > 1)
-            spinner_step<G, C, CB, G::layout_after(1), true, false, true, SIGNS, T, NPF, (NSTEPS > 2)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2]);
+            spinner_step<G, C, CB, G::layout_after(1), true, false, ODD, SIGNS, T, NPF, (NSTEPS > 2)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2]);
         bool wave_live = true;
         // features of fp32 values (n = 2^15, 2^16): the angles in fp64, at 2^16 the last butterflies too (see feature_sincos)
         constexpr bool WIDE_ANGLE = EPI == EPI_STORE_COSSIN && std::is_same<T, float>::value && NSTEPS == 3;
@@ -982,9 +988,9 @@ spinner_tile_kernel(TileParams p)
         static_assert(!WIDE_LAST || G::WB > 0, "the last stage is one between registers, behind the exchange");
         if constexpr (NSTEPS > 2) {
             if constexpr (PRUNE > 0)
-                spinner_step_pruned<G, C, CB, G::layout_after(2), false, SIGNS, PRUNE, NPF>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm);
+                spinner_step_pruned<G, C, CB, G::layout_after(2), !ODD, SIGNS, PRUNE, NPF>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm);
             else
-                spinner_step<G, C, CB, G::layout_after(2), true, false, false, SIGNS, T, NPF, false, WIDE_LAST>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
+                spinner_step<G, C, CB, G::layout_after(2), true, false, !ODD, SIGNS, T, NPF, false, WIDE_LAST>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
         }
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs
@@ -995,7 +1001,7 @@ spinner_tile_kernel(TileParams p)
             const long long m = p.m;
             // held values carry the tracked lane sign after an odd number of transforms
             float lane_factor = p.factor;
-            if constexpr (NSTEPS & 1) lane_factor *= tracked_sign<G, CB, T>(c);
+            if constexpr ((NSTEPS & 1) && ODD) lane_factor *= tracked_sign<G, CB, T>(c);
             // whole tile inside the kept range and rows 16-byte aligned: no per-store checks
             // (with a pruned last round, lanes whose pruned bits are set hold nothing to store)
             constexpr bool LANES_PRUNED = PRUNE > 0 && (prune_positions<G>(PRUNE) & lane_positions<G>(LAYF)) != 0;

@@ -60,6 +60,25 @@ def test_sketch_matches_oracle(gpu, oracle, n, d, m, weights):
     assert err.max() <= REL_L2_TOL, err.max()
 
 
+@pytest.mark.parametrize("log2n", [11, 13, 14, 15, 16])
+def test_sketch_with_the_first_stages_in_the_transposition(gpu, oracle, log2n):
+    # Columns for tiles of 32: a lone one, one short of a tile, one over, a last tile whose second wave of columns is cut; m on
+    # both sides of n / 16, where the projection takes other kernels; general diagonals, so that a
+    # swapped or dropped one, or one met in the wrong order of rows, would show.
+    n = 1 << log2n
+    rng = np.random.default_rng(8250 + log2n)
+    for d, m, weights in [(1, n // 16, True), (31, n // 32 - 1, False), (33, n // 16 + 1, True), (74, n - 1, False), (45, n // 16 - 3, True)]:
+        A, w = W.newton_sketch_problem(n, d, 8260 + log2n + d)
+        dg = (rng.standard_normal((3, n)) * 0.5 + 1.0).astype(np.float32)
+        scale = math.sqrt(n / m)
+        B = gpu.b.spinner_sketch(_to(gpu, A), _to(gpu, w) if weights else None, *[_to(gpu, dg[k]) for k in range(3)], m, scale)
+        gpu.torch.cuda.synchronize()
+        assert B.shape == (m, d)
+        want = oracle.sketch(A, w if weights else None, dg[0], dg[1], dg[2], m, scale)
+        err = rel_l2_per_vector(B.cpu().numpy().T, want.T)
+        assert err.max() <= REL_L2_TOL, (d, m, err.max())
+
+
 @pytest.mark.parametrize("log2n", [22, 24])
 def test_sketch_of_the_longest_columns(gpu, log2n):
     # 2^16 and more tiles of rows in the transposition; projections of these sizes are compared with the oracle in
