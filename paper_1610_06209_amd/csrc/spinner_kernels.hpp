@@ -617,6 +617,56 @@ __device__ __forceinline__ void transpose(double (&v)[G::R], const ThreadCtx<G>&
 }
 
 // ------------------------------------------------------------------ diagonal product
+// Entries of a diagonal in flight, four registers' worth in a piece: the first N pieces are asked for before the exchange that
+// precedes the product, and each product asks for the piece N further on into the place that it empties.
+// Without it the compiler, short of registers beside 64 values, asks for a piece and waits for it sixteen times over in the pruned round,
+// where a product and a sum follow each load.
+// Piece k of a walk: k itself, or (PAIRED: the pruned last round) 0, R/8, 1, R/8 + 1, ..: the two sides of its first sums next to each other.
+template <int N>
+struct DiagAhead { float4 q[N > 0 ? N : 1]; };
+// Pieces ahead in the fused kernels: as many as fit without spills, where they gain.  None / 4 pieces, in us, 2^27 elements, first 1000 rows: 2^14
+// 176 / 156, 2^16 230 / 226, 2^15 169 / 169 (not taken); 2^13, first 500, none / 4 / 8 152 / 156 / 144; 2^12, first 200, 141 / 142; all rows 2^16 328.6 /
+// 325.1, 20000 of them 295.6 / 290.4, 2^15 249 / 256, 2^14 220 / 232 (2^16 with six and eight pieces 334 and 369, and spills).
+// Vectors of the sketch, which arrive begun: 2^16, m = 2048, d = 500 (whole call) 125.9 / 120.5, m = 20000 192.4 / 195.5.
+constexpr int diag_pieces_ahead(int log2n, bool pruned, bool begun)
+{
+    if (pruned) return log2n == 13 ? 8 : (log2n == 14 || log2n == 16 ? 4 : 0);
+    return log2n == 16 && !begun ? 4 : 0;
+}
+template <typename G, bool PAIRED>
+constexpr int diag_piece(int k) { return PAIRED ? (k >> 1) + (k & 1) * (G::R / 8) : k; }
+
+template <typename G, int LAY>
+__device__ __forceinline__ float4 diag_load(const float* dtile, unsigned own, int piece)
+{
+    return *reinterpret_cast<const float4*>(dtile + G::reg_index(LAY, piece * 4) + own);
+}
+template <typename G, int LAY, int N, bool PAIRED>
+__device__ __forceinline__ void fetch_diag(DiagAhead<N>& da, const ThreadCtx<G>& c, const float* dtile)
+{
+    const unsigned own = (unsigned)c.base_index(LAY);
+#pragma unroll
+    for (int k = 0; k < N; ++k) da.q[k] = diag_load<G, LAY>(dtile, own, diag_piece<G, PAIRED>(k));
+    __builtin_amdgcn_sched_barrier(0);
+}
+// PAIRED: the sums over the highest register bit too; registers 0 .. R / 2 - 1 are left
+template <typename G, int LAY, int N, bool PAIRED>
+__device__ __forceinline__ void diag_multiply_ahead(float (&v)[G::R], const ThreadCtx<G>& c, const float* dtile, DiagAhead<N>& da)
+{
+    const unsigned own = (unsigned)c.base_index(LAY);
+    static_for<0, G::R / 4>([&](auto kk) {
+        constexpr int k = kk.value, jh = diag_piece<G, PAIRED>(k);
+        const float4 t = da.q[k % N];
+        v[jh * 4] *= t.x; v[jh * 4 + 1] *= t.y; v[jh * 4 + 2] *= t.z; v[jh * 4 + 3] *= t.w;
+        if constexpr (k + N < G::R / 4) da.q[k % N] = diag_load<G, LAY>(dtile, own, diag_piece<G, PAIRED>(k + N));
+        if constexpr (PAIRED && (k & 1)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[(jh - G::R / 8) * 4 + i] += v[jh * 4 + i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
 template <typename G, int C, int LAY, typename T>
 __device__ __forceinline__ void diag_multiply(T (&v)[G::R], const ThreadCtx<G>& c,
                                               const float* dtile, int sl)
@@ -721,10 +771,11 @@ __device__ __forceinline__ void sign_flip(T (&v)[G::R], const ThreadCtx<G>& c, c
 // PF_NEXT, receives those of the next step (packed words at next_words) before this step's exchange.
 // BUT_LAST (tiles of several waves): the last register stage is left to the caller.
 template <typename G, int C, int CB, int LAY, bool HAS_DIAG, bool FIRST_TRANSPOSE, bool NEGATE, bool SIGNS, typename T, int NPF = 0,
-          bool PF_NEXT = false, bool BUT_LAST = false>
+          bool PF_NEXT = false, bool BUT_LAST = false, int NPD = 0, bool PAIRED_NEXT = false>
 __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c,
                                              const float* dtile, const unsigned long long* words, int sl, float4* lds,
-                                             SignMasks<NPF>* pm = nullptr, const unsigned long long* next_words = nullptr)
+                                             SignMasks<NPF>* pm = nullptr, const unsigned long long* next_words = nullptr,
+                                             DiagAhead<NPD>* da = nullptr, const float* next_diag = nullptr)
 {
     constexpr bool DIRECT = SIGNS && C < G::NT;      // column tiles bring their lane masks as they are used
     if constexpr (HAS_DIAG) {
@@ -732,11 +783,13 @@ __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c
             if constexpr (NPF > 0 && !FIRST_TRANSPOSE) sign_flip<G, LAY, NPF, DIRECT>(v, c, words, pm);
             else sign_flip<G, LAY, 0, DIRECT>(v, c, words);
         }
+        else if constexpr (NPD > 0 && !FIRST_TRANSPOSE) diag_multiply_ahead<G, LAY, NPD, false>(v, c, dtile, *da);
         else diag_multiply<G, C, LAY>(v, c, dtile, sl);
     }
     constexpr bool SWAP = G::LANE_SWAPS && CB <= G::lane_pos(LAY, 4);
     local_stages<G, CB, LAY, NEGATE, SWAP>(v, c);
     if constexpr (NPF > 0 && PF_NEXT) fetch_sign_masks<G, (G::WB > 0 ? 1 - LAY : LAY), NPF, DIRECT>(*pm, c, next_words);
+    if constexpr (NPD > 0 && PF_NEXT) fetch_diag<G, 1 - LAY, NPD, PAIRED_NEXT>(*da, c, next_diag);
     if constexpr (G::WB > 0) {
         if constexpr (std::is_same<T, float>::value) transpose<G, LAY, !FIRST_TRANSPOSE, 0, 0, SWAP>(v, c, lds);
         else transpose<G, LAY, !FIRST_TRANSPOSE, SWAP>(v, c, lds);
@@ -817,17 +870,21 @@ __device__ __forceinline__ void pruned_reg_stages(T (&v)[G::R])
 // The last (diagonal, transform) step with the P highest index bits pruned.  Returns,
 // through wave_live, whether this wave still holds outputs; pruned_final_regs() tells
 // how many leading registers do.
-template <typename G, int C, int CB, int LAY, bool NEGATE, bool SIGNS, int P, int NPF = 0>
+template <typename G, int C, int CB, int LAY, bool NEGATE, bool SIGNS, int P, int NPF = 0, int NPD = 0>
 __device__ __forceinline__ void spinner_step_pruned(float (&v)[G::R], const ThreadCtx<G>& c, const float* dtile,
                                                     const unsigned long long* words, int sl, float4* lds,
-                                                    bool& wave_live, const SignMasks<NPF>* pm = nullptr)
+                                                    bool& wave_live, const SignMasks<NPF>* pm = nullptr,
+                                                    DiagAhead<NPD>* da = nullptr)
 {
     static_assert(C >= G::NT && CB == 0, "pruning is for whole-vector tiles");
     constexpr unsigned PM = prune_positions<G>(P);
     constexpr unsigned REGS = reg_positions<G>(LAY);
     if constexpr (SIGNS) sign_flip<G, LAY, NPF>(v, c, words, pm);
+    else if constexpr (NPD > 0) diag_multiply_ahead<G, LAY, NPD, true>(v, c, dtile, *da);
     else diag_multiply<G, C, LAY>(v, c, dtile, sl);
-    pruned_reg_stages<G, LAY, REGS, PM, 0u>(v);
+    constexpr unsigned TOP = 1u << (G::NT - 1);
+    static_assert(NPD == 0 || G::reg_pos(LAY, G::r - 1) == G::NT - 1, "the highest register bit is the highest index bit");
+    pruned_reg_stages<G, LAY, (NPD > 0 ? REGS & ~TOP : REGS), PM, (NPD > 0 ? TOP : 0u)>(v);
     constexpr unsigned DONE1 = PM & REGS;
     constexpr int RL1 = live_regs<G>(LAY, DONE1);
     static_for<0, G::LANE_STAGES>([&](auto b) {
@@ -973,14 +1030,17 @@ spinner_tile_kernel(TileParams p)
         // (measured: 1.4 % at n = 2^14, nothing elsewhere; only tiles of several waves with 64 values per thread use it)
         constexpr int NPF = (SIGNS && G::WB > 0 && R == 64) ? kMaskPrefetch : 0;
         SignMasks<NPF> pm;
+        constexpr int NPD = (!SIGNS && NSTEPS == 3 && C >= NT && EPI == EPI_STORE_NONE && std::is_same<T, float>::value)
+                                ? diag_pieces_ahead(NT, PRUNE > 0, BEGUN > 0) : 0;
+        DiagAhead<NPD> da;
         // words of this tile's part of the diagonals (tile q of a longer vector: 2^NT / 64 words per tile)
         const unsigned long long* sw0 = p.sw[0];
         const unsigned long long* sw1 = p.sw[1];
         if constexpr (SIGNS && NSTEPS < 3) { sw0 += q << (NT - 6); sw1 += q << (NT - 6); }
         // steps (layout alternates only when a tile spans several waves)
-        spinner_step<G, C, (BEGUN ? BEGUN : CB), G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1)>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1);
+        spinner_step<G, C, (BEGUN ? BEGUN : CB), G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1), false, NPD, false>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1, &da, p.d[1]);
         if constexpr (NSTEPS > 1)
-            spinner_step<G, C, CB, G::layout_after(1), true, false, ODD, SIGNS, T, NPF, (NSTEPS > 2)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2]);
+            spinner_step<G, C, CB, G::layout_after(1), true, false, ODD, SIGNS, T, NPF, (NSTEPS > 2), false, NPD, (PRUNE > 0)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2], &da, p.d[2]);
         bool wave_live = true;
         // features of fp32 values (n = 2^15, 2^16): the angles in fp64, at 2^16 the last butterflies too (see feature_sincos)
         constexpr bool WIDE_ANGLE = EPI == EPI_STORE_COSSIN && std::is_same<T, float>::value && NSTEPS == 3;
@@ -988,9 +1048,9 @@ spinner_tile_kernel(TileParams p)
         static_assert(!WIDE_LAST || G::WB > 0, "the last stage is one between registers, behind the exchange");
         if constexpr (NSTEPS > 2) {
             if constexpr (PRUNE > 0)
-                spinner_step_pruned<G, C, CB, G::layout_after(2), !ODD, SIGNS, PRUNE, NPF>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm);
+                spinner_step_pruned<G, C, CB, G::layout_after(2), !ODD, SIGNS, PRUNE, NPF, NPD>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm, &da);
             else
-                spinner_step<G, C, CB, G::layout_after(2), true, false, !ODD, SIGNS, T, NPF, false, WIDE_LAST>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm);
+                spinner_step<G, C, CB, G::layout_after(2), true, false, !ODD, SIGNS, T, NPF, false, WIDE_LAST, NPD>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm, nullptr, &da);
         }
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs

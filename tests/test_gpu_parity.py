@@ -172,6 +172,21 @@ def test_first_m_rows_with_pruned_last_round(gpu, oracle, log2n):
 
 
 # ------------------------------------------------------------------ random features
+@pytest.mark.parametrize("log2n,pruned", [(13, True), (14, True), (16, True), (16, False)])
+def test_first_m_rows_with_diagonals_in_flight_ahead(gpu, oracle, log2n, pruned):
+    # every entry of every diagonal another value: one that meets the wrong coordinate, or meets it twice, shows
+    n = 1 << log2n
+    rng = np.random.default_rng(1900 + log2n + pruned)
+    d = (rng.standard_normal((3, n)) * 0.5 + 1.0).astype(np.float32)
+    for m, batch in ((n // 16, 3), (n // 16 - 3, 2), (n // 64, 2)) if pruned else ((n - 1, 2), (n // 2, 3), (n, 49)):
+        x = rng.standard_normal((batch, n)).astype(np.float32)
+        got = _run_apply(gpu, x, d, m, "none", 1.0)
+        if batch > 3:                                   # the kernel for more than a few vectors, checked on the last
+            x, got = x[-2:], got[-2:]
+        want = oracle.apply(x, d[0], d[1], d[2], m, "none", 1.0)
+        assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL, (m, batch)
+
+
 @pytest.mark.parametrize("n,m,scale", [(64, 64, 8.0), (1024, 1024, 32.0), (1024, 100, 3.0), (4096, 4096, 64.0),
                                        (16384, 16384, 1.0)])
 def test_cos_sin_features(gpu, oracle, n, m, scale):
