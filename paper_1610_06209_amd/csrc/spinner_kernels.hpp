@@ -26,8 +26,7 @@ namespace spinner {
 // Fixed choices, each the best of a timing sweep on MI355X.
 constexpr int kWavesPerWorkgroup = 4;     // waves per workgroup when a tile fits one wave
 constexpr int kLaneChunk = 32;            // registers exchanged per batch in the lane stages that cross the LDS crossbar
-constexpr int kMaskPrefetch = 16;         // lane masks of the next step's sign flips fetched before the current step's exchange
-                                          // (each takes two scalar registers)
+constexpr int kMaskBatch = 16;            // lane masks of a step's sign flips that are fetched together (each takes two scalar registers)
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -740,26 +739,71 @@ __device__ __forceinline__ unsigned long long sign_mask(sign_words_t w, const Th
 template <int N>
 struct SignMasks { unsigned long long m[N > 0 ? N : 1]; };
 
+// Tiles of several waves: the masks of a wave start at one address and the rest of a register's place is a constant, so that the loads
+// of neighbouring registers become one of up to 64 bytes
+template <typename G, int LAY, bool DIRECT>
+__device__ __forceinline__ sign_words_t sign_mask_base(sign_words_t w, const ThreadCtx<G>& c, int ew)
+{
+    static_assert(G::WB > 0, "the wave's index bits and the registers' are apart from the lanes'");
+    if constexpr (DIRECT) return w + (c.wv << G::r);
+    else if constexpr (G::WIDE && LAY == 1) return w + (c.wide_off + (c.wv << G::r));
+    else return w + ((ew >> 8) << 2);
+}
+template <typename G, int LAY, bool DIRECT>
+constexpr int sign_mask_offset(int j)
+{
+    if (DIRECT || (G::WIDE && LAY == 1)) return j;
+    return ((G::reg_index(LAY, j) >> 8) << 2) | (G::reg_index(LAY, j) & 3);
+}
+
 template <typename G, int LAY, int N, bool DIRECT = false>
 __device__ __forceinline__ void fetch_sign_masks(SignMasks<N>& pm, const ThreadCtx<G>& c, const unsigned long long* words)
 {
-    sign_words_t w = (sign_words_t)words;
-    const int ew = wave_index_bits<G, LAY>(c);
-#pragma unroll
-    for (int j = 0; j < N; ++j) pm.m[j] = sign_mask<G, LAY, DIRECT>(w, c, ew, j);
+    const sign_words_t w = sign_mask_base<G, LAY, DIRECT>((sign_words_t)words, c, wave_index_bits<G, LAY>(c));
+    static_for<0, N>([&](auto j) { pm.m[j.value] = w[sign_mask_offset<G, LAY, DIRECT>(j.value)]; });
 }
 
 // NPF: the masks of registers 0 .. NPF-1 come from `pm` instead of from memory
-template <typename G, int LAY, int NPF = 0, bool DIRECT = false, typename T>
+// Masks are fetched sixteen at a time (32 scalar registers), the next sixteen behind the first flip of the present ones: scalar loads return in any
+// order, so whoever waits for one waits for all.  Left to the compiler, four masks were fetched, waited for and used, sixteen times over.
+// That way / this way, in us: n = 2^14, hash of 2048 vectors, L = 8, 373 / 331, codes of 8000 198 / 194, 3000 vectors, first 9999 95.7 / 83.3, first 999
+// 59.4 / 55.9; 2^13, hash of 4000 314 / 305, 3000 vectors, first 4001 52.3 / 44.2; 2^12, hash of 8192 324 / 304, of 100 9.8 / 8.7, 3000 vectors, first 3001
+// 27.9 / 24.3; 2^15, all rows 429 / 423; 2^13 and 2^14, all rows, alike.  Not taken: tiles of one wave (hash, 2^11, 138.5 / 140.1), fp64 values (features,
+// 2^11, 95.8 / 101) and all rows of 2^12, which is at the memory's rate (65536 vectors 345.7 / 347.0).
+// FOURS: left to the compiler
+template <typename G, int LAY, int NPF = 0, bool DIRECT = false, bool FOURS = false, typename T>
 __device__ __forceinline__ void sign_flip(T (&v)[G::R], const ThreadCtx<G>& c, const unsigned long long* words,
                                           const SignMasks<NPF>* pm = nullptr)
 {
-    sign_words_t w = (sign_words_t)words;
     const int ew = wave_index_bits<G, LAY>(c);
+    if constexpr (G::WB == 0 || FOURS || std::is_same<T, double>::value) {
+        static_assert(NPF == 0, "no masks ahead");
+        sign_words_t w = (sign_words_t)words;
 #pragma unroll
-    for (int j = 0; j < G::R; ++j) {
-        if (j < NPF) flip_by_mask(v[j], pm->m[j]);
-        else flip_by_mask(v[j], sign_mask<G, LAY, DIRECT>(w, c, ew, j));
+        for (int j = 0; j < G::R; ++j) flip_by_mask(v[j], sign_mask<G, LAY, DIRECT>(w, c, ew, j));
+    } else {
+        constexpr int B = G::R < kMaskBatch ? G::R : kMaskBatch;
+        static_assert(NPF == 0 || NPF == B, "one batch is fetched ahead");
+        const sign_words_t w = sign_mask_base<G, LAY, DIRECT>((sign_words_t)words, c, ew);
+        unsigned long long m[B];
+        static_for<0, B>([&](auto k) {
+            if constexpr (NPF > 0) m[k.value] = pm->m[k.value];
+            else m[k.value] = w[sign_mask_offset<G, LAY, DIRECT>(k.value)];
+        });
+        static_for<0, G::R / B>([&](auto b) {
+            flip_by_mask(v[b.value * B], m[0]);
+            unsigned long long next[B];
+            if constexpr (b.value + 1 < G::R / B) {
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, B>([&](auto k) { next[k.value] = w[sign_mask_offset<G, LAY, DIRECT>((b.value + 1) * B + k.value)]; });
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            static_for<1, B>([&](auto k) { flip_by_mask(v[b.value * B + k.value], m[k.value]); });
+            if constexpr (b.value + 1 < G::R / B) {
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, B>([&](auto k) { m[k.value] = next[k.value]; });
+            }
+        });
     }
 }
 
@@ -771,7 +815,7 @@ __device__ __forceinline__ void sign_flip(T (&v)[G::R], const ThreadCtx<G>& c, c
 // PF_NEXT, receives those of the next step (packed words at next_words) before this step's exchange.
 // BUT_LAST (tiles of several waves): the last register stage is left to the caller.
 template <typename G, int C, int CB, int LAY, bool HAS_DIAG, bool FIRST_TRANSPOSE, bool NEGATE, bool SIGNS, typename T, int NPF = 0,
-          bool PF_NEXT = false, bool BUT_LAST = false, int NPD = 0, bool PAIRED_NEXT = false>
+          bool PF_NEXT = false, bool BUT_LAST = false, int NPD = 0, bool PAIRED_NEXT = false, bool FOURS = false>
 __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c,
                                              const float* dtile, const unsigned long long* words, int sl, float4* lds,
                                              SignMasks<NPF>* pm = nullptr, const unsigned long long* next_words = nullptr,
@@ -781,7 +825,7 @@ __device__ __forceinline__ void spinner_step(T (&v)[G::R], const ThreadCtx<G>& c
     if constexpr (HAS_DIAG) {
         if constexpr (SIGNS) {
             if constexpr (NPF > 0 && !FIRST_TRANSPOSE) sign_flip<G, LAY, NPF, DIRECT>(v, c, words, pm);
-            else sign_flip<G, LAY, 0, DIRECT>(v, c, words);
+            else sign_flip<G, LAY, 0, DIRECT, FOURS>(v, c, words);
         }
         else if constexpr (NPD > 0 && !FIRST_TRANSPOSE) diag_multiply_ahead<G, LAY, NPD, false>(v, c, dtile, *da);
         else diag_multiply<G, C, LAY>(v, c, dtile, sl);
@@ -1028,8 +1072,9 @@ spinner_tile_kernel(TileParams p)
 
         // lane masks of the next step's sign flips travel in scalar registers across the exchange (see SignMasks)
         // (measured: 1.4 % at n = 2^14, nothing elsewhere; only tiles of several waves with 64 values per thread use it)
-        constexpr int NPF = (SIGNS && G::WB > 0 && R == 64) ? kMaskPrefetch : 0;
+        constexpr int NPF = (SIGNS && G::WB > 0 && R == 64) ? kMaskBatch : 0;
         SignMasks<NPF> pm;
+        constexpr bool FOURS = NSTEPS == 3 && !RAGGED && NT == 12;
         constexpr int NPD = (!SIGNS && NSTEPS == 3 && C >= NT && EPI == EPI_STORE_NONE && std::is_same<T, float>::value)
                                 ? diag_pieces_ahead(NT, PRUNE > 0, BEGUN > 0) : 0;
         DiagAhead<NPD> da;
@@ -1038,9 +1083,9 @@ spinner_tile_kernel(TileParams p)
         const unsigned long long* sw1 = p.sw[1];
         if constexpr (SIGNS && NSTEPS < 3) { sw0 += q << (NT - 6); sw1 += q << (NT - 6); }
         // steps (layout alternates only when a tile spans several waves)
-        spinner_step<G, C, (BEGUN ? BEGUN : CB), G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1), false, NPD, false>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1, &da, p.d[1]);
+        spinner_step<G, C, (BEGUN ? BEGUN : CB), G::layout_after(0), FIRST_DIAG, true, false, SIGNS, T, NPF, (NSTEPS > 1), false, NPD, false, FOURS>(v, c, p.d[0] + tile_first, sw0, p.sl, lds, &pm, sw1, &da, p.d[1]);
         if constexpr (NSTEPS > 1)
-            spinner_step<G, C, CB, G::layout_after(1), true, false, ODD, SIGNS, T, NPF, (NSTEPS > 2), false, NPD, (PRUNE > 0)>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2], &da, p.d[2]);
+            spinner_step<G, C, CB, G::layout_after(1), true, false, ODD, SIGNS, T, NPF, (NSTEPS > 2), false, NPD, (PRUNE > 0), FOURS>(v, c, p.d[1] + tile_first, sw1, p.sl, lds, &pm, p.sw[2], &da, p.d[2]);
         bool wave_live = true;
         // features of fp32 values (n = 2^15, 2^16): the angles in fp64, at 2^16 the last butterflies too (see feature_sincos)
         constexpr bool WIDE_ANGLE = EPI == EPI_STORE_COSSIN && std::is_same<T, float>::value && NSTEPS == 3;
@@ -1050,7 +1095,7 @@ spinner_tile_kernel(TileParams p)
             if constexpr (PRUNE > 0)
                 spinner_step_pruned<G, C, CB, G::layout_after(2), !ODD, SIGNS, PRUNE, NPF, NPD>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, wave_live, &pm, &da);
             else
-                spinner_step<G, C, CB, G::layout_after(2), true, false, !ODD, SIGNS, T, NPF, false, WIDE_LAST, NPD>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm, nullptr, &da);
+                spinner_step<G, C, CB, G::layout_after(2), true, false, !ODD, SIGNS, T, NPF, false, WIDE_LAST, NPD, false, FOURS>(v, c, p.d[2] + tile_first, p.sw[2], p.sl, lds, &pm, nullptr, &da);
         }
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs
