@@ -875,10 +875,23 @@ constexpr unsigned lane_positions(int lay)
     for (int b = 0; b < G::LB; ++b) m |= 1u << G::lane_pos(lay, b);
     return m;
 }
+// Where the sums leave four registers (index bits 0, 1) of a layout 0, what is left of the transform is bits of lanes and waves: it stays in
+// that layout, the waves' quads meet in LDS once and every wave forms its own.  The exchange of the other rounds would leave
+// all of it to one wave (n = 2^14: 256 butterfly operations on sixteen lanes while the others' registers lie idle).
+// That exchange / this tail, in us, sign words: n = 2^14, 32768 vectors, first 1000 511 / 500, 3000 vectors, first 333 54.7 / 50.0, 500 vectors 16.2 /
+// 15.1; 2^13, 65536 vectors, first 500 482 / 474, 1000 vectors 15.1 / 13.8; 2^12, 131072 vectors, first 256 452 / 448; 2^15, 4096, first 1000 148.5 / 145.6;
+// 2^16, 2048, first 3000 190.5 / 182.5; fp32 diagonals: 2^14, 8192, first 1000 158.3 / 156.0, 2^15, 4096 177 / 171, 2^16, 2048 226 / 217.
+// With 32 values and fewer and fp32 diagonals the exchange is as short: 2^13 143.9 / 144.7, 2^12 140.2 / 140.8 (not taken).
+template <typename G>
+constexpr bool short_tail(int lay, int P)
+{
+    return G::WB > 0 && (G::WIDE || G::R == 64) && G::LB == 6 && lay == 0 && live_regs<G>(0, prune_positions<G>(P) & reg_positions<G>(0)) == 4;
+}
 // registers live at the end of a pruned last step that started in layout LAY
 template <typename G>
 constexpr int pruned_final_regs(int lay, int P)
 {
+    if (short_tail<G>(lay, P)) return 4;
     const unsigned pm = prune_positions<G>(P);
     if (G::WB == 0) return live_regs<G>(lay, pm & reg_positions<G>(lay));
     return live_regs<G>(1 - lay, pm & (reg_positions<G>(lay) | reg_positions<G>(1 - lay)));
@@ -938,7 +951,29 @@ __device__ __forceinline__ void spinner_step_pruned(float (&v)[G::R], const Thre
             lane_stage<b.value, RL1, G::LANE_CHUNK>(v, c.sg[b.value]);
     });
     wave_live = true;
-    if constexpr (G::WB > 0) {
+    if constexpr (short_tail<G>(LAY, P)) {
+        if constexpr (G::WIDE) {
+            lane_stage<4, 4>(v, c.sg[4]);
+            lane_stage<5, 4>(v, c.sg[5]);
+        }
+        lds[c.wv * 64 + c.lit] = make_float4(v[0], v[1], v[2], v[3]);
+        __syncthreads();
+        wave_live = (wave_index_bits<G, LAY>(c) & (int)PM) == 0;
+        if (wave_live) {
+            float4 q[G::WAVES];
+#pragma unroll
+            for (int w = 0; w < G::WAVES; ++w) q[w] = lds[w * 64 + c.lit];
+#pragma unroll
+            for (int b = 0; b < G::WB; ++b) {
+                const float sgn = (c.wv >> b) & 1 ? -1.0f : 1.0f;
+#pragma unroll
+                for (int w = 0; w < (G::WAVES >> (b + 1)); ++w)
+                    q[w] = make_float4(__builtin_fmaf(sgn, q[2 * w + 1].x, q[2 * w].x), __builtin_fmaf(sgn, q[2 * w + 1].y, q[2 * w].y),
+                                       __builtin_fmaf(sgn, q[2 * w + 1].z, q[2 * w].z), __builtin_fmaf(sgn, q[2 * w + 1].w, q[2 * w].w));
+            }
+            v[0] = q[0].x; v[1] = q[0].y; v[2] = q[0].z; v[3] = q[0].w;
+        }
+    } else if constexpr (G::WB > 0) {
         constexpr int TO = 1 - LAY;
         constexpr unsigned POST = reg_positions<G>(TO) & ~REGS;     // bits that become register bits only now
         constexpr int RL2 = live_regs<G>(TO, DONE1);
@@ -1100,7 +1135,7 @@ spinner_tile_kernel(TileParams p)
         static_assert(PRUNE == 0 || (NSTEPS == 3 && std::is_same<T, float>::value), "pruning: fused fp32 kernels only");
         constexpr int RF = PRUNE > 0 ? pruned_final_regs<G>(G::layout_after(2), PRUNE) : R;   // registers that hold outputs
 
-        constexpr int LAYF = G::layout_after(NSTEPS);
+        constexpr int LAYF = PRUNE > 0 && short_tail<G>(G::layout_after(2), PRUNE) ? 0 : G::layout_after(NSTEPS);
         const int ebase = c.base_index(LAYF);
         if (active && wave_live) {
             const long long m = p.m;
