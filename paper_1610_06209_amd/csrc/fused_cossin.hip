@@ -43,6 +43,32 @@ __device__ __forceinline__ void feat_ar_a_to_b(double (&v)[G::R], float4* pa, fl
     wave_lds_fence();
 }
 
+// The same with one word per access, a lane's row 2^r + 1 words from the next, so that both sides touch different banks: low and high words lie in every
+// other register, and the 16 bytes of one kind above are put together by four moves, their pairs taken apart by two more (n = 4096: 384 moves per
+// vector).  The loads are written as atomic ones, which nothing joins into pairs.
+// 16 bytes / one word, in us: n = 4096, sign words, 131072 vectors 1223 / 1200, first 1000, 8000 vectors 65.4 / 62.5; fp32 diagonals, 131072 1388 /
+// 1336, L = 4, 32768 1333 / 1323, L = 3, first 2000, 8000 213 / 200; n = 1024, fp32 diagonals 298 / 293, L = 4 264 / 261, but sign words 277.7 / 282.9.
+__device__ __forceinline__ int lds_word(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); }
+template <typename G>
+__device__ __forceinline__ void feat_ar_a_to_b_words(double (&v)[G::R], float* w, int l)
+{
+    int* ia = reinterpret_cast<int*>(w) + l * (G::R + 1);
+    const int* ib = reinterpret_cast<const int*>(w) + l;
+    int lo[G::R];
+#pragma unroll
+    for (int j = 0; j < G::R; ++j) ia[j] = __double2loint(v[j]);
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < G::R; ++j) lo[j] = lds_word(ib + j * (G::R + 1));
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < G::R; ++j) ia[j] = __double2hiint(v[j]);
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < G::R; ++j) v[j] = __hiloint2double(lds_word(ib + j * (G::R + 1)), lo[j]);
+    wave_lds_fence();
+}
+
 template <typename G>
 __device__ __forceinline__ void feat_ar_b_to_a(double (&v)[G::R], float4* pa, float* pb)
 {
@@ -141,6 +167,7 @@ spinner_feature_ar_kernel(TileParams p, int L)
     static_assert(!BLOCKS || (!SIGNS && G::WAVES == 1), "stacked blocks: fp32 diagonals, one wave per workgroup");
     static_assert(G::LB == G::r, "no lane bit is shared by the two layouts");
     constexpr int R = G::R, r = G::r, n = 1 << G::NT;
+    constexpr bool WORDS = r >= 6 || !SIGNS;        // see feat_ar_a_to_b_words
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int g = lane >> G::LB, l = lane & (G::LANES - 1);
@@ -192,7 +219,7 @@ spinner_feature_ar_kernel(TileParams p, int L)
         if constexpr (SIGNS) feat_ar_flip<G>(v, hw);
         else da.multiply(v, put, pa);
         ar_stages<G>(v);
-        feat_ar_a_to_b<G>(v, pa, pb);
+        if constexpr (WORDS) feat_ar_a_to_b_words<G>(v, w, l); else feat_ar_a_to_b<G>(v, pa, pb);
         if constexpr (!SIGNS) db.load(p.d[1], ebase);
         ar_stages<G>(v);
         if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 3 * R);
@@ -204,7 +231,7 @@ spinner_feature_ar_kernel(TileParams p, int L)
         if constexpr (SIGNS) feat_ar_flip<G>(v, hw + 4 * R);
         else da.multiply(v, put, pa);
         ar_stages<G>(v);
-        feat_ar_a_to_b<G>(v, pa, pb);
+        if constexpr (WORDS) feat_ar_a_to_b_words<G>(v, w, l); else feat_ar_a_to_b<G>(v, pa, pb);
         ar_stages<G>(v);
 
         float* dst = p.out + (active ? vec : 0) * p.out_stride + ebase;

@@ -30,12 +30,14 @@ constexpr long long few_wide_vectors(int log2n, bool plain)
 struct NotWide { static constexpr int wide = 0, start = 0, chunk = kLaneChunk; };
 template <typename T, int NT> struct Tuning : NotWide { static constexpr int rmax = std::is_same<T, double>::value ? clamp_rmax(NT, 5) : 6, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<double, 12> : NotWide { static constexpr int rmax = 4, waves = 4, min_waves = 0, trips = 0; };
-// held to 128 registers (they take 133 .. 147 otherwise; 2^14 spills 60 bytes per thread): four and two tiles per compute unit
-// instead of three and one, for batches that need them (fused_cossin.hip).
-// Measured on 2^27 elements, sign words / fp32 diagonals, in us: 2^13 428 -> 405 / 461 -> 439, 2^14 581 -> 472 / 619 -> 504
-// (no gain for 2^7 .. 2^11, where the same limit spills more than it helps)
-template <> struct Tuning<double, 13> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
-template <> struct Tuning<double, 14> : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0; };
+// held to 128 registers (they take 140 .. 148 otherwise): four and two tiles per compute unit instead of three and one, for batches
+// that need them (fused_cossin.hip).  Lane stages in batches of eight registers, whose exchanged copies are what else would spill (52 .. 60
+// bytes per thread; now none at 2^13, 8 .. 12 at 2^14).
+// 2^27 elements, sign words / fp32 diagonals, in us: without the limit 2^13 428 / 461, 2^14 581 / 619, with it 405 / 439, 472 / 504; then in another
+// run, low and high words exchanged apart 373 / 406, 433 / 465, pairs of values and batches of 32 361 / 416, 428 / 457, of 16 356 / 389, 405 / 435, of
+// 8 355 / 375, 389 / 425, of 4 355 / 389, 394 / 423.  (No gain from the limit for 2^7 .. 2^11, where it spills more than it helps.)
+template <> struct Tuning<double, 13> { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0, wide = 0, start = 0, chunk = 8; };
+template <> struct Tuning<double, 14> { static constexpr int rmax = 5, waves = 4, min_waves = 4, trips = 0, wide = 0, start = 0, chunk = 8; };
 template <> struct Tuning<float, 4> : NotWide { static constexpr int rmax = 2, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<float, 5> : NotWide { static constexpr int rmax = 2, waves = 4, min_waves = 0, trips = 0; };
 template <> struct Tuning<float, 6> : NotWide { static constexpr int rmax = 3, waves = 4, min_waves = 0, trips = 0; };

@@ -574,44 +574,31 @@ __device__ __forceinline__ void transpose(float (&v)[G::R], const ThreadCtx<G>& 
     }
 }
 
-// fp64 values cross in two trips (low words, then high words) so that the LDS
-// footprint stays 4 bytes per element.
+// fp64 values cross in two trips so that the LDS footprint stays 4 bytes per element: trip h moves registers 4k+2h, 4k+2h+1 of every thread, the
+// elements with a given value of index bit 1, as 16 bytes per lane.  Two values are four consecutive registers as they lie; low and high
+// words by themselves would have to be moved together on one side and apart on the other.
 template <typename G, int FROM, bool SYNC_BEFORE, bool SW = false>
 __device__ __forceinline__ void transpose(double (&v)[G::R], const ThreadCtx<G>& c, float4* lds)
 {
     constexpr int TO = 1 - FROM;
-    int4* ilds = reinterpret_cast<int4*>(lds);
+    double2* pairs = reinterpret_cast<double2*>(lds);
     const int ef = SW ? c.base_index_sw(FROM) : c.base_index(FROM);
     const int et = c.base_index(TO);
-    int lo[G::R];
     if constexpr (SYNC_BEFORE) __syncthreads();
 #pragma unroll
-    for (int jh = 0; jh < G::R / 4; ++jh) {
-        const int e = ef | (SW ? G::reg_index_sw(FROM, jh * 4) : G::reg_index(FROM, jh * 4));
-        ilds[e >> 2] = make_int4(__double2loint(v[jh * 4]), __double2loint(v[jh * 4 + 1]),
-                                 __double2loint(v[jh * 4 + 2]), __double2loint(v[jh * 4 + 3]));
-    }
-    __syncthreads();
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1) __syncthreads();
 #pragma unroll
-    for (int jh = 0; jh < G::R / 4; ++jh) {
-        const int4 t = ilds[(et | G::reg_index(TO, jh * 4)) >> 2];
-        lo[jh * 4] = t.x; lo[jh * 4 + 1] = t.y; lo[jh * 4 + 2] = t.z; lo[jh * 4 + 3] = t.w;
-    }
-    __syncthreads();
+        for (int jh = 0; jh < G::R / 4; ++jh) {
+            const int e = ef | (SW ? G::reg_index_sw(FROM, jh * 4) : G::reg_index(FROM, jh * 4));
+            pairs[e >> 2] = make_double2(v[jh * 4 + 2 * h], v[jh * 4 + 2 * h + 1]);
+        }
+        __syncthreads();
 #pragma unroll
-    for (int jh = 0; jh < G::R / 4; ++jh) {
-        const int e = ef | (SW ? G::reg_index_sw(FROM, jh * 4) : G::reg_index(FROM, jh * 4));
-        ilds[e >> 2] = make_int4(__double2hiint(v[jh * 4]), __double2hiint(v[jh * 4 + 1]),
-                                 __double2hiint(v[jh * 4 + 2]), __double2hiint(v[jh * 4 + 3]));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int jh = 0; jh < G::R / 4; ++jh) {
-        const int4 t = ilds[(et | G::reg_index(TO, jh * 4)) >> 2];
-        v[jh * 4] = __hiloint2double(t.x, lo[jh * 4]);
-        v[jh * 4 + 1] = __hiloint2double(t.y, lo[jh * 4 + 1]);
-        v[jh * 4 + 2] = __hiloint2double(t.z, lo[jh * 4 + 2]);
-        v[jh * 4 + 3] = __hiloint2double(t.w, lo[jh * 4 + 3]);
+        for (int jh = 0; jh < G::R / 4; ++jh) {
+            const double2 t = pairs[(et | G::reg_index(TO, jh * 4)) >> 2];
+            v[jh * 4 + 2 * h] = t.x; v[jh * 4 + 2 * h + 1] = t.y;
+        }
     }
 }
 
