@@ -201,12 +201,21 @@ spinner_feature_ar_kernel(TileParams p, int L)
         const float* src = p.x + (active ? vec : 0) * p.in_stride;
         const unsigned at = 4 * l;
         float* put = w + ar_word_of<G>(at);             // a lane's pieces lie 4 LANES floats apart, four rows of the buffer
-        float4 t[R / 4];
+        if constexpr (SIGNS) {          // each piece as it arrives (n = 1024, 30000 vectors 68.7 -> 67.4 us, n = 4096 alike)
+            src += at;
 #pragma unroll
-        for (int k = 0; k < R / 4; ++k) t[k] = load4<!BLOCKS>(src + 4 * k * G::LANES + at);      // a vector past the end reads the first one
-        if constexpr (!SIGNS) da.load(p.d[0], at);
+            for (int k = 0; k < R / 4; ++k) {
+                const float4 t = load4<true>(src + 4 * k * G::LANES);      // a vector past the end reads the first one
+                *reinterpret_cast<float4*>(w + ar_word_of<G>(4 * (k * G::LANES + l))) = t;
+            }
+        } else {
+            float4 t[R / 4];
 #pragma unroll
-        for (int k = 0; k < R / 4; ++k) *reinterpret_cast<float4*>(put + 4 * k * G::STRIDE) = t[k];
+            for (int k = 0; k < R / 4; ++k) t[k] = load4<!BLOCKS>(src + 4 * k * G::LANES + at);
+            da.load(p.d[0], at);
+#pragma unroll
+            for (int k = 0; k < R / 4; ++k) *reinterpret_cast<float4*>(put + 4 * k * G::STRIDE) = t[k];
+        }
         wave_lds_fence();
 #pragma unroll
         for (int k = 0; k < R / 4; ++k) {
