@@ -171,6 +171,13 @@ struct Apart {
     static constexpr bool middle = CLOSE || (PADDED ? n <= 10 : n != 11 && n != 14), last = !PADDED;        // backward
 };
 
+// The second diagonal asked for two phases ahead of its use, the spectrum in two halves ahead of the low stages and ahead of the first products: where
+// the registers of two waves per SIMD have room for it.  As they are needed / ahead, in us: 2^13 Toeplitz, 4096 vectors 120.3 / 112.6, circulant 83.1 /
+// 75.8, skew-circulant, 30 vectors 25.0 / 23.0; 2^14 circulant, 2048 vectors 101.9 / 98.3, but Toeplitz 150.3 / 160.4.  Below, with
+// four waves per SIMD: 2^12 Toeplitz, 16383 vectors 226.6 / 230.5, 2^11, 16384 86.9 / 103.8, 2^10, 32768 81.0 / 92.3, circulants 155.5 / 156.9, 58.1 / 58.0, 55.1 / 55.5.
+template <typename G, bool PADDED>
+constexpr bool asks_ahead = G::LOGN_ == 13 || (G::LOGN_ == 14 && !PADDED);
+
 template <int B, int R>
 __device__ __forceinline__ void hadamard_regs(C (&v)[R])
 {
@@ -341,6 +348,10 @@ __device__ __forceinline__ void convolve(C (&v)[G::R], C* X, const float2* __res
 {
     constexpr int B0 = G::bits(0), B1 = G::bits(1), B2 = G::bits(2);
     using A = Apart<G, PADDED, CLOSE>;
+    // a thread's points of the low phase are runs of 2^B2 consecutive ones: 16-byte loads of two spectrum points
+    constexpr int HALF = G::R / 4;
+    constexpr bool AHEAD = asks_ahead<G, PADDED>;
+    float4 first[HALF], second[HALF];
     {
         ForwardTwiddles<G, 1, SKEW, PADDED> f1;
         ForwardTwiddles<G, 2, SKEW, PADDED> f2;
@@ -350,13 +361,24 @@ __device__ __forceinline__ void convolve(C (&v)[G::R], C* X, const float2* __res
         f2.load(tw, log2p, t);
         forward_group<(A::forward ? 0 : B1), G, 1, SKEW, PADDED>(v, f1);
         exchange<G, 1, 2>(v, X, t);
+        if constexpr (AHEAD) {
+            const float2* s = spec + G::base_index(2, t);
+            static_for<0, HALF>([&](auto k) { first[k.value] = *reinterpret_cast<const float4*>(s + G::reg_index(2, 2 * k.value)); });
+            __builtin_amdgcn_sched_barrier(0);
+        }
         forward_group<(A::low ? B2 - 1 : B2), G, 2, SKEW, PADDED>(v, f2);
     }
     {
-        // a thread's points of the low phase are runs of 2^B2 consecutive ones: 16-byte loads of two spectrum points
         const float2* s = spec + G::base_index(2, t);
+        if constexpr (AHEAD) {
+            static_for<0, HALF>([&](auto k) { second[k.value] = *reinterpret_cast<const float4*>(s + G::reg_index(2, 2 * (HALF + k.value))); });
+            __builtin_amdgcn_sched_barrier(0);
+        }
         static_for<0, G::R / 2>([&](auto k2) {
-            const float4 f = *reinterpret_cast<const float4*>(s + G::reg_index(2, 2 * k2.value));
+            float4 f;
+            if constexpr (!AHEAD) f = *reinterpret_cast<const float4*>(s + G::reg_index(2, 2 * k2.value));
+            else if constexpr (k2.value < HALF) f = first[k2.value];
+            else f = second[k2.value - HALF];
             v[2 * k2.value] = mul(v[2 * k2.value], C{f.x, f.y});
             v[2 * k2.value + 1] = mul(v[2 * k2.value + 1], C{f.z, f.w});
             if constexpr ((k2.value & 3) == 3) __builtin_amdgcn_sched_barrier(0);
@@ -407,15 +429,24 @@ struct_fft_kernel(StructFftParams p)
     }
     fft::hadamard_regs<G::bits(1)>(v);
     fft::exchange<G, 1, 2>(v, X, t);
-    fft::hadamard_regs<G::bits(2)>(v);
-    fft::exchange<G, 2, 0>(v, X, t);
-    fft::hadamard_regs<G::bits(0)>(v);
+    constexpr bool AHEAD = fft::asks_ahead<G, HALVES>;
+    if constexpr (!AHEAD) {
+        fft::hadamard_regs<G::bits(2)>(v);
+        fft::exchange<G, 2, 0>(v, X, t);
+        fft::hadamard_regs<G::bits(0)>(v);
+    }
     {
         const int e = G::base_index(0, t);
         const float* __restrict__ d2 = p.reverse ? p.d2 + (N - 1 - e) : p.d2 + e;
         float d[R];
         if (p.reverse) static_for<0, R>([&](auto k) { d[k.value] = d2[-G::reg_index(0, k.value)]; });
         else static_for<0, R>([&](auto k) { d[k.value] = d2[G::reg_index(0, k.value)]; });
+        if constexpr (AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            fft::hadamard_regs<G::bits(2)>(v);
+            fft::exchange<G, 2, 0>(v, X, t);
+            fft::hadamard_regs<G::bits(0)>(v);
+        }
         static_for<0, R>([&](auto k) { v[k.value].x *= d[k.value]; v[k.value].y *= d[k.value]; });
     }
     if constexpr (HALVES) {
