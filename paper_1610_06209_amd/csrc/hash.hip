@@ -16,12 +16,39 @@ __device__ __forceinline__ void hash_ar_shared_lane_stages(float (&v)[G::R], int
 {
     static_for<G::r, G::LB>([&](auto b) { lane_stage<b.value>(v, ((l >> b.value) & 1) ? -1.0f : 1.0f); });
 }
+// n = 1024: the masks of a flip come sixteen at a time (see sign_flip), the first sixteen asked for a phase ahead: L = 16, batch 65536 733 -> 703 us,
+// 2000 vectors 31.9 -> 30.7, 300 vectors, L = 5, 6.1 -> 5.7.  Not the first diagonal's (batch 30000, L = 3, 68.0 -> 66.4, but 703 -> 730 above) and not
+// n = 256, whose sixteen would all come ahead (batch 65536 148.3 -> 149.4).
+template <typename G> constexpr bool hash_ar_ahead = G::R == 2 * kMaskBatch;
+using HashMasks = SignMasks<kMaskBatch>;
 template <typename G>
-__device__ __forceinline__ void hash_ar_flip(float (&v)[G::R], const unsigned long long* words)
+__device__ __forceinline__ void hash_ar_fetch(HashMasks& m, const unsigned long long* words)
 {
-    sign_words_t w = (sign_words_t)words;
+    if constexpr (hash_ar_ahead<G>) {
+        sign_words_t w = (sign_words_t)words;
 #pragma unroll
-    for (int j = 0; j < G::R; ++j) flip_by_mask(v[j], w[j]);
+        for (int j = 0; j < kMaskBatch; ++j) m.m[j] = w[j];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+template <typename G>
+__device__ __forceinline__ void hash_ar_flip(float (&v)[G::R], const HashMasks& m, const unsigned long long* words)
+{
+    if constexpr (hash_ar_ahead<G>) {
+        HashMasks next;
+        flip_by_mask(v[0], m.m[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        hash_ar_fetch<G>(next, words + kMaskBatch);
+#pragma unroll
+        for (int j = 1; j < kMaskBatch; ++j) flip_by_mask(v[j], m.m[j]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kMaskBatch; ++j) flip_by_mask(v[kMaskBatch + j], next.m[j]);
+    } else {
+        sign_words_t w = (sign_words_t)words;
+#pragma unroll
+        for (int j = 0; j < G::R; ++j) flip_by_mask(v[j], w[j]);
+    }
 }
 // v = D x for a diagonal given as lane masks (reads the resident copy, writes the working registers)
 template <typename G>
@@ -204,17 +231,20 @@ __global__ void __launch_bounds__(G::THREADS) spinner_hash_ar_kernel(HashParams 
     for (int t = first; t < last; ++t) {
         const unsigned long long* hw = p.signs + (long long)t * p.triple_words + 3 * W;   // [3][2][R]: diagonal, layout
         float v[R];
+        HashMasks masks;
         hash_ar_flip_from<G>(v, x0, hw);            // D1 in layout A
         hash_ar_stages<G>(v);
         hash_ar_a_to_b<G>(v, pa, pb);
+        hash_ar_fetch<G>(masks, hw + 3 * R);
         hash_ar_stages<G>(v);
         hash_ar_shared_lane_stages<G>(v, l);
-        hash_ar_flip<G>(v, hw + 3 * R);             // D2 in layout B
+        hash_ar_flip<G>(v, masks, hw + 3 * R);      // D2 in layout B
         hash_ar_stages<G>(v);
         hash_ar_b_to_a<G>(v, pa, pb);
+        hash_ar_fetch<G>(masks, hw + 4 * R);
         hash_ar_stages<G>(v);
         hash_ar_shared_lane_stages<G>(v, l);
-        hash_ar_flip<G>(v, hw + 4 * R);             // D3 in layout A
+        hash_ar_flip<G>(v, masks, hw + 4 * R);      // D3 in layout A
         hash_ar_stages<G>(v);
         hash_ar_a_to_b<G>(v, pa, pb);
         hash_ar_stages<G>(v);
