@@ -84,8 +84,10 @@ hipError_t launch_pack_codes(const float* y, long long y_stride, unsigned long l
 // that a lane reads at once are the operands of four instructions at one logic instruction a dword.  With the rows' bits in planes
 // 0 to 2 counted apart (w),
 //     popcount(a xor b) = w(a) + w(b) + m / 8 - S / 2,      S = sum of the four products,
-// where all is whole numbers below 2^24 up to m = 2^22; longer codes (WIDE) take plane 3 as 0 or 2 as well, and then S is a
-// multiple of 4.  Which bit lands in which of the 64 k-slots does not matter, as long as both operands are laid out the same way.
+// where all is whole numbers below 2^24 up to m = 2^22; longer codes (WIDE) take plane 3 as 0 or 2 as well, and then
+// popcount = w(a) + w(b) - S / 2 with S four times the common bits: w(a) - S / 2 lies between -w(a) and w(a), so that it and the distance
+// are whole numbers up to m, exact in fp32 to m = 2^24 (w(a) + w(b) by itself is not, from 2^23 on).  Which bit lands in which
+// of the 64 k-slots does not matter, as long as both operands are laid out the same way.
 // A workgroup of four waves owns 128 x 128 pairs (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 8, which
 // loads write to LDS directly, one chunk ahead into the other of two buffers: a barrier a chunk.  The 16-byte pieces of a row lie
 // exchanged by its number, so that the sixteen lanes of a phase cover all banks once.  Lane group g = lane / 32 takes the pieces
@@ -230,7 +232,7 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
                 const int r = t * 32 + 8 * (v >> 2) + (v & 3);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const float dh = __builtin_fmaf(acc[t][u][v], -0.5f, wa[r] + wb[u * 32]);      // exact
+                    const float dh = __builtin_fmaf(acc[t][u][v], -0.5f, wa[r]) + wb[u * 32];      // both steps exact, in this order
                     const float k = __builtin_fmaf(-dh, inv_m, 1.0f);
                     if (decltype(whole)::value || (r < left && u * 32 < cols)) {
                         if constexpr (LINES) __builtin_nontemporal_store(k, dst + r * nb + u * 32);

@@ -165,11 +165,19 @@ def test_angular_gram_is_exact_on_its_codes(gpu, oracle, na, nb, m):
     assert np.all(np.diag(got[: min(na, nb), : min(na, nb)]) == 1.0)
 
 
+def _first_bits(k, m):
+    words = np.zeros(m // 64, dtype=np.uint64)
+    words[: k // 64] = 2**64 - 1
+    if k % 64:
+        words[k // 64] = 2 ** (k % 64) - 1
+    return words.view(np.int64)
+
+
 @pytest.mark.parametrize("na,nb,m", [(1, 1, 256), (128, 128, 768), (1100, 643, 1280), (130, 2050, 256), (2500, 3, 1024),
                                      (300, 160, 512)])
 def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
     # 128 x 128 tiles in bands of four tile rows (a shorter last band), dealt to the XCDs in runs; code words in chunks of
-    # sixteen (a shorter last chunk): every entry, from the Hamming distance counted in numpy
+    # eight (a shorter last chunk): every entry, from the Hamming distance counted in numpy
     rng = np.random.default_rng(na * 7 + nb + m)
     ca = rng.integers(-2**63, 2**63 - 1, (na, m // 64), dtype=np.int64)
     cb = rng.integers(-2**63, 2**63 - 1, (nb, m // 64), dtype=np.int64)
@@ -188,15 +196,25 @@ def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
 def test_angular_gram_over_code_lengths(gpu, m):
     # chunks of eight words, two buffers in turn: half a chunk, one, one and a half, two ..; up to 2^22 bits three planes of a nibble
     # are 0 / 1 numbers and one +-1, beyond that all are 0 / 1.  Distances are whole numbers in both: one rounding of the quotient and
-    # one of the difference remain.  All bits set against all set, none and half of them are the largest sums.
+    # one of the difference remain, and only the latter where m is a power of two.  All bits set against all set, none and half of them
+    # are the largest sums.  Pairs one bit apart: weights add up to odd numbers, beyond 2^24 where m is.
     rng = np.random.default_rng(m)
-    ca = rng.integers(-2**63, 2**63 - 1, (5, m // 64), dtype=np.int64)
-    cb = rng.integers(-2**63, 2**63 - 1, (7, m // 64), dtype=np.int64)
+    ca = rng.integers(-2**63, 2**63 - 1, (8, m // 64), dtype=np.int64)
+    cb = rng.integers(-2**63, 2**63 - 1, (9, m // 64), dtype=np.int64)
     ca[0], ca[1], ca[2] = -1, 0, 0x7777777777777777
     cb[0], cb[1], cb[2], cb[3] = -1, 0, 0x7777777777777777, 0x0F0F0F0F0F0F0F0F
+    ca[3], cb[4] = -1, -1
+    ca[3, -1] = -2                                               # all but one
+    ca[4], ca[5] = _first_bits(m // 2, m), _first_bits(m // 2 + 1, m)
+    cb[5], cb[6] = ca[4], _first_bits(m // 2 + 2, m)
+    cb[7] = ca[6]
+    cb[7, 0] ^= 1 << 40
     got = gpu.b.spinner_angular_gram(_to(gpu, ca), _to(gpu, cb), m).cpu().numpy()
-    dh = np.array([[int(np.unpackbits((a ^ b).view(np.uint8)).sum()) for b in cb] for a in ca])
+    dh = np.array([[int(np.bitwise_count((a ^ b).view(np.uint64)).sum(dtype=np.int64)) for b in cb] for a in ca])
+    assert [dh[3, 4], dh[4, 5], dh[5, 5], dh[5, 6], dh[6, 7]] == [1, 0, 1, 1, 1]
     assert np.abs(got.astype(np.float64) - (1.0 - dh / m)).max() <= 2.0 ** -23
+    if m & (m - 1) == 0:
+        assert np.array_equal(got, (1.0 - dh / m).astype(np.float32))
 
 
 def test_angular_gram_of_the_most_tiles(gpu):
