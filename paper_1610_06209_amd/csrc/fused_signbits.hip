@@ -84,10 +84,13 @@ hipError_t launch_pack_codes(const float* y, long long y_stride, unsigned long l
 // that a lane reads at once are the operands of four instructions at one logic instruction a dword.  With the rows' bits in planes
 // 0 to 2 counted apart (w),
 //     popcount(a xor b) = w(a) + w(b) + m / 8 - S / 2,      S = sum of the four products,
-// where all is whole numbers below 2^24 up to m = 2^22; longer codes (WIDE) take plane 3 as 0 or 2 as well, and then
+// where all is whole numbers below 2^24 up to m = 2^22 (kGramMixed); longer codes (kGramCounted) take plane 3 as 0 or 2 as well, and then
 // popcount = w(a) + w(b) - S / 2 with S four times the common bits: w(a) - S / 2 lies between -w(a) and w(a), so that it and the distance
-// are whole numbers up to m, exact in fp32 to m = 2^24 (w(a) + w(b) by itself is not, from 2^23 on).  Which bit lands in which
-// of the 64 k-slots does not matter, as long as both operands are laid out the same way.
+// are whole numbers up to m, exact in fp32 to m = 2^24 (w(a) + w(b) by itself is not, from 2^23 on).  Codes beyond that (kGramSigned) take
+// every bit as +1 or -1: popcount = (m - S) / 2, where S stays small for unrelated codes and a sum of whole 64s for equal and opposite
+// ones, so that these remain exact; a dword of bits is then spread over four operand dwords at seven instructions (counted / signed,
+// in ms: 1024 x 2048 codes of 2^25 bits 71.2 / 72.1, 5 x 70 of 2^26 111 / 115).
+// Which bit lands in which of the 64 k-slots does not matter, as long as both operands are laid out the same way.
 // A workgroup of four waves owns 128 x 128 pairs (each wave 64 x 64 = 2 x 2 tiles) and walks the code words in chunks of 8, which
 // loads write to LDS directly, one chunk ahead into the other of two buffers: a barrier a chunk.  The 16-byte pieces of a row lie
 // exchanged by its number, so that the sixteen lanes of a phase cover all banks once.  Lane group g = lane / 32 takes the pieces
@@ -107,17 +110,19 @@ constexpr int kGramRows = 128, kGramCols = 128, kGramChunk = 8;       // chunk: 
 constexpr int kGramPieces = kGramChunk / 2;                           // 16-byte pieces of a row's chunk
 constexpr unsigned kGramBand = 4;                                     // tile rows per band (see the kernel)
 constexpr unsigned kGramSpareLds = 14 << 10;                          // asked for and not used: three workgroups per compute unit, not four
-constexpr int kGramWide = 1 << 22;                                    // codes longer than this: see above
+enum { kGramMixed, kGramCounted, kGramSigned };                       // forms of the operands, see above
+constexpr int kGramMixedBits = 1 << 22, kGramCountedBits = 1 << 24;   // longest codes of the first two
 
-// plane P of 128 code bits as 32 fp4 numbers
-template <int P, bool WIDE>
-__device__ __forceinline__ intx8 code_plane(uintx4 w, unsigned sign, unsigned one)
+// operand P of four from 128 code bits, 32 fp4 numbers: plane P of them, signed codes dword P
+template <int P, int FORM>
+__device__ __forceinline__ intx8 code_operand(uintx4 w, unsigned sign, unsigned one)
 {
     intx8 f = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        if constexpr (P < 3) f[k] = (int)(w[k] & (0x11111111u << P));
-        else if constexpr (WIDE) f[k] = (int)((w[k] >> 1) & 0x44444444u);
+        if constexpr (FORM == kGramSigned) f[k] = (int)__builtin_amdgcn_bitop3_b32(w[P] << (3 - k), sign, one, 0xEA);
+        else if constexpr (P < 3) f[k] = (int)(w[k] & (0x11111111u << P));
+        else if constexpr (FORM == kGramCounted) f[k] = (int)((w[k] >> 1) & 0x44444444u);
         else f[k] = (int)__builtin_amdgcn_bitop3_b32(w[k], sign, one, 0xEA);      // (w & sign) | one
     }
     return f;
@@ -126,7 +131,7 @@ __device__ __forceinline__ intx8 code_plane(uintx4 w, unsigned sign, unsigned on
 // LINES: rows of `out` are whole 128-byte lines (nb a multiple of 32) and bypass cache retention (4096 x 4096, m = 1024 18.2 ->
 // 16.4 us; 16384 x 16384, m = 4096 625 -> 607); the pieces of other rows' lines have to meet in the L2 (16384 x 10007, m = 256:
 // 152 us, with the hint 338)
-template <bool LINES, bool WIDE>
+template <bool LINES, int FORM>
 __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __restrict__ a, long long na, const uintx4* __restrict__ b,
                                                            long long nb, int words, float inv_m, unsigned gx, unsigned gy, float* __restrict__ out)
 {
@@ -195,14 +200,15 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
             const uintx4 w0 = hw[s ^ swap], w1 = hw[(s + 1) ^ swap];
             static_for<0, 4>([&](auto plane) {
                 constexpr int P = plane.value;
-                constexpr int scale = (int)(0x01010101u * (P < 2 ? 0x7fu + 2 - P : 0x7fu));      // exponents (E8M0)
+                constexpr int scale = (int)(0x01010101u * (FORM != kGramSigned && P < 2 ? 0x7fu + 2 - P : 0x7fu));      // exponents (E8M0)
                 intx8 fa[2], fb[2];
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    fa[t] = code_plane<P, WIDE>(qa[t], sign, one);
-                    fb[t] = code_plane<P, WIDE>(qb[t], sign, one);
+                    fa[t] = code_operand<P, FORM>(qa[t], sign, one);
+                    fb[t] = code_operand<P, FORM>(qb[t], sign, one);
                 }
-                weight += __popc(w0[P] & (WIDE ? ~0u : 0x77777777u)) + __popc(w1[P] & (WIDE ? ~0u : 0x77777777u));
+                constexpr unsigned counted = FORM == kGramMixed ? 0x77777777u : ~0u;
+                if constexpr (FORM != kGramSigned) weight += __popc(w0[P] & counted) + __popc(w1[P] & counted);
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -216,7 +222,7 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
         chunk(p0, even, odd);
         if (p0 + kGramPieces < pieces) chunk(p0 + kGramPieces, odd, even);
     }
-    weights[threadIdx.x] = (float)(weight + (!WIDE && threadIdx.x < kGramRows ? words * 8 : 0));
+    weights[threadIdx.x] = (float)(weight + (FORM == kGramMixed && threadIdx.x < kGramRows ? words * 8 : 0));
     __syncthreads();
     // result register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its 32 x 32 tile
     const long long i = i0 + wr * 64 + 4 * g, j = j0 + wc * 64 + l32;
@@ -232,7 +238,8 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
                 const int r = t * 32 + 8 * (v >> 2) + (v & 3);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const float dh = __builtin_fmaf(acc[t][u][v], -0.5f, wa[r]) + wb[u * 32];      // both steps exact, in this order
+                    const float dh = FORM == kGramSigned ? (float)((64u * words - (unsigned)(int)acc[t][u][v]) >> 1)
+                                                         : __builtin_fmaf(acc[t][u][v], -0.5f, wa[r]) + wb[u * 32];      // both steps exact, in this order
                     const float k = __builtin_fmaf(-dh, inv_m, 1.0f);
                     if (decltype(whole)::value || (r < left && u * 32 < cols)) {
                         if constexpr (LINES) __builtin_nontemporal_store(k, dst + r * nb + u * 32);
@@ -253,8 +260,9 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
     // one workgroup of 256 threads per tile, and a grid holds fewer than 2^32 threads; the caller keeps gy below 2^16
     if (gx > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;
     const bool lines = (nb & 31) == 0;
-    const auto kernel = m > kGramWide ? (lines ? hamming_gram_kernel<true, true> : hamming_gram_kernel<false, true>)
-                                      : (lines ? hamming_gram_kernel<true, false> : hamming_gram_kernel<false, false>);
+    const auto kernel = m > kGramCountedBits ? (lines ? hamming_gram_kernel<true, kGramSigned> : hamming_gram_kernel<false, kGramSigned>)
+                        : m > kGramMixedBits ? (lines ? hamming_gram_kernel<true, kGramCounted> : hamming_gram_kernel<false, kGramCounted>)
+                                             : (lines ? hamming_gram_kernel<true, kGramMixed> : hamming_gram_kernel<false, kGramMixed>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(256), kGramSpareLds, s, reinterpret_cast<const uintx4*>(a), na,
                        reinterpret_cast<const uintx4*>(b), nb, m / 64, 1.0f / (float)m, (unsigned)gx, (unsigned)gy, out);
     return hipGetLastError();

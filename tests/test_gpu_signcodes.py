@@ -217,6 +217,29 @@ def test_angular_gram_over_code_lengths(gpu, m):
         assert np.array_equal(got, (1.0 - dh / m).astype(np.float32))
 
 
+@pytest.mark.parametrize("m", [2**24 + 256, 2**25])
+def test_angular_gram_of_codes_beyond_2p24_bits(gpu, m):
+    # sums of bits no longer fit 24 bits, the inner product of the bits as +-1 numbers does for codes that are equal, opposite or
+    # unrelated: it is exact for these and for pairs one bit apart (an even number up to 2^25).  Then the distance is rounded to 24 bits
+    # (half of its last place, 2, is 1 bit), which a power of two as m keeps to the final rounding of 2^-25; otherwise the bound of shorter codes
+    # holds with that rounding on top: 2^-23 + 2^-24.
+    rng = np.random.default_rng(m)
+    ca = rng.integers(-2**63, 2**63 - 1, (4, m // 64), dtype=np.int64)
+    cb = rng.integers(-2**63, 2**63 - 1, (5, m // 64), dtype=np.int64)
+    ca[0], cb[0] = -1, -1
+    cb[0, 5] = -1 - 2**17
+    cb[1], cb[2], cb[3] = ca[1], ~ca[2], ca[3]
+    cb[3, -1] ^= 1
+    got = gpu.b.spinner_angular_gram(_to(gpu, ca), _to(gpu, cb), m).cpu().numpy()
+    dh = np.array([[int(np.bitwise_count((a ^ b).view(np.uint64)).sum(dtype=np.int64)) for b in cb] for a in ca])
+    assert [dh[0, 0], dh[1, 1], dh[2, 2], dh[3, 3]] == [1, 0, m, 1]
+    assert np.abs(got.astype(np.float64) - (1.0 - dh / m)).max() <= (2.0 ** -24 if m & (m - 1) == 0 else 2.0 ** -23 + 2.0 ** -24)
+    assert got[1, 1] == 1.0
+    if m & (m - 1) == 0:
+        exact = dh < 2**24
+        assert exact[[0, 1, 3], [0, 1, 3]].all() and np.array_equal(got[exact], (1.0 - dh / m).astype(np.float32)[exact])
+
+
 def test_angular_gram_of_the_most_tiles(gpu):
     # one row of codes against as many as a grid of one workgroup per tile takes (2^24 - 1 tiles, 64 GiB of codes): every tile
     # is computed once, the last and ragged one included
