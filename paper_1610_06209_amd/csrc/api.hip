@@ -650,7 +650,7 @@ int spinner_sketch(const float* A, int n, int d, const float* w, const float* d1
     float* At = reinterpret_cast<float*>(base);                                             // [d][n]
     float* Ut = reinterpret_cast<float*>(base + align256((size_t)d * n * sizeof(float)));   // [d][m]
     void* ws2 = base + align256((size_t)d * n * sizeof(float)) + align256((size_t)d * m * sizeof(float));
-    const bool begun = spinner::sketch_begun_pays(log2n, m);
+    const bool begun = spinner::sketch_begun_pays(log2n, m, d);
     hipError_t e = begun ? spinner::launch_transpose_transform(A, n, d, w, d1, At, s) : spinner::launch_transpose_scale(A, n, d, w, At, s);
     if (e != hipSuccess) return hip_fail(e);
     const int rc = apply_impl(At, n, log2n, d, begun ? nullptr : d1, d2, d3, nullptr, m, SPINNER_EPI_NONE, scale, Ut,

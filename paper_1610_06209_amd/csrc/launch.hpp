@@ -294,13 +294,17 @@ constexpr int kColumnBits = 8;
 // Where the two are ahead of transposition and whole projection.  Whole call and Gram, in us, without / with: n = 2^16, m = 2048, d = 500 132.5 /
 // 125.9, 256 68.7 / 68.2, 64 45.4 / 44.4, 16 42.4 / 39.2, m = 20000, d = 500 210.6 / 192.4; 2^15, m = 1024, d = 1000 127.9 / 121.2, 128 37.0 / 34.2,
 // m = 10000, d = 1000 300.6 / 293.7, m = 2000, d = 17 33.4 / 30.8; 2^14, m = 1000, d = 1999 188 / 177, 300 41.3 / 38.1; 2^13, m = 500, d = 1999 92.2 /
-// 90.0, 333 26.4 / 26.3; 2^11, m = 1000, d = 300 31.2 / 29.3, m = 128, d = 1999 36.2 / 34.4.  Where more than n / 16 rows are kept at 2^13 and 2^14 the
+// 90.0; 2^11, m = 1000, d = 300 31.2 / 29.3, m = 128, d = 1999 36.2 / 34.4.  The sketch alone, few columns, m = n / 16: 2^16, d = 4 29.1 / 24.3, 32 32.7 /
+// 29.3; 2^15, 4 20.4 / 18.8, 32 22.2 / 20.7; 2^14, 4 17.0 / 15.7, 32 17.9 / 16.8; 2^11, 16 13.8 / 13.7, 64 14.2 / 13.7, 300 15.3 / 14.2.  At 2^13 it takes
+// more than 512 columns: 32 13.4 / 13.6, 128 14.0 / 14.4, 200 15.8 / 16.3, 300 20.2 / 19.4, 400 20.5 / 20.7, 500 21.4 / 22.4, 512 20.5 / 22.4, 550 22.5 /
+// 22.0, 700 24.0 / 22.6, 1000 28.1 / 26.0, 4095 86 / 80 (up to there the tiles are at most two per compute unit).  Where more than n / 16 rows are kept at 2^13 and 2^14 the
 // kernels of the whole projection have a better split of their own (m = 3000: 2^14, d = 40 30.2 / 31.2, 2^13, d = 100 31.4 / 32.2), as they do at
 // 2^12 (m = 256, d = 500 22.6 / 22.9, m = 2000, d = 25 22.9 / 23.6), at 2^10 (d = 1999 63.1 / 64.0) and where all rows are kept.
-inline bool sketch_begun_pays(int log2n, int m)
+inline bool sketch_begun_pays(int log2n, int m, int d)
 {
     const int n = 1 << log2n;
-    return log2n == 13 || log2n == 14 ? m <= n >> 4 : (log2n == 11 || log2n == 15 || log2n == 16) && m < n;
+    if (log2n == 13) return m <= n >> 4 && d > 512;
+    return log2n == 14 ? m <= n >> 4 : (log2n == 11 || log2n == 15 || log2n == 16) && m < n;
 }
 hipError_t launch_transpose_transform(const float* src, long long rows, long long cols, const float* row_scale, const float* diag,
                                       float* dst, hipStream_t s);

@@ -64,10 +64,12 @@ def test_sketch_matches_oracle(gpu, oracle, n, d, m, weights):
 def test_sketch_with_the_first_stages_in_the_transposition(gpu, oracle, log2n):
     # Columns for tiles of 32: a lone one, one short of a tile, one over, a last tile whose second wave of columns is cut; m on
     # both sides of n / 16, where the projection takes other kernels; general diagonals, so that a
-    # swapped or dropped one, or one met in the wrong order of rows, would show.
+    # swapped or dropped one, or one met in the wrong order of rows, would show.  n = 2^13 takes this way from 513 columns on.
     n = 1 << log2n
+    more = 512 if log2n == 13 else 0
     rng = np.random.default_rng(8250 + log2n)
-    for d, m, weights in [(1, n // 16, True), (31, n // 32 - 1, False), (33, n // 16 + 1, True), (74, n - 1, False), (45, n // 16 - 3, True)]:
+    for d, m, weights in [(1 + more, n // 16, True), (31 + more, n // 32 - 1, False), (33 + more, n // 16 + 1, True), (74, n - 1, False),
+                          (45 + more, n // 16 - 3, True), (max(more, 32), n // 16, True)]:
         A, w = W.newton_sketch_problem(n, d, 8260 + log2n + d)
         dg = (rng.standard_normal((3, n)) * 0.5 + 1.0).astype(np.float32)
         scale = math.sqrt(n / m)
