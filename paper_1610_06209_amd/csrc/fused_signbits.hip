@@ -131,7 +131,12 @@ __device__ __forceinline__ intx8 code_operand(uintx4 w, unsigned sign, unsigned 
 // LINES: rows of `out` are whole 128-byte lines (nb a multiple of 32) and bypass cache retention (4096 x 4096, m = 1024 18.2 ->
 // 16.4 us; 16384 x 16384, m = 4096 625 -> 607); the pieces of other rows' lines have to meet in the L2 (16384 x 10007, m = 256:
 // 152 us, with the hint 338)
-template <bool LINES, int FORM>
+// FEW: few tiles of short codes, ragged ones among them, are over soon enough that fetching the instructions counts (those of the stores with
+// checks lie behind the rest), and half as many in the chunk gain more than an index known in advance.  Unrolled / not, in us: 300 x 300,
+// m = 256 5.06 / 4.74, m = 1024 6.17 / 5.92; 100 x 5000, m = 512 5.84 / 5.50, m = 1024 6.57 / 6.37; 2000 x 2000, m = 256 6.89 / 6.63, m = 1024 8.18 / 8.01;
+// 12000 x 300, m = 1024 9.17 / 9.03; but whole tiles, 1024 x 1024, m = 1024, 4.91 / 4.97, 4096 x 2048, m = 512, 7.83 / 8.03, more tiles, 700 x 11000, m = 256, 8.88 /
+// 8.98, longer codes, 1000 x 1000, m = 4096, 11.64 / 11.90, 16384 x 10007, m = 4096, 294.8 / 297.5
+template <bool LINES, int FORM, bool FEW>
 __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __restrict__ a, long long na, const uintx4* __restrict__ b,
                                                            long long nb, int words, float inv_m, unsigned gx, unsigned gy, float* __restrict__ out)
 {
@@ -188,9 +193,7 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
         const uintx4* hb = now + (kGramRows + wc * 64 + l32) * kGramPieces;
         const uintx4* hw = now + threadIdx.x * kGramPieces;
         const int have = pieces - p0 < kGramPieces ? pieces - p0 : kGramPieces;      // 2 or 4
-#pragma unroll
-        for (int s = 0; s < kGramPieces; s += 2) {
-            if (s >= have) break;
+        const auto two_pieces = [&](int s) {
             uintx4 qa[2], qb[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -215,6 +218,16 @@ __global__ void __launch_bounds__(256, 3) hamming_gram_kernel(const uintx4* __re
                     for (int u = 0; u < 2; ++u)
                         acc[t][u] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[t], fb[u], acc[t][u], 4, 4, 0, scale, 0, scale);
             });
+        };
+        if constexpr (FEW) {
+#pragma unroll 1
+            for (int s = 0; s < have; s += 2) two_pieces(s);
+        } else {
+#pragma unroll
+            for (int s = 0; s < kGramPieces; s += 2) {
+                if (s >= have) break;
+                two_pieces(s);
+            }
         }
     };
     load(0, even);
@@ -260,9 +273,12 @@ hipError_t launch_hamming_gram(const unsigned long long* a, long long na, const 
     // one workgroup of 256 threads per tile, and a grid holds fewer than 2^32 threads; the caller keeps gy below 2^16
     if (gx > 0xffffffLL || gx * gy > 0xffffffLL) return hipErrorInvalidConfiguration;
     const bool lines = (nb & 31) == 0;
-    const auto kernel = m > kGramCountedBits ? (lines ? hamming_gram_kernel<true, kGramSigned> : hamming_gram_kernel<false, kGramSigned>)
-                        : m > kGramMixedBits ? (lines ? hamming_gram_kernel<true, kGramCounted> : hamming_gram_kernel<false, kGramCounted>)
-                                             : (lines ? hamming_gram_kernel<true, kGramMixed> : hamming_gram_kernel<false, kGramMixed>);
+    const bool ragged = na % kGramRows != 0 || nb % kGramCols != 0;
+    const bool few = ragged && m <= 2 * 64 * kGramChunk && gx * gy <= 2 * kComputeUnits;
+    const auto kernel = m > kGramCountedBits ? (lines ? hamming_gram_kernel<true, kGramSigned, false> : hamming_gram_kernel<false, kGramSigned, false>)
+                        : m > kGramMixedBits ? (lines ? hamming_gram_kernel<true, kGramCounted, false> : hamming_gram_kernel<false, kGramCounted, false>)
+                        : few                ? (lines ? hamming_gram_kernel<true, kGramMixed, true> : hamming_gram_kernel<false, kGramMixed, true>)
+                                             : (lines ? hamming_gram_kernel<true, kGramMixed, false> : hamming_gram_kernel<false, kGramMixed, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(gx * gy)), dim3(256), kGramSpareLds, s, reinterpret_cast<const uintx4*>(a), na,
                        reinterpret_cast<const uintx4*>(b), nb, m / 64, 1.0f / (float)m, (unsigned)gx, (unsigned)gy, out);
     return hipGetLastError();

@@ -174,10 +174,11 @@ def _first_bits(k, m):
 
 
 @pytest.mark.parametrize("na,nb,m", [(1, 1, 256), (128, 128, 768), (1100, 643, 1280), (130, 2050, 256), (2500, 3, 1024),
-                                     (300, 160, 512)])
+                                     (300, 160, 512), (1, 65536, 512), (1, 65537, 1024), (384, 256, 1024), (300, 96, 768), (90, 40, 1280)])
 def test_angular_gram_over_tile_bands_and_chunks(gpu, na, nb, m):
     # 128 x 128 tiles in bands of four tile rows (a shorter last band), dealt to the XCDs in runs; code words in chunks of
-    # eight (a shorter last chunk): every entry, from the Hamming distance counted in numpy
+    # eight (a shorter last chunk), in a loop of their own where ragged tiles (up to 512 in all) meet at most two chunks: every
+    # entry, from the Hamming distance counted in numpy
     rng = np.random.default_rng(na * 7 + nb + m)
     ca = rng.integers(-2**63, 2**63 - 1, (na, m // 64), dtype=np.int64)
     cb = rng.integers(-2**63, 2**63 - 1, (nb, m // 64), dtype=np.int64)
