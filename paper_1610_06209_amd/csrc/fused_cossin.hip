@@ -274,10 +274,11 @@ spinner_feature_ar_kernel(TileParams p, int L)
 constexpr int kFeatureArWaves = 1;
 template <int NT>
 static bool feature_ar_streams(int m) { return NT != 10 || (m & 31) == 0 || m < (1 << NT) / 2; }
-// n = 2^13, 2^14 without the limit of 128 registers (launch.hpp), for batches whose tiles are all on the chip without it (three
-// and one per compute unit): nothing is gained from more of them, and the spills cost (fp32 diagonals, with / without the
-// limit, in us: 2^13, m = 500, batch 256 13.6 / 12.5, 768 24.7 / 22.5, m = n, 768 25.4 / 23.2; 2^14, m = 1001, 256 21.1 / 18.7; sign
-// words: 2^14, m = 1001, 256 20.4 / 19.0, 2^13 alike)
+// n = 2^13, 2^14 without the limit of 128 registers (launch.hpp), for batches of at most one tile per compute unit: nothing is gained from more of
+// them there, and lane stages in larger batches wait less often (at 2^14 the limit also spills one or two registers).  With / without the limit, in us:
+// 2^14, fp32 diagonals, m = n, batch 64 16.4 / 15.9, 256 20.2 / 19.9, m = 1001, 256 18.3 / 17.1, sign words, m = n, 64 16.3 / 16.0, m = 1001, 256 17.5 / 17.1;
+// 2^13, fp32 diagonals, m = n, 64 10.1 / 10.0, 256 11.6 / 11.4, m = 500, 256 9.9 / 9.8, but two and three tiles per compute unit: m = n, 400 15.5 / 15.9, 700
+// 20.7 / 21.3, m = 500, 512 14.0 / 14.5, 768 18.2 / 19.1
 struct FeatureFewTuning : NotWide { static constexpr int rmax = 5, waves = 4, min_waves = 0, trips = 0; };
 template <int NT, bool SIGNS>
 static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_t s)
@@ -292,7 +293,7 @@ static hipError_t launch_cossin(const TileParams& p, long long tiles, hipStream_
         return hipGetLastError();
     } else {
         if constexpr (NT == 14 || (NT == 13 && !SIGNS)) {
-            if (tiles <= (NT == 13 ? 3 : 1) * kComputeUnits)
+            if (tiles <= kComputeUnits)
                 return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS, 0, true, GeomFrom<FeatureFewTuning, NT>>(p, tiles, s);
         }
         return launch_tile<double, NT, NT, 3, true, EPI_STORE_COSSIN, SIGNS>(p, tiles, s);
