@@ -237,7 +237,9 @@ int spinner_apply_blocks(const float *x, int n, long batch, int L,
  *
  * spinner_angular_gram computes out[i][j] = 1 - d_H(a_i, b_j) / m (fp32,
  * row-major [na][nb]) for two sets of codes of the same m; the Hamming
- * distances are exact integers.  na is limited to 128 * 65535 rows per call.
+ * distances are exact integers up to m = 2^24 (longer codes: where the sums of
+ * their products of bits as +1 and -1 stay within 24 bits, as for equal,
+ * opposite and unrelated codes).  na is limited to 128 * 65535 rows per call.
  */
 size_t spinner_code_bytes(int m);
 size_t spinner_codes_workspace_bytes(int n, long batch);

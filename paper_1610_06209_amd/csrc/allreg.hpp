@@ -9,7 +9,8 @@
 // r register stages, the exchange, r register stages (plus lane stages for the LB - r lane bits both layouts
 // share).  Element e sits at word (e >> r) * (2^r + 4) + (e mod 2^r) (+ a skew per group of 2^r lanes and per
 // vector): layout A accesses it 16 bytes per lane, layout B 4 bytes per lane with consecutive lanes on
-// consecutive words; the padding of 4 words keeps both free of bank conflicts.  No barrier is needed: the buffer
+// consecutive words; the padding of 4 words keeps both free of bank conflicts.  (The fp64 feature kernel also has an exchange of single words on both
+// sides, in rows of 2^r + 1 words: feat_ar_a_to_b_words in fused_cossin.hip.)  No barrier is needed: the buffer
 // belongs to one wave, whose LDS accesses only have to be ordered among themselves.
 // The lane masks of the sign flips in these layouts are prepared by spinner_pack_signs (pack_hash_words_kernel).
 #pragma once

@@ -335,7 +335,7 @@ hipError_t launch_feature_blocks_ar(int log2n, const TileParams& p, const float*
 
 #define CASE(NT) case NT: return signs ? launch_cossin<NT, true>(p, tiles, s) : launch_cossin<NT, false>(p, tiles, s);
 // n = 2^15, 2^16: fp64 values do not fit a compute unit; fp32 butterflies on the plain kernels' geometries.  At 2^16 sine and cosine
-// beside 64 values in 128 registers spill 28 of them with sign words, 27 with fp32 diagonals (92, 100 bytes per thread); 2^15 none
+// beside 64 values in 128 registers spill 27 of them (92 bytes per thread with sign words, 100 with fp32 diagonals); 2^15 none
 #define WIDECASE(NT) case NT: return signs ? launch_tile<float, NT, NT, 3, true, EPI_STORE_COSSIN, true>(p, tiles, s) \
                                            : launch_tile<float, NT, NT, 3, true, EPI_STORE_COSSIN, false>(p, tiles, s);
 hipError_t launch_fused_cossin(int log2n, bool signs, const TileParams& p, long long tiles, hipStream_t s)

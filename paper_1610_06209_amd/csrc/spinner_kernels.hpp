@@ -610,9 +610,11 @@ __device__ __forceinline__ void transpose(double (&v)[G::R], const ThreadCtx<G>&
 // Piece k of a walk: k itself, or (PAIRED: the pruned last round) 0, R/8, 1, R/8 + 1, ..: the two sides of its first sums next to each other.
 template <int N>
 struct DiagAhead { float4 q[N > 0 ? N : 1]; };
-// Pieces ahead in the fused kernels: as many as fit without spills, where they gain.  None / 4 pieces, in us, 2^27 elements, first 1000 rows: 2^14
+// Pieces ahead in the fused kernels: as many as gain, which is few where registers are short: all rows of 2^16 spill three or four of them for the
+// four pieces (16, 20 bytes of scratch per thread) and stay 1 to 4 % ahead; the pruned kernels that ask ahead spill none.  None / 4 pieces, in us, 2^27 elements, first 1000 rows: 2^14
 // 176 / 156, 2^16 230 / 226, 2^15 169 / 169 (not taken); 2^13, first 500, none / 4 / 8 152 / 156 / 144; 2^12, first 200, 141 / 142; all rows 2^16 328.6 /
-// 325.1, 20000 of them 295.6 / 290.4, 2^15 249 / 256, 2^14 220 / 232 (2^16 with six and eight pieces 334 and 369, and spills).
+// 325.1 (64 vectors 31.8 / 31.3, 512 85.8 / 85.1), 20000 of them 295.6 / 290.4, 43690 405 / 391, 2^15 249 / 256, 2^14 220 / 232 (2^16 with six and eight
+// pieces 334 and 369).
 // Vectors of the sketch, which arrive begun: 2^16, m = 2048, d = 500 (whole call) 125.9 / 120.5, m = 20000 192.4 / 195.5.
 constexpr int diag_pieces_ahead(int log2n, bool pruned, bool begun)
 {

@@ -171,7 +171,6 @@ def test_first_m_rows_with_pruned_last_round(gpu, oracle, log2n):
         check(gpu.b.spinner_apply_signs(xd, signs, m, "none", scale).cpu().numpy(), want, m, scale, "sign words")
 
 
-# ------------------------------------------------------------------ random features
 @pytest.mark.parametrize("log2n,pruned", [(13, True), (14, True), (16, True), (16, False)])
 def test_first_m_rows_with_diagonals_in_flight_ahead(gpu, oracle, log2n, pruned):
     # every entry of every diagonal another value: one that meets the wrong coordinate, or meets it twice, shows
@@ -187,6 +186,7 @@ def test_first_m_rows_with_diagonals_in_flight_ahead(gpu, oracle, log2n, pruned)
         assert rel_l2_per_vector(got, want).max() <= REL_L2_TOL, (m, batch)
 
 
+# ------------------------------------------------------------------ random features
 @pytest.mark.parametrize("n,m,scale", [(64, 64, 8.0), (1024, 1024, 32.0), (1024, 100, 3.0), (4096, 4096, 64.0),
                                        (16384, 16384, 1.0)])
 def test_cos_sin_features(gpu, oracle, n, m, scale):
