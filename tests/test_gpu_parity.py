@@ -814,7 +814,8 @@ def test_stacked_features_on_both_sides_of_a_batch_limit(gpu, n, m, L, batch):
         assert float((both - one).abs().max()) <= 2.0 * tol
 
 
-@pytest.mark.parametrize("n,m,batch", [(1 << 13, 1 << 13, 768), (1 << 13, 501, 768), (1 << 14, 1 << 14, 256), (1 << 14, 8196, 256)])
+@pytest.mark.parametrize("n,m,batch", [(1 << 13, 1 << 13, 256), (1 << 13, 501, 256), (1 << 13, 1 << 13, 768), (1 << 13, 501, 768),
+                                       (1 << 14, 1 << 14, 256), (1 << 14, 8196, 256)])
 def test_features_on_both_sides_of_a_batch_limit(gpu, n, m, batch):
     # `batch` vectors and one more go to kernels that differ in nothing but the registers they may take: the same bits
     t = gpu.torch
